@@ -95,6 +95,48 @@ def test_quantize_weights_bf16(mq, orc):
     assert np.array_equal(host(c), oc) and np.array_equal(host(s), os_) and np.array_equal(host(z), oz)
 
 
+@pytest.mark.parametrize("offset", (0, 1, 4, 8))
+@pytest.mark.parametrize("K", (8, 64, 1000, 2048, 2056, 8192, 8200, 16384, 16392))
+def test_quantize_weights_at_the_edges_of_its_row_forms(mq, orc, K, offset):
+    """Rows of one wave, of a workgroup and beyond, odd row counts, matrices that do not start on a 16-byte boundary, rows
+    of zeros or of one sign: bit for bit as the oracle."""
+    N = 7
+    w = si.weights_f16(11, f"qe/{K}", N, K)
+    w[1] = 0
+    w[2] = np.abs(w[2])
+    flat = torch.empty(N * K + 16, dtype=torch.float16, device="cuda")
+    wd = flat[offset:offset + N * K].view(N, K)
+    wd.copy_(dev(w))
+    for bits, sym in ((4, False), (8, True)):
+        c, s, z = mq.quantize_weights(wd, bits, sym)
+        oc, os_, oz = orc.quantize_weights(w, bits, sym)
+        assert np.array_equal(host(c), oc) and np.array_equal(host(z), oz)
+        assert np.array_equal(host(s).view(np.uint32), os_.view(np.uint32))
+
+
+@pytest.mark.parametrize("bits,signed", [(2, False), (3, False), (4, False), (8, False), (8, True)])
+def test_pack_and_sums_in_one_pass(mq, orc, bits, signed):
+    """Channel counts that leave part of a workgroup or of a tile empty, one round and several, a code matrix that does
+    not start on a 16-byte boundary, codes with bits above their width (masked off)."""
+    rng = np.random.default_rng(40 + bits)
+    for (N, K) in ((1, 64), (9, 128), (33, 2048), (31, 2112), (40, 5120)):
+        codes = rng.integers(0, 256, (N, K)).astype(np.uint8)
+        low = codes & ((1 << bits) - 1)
+        sums = orc.code_rowsum(codes, signed=True) if signed else low.astype(np.int64).sum(1)
+        first = None
+        for offset in (0, 1):
+            flat = torch.empty(N * K + 1, dtype=torch.uint8, device="cuda")
+            cd = flat[offset:offset + N * K].view(N, K)
+            cd.copy_(dev(codes))
+            p, cs = mq.pack_weights(cd, bits, mq.LAYOUT_KERNEL, codes_signed=signed)
+            assert np.array_equal(host(cs), sums)
+            assert np.array_equal(host(mq.unpack_weights(p, N, K, bits, mq.LAYOUT_KERNEL)), low)
+            first = host(p) if first is None else first
+            assert np.array_equal(host(p), first)
+            p2, none = mq.pack_weights(cd, bits, mq.LAYOUT_KERNEL, codes_signed=signed, want_colsum=False)
+            assert none is None and np.array_equal(host(p2), first)
+
+
 @pytest.mark.parametrize("bits", ALL_BITS)
 def test_pack_canonical_bytes_bit_exact(mq, orc, bits):
     rng = np.random.default_rng(bits)

@@ -33,55 +33,104 @@ __device__ inline T wave_reduce(T v, Op op) {
 static constexpr int MM_U = 8;  // vectors per lane per round, pass 1
 static constexpr int Q_U = 4;   // vectors per lane per round, pass 2
 
-__global__ __launch_bounds__(256) void act_minmax_kernel(const _Float16* __restrict__ x, uint32_t nv, uint32_t K8,
-                                                         long ldx, RowMap map, int flat,
-                                                         float* __restrict__ partials) {
+// Physical row of logical row r (RowMap::phys with its division prepared by the host).
+struct RowWalk {
+    FastDiv group;  // d = rows per group; used where `mapped` says so
+    int mapped, group_stride, row_offset;
+    static RowWalk make(const RowMap& m) {
+        return RowWalk{FastDiv::make((uint32_t)(m.rows_per_group > 0 ? m.rows_per_group : 1)), m.rows_per_group > 0,
+                       m.group_stride, m.row_offset};
+    }
+    __device__ inline long phys(uint32_t r) const {
+        if (!mapped) return r;
+        uint32_t q, rem;
+        group.divmod(r, q, rem);
+        return (long)q * group_stride + rem + row_offset;
+    }
+};
+
+// The extremes are found in pairs of fp16 values (a minimum or maximum of fp16 values is one of them: nothing is lost)
+// and widened once at the end; NaN is ignored as by fminf / fmaxf.  THREADS: a tensor that needs all partial slots takes
+// four times the threads per workgroup, so that a compute unit holds 32 waves instead of 8.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void act_minmax_kernel(const _Float16* __restrict__ x, uint32_t nv, FastDiv K8,
+                                                             long ldx, RowWalk map, int flat,
+                                                             float* __restrict__ partials) {
+    constexpr uint32_t U = THREADS == 256 ? MM_U : MM_U / 2, STEP = THREADS * U;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    float mn = INFINITY, mx = -INFINITY;
-    for (uint32_t base = blockIdx.x * (256u * MM_U); base < nv; base += gridDim.x * (256u * MM_U)) {
-        half8 v[MM_U];
+    half8 mn8, mx8;
 #pragma unroll
-        for (int u = 0; u < MM_U; ++u) {
-            uint32_t i = base + u * 256u + threadIdx.x;
+    for (int e = 0; e < 8; ++e) {
+        mn8[e] = (_Float16)INFINITY;
+        mx8[e] = -(_Float16)INFINITY;
+    }
+    for (uint32_t base = blockIdx.x * STEP; base < nv; base += gridDim.x * STEP) {
+        half8 v[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            uint32_t i = base + u * THREADS + threadIdx.x;
             i = i < nv ? i : nv - 1;  // a repeated vector does not change a min or a max
             if (flat) {
                 v[u] = ((const half8*)x)[i];
             } else {
-                const uint32_t row = i / K8, p = i - row * K8;
+                uint32_t row, p;
+                K8.divmod(i, row, p);
                 v[u] = ((const half8*)(x + map.phys(row) * ldx))[p];
             }
         }
 #pragma unroll
-        for (int u = 0; u < MM_U; ++u)
+        for (uint32_t u = 0; u < U; ++u) {
+            mn8 = __builtin_elementwise_min(mn8, v[u]);
+            mx8 = __builtin_elementwise_max(mx8, v[u]);
+        }
+    }
+    float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float f = (float)v[u][e];
-                mn = fminf(mn, f);
-                mx = fmaxf(mx, f);
-            }
+    for (int e = 0; e < 8; ++e) {
+        mn = fminf(mn, (float)mn8[e]);
+        mx = fmaxf(mx, (float)mx8[e]);
     }
     mn = wave_reduce(mn, [](float a, float b) { return fminf(a, b); });
     mx = wave_reduce(mx, [](float a, float b) { return fmaxf(a, b); });
-    __shared__ float smn[4], smx[4];
+    __shared__ float smn[THREADS / 64], smx[THREADS / 64];
     if (lane == 0) {
         smn[wv] = mn;
         smx[wv] = mx;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        partials[2 * blockIdx.x] = fminf(fminf(smn[0], smn[1]), fminf(smn[2], smn[3]));
-        partials[2 * blockIdx.x + 1] = fmaxf(fmaxf(smx[0], smx[1]), fmaxf(smx[2], smx[3]));
+#pragma unroll
+        for (int i = 1; i < THREADS / 64; ++i) {
+            mn = fminf(mn, smn[i]);
+            mx = fmaxf(mx, smx[i]);
+        }
+        partials[2 * blockIdx.x] = mn;
+        partials[2 * blockIdx.x + 1] = mx;
     }
 }
 
-static constexpr int Q_MAX_ROWS = 128;  // rows per workgroup, pass 2 (1024 output vectors of at least 8 per row)
+// Sum over each aligned group of eight lanes, in every lane of the group (two quad permutes and a mirror of the group:
+// register moves inside the vector ALU, no trip through LDS).
+__device__ inline int sum8(int v) {
+    v += __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);   // lanes 1 0 3 2
+    v += __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);   // lanes 2 3 0 1
+    v += __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true);  // lanes 7 6 5 4 3 2 1 0
+    return v;
+}
 
-// A workgroup converts R whole rows (so that it owns their row sums): R * Kp/8 output vectors, 1024 per round.
+static constexpr int Q_MAX_ROWS = 128;   // rows per workgroup, pass 2
+static constexpr int kQuantGrid = 2048;  // workgroups of a large tensor, pass 2: eight per compute unit
+
+// A workgroup converts R whole rows (so that it owns their row sums): R * Kp/8 output vectors, 1024 per round.  Up to a
+// few MB it is bound by memory latency, above by HBM as long as a value costs few instructions: one fused multiply-add
+// that widens it, one rounding, one addition and one saturating conversion into its byte (the conversion also takes NaN
+// to code 0, as the clamp of the formula does), with the division of a vector index by the row length prepared by the
+// host.  rowsum == nullptr: the caller's GEMM takes the sums itself, they are left out here.
 // BOS: workgroups from index qgrid on compute the BOS rows of a BOS-aware K/V projection instead (they depend on
 // nothing this kernel produces; one launch less on a path whose kernels are all bound by launch latency).
 template <bool BOS>
 __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __restrict__ x, int M, int K, long ldx,
-                                                           RowMap map, int R, const float* __restrict__ partials,
+                                                           RowWalk map, int R, FastDiv Kp8d, const float* __restrict__ partials,
                                                            int n_partials, const float* __restrict__ act_scale,
                                                            const int32_t* __restrict__ act_zp,
                                                            int8_t* __restrict__ a8, int32_t* __restrict__ rowsum,
@@ -105,7 +154,7 @@ __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __res
     if (threadIdx.x < Q_MAX_ROWS) lsum[threadIdx.x] = 0;
     const uint32_t K8 = K >> 3;
     const uint32_t Kp = (K + 127) / 128 * 128;  // row stride of the int8 copy; the padding is zero
-    const uint32_t Kp8 = Kp >> 3;               // a multiple of 16: an aligned group of 8 lanes never straddles rows
+    const uint32_t Kp8 = Kp8d.d;                // Kp / 8, a multiple of 16: an aligned group of 8 lanes never straddles rows
     const uint32_t nvo = (uint32_t)Rr * Kp8;
     half8 v[Q_U];
     uint32_t lr[Q_U], pp[Q_U];
@@ -113,8 +162,7 @@ __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __res
 #pragma unroll
         for (int u = 0; u < Q_U; ++u) {
             const uint32_t i = base + u * 256u + threadIdx.x;
-            lr[u] = i / Kp8;
-            pp[u] = i - lr[u] * Kp8;
+            Kp8d.divmod(i, lr[u], pp[u]);
             if (i < nvo && pp[u] < K8) v[u] = ((const half8*)(x + map.phys(r0 + lr[u]) * ldx))[pp[u]];
         }
     };
@@ -122,9 +170,19 @@ __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __res
     float s, zf;
     if (partials) {
         float mn = INFINITY, mx = -INFINITY;
-        for (int i = threadIdx.x; i < n_partials; i += 256) {
-            mn = fminf(mn, partials[2 * i]);
-            mx = fmaxf(mx, partials[2 * i + 1]);
+        constexpr int PU = 4;  // pairs requested together
+        for (int i0 = threadIdx.x; i0 < n_partials; i0 += 256 * PU) {
+            float2 pr[PU];
+#pragma unroll
+            for (int u = 0; u < PU; ++u) {
+                const int i = i0 + u * 256;
+                pr[u] = ((const float2*)partials)[i < n_partials ? i : n_partials - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < PU; ++u) {
+                mn = fminf(mn, pr[u].x);
+                mx = fmaxf(mx, pr[u].y);
+            }
         }
         mn = wave_reduce(mn, [](float a, float b) { return fminf(a, b); });
         mx = wave_reduce(mx, [](float a, float b) { return fmaxf(a, b); });
@@ -163,33 +221,30 @@ __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __res
             const uint32_t i = base + u * 256u + threadIdx.x;
             const bool valid = i < nvo;
             uint32_t w0 = 0, w1 = 0;
-            int sum = 0;
             if (valid && pp[u] < K8) {
-                int q[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    float t = rintf((float)v[u][e] * inv) + zf;
-                    t = fminf(fmaxf(t, 0.0f), 255.0f);
-                    q[e] = (int)t - 128;
-                    sum += q[e];
-                }
+                // t of element e of the group; byte b of word h holds element k8_perm(4 h + b)
+                auto t = [&](int e) { return rintf(__builtin_fmaf((float)v[u][e], inv, 0.0f)) + zf; };
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
-                    w0 |= ((uint32_t)(q[k8_perm(b)] & 255)) << (8 * b);
-                    w1 |= ((uint32_t)(q[k8_perm(4 + b)] & 255)) << (8 * b);
+                    w0 = __builtin_amdgcn_cvt_pk_u8_f32(t(k8_perm(b)), b, w0);
+                    w1 = __builtin_amdgcn_cvt_pk_u8_f32(t(k8_perm(4 + b)), b, w1);
                 }
+                w0 ^= 0x80808080u;  // code - 128
+                w1 ^= 0x80808080u;
             }
             // (streaming store: read next by another kernel, nothing gained by keeping it in this XCD's L2)
             if (valid) {
                 const uint2v out = {w0, w1};
                 __builtin_nontemporal_store(out, (uint2v*)(a8 + (long)(r0 + lr[u]) * Kp) + pp[u]);
             }
-            sum += __shfl_xor(sum, 1, 64);
-            sum += __shfl_xor(sum, 2, 64);
-            sum += __shfl_xor(sum, 4, 64);
-            if (valid && (lane & 7) == 0) atomicAdd(&lsum[lr[u]], sum);
+            if (rowsum) {
+                int sum = __builtin_amdgcn_sdot4((int)w0, 0x01010101, 0, false);
+                sum = sum8(__builtin_amdgcn_sdot4((int)w1, 0x01010101, sum, false));
+                if (valid && (lane & 7) == 0) atomicAdd(&lsum[lr[u]], sum);
+            }
         }
     }
+    if (!rowsum) return;
     __syncthreads();
     if ((int)threadIdx.x < Rr) rowsum[r0 + threadIdx.x] = lsum[threadIdx.x];
 }
@@ -202,6 +257,7 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
     const uint32_t nv = (uint32_t)M * K8;  // M * ldx * 2 < 2^31 has been checked: this fits easily
     long g1 = ((long)nv + 256 * MM_U - 1) / (256 * MM_U);
     int grid = (int)(g1 > kPartialSlots ? kPartialSlots : g1);
+    const RowWalk walk = RowWalk::make(in_map);
     const bool dynamic = act_scale == nullptr;
     // given_partials > 0: the producer of x has left that many (min, max) pairs in `partials` already (the gated
     // projection's epilogue does), so the pass over x that would find them is skipped
@@ -210,23 +266,33 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
     } else if (dynamic) {
         const int flat = in_map.rows_per_group <= 0 && ldx == K;
         ProfScope prof(st, PROF_ACT_MINMAX, 0.0, 2.0 * M * K);
-        hipLaunchKernelGGL(act_minmax_kernel, dim3(grid), dim3(256), 0, st, (const _Float16*)x, nv, K8, (long)ldx,
-                           in_map, flat, partials);
+        if (g1 > kPartialSlots)
+            hipLaunchKernelGGL(act_minmax_kernel<1024>, dim3(grid), dim3(1024), 0, st, (const _Float16*)x, nv,
+                               FastDiv::make(K8), (long)ldx, walk, flat, partials);
+        else
+            hipLaunchKernelGGL(act_minmax_kernel<256>, dim3(grid), dim3(256), 0, st, (const _Float16*)x, nv,
+                               FastDiv::make(K8), (long)ldx, walk, flat, partials);
         MQ_HIP_CHECK_LAUNCH();
     }
+    // Rows per workgroup: one round (1024 vectors) while that keeps the grid within eight workgroups per compute unit;
+    // a larger tensor takes as many rounds per workgroup as bring it there, so that the parameters are derived (and the
+    // pairs read: the gated projection leaves thousands) that many times less often.
     const int Kp8 = (K + 127) / 128 * 16;
     int R = 256 * Q_U / Kp8;
-    R = R < 1 ? 1 : (R > Q_MAX_ROWS ? Q_MAX_ROWS : R);
+    R = R < 1 ? 1 : R;
+    if ((M + R - 1) / R > kQuantGrid) R = (M + kQuantGrid - 1) / kQuantGrid;
+    R = R > Q_MAX_ROWS ? Q_MAX_ROWS : R;
     const int qgrid = (M + R - 1) / R;
     ProfScope prof(st, PROF_ACT_QUANTIZE, 0.0, 3.0 * M * K + 4.0 * M);
     if (bos)
         hipLaunchKernelGGL(act_quantize_kernel<true>, dim3(qgrid + bos_blocks(*bos)), dim3(256), 0, st,
-                           (const _Float16*)x, M, K, (long)ldx, in_map, R, dynamic ? partials : (const float*)nullptr,
-                           grid, act_scale, act_zp, a8, rowsum, params, act_scale_out, act_zp_out, qgrid, *bos);
+                           (const _Float16*)x, M, K, (long)ldx, walk, R, FastDiv::make(Kp8),
+                           dynamic ? partials : (const float*)nullptr, grid, act_scale, act_zp, a8, rowsum, params,
+                           act_scale_out, act_zp_out, qgrid, *bos);
     else
         hipLaunchKernelGGL(act_quantize_kernel<false>, dim3(qgrid), dim3(256), 0, st, (const _Float16*)x, M, K,
-                           (long)ldx, in_map, R, dynamic ? partials : (const float*)nullptr, grid, act_scale, act_zp,
-                           a8, rowsum, params, act_scale_out, act_zp_out, qgrid, BosWork{});
+                           (long)ldx, walk, R, FastDiv::make(Kp8), dynamic ? partials : (const float*)nullptr, grid,
+                           act_scale, act_zp, a8, rowsum, params, act_scale_out, act_zp_out, qgrid, BosWork{});
     MQ_HIP_CHECK_LAUNCH();
     return MQ_OK;
 }

@@ -42,7 +42,8 @@ struct A8Workspace {
 // Upper bound of what the split of an [M,K] x [N,K] GEMM's reduction over workgroups can use: arrival counters of the
 // smallest tile (64 x 64) plus `parts` partial accumulator sets over the output padded to the largest splitting tile
 // (128 x 128).  The automatic choice splits only where there are at most 64 tiles and at least 16 pipeline stages, into
-// at most min(16, stages / 4) parts; a forced part count (test hook) is taken as it is.
+// at most min(16, stages / 4) parts; a forced part count (test hook) is taken as it is.  (64 counters of 8 bytes fit the
+// 512 that any shape gets; the larger tile counts of the test hook get theirs beside.)
 size_t split_workspace_bytes(long M, long N, long K) {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
     const long Mp = (M + 127) / 128 * 128, Np = (N + 127) / 128 * 128;
@@ -54,7 +55,7 @@ size_t split_workspace_bytes(long M, long N, long K) {
         parts = parts > 16 ? 16 : parts;
     }
     if (parts <= 1) return 0;
-    return up256((size_t)(Mp / 64) * (Np / 64) * 4) + (size_t)parts * Mp * Np * 4 + 256;
+    return up256((size_t)(Mp / 64) * (Np / 64) * (forced_splits() > 1 ? 8 : 4)) + (size_t)parts * Mp * Np * 4 + 256;
 }
 
 static int check_linear_common(const void* x, int M, int K, int ldx, const void* packed, int N, int layout,
@@ -261,8 +262,8 @@ int mq_qlinear_a8_geglu(const void* x, int M, int K, int ldx, const void* packed
 }
 
 // Dynamic output parameters: behind the input's workspace lie the parameters of the output pass, one (min, max)
-// pair per workgroup of the gated projection (at most one per 128 rows x 64 gated columns) and the row sums that
-// the quantise kernel writes beside its codes (the consumer takes its own inside its main loop).
+// pair per workgroup of the gated projection (at most one per 128 rows x 64 gated columns).  (The size counts four more
+// bytes per row, which nothing uses: the consumer takes the row sums inside its main loop.)
 static size_t geglu_dynamic_pairs(long M, long H) { return (size_t)((M + 127) / 128) * (size_t)((H + 127) / 128 * 2); }
 
 size_t mq_qlinear_a8_geglu_dynamic_workspace_bytes(int M, int K, int H) {
@@ -293,7 +294,6 @@ int mq_qlinear_a8_geglu_dynamic(const void* x, int M, int K, int ldx, const void
     uint8_t* q = (uint8_t*)ws + A8Workspace::bytes(M, K);
     ActParams* out_params = (ActParams*)q;
     float* pairs = (float*)(q + 256);
-    int32_t* out_rowsum = (int32_t*)(q + 256 + up256(8 * geglu_dynamic_pairs(M, H)));
     rc = launch_act_quant(x, M, K, ldx, RowMap{0, 0, 0}, act_scale, act_zp, w.a8, w.rowsum, w.params, w.partials,
                           act_scale_out, act_zp_out, nullptr, st);
     if (rc) return rc;
@@ -303,7 +303,7 @@ int mq_qlinear_a8_geglu_dynamic(const void* x, int M, int K, int ldx, const void
     if (rc) return rc;
     if (n_pairs <= 0 || (size_t)n_pairs > geglu_dynamic_pairs(M, H)) return MQ_ERR_BAD_SHAPE;  // (cannot happen)
     // the ordinary dynamic quantisation of the fp16 product, minus its pass for the range
-    return launch_act_quant(h16, M, H, ldh, RowMap{0, 0, 0}, nullptr, nullptr, a8_out, out_rowsum, out_params, pairs,
+    return launch_act_quant(h16, M, H, ldh, RowMap{0, 0, 0}, nullptr, nullptr, a8_out, nullptr, out_params, pairs,
                             out_scale_out, out_zp_out, nullptr, st, n_pairs);
 }
 
@@ -414,7 +414,7 @@ int mq_conv3x3_a8(const void* x, int B, int H, int W, int Cin, int stride, const
     if (ws_bytes < A8Workspace::bytes(M, Cin)) return MQ_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t st = (hipStream_t)stream;
     A8Workspace w(ws, M, Cin);
-    rc = launch_act_quant(x, (int)M, Cin, Cin, RowMap{0, 0, 0}, act_scale, act_zp, w.a8, w.rowsum, w.params, w.partials,
+    rc = launch_act_quant(x, (int)M, Cin, Cin, RowMap{0, 0, 0}, act_scale, act_zp, w.a8, nullptr, w.params, w.partials,
                           act_scale_out, act_zp_out, nullptr, st);
     if (rc) return rc;
     return launch_conv3x3_a8(w.a8, w.params, B, H, W, Cin, stride, packed, N, w_bits, w_signed ? 1 : 0, w_scale, w_zp, w_colsum,

@@ -375,6 +375,34 @@ def test_split_reduction_is_deterministic_and_reuses_its_workspace(mq, orc):
         assert_close16(host(plan.keepalive[3]), ref, "automatic split, full / no / small workspace")
 
 
+@pytest.mark.parametrize("fill", (0, 1, 0xA5, 0xFF))
+def test_split_reduction_takes_a_workspace_with_any_contents(mq, orc, fill):
+    """The arrival counters count under a tag of their launch: what lies in the workspace beforehand does not matter,
+    not on the first call and not on those behind it, and a captured call finds what its replay before left."""
+    M, K, N = 77, 2048, 320
+    x, w = si.activations_f16(33, "anyws/x", M, K), si.weights_f16(33, "anyws/w", N, K)
+    pw, *_ = make_weight(mq, orc, w, 4)
+    xd = dev(x)
+    ref = mq.qlinear_w_only(xd, pw, ws=torch.zeros(mq.split_workspace_bytes(M, N, K), dtype=torch.uint8, device="cuda"))
+    ws = torch.full((mq.split_workspace_bytes(M, N, K),), fill, dtype=torch.uint8, device="cuda")
+    out = torch.empty(M, N, dtype=torch.float16, device="cuda")
+    for _ in range(3):
+        out.zero_()
+        mq.qlinear_w_only(xd, pw, out=out, ws=ws)
+        assert torch.equal(out, ref)
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=side):
+        mq.qlinear_w_only(xd, pw, out=out, ws=ws)
+    for i in range(4):
+        out.zero_()
+        if i % 2:
+            ws[:512].fill_(fill)  # eager work between the replays, in the same memory
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+
+
 def test_split_reductions_on_two_streams_with_a_workspace_each(mq, orc):
     """Split launches queued on two streams at once, each stream with its own workspace, one of them behind a long
     kernel so that the launches of the other overtake it: all results equal the single-stream result bit for bit.
@@ -436,6 +464,38 @@ def test_a8_small_shapes(mq, orc, mode, tile):
         assert np.array_equal(host(acc), racc)
         assert_close16(host(y), ry, f"a8 static {mode}")
     mq.tune_force_tile(-1)
+
+
+@pytest.mark.parametrize("M,K,N", [(4200, 2048, 32), (2100, 64, 32), (16390, 320, 40)])
+def test_activation_passes_at_the_edges_of_their_grids(mq, orc, M, K, N):
+    """Tensors that need every slot of the range pass and several rounds per workgroup of the conversion, with a ragged
+    last workgroup; NaN is outside every range and becomes code 0, infinities saturate.  The weight is the identity on
+    its first N channels, so that the integer sums are the activation codes themselves."""
+    x = si.activations_f16(31, f"edge/x{M}x{K}", M, K, outlier_prob=0.01)
+    x[M - 1, min(K, N) - 1] = np.float16(93.0)   # the extremes sit in the last row and in the first
+    x[0, 0] = np.float16(-71.0)
+    eye = np.zeros((N, K), np.uint8)
+    eye[np.arange(N), np.arange(N)] = 1
+    packed, colsum = mq.pack_weights(dev(eye), 8, mq.LAYOUT_KERNEL)
+    pw = mq.PackedWeight(packed, dev(np.ones(N, np.float32)), dev(np.zeros(N, np.int32)), colsum, N, K, 8,
+                         mq.LAYOUT_KERNEL, False)
+    ws = dev(np.full(mq.qlinear_a8_workspace_bytes(M, K), 0xA5, np.uint8))
+    _, acc, (s, z) = mq.qlinear_w8a8(dev(x), pw, ws=ws, want_acc=True, want_act=True)
+    s, z = host(s)[0], int(host(z)[0])
+    lo, hi = np.float32(-71.0), np.float32(93.0)
+    assert s == np.float32((hi - lo) / np.float32(255.0))
+    assert z == int(np.rint(np.float32(-lo) * (np.float32(1.0) / s)))
+    inv = np.float32(1.0) / s
+    codes = np.clip(np.rint(x[:, :N].astype(np.float32) * inv) + z, 0, 255).astype(np.int32)
+    assert np.array_equal(host(acc) + z, codes)
+    # calibrated parameters: values far outside the range, infinities and NaN
+    x[1, :4] = np.array([np.inf, -np.inf, np.nan, 60000.0], np.float16)
+    act = (dev(np.array([0.03], np.float32)), dev(np.array([117], np.int32)))
+    _, acc, _ = mq.qlinear_w8a8(dev(x), pw, act=act, ws=ws, want_acc=True)
+    with np.errstate(invalid="ignore", over="ignore"):
+        t = np.rint(x[:, :N].astype(np.float32) * (np.float32(1.0) / np.float32(0.03))) + np.float32(117)
+        t = np.fmin(np.fmax(t, np.float32(0)), np.float32(255))
+    assert np.array_equal(host(acc) + 117, t.astype(np.int32))
 
 
 def test_a8_is_deterministic(mq, orc):

@@ -31,6 +31,7 @@
 //     one rounding; kernels without it contain none of this.
 #include <stdio.h>
 
+#include <atomic>
 #include <mutex>
 #include <type_traits>
 
@@ -361,10 +362,11 @@ struct GemmArgs {
     RowMap out_map;
     int32_t* acc_debug;
     // split of the reduction over `splits` workgroups per tile (1 = none): partial accumulators in `partial`
-    // ([tile][split][BM * BN] 4-byte values, register order), one arrival counter per tile (cleared before the launch)
+    // ([tile][split][BM * BN] 4-byte values, register order), one arrival counter per tile (counts under the launch's tag)
     int splits;
     uint32_t* partial;
-    uint32_t* counters;
+    unsigned long long* counters;
+    unsigned long long split_tag;
     // (host side only) the caller's workspace that partial sums and counters are carved from; may be null
     void* split_ws;
     size_t split_ws_bytes;
@@ -713,6 +715,18 @@ void gemm_kernel(const GemmArgs g) {
 #pragma unroll
     for (int s = 0; s < S; ++s)
         if (s < KT) issue(s, s);
+    if (CAN_SPLIT && splits > 1 && threadIdx.x == 0) {
+        // The tile's arrival counter arrives with unknown contents.  Every part makes sure, while its first stages travel,
+        // that the upper 48 bits hold this launch's tag (a cleared word, then whatever the first exchange found, is
+        // replaced; where the second exchange fails another part's has succeeded), and counts below the tag at its end.
+        unsigned long long* const counter = g.counters + tile_id;
+        unsigned long long seen = 0;
+        if (!__hip_atomic_compare_exchange_strong(counter, &seen, g.split_tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT) &&
+            (seen & ~0xFFFFull) != g.split_tag)
+            __hip_atomic_compare_exchange_strong(counter, &seen, g.split_tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (g.phase_clk) t1 = clock64();
 
     // Main loop.  A 32-cycle MFMA leaves room for about five vector ALU instructions on its SIMD (measured: four
@@ -944,10 +958,15 @@ void gemm_kernel(const GemmArgs g) {
         wait_vmcnt<0>();  // this wave's stores have completed (reached the level all compute units see)
         __syncthreads();
         uint32_t* ticket = (uint32_t*)(lds + P::SINK);  // the sink of padding loads is idle by now
-        if (threadIdx.x == 0)
-            *ticket = __hip_atomic_fetch_add(g.counters + tile_id, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) {
+            unsigned long long* const counter = g.counters + tile_id;
+            const uint32_t n = (uint32_t)__hip_atomic_fetch_add(counter, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) & 0xFFFFu;
+            if (n == (uint32_t)(splits - 1))  // the word goes back cleared
+                __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *ticket = n;
+        }
         __syncthreads();
-        if (*ticket != (uint32_t)(splits - 1)) return;  // (the counters are cleared on the stream before every launch)
+        if (*ticket != (uint32_t)(splits - 1)) return;
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
@@ -1356,22 +1375,27 @@ void set_force_tile(int t) { g_force_tile = t; }
 // ---- reduction split over workgroups ------------------------------------------------------------------------
 // Problems with few tiles and a long reduction (K/V projections, a handful of activation rows) are bound by memory
 // latency: the only remedy is to have more workgroups request the operands at once.  Their partial sums and one
-// arrival counter per tile live in the CALLER's workspace: [counters: tiles x 4 bytes, rounded up to 256]
-// [partial sums: tiles x parts x BM x BN x 4 bytes].  The counters are cleared by a small kernel on the same stream
-// right before the GEMM (the workspace arrives with unknown contents); whoever owns the workspace owns the hazard,
-// as with any workspace: one stream at a time.
+// arrival counter per tile live in the CALLER's workspace: [counters: tiles x 8 bytes, rounded up to 256]
+// [partial sums: tiles x parts x BM x BN x 4 bytes].  The workspace arrives with unknown contents: a counter word
+// counts only under the tag of the launch that reads it (48 bits, another one for every launch; a replayed graph finds
+// the zero that the last arrival of the replay before it left), so that no launch of its own has to clear the words
+// first.  That launch took 4.5 us beside GEMMs of 10 us.  Whoever owns the workspace owns the hazard, as with any
+// workspace: one stream at a time.
 static int g_force_splits = 0;  // 0: automatic, 1: never, n > 1: n parts wherever the reduction is long enough
 void set_force_splits(int n) { g_force_splits = n < 0 ? 0 : n; }
 int forced_splits() { return g_force_splits; }
 static int g_force_band = 0;  // 0: automatic, n >= 1: n row blocks per band of the workgroup -> tile map
 void set_force_band(int n) { g_force_band = n < 0 ? 0 : n; }
 
-__global__ void split_clear_kernel(uint32_t* counters, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) counters[i] = 0;
+// Tag of one launch: the upper 48 bits of a Weyl sequence, never zero, so that neither cleared memory nor small numbers
+// or 16-bit data left in the workspace look like it.
+static unsigned long long next_split_tag() {
+    static std::atomic<unsigned long long> count{1};
+    const unsigned long long tag = (count.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull) & ~0xFFFFull;
+    return tag ? tag : 0xA5A5A5A5A5A50000ull;
 }
 
-static inline size_t split_counter_bytes(long tiles) { return ((size_t)tiles * 4 + 255) / 256 * 256; }
+static inline size_t split_counter_bytes(long tiles) { return ((size_t)tiles * 8 + 255) / 256 * 256; }
 
 // Measured on the SDXL shapes: the large tile wins once it yields two or more workgroups per compute unit; the
 // k-split variants only pay where tiles are few and k is long (FF-out at the 640 level, the K/V projections).
@@ -1463,7 +1487,8 @@ static int run_gemm_r(GemmArgs& g, int tile_index, hipStream_t st) {
         if (room < (size_t)splits) splits = (int)room;
         if (splits > 1) {
             g.splits = splits;
-            g.counters = (uint32_t*)g.split_ws;
+            g.counters = (unsigned long long*)g.split_ws;
+            g.split_tag = next_split_tag();
             g.partial = (uint32_t*)((uint8_t*)g.split_ws + cbytes);
         }
     }
@@ -1505,10 +1530,6 @@ static int run_gemm_r(GemmArgs& g, int tile_index, hipStream_t st) {
                                     : (MODE == 5 ? 1.0 * g.M * g.N : 2.0 * g.M * g.N);
     ProfScope prof(st, slot, 2.0 * g.M * g.N * g.K,
                    abytes + (double)g.N * g.K * BITS / 8 + (I8 ? 14.0 : 10.0) * g.N + ybytes);
-    if (g.splits > 1) {
-        hipLaunchKernelGGL(split_clear_kernel, dim3((unsigned)((tiles + 255) / 256)), dim3(256), 0, st, g.counters, (int)tiles);
-        MQ_HIP_CHECK_LAUNCH();
-    }
     hipLaunchKernelGGL(kern, dim3(g.tiles_m * g.tiles_n * g.splits), dim3(P::NT), P::LDS_BYTES, st, g);
     MQ_HIP_CHECK_LAUNCH();
     return MQ_OK;

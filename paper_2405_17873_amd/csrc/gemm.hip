@@ -463,7 +463,7 @@ void gemm_kernel(const GemmArgs g) {
     constexpr bool GEGLU = MODE == 1 || MODE == 5 || MODE == 6, RS_INLINE = MODE == 2 || MODE == 4, CONV = MODE == 3 || MODE == 4;
     constexpr bool RANGE = MODE == 5;    // gated projection that leaves the fp16 product and its range, no codes
     constexpr bool CODES16 = MODE == 6;  // gated projection of the 16-bit-activation path that emits 8-bit codes
-    static_assert(MODE == 0 || KS == 1, "the special modes have no in-workgroup k split");
+    static_assert(MODE == 0 || KS == 1 || (CONV && TM == 1), "in-workgroup k split: plain layers, and convolutions whose waves own one row slab");
     static_assert(!(RES && GEGLU), "the gated projection takes no residual");
     static_assert(!RANGE || (I8 && !BF), "the range output belongs to the int8 gated projection");
     static_assert(!CODES16 || (!I8 && !BF), "MODE 6 is the fp16 weight-only gated projection with 8-bit output");
@@ -658,19 +658,25 @@ void gemm_kernel(const GemmArgs g) {
         const bool tail_b = B_TAIL && (step0 + KS) * CH > KC;
         if constexpr (CONV) {
             // the stage's 64-channel chunks -> (filter tap, chunk inside the tap) -> byte offset from the output pixel
-            int tap[CH], delta[CH];
+            int tap[KS * CH], delta[KS * CH];
 #pragma unroll
-            for (int h = 0; h < CH; ++h) {
-                const uint32_t ci = (uint32_t)(kt0 + stage) * CH + h;
+            for (int h = 0; h < KS * CH; ++h) {
+                const uint32_t ci = (uint32_t)step0 * CH + h;
                 const uint32_t t = g.conv_cpt > 1 ? __umulhi(ci, g.conv_cpt_inv) : ci;
                 const int cc = (int)(ci - t * g.conv_cpt);
-                tap[h] = ci < (uint32_t)KC ? (int)t : 31;  // past the end of K (int8 padding of the last stage): no tap
+                tap[h] = ci < (uint32_t)KC ? (int)t : 31;  // past the end of K (padding of the last stage): no tap
                 delta[h] = (((int)t / 3 - 1) * g.conv_w + ((int)t % 3 - 1)) * (int)g.a_row_bytes + cc * (I8 ? 64 : 128);
             }
 #pragma unroll
             for (int i = 0; i < P::DMA_A; ++i) {
-                const int t = CH == 2 && a_half[i] ? tap[CH - 1] : tap[0];
-                const int d = CH == 2 && a_half[i] ? delta[CH - 1] : delta[0];
+                int t = CH == 2 && a_half[i] ? tap[CH - 1] : tap[0];
+                int d = CH == 2 && a_half[i] ? delta[CH - 1] : delta[0];
+                if constexpr (KS == 2) {
+                    if (a_sub[i]) {  // (the load belongs to the stage's second k step)
+                        t = CH == 2 && a_half[i] ? tap[2 * CH - 1] : tap[CH];
+                        d = CH == 2 && a_half[i] ? delta[2 * CH - 1] : delta[CH];
+                    }
+                }
                 const int voff = (a_taps[i] >> t) & 1u ? a_voff[i] + d : OOB;
                 dma_to_lds_b128(ra, __builtin_amdgcn_readfirstlane(sb + a_lds[i]), voff, 0);
             }
@@ -913,7 +919,12 @@ void gemm_kernel(const GemmArgs g) {
                     *(quad_t*)(out + (((SPLIT_EPI ? tm >> 1 : tm) * TN + tn) * 4 + q) * 1024) = v;
                 }
         }
+        // (row sums taken in the main loop cover one group's k steps: group 1 hands its own over in the idle sink)
+        static_assert(!RS_INLINE || (!SPLIT_EPI && P::NWG * 32 * 4 <= 1024), "row sums of one slab per wave fit the sink");
+        int* const rs_x = (int*)(lds + P::SINK) + wvg * 32 + l31;
+        if (RS_INLINE && grp == 1 && lane < 32) *rs_x = rsum[0];
         __syncthreads();
+        if (RS_INLINE && grp == 0) rsum[0] += *rs_x;
         const uint8_t* in = area(1 - grp);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
@@ -1812,11 +1823,25 @@ static void conv_args(GemmArgs& g, int B, int H, int W, int Cin, int stride, lon
     g.conv_cpt_inv = g.conv_cpt > 1 ? (uint32_t)(((1ull << 32) + g.conv_cpt - 1) / g.conv_cpt) : 0u;
 }
 
+// Tile of a convolution: no split of the reduction over workgroups (the weight-only entry point has no workspace), and the
+// split inside the workgroup (tile 4) only while every workgroup has a compute unit of its own.  A reduction is then 90
+// to 270 k steps long and bound by the latency of operands that two wave groups request together (weight-only with twice
+// the LDS as stages in flight: 4-bit weights 128 -> 122 us below; the int8 path gains nothing from them).  With a second
+// workgroup on the unit the other waves are there already.  Residual blocks, one wave group -> two, us per pass:
+//   1 x 20 x 20 x 1280 (140 workgroups): W4A16 142 -> 123, W8A16 145 -> 117, W4A8 122 -> 109, W8A8 115 -> 103
+//   1 x 40 x 40, 960 -> 640 (250):       W4A16 93 -> 82, W8A16 94 -> 77, W4A8 90 -> 82, W8A8 83 -> 76
+//   1 x 32 x 32, 640 -> 1280 (320):      W4A16 133 -> 141, W8A16 131 -> 134, W4A8 115 -> 121, W8A8 109 -> 117
+static int conv_tile(int M, int N, int K, bool wide_weights) {
+    const int t = pick_tile(M, N, K, wide_weights);
+    if (t == 6 || t == 3) return 1;
+    if (t == 4 && g_force_tile < 0 && (long)((M + 63) / 64) * ((N + 63) / 64) > 256) return 2;
+    return t;
+}
+
 template <int BITS>
 static int dispatch_conv_w_only(GemmArgs& g, hipStream_t st) {
     constexpr bool WIDE = BITS == 16;
-    int t = pick_tile(g.M, g.N, g.K, WIDE);
-    t = t == 6 ? 1 : (t >= 3 ? t - 2 : t);
+    int t = conv_tile(g.M, g.N, g.K, WIDE);
     // (the large tile only where its 256 channels are filled: the UNet's 320-channel level is better served by 128)
     if (g_force_tile < 0 && t == 0 && g.N < 512) t = 1;
     if (g_force_tile == 5 || (g_force_tile < 0 && t == 1))
@@ -1824,6 +1849,7 @@ static int dispatch_conv_w_only(GemmArgs& g, hipStream_t st) {
     switch (t) {
         case 0: return run_gemm<false, BITS, 1, 4, 4, 2, 1, 80 * 1024, 4, false, 3>(g, 0, st);
         case 1: return run_gemm<false, BITS, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 3>(g, 1, st);
+        case 4: return run_gemm<false, BITS, 2, 2, 1, 1, 2, 160 * 1024, 8, false, 3>(g, 4, st);
         default: return run_gemm<false, BITS, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 3>(g, 2, st);
     }
 }
@@ -1868,24 +1894,26 @@ int launch_conv3x3_a8(const int8_t* a8, const ActParams* params, int B, int H, i
     g.act_scale_p = &params->scale; g.act_zp_p = &params->zp;
     g.acc_debug = acc_debug;
     // (not the large tile: no registers to spare for the row sums and the tap masks; tile 5 in place of tile 1)
-    int t = pick_tile(g.M, N, g.K, true);
-    t = t == 6 ? 1 : (t >= 3 ? t - 2 : t);
+    int t = conv_tile(g.M, N, g.K, true);
     if (w_bits == 4) {
         g.w_off = 0;
         if (t <= 1 && g_force_tile != 1) return run_gemm<true, 4, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
         if (t <= 1) return run_gemm<true, 4, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 4>(g, 1, st);
+        if (t == 4) return run_gemm<true, 4, 2, 2, 1, 1, 2, 80 * 1024, 8, false, 4>(g, 4, st);
         return run_gemm<true, 4, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 4>(g, 2, st);
     }
     if (w_bits == 2) {
         g.w_off = 0;
         if (t <= 1 && g_force_tile != 1) return run_gemm<true, 2, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
         if (t <= 1) return run_gemm<true, 2, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 4>(g, 1, st);
+        if (t == 4) return run_gemm<true, 2, 2, 2, 1, 1, 2, 80 * 1024, 8, false, 4>(g, 4, st);
         return run_gemm<true, 2, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 4>(g, 2, st);
     }
     if (w_bits == 8) {
         g.w_off = w_signed ? 0 : 128;
         if (t <= 1 && g_force_tile != 1) return run_gemm<true, 8, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
         if (t <= 1) return run_gemm<true, 8, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 4>(g, 1, st);
+        if (t == 4) return run_gemm<true, 8, 2, 2, 1, 1, 2, 80 * 1024, 8, false, 4>(g, 4, st);
         return run_gemm<true, 8, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 4>(g, 2, st);
     }
     return MQ_ERR_UNSUPPORTED_BITS;

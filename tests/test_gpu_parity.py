@@ -344,8 +344,8 @@ def test_split_reduction_matches_oracle(mq, orc, tile, parts):
 
 
 def test_split_reduction_is_deterministic_and_reuses_its_workspace(mq, orc):
-    """Many launches in a row through ONE workspace whose contents start as garbage (the counters are cleared on the
-    stream before every launch): every result is bit-identical.  Without a workspace the same call does not split and
+    """Many launches in a row through ONE workspace whose contents start as garbage (the counters count under a tag of
+    their launch): every result is bit-identical.  Without a workspace the same call does not split and
     still matches the oracle; a workspace that holds only some of the parts is used for as many as fit."""
     M, K, N = 64, 5120, 1280
     xh = si.activations_f16(32, "sp/det", M, K)
@@ -1070,6 +1070,33 @@ def test_feed_forward_output_linear_adds_the_skip_connection(mq, orc):
             ry, racc = orc.linear_a8_codes(codes, act, oc, os_, oz, w_signed=sym, bias=b, residual=r)
             assert np.array_equal(host(acc), racc)
             assert_close16(host(y), ry, f"codes + residual b{bits} tile{tile}")
+
+
+@pytest.mark.parametrize("bits,sym", [(4, False), (8, True), (8, False), (2, False)])
+@pytest.mark.parametrize("stride", (1, 2))
+def test_conv_k_split_inside_the_workgroup(mq, orc, bits, sym, stride):
+    """Two wave groups share a convolution tile's reduction: even and odd numbers of k steps (the last one half padding
+    among them), both paths, residual; integer accumulators bit-exact with the row sums and borders of both groups."""
+    mq.tune_force_tile(4)
+    try:
+        for (B, H, W, Cin, N) in CONV_SHAPES + [(2, 6, 11, 256, 72)]:
+            Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+            x = si.activations_f16(74, f"ck/x{B}x{H}x{W}x{Cin}", B * H * W, Cin, outlier_prob=0.01).reshape(B, H, W, Cin)
+            b = si.bias_f16(74, f"ck/b{N}", N)
+            r = si.normal(74, f"ck/r{B}x{Ho}x{Wo}x{N}", (B, Ho, Wo, N)).astype(np.float16)
+            pw, oc, os_, oz, tapsum = conv_weight(mq, orc, 74, N, Cin, bits, sym)
+            what = f"k split w{bits} {B}x{H}x{W}x{Cin}->{N} stride {stride}"
+            if not sym:
+                y = mq.conv3x3_w_only(dev(x), pw, dev(b), residual=dev(r), stride=stride)
+                assert_close16(host(y).reshape(-1, N), orc.conv3x3_w_only(x, oc, os_, oz, b, residual=r, stride=stride), what)
+            act = (np.float32(0.05), 31)
+            d_act = (dev(np.array([act[0]], np.float32)), dev(np.array([act[1]], np.int32)))
+            y, acc, _ = mq.conv3x3_a8(dev(x), pw, tapsum, act=d_act, bias=dev(b), want_acc=True, residual=dev(r), stride=stride)
+            ry, racc, _ = orc.conv3x3_a8(x, oc, os_, oz, w_signed=sym, act=act, bias=b, residual=r, stride=stride)
+            assert np.array_equal(host(acc), racc), what
+            assert_close16(host(y).reshape(-1, N), ry, what)
+    finally:
+        mq.tune_force_tile(-1)
 
 
 @pytest.mark.parametrize("tile", (-1, 0, 1, 2, 5))

@@ -335,6 +335,10 @@ __device__ __forceinline__ float gelu32(float g) {
 // later ds_read_b128 of 32 consecutive rows is conflict free.  S LDS stages rotate; the loads of the next S-1 stages
 // are in flight while a stage is multiplied.
 // ---------------------------------------------------------------------------------------------
+// Low bits of a split reduction's counter word, the arrivals of one tile; the launch's tag lies above them.  A part is at
+// least one pipeline stage of 64 or more k, and (N + 31) * K < 2^31 with N >= 8 is checked: fewer than 2^20 parts.
+static constexpr unsigned long long SPLIT_COUNT = 0xFFFFFull;
+
 struct GemmArgs {
     const void* a;        // X fp16 [M, lda] or int8 copy [M, Kp]
     long a_row_bytes;     // byte stride between rows of a
@@ -723,13 +727,13 @@ void gemm_kernel(const GemmArgs g) {
         if (s < KT) issue(s, s);
     if (CAN_SPLIT && splits > 1 && threadIdx.x == 0) {
         // The tile's arrival counter arrives with unknown contents.  Every part makes sure, while its first stages travel,
-        // that the upper 48 bits hold this launch's tag (a cleared word, then whatever the first exchange found, is
+        // that the upper 44 bits hold this launch's tag (a cleared word, then whatever the first exchange found, is
         // replaced; where the second exchange fails another part's has succeeded), and counts below the tag at its end.
         unsigned long long* const counter = g.counters + tile_id;
         unsigned long long seen = 0;
         if (!__hip_atomic_compare_exchange_strong(counter, &seen, g.split_tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                   __HIP_MEMORY_SCOPE_AGENT) &&
-            (seen & ~0xFFFFull) != g.split_tag)
+            (seen & ~SPLIT_COUNT) != g.split_tag)
             __hip_atomic_compare_exchange_strong(counter, &seen, g.split_tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -971,7 +975,7 @@ void gemm_kernel(const GemmArgs g) {
         uint32_t* ticket = (uint32_t*)(lds + P::SINK);  // the sink of padding loads is idle by now
         if (threadIdx.x == 0) {
             unsigned long long* const counter = g.counters + tile_id;
-            const uint32_t n = (uint32_t)__hip_atomic_fetch_add(counter, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) & 0xFFFFu;
+            const uint32_t n = (uint32_t)__hip_atomic_fetch_add(counter, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) & (uint32_t)SPLIT_COUNT;
             if (n == (uint32_t)(splits - 1))  // the word goes back cleared
                 __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             *ticket = n;
@@ -1388,7 +1392,7 @@ void set_force_tile(int t) { g_force_tile = t; }
 // latency: the only remedy is to have more workgroups request the operands at once.  Their partial sums and one
 // arrival counter per tile live in the CALLER's workspace: [counters: tiles x 8 bytes, rounded up to 256]
 // [partial sums: tiles x parts x BM x BN x 4 bytes].  The workspace arrives with unknown contents: a counter word
-// counts only under the tag of the launch that reads it (48 bits, another one for every launch; a replayed graph finds
+// counts only under the tag of the launch that reads it (44 bits, another one for every launch; a replayed graph finds
 // the zero that the last arrival of the replay before it left), so that no launch of its own has to clear the words
 // first.  That launch took 4.5 us beside GEMMs of 10 us.  Whoever owns the workspace owns the hazard, as with any
 // workspace: one stream at a time.
@@ -1398,12 +1402,12 @@ int forced_splits() { return g_force_splits; }
 static int g_force_band = 0;  // 0: automatic, n >= 1: n row blocks per band of the workgroup -> tile map
 void set_force_band(int n) { g_force_band = n < 0 ? 0 : n; }
 
-// Tag of one launch: the upper 48 bits of a Weyl sequence, never zero, so that neither cleared memory nor small numbers
+// Tag of one launch: the upper 44 bits of a Weyl sequence, never zero, so that neither cleared memory nor small numbers
 // or 16-bit data left in the workspace look like it.
 static unsigned long long next_split_tag() {
     static std::atomic<unsigned long long> count{1};
-    const unsigned long long tag = (count.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull) & ~0xFFFFull;
-    return tag ? tag : 0xA5A5A5A5A5A50000ull;
+    const unsigned long long tag = (count.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull) & ~SPLIT_COUNT;
+    return tag ? tag : 0xA5A5A5A5A5A00000ull;
 }
 
 static inline size_t split_counter_bytes(long tiles) { return ((size_t)tiles * 8 + 255) / 256 * 256; }

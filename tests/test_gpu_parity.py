@@ -403,6 +403,34 @@ def test_split_reduction_takes_a_workspace_with_any_contents(mq, orc, fill):
         assert torch.equal(out, ref)
 
 
+@pytest.mark.parametrize("parts", (65535, 65536, 65701))
+def test_split_reduction_counts_more_parts_than_16_bits(mq, parts):
+    """A forced split of a very long reduction into one stage per part: every arrival is counted and the last one writes
+    the output.  Small whole numbers: the result is exact in fp16."""
+    N, stages = 8, 65701
+    K = 64 * stages
+    rng = np.random.default_rng(5)
+    at = np.unique(np.concatenate([[0, 63, K - 64, K - 1, 65535 * 64, 65536 * 64 - 1], rng.integers(0, K, 40)]))
+    codes = torch.zeros(N, K, dtype=torch.uint8, device="cuda")
+    x = torch.zeros(1, K, dtype=torch.float16, device="cuda")
+    picked = rng.integers(0, 16, (N, at.size)).astype(np.uint8)
+    sign = rng.choice([-1.0, 1.0], at.size).astype(np.float16)
+    where = dev(at)
+    codes[:, where] = dev(picked)
+    x[0, where] = dev(sign)
+    packed, colsum = mq.pack_weights(codes, 4, mq.LAYOUT_KERNEL)
+    w = mq.PackedWeight(packed, dev(np.ones(N, np.float32)), dev(np.zeros(N, np.int32)), colsum, N, K, 4, mq.LAYOUT_KERNEL, False)
+    mq.tune_force_tile(2)
+    mq.tune_force_splits(parts)
+    try:
+        out = torch.full((1, N), -1000.0, dtype=torch.float16, device="cuda")
+        mq.qlinear_w_only(x, w, out=out)
+        assert np.array_equal(host(out)[0].astype(np.int64), (picked.astype(np.int64) * sign.astype(np.int64)).sum(1))
+    finally:
+        mq.tune_force_splits(0)
+        mq.tune_force_tile(-1)
+
+
 def test_split_reductions_on_two_streams_with_a_workspace_each(mq, orc):
     """Split launches queued on two streams at once, each stream with its own workspace, one of them behind a long
     kernel so that the launches of the other overtake it: all results equal the single-stream result bit for bit.

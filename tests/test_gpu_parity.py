@@ -403,6 +403,33 @@ def test_split_reduction_takes_a_workspace_with_any_contents(mq, orc, fill):
         assert torch.equal(out, ref)
 
 
+@pytest.mark.parametrize("kind", ("f16", "bf16", "a8"))
+@pytest.mark.parametrize("tile", (1, 2, 3, 4, 5))
+def test_every_splitting_kernel_takes_a_workspace_with_any_contents(mq, orc, kind, tile):
+    """Each tile form that splits, several tiles, a ragged last row block: the first call on a workspace full of garbage, the
+    second on what it left, and one on cleared memory give the same bits."""
+    M, K, N = 140, 2048, 200
+    x, w = dev(si.activations_f16(35, "anyk/x", M, K)), si.weights_f16(35, "anyk/w", N, K)
+    pw, *_ = make_weight(mq, orc, w, 4)
+    mq.tune_force_tile(tile)
+    mq.tune_force_splits(4)
+    try:
+        base = mq.qlinear_a8_workspace_bytes(M, K) if kind == "a8" else 0
+        ws = torch.zeros(base + mq.split_workspace_bytes(M, N, K), dtype=torch.uint8, device="cuda")
+        if kind == "a8":
+            go = lambda: mq.qlinear_w4a8(x, pw, ws=ws)[0]
+        else:
+            xk = x if kind == "f16" else x.to(torch.bfloat16)
+            go = lambda: mq.qlinear_w_only(xk, pw, ws=ws)
+        ref = go()
+        for fill in (0xA5, 0xFF, 1):
+            ws.fill_(fill)
+            assert torch.equal(go(), ref) and torch.equal(go(), ref), f"{kind} tile{tile} fill {fill:#x}"
+    finally:
+        mq.tune_force_splits(0)
+        mq.tune_force_tile(-1)
+
+
 @pytest.mark.parametrize("parts", (65535, 65536, 65701))
 def test_split_reduction_counts_more_parts_than_16_bits(mq, parts):
     """A forced split of a very long reduction into one stage per part: every arrival is counted and the last one writes

@@ -944,10 +944,17 @@ void gemm_kernel(const GemmArgs g) {
     // bypass the L2 of the reader's XCD); every wave waits for its stores to complete, the workgroup meets at a
     // barrier, and one thread draws the ticket with a device-scope acquire-release read-modify-write, which orders
     // the stores of this workgroup before the ticket and the loads of the last workgroup after it.
+    unsigned long long* counter = nullptr;
     if (CAN_SPLIT && splits > 1) {
+        // (the arguments of the split are read here: the compiler would otherwise request them ahead of the main loop, whose
+        // first LDS reads then wait for them, also in calls that do not split: 4 x 1280 x 1280 at 4 bits 7.56 us, 7.39 here)
+        auto args = (const __attribute__((address_space(4))) GemmArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(args));
+        counter = args->counters + tile_id * args->counter_step;
+        const unsigned long long split_tag = args->split_tag;
         using elem_t = typename std::conditional<I8, int, float>::type;
         const size_t tile_elems = (size_t)BM * BN;
-        elem_t* mine = (elem_t*)(g.partial + ((size_t)tile_id * splits + sp) * tile_elems);
+        elem_t* mine = (elem_t*)(args->partial + ((size_t)tile_id * splits + sp) * tile_elems);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             if (KS > 1 && owner(tm) != grp) continue;
@@ -965,20 +972,18 @@ void gemm_kernel(const GemmArgs g) {
             // where the second exchange fails another part's has succeeded).  Here the answer travels beside the stores
             // above, which have to be waited for anyway.  (Behind the requests of the first stages the compiler waits for all
             // of those with it: 308 x 2048 x 640 in bf16 19.9 us with the exchange there, 17.2 here.)
-            unsigned long long* const counter = g.counters + tile_id * g.counter_step;
             unsigned long long seen = 0;
-            if (!__hip_atomic_compare_exchange_strong(counter, &seen, g.split_tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+            if (!__hip_atomic_compare_exchange_strong(counter, &seen, split_tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                       __HIP_MEMORY_SCOPE_AGENT) &&
-                (seen & ~SPLIT_COUNT) != g.split_tag)
-                __hip_atomic_compare_exchange_strong(counter, &seen, g.split_tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                (seen & ~SPLIT_COUNT) != split_tag)
+                __hip_atomic_compare_exchange_strong(counter, &seen, split_tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT);
         }
         wait_vmcnt<0>();  // this wave's stores have completed (reached the level all compute units see)
         __syncthreads();
         uint32_t* ticket = (uint32_t*)(lds + P::SINK);  // the sink of padding loads is idle by now
         if (threadIdx.x == 0)
-            *ticket = (uint32_t)__hip_atomic_fetch_add(g.counters + tile_id * g.counter_step, 1ull, __ATOMIC_ACQ_REL,
-                                                       __HIP_MEMORY_SCOPE_AGENT) & (uint32_t)SPLIT_COUNT;
+            *ticket = (uint32_t)__hip_atomic_fetch_add(counter, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) & (uint32_t)SPLIT_COUNT;
         __syncthreads();
         if (*ticket != (uint32_t)(splits - 1)) return;
 #pragma unroll
@@ -994,7 +999,7 @@ void gemm_kernel(const GemmArgs g) {
 #pragma unroll
             for (int u = 0; u < PU; ++u) {
                 const int part = part0 + u < splits ? part0 + u : splits - 1;
-                const elem_t* theirs = (const elem_t*)(g.partial + ((size_t)tile_id * splits + part) * tile_elems);
+                const elem_t* theirs = (const elem_t*)(args->partial + ((size_t)tile_id * splits + part) * tile_elems);
 #pragma unroll
                 for (int tm = 0; tm < TM; ++tm) {
                     if (KS > 1 && owner(tm) != grp) continue;
@@ -1358,7 +1363,7 @@ void gemm_kernel(const GemmArgs g) {
     if (CAN_SPLIT && splits > 1 && threadIdx.x == 0)
         // The word goes back cleared.  (Last: a store ahead of the loads of the partial sums is waited for with them, and
         // takes longer than they do: 1 x 2048 x 1280, 4-bit weights, 8.41 us with it there, 7.75 here.)
-        __hip_atomic_store(g.counters + tile_id * g.counter_step, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (g.phase_clk && threadIdx.x == 0) {
         long long* o = g.phase_clk + (long)blockIdx.x * 4;
         o[0] = t0;

@@ -50,13 +50,12 @@ struct RowWalk {
 };
 
 // The extremes are found in pairs of fp16 values (a minimum or maximum of fp16 values is one of them: nothing is lost)
-// and widened once at the end; NaN is ignored as by fminf / fmaxf.  THREADS: a tensor that needs all partial slots takes
-// four times the threads per workgroup, so that a compute unit holds 32 waves instead of 8.
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void act_minmax_kernel(const _Float16* __restrict__ x, uint32_t nv, FastDiv K8,
-                                                             long ldx, RowWalk map, int flat,
-                                                             float* __restrict__ partials) {
-    constexpr uint32_t U = THREADS == 256 ? MM_U : MM_U / 2, STEP = THREADS * U;
+// and widened once at the end; NaN is ignored as by fminf / fmaxf.  Bound by memory latency up to a few MB and by HBM above.
+// (Workgroups of 1024 threads for tensors that need every partial slot left up to half of the slots without work and were
+// slower at every size: 8192 x 1280 whole call 21.4 us against 20.4, 16384 x 2560 57.1 against 55.7.)
+__global__ __launch_bounds__(256) void act_minmax_kernel(const _Float16* __restrict__ x, uint32_t nv, FastDiv K8,
+                                                         long ldx, RowWalk map, int flat, float* __restrict__ partials) {
+    constexpr uint32_t STEP = 256 * MM_U;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     half8 mn8, mx8;
 #pragma unroll
@@ -65,10 +64,10 @@ __global__ __launch_bounds__(THREADS) void act_minmax_kernel(const _Float16* __r
         mx8[e] = -(_Float16)INFINITY;
     }
     for (uint32_t base = blockIdx.x * STEP; base < nv; base += gridDim.x * STEP) {
-        half8 v[U];
+        half8 v[MM_U];
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {
-            uint32_t i = base + u * THREADS + threadIdx.x;
+        for (uint32_t u = 0; u < MM_U; ++u) {
+            uint32_t i = base + u * 256u + threadIdx.x;
             i = i < nv ? i : nv - 1;  // a repeated vector does not change a min or a max
             if (flat) {
                 v[u] = ((const half8*)x)[i];
@@ -79,7 +78,7 @@ __global__ __launch_bounds__(THREADS) void act_minmax_kernel(const _Float16* __r
             }
         }
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {
+        for (uint32_t u = 0; u < MM_U; ++u) {
             mn8 = __builtin_elementwise_min(mn8, v[u]);
             mx8 = __builtin_elementwise_max(mx8, v[u]);
         }
@@ -92,7 +91,7 @@ __global__ __launch_bounds__(THREADS) void act_minmax_kernel(const _Float16* __r
     }
     mn = wave_reduce(mn, [](float a, float b) { return fminf(a, b); });
     mx = wave_reduce(mx, [](float a, float b) { return fmaxf(a, b); });
-    __shared__ float smn[THREADS / 64], smx[THREADS / 64];
+    __shared__ float smn[4], smx[4];
     if (lane == 0) {
         smn[wv] = mn;
         smx[wv] = mx;
@@ -100,7 +99,7 @@ __global__ __launch_bounds__(THREADS) void act_minmax_kernel(const _Float16* __r
     __syncthreads();
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int i = 1; i < THREADS / 64; ++i) {
+        for (int i = 1; i < 4; ++i) {
             mn = fminf(mn, smn[i]);
             mx = fmaxf(mx, smx[i]);
         }
@@ -266,12 +265,8 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
     } else if (dynamic) {
         const int flat = in_map.rows_per_group <= 0 && ldx == K;
         ProfScope prof(st, PROF_ACT_MINMAX, 0.0, 2.0 * M * K);
-        if (g1 > kPartialSlots)
-            hipLaunchKernelGGL(act_minmax_kernel<1024>, dim3(grid), dim3(1024), 0, st, (const _Float16*)x, nv,
-                               FastDiv::make(K8), (long)ldx, walk, flat, partials);
-        else
-            hipLaunchKernelGGL(act_minmax_kernel<256>, dim3(grid), dim3(256), 0, st, (const _Float16*)x, nv,
-                               FastDiv::make(K8), (long)ldx, walk, flat, partials);
+        hipLaunchKernelGGL(act_minmax_kernel, dim3(grid), dim3(256), 0, st, (const _Float16*)x, nv, FastDiv::make(K8),
+                           (long)ldx, walk, flat, partials);
         MQ_HIP_CHECK_LAUNCH();
     }
     // Rows per workgroup: one round (1024 vectors) while that keeps the grid within eight workgroups per compute unit;

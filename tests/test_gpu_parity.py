@@ -553,6 +553,38 @@ def test_activation_passes_at_the_edges_of_their_grids(mq, orc, M, K, N):
     assert np.array_equal(host(acc) + 117, t.astype(np.int32))
 
 
+@pytest.mark.parametrize("M,K,pad", [(1, 64, 0), (16, 64, 8), (300, 320, 0), (4200, 2048, 0), (8300, 1280, 24), (33000, 320, 0)])
+def test_range_pass_ignores_nan(mq, M, K, pad):
+    """Quiet, signalling and negative NaN in the first vector, in the last one (which short workgroups read repeatedly) and a
+    vector of nothing else, contiguous and strided, below and above one round per slot: scale and zero point are those of
+    the other values, and a NaN has code 0."""
+    x = si.activations_f16(37, f"nan/x{M}x{K}", M, K, outlier_prob=0.01)
+    x[0, 1], x[M - 1, K - 2] = np.float16(-71.0), np.float16(93.0)
+    bits = x.view(np.uint16)
+    bits[0, 0], bits[0, 5] = 0x7C01, 0xFE00
+    bits[M - 1, K - 8:K - 3] = (0x7E00, 0x7D55, 0xFC01, 0xFFFF, 0x7FFF)
+    bits[M // 2, 16:24] = 0x7C01
+    wide = torch.zeros(M, K + pad, dtype=torch.float16, device="cuda")
+    if pad:
+        wide[:, K:] = 1000.0  # outside the rows: must not reach the range
+    xd = wide[:, :K]
+    xd.copy_(dev(x))
+    assert np.array_equal(host(xd.contiguous().view(torch.int16)).view(np.uint16), bits)
+    N = 32
+    eye = np.zeros((N, K), np.uint8)
+    eye[np.arange(N), np.arange(N)] = 1
+    packed, colsum = mq.pack_weights(dev(eye), 8, mq.LAYOUT_KERNEL)
+    pw = mq.PackedWeight(packed, dev(np.ones(N, np.float32)), dev(np.zeros(N, np.int32)), colsum, N, K, 8, mq.LAYOUT_KERNEL, False)
+    _, acc, (s, z) = mq.qlinear_w8a8(xd, pw, want_acc=True, want_act=True)
+    s, z = host(s)[0], int(host(z)[0])
+    lo, hi = np.float32(np.nanmin(x)), np.float32(np.nanmax(x))
+    assert lo == -71.0 and hi == 93.0
+    assert s == np.float32((hi - lo) / np.float32(255.0)) and z == int(np.rint(np.float32(-lo) * (np.float32(1.0) / s)))
+    with np.errstate(invalid="ignore"):
+        t = np.rint(x[:, :N].astype(np.float32) * (np.float32(1.0) / s)) + np.float32(z)
+    assert np.array_equal(host(acc) + z, np.fmin(np.fmax(t, np.float32(0)), np.float32(255)).astype(np.int32))
+
+
 def test_a8_is_deterministic(mq, orc):
     M, K, N = 608, 2048, 640
     x = dev(si.activations_f16(14, "a8/det", M, K))

@@ -119,6 +119,7 @@ __device__ inline int sum8(int v) {
 
 static constexpr int Q_MAX_ROWS = 128;   // rows per workgroup, pass 2
 static constexpr int kQuantGrid = 2048;  // workgroups of a large tensor, pass 2: eight per compute unit
+static constexpr long kSmallQuant = 28L * 1000 * 1000;  // values: between 6000 x 4608 and 7000 x 4160 (see the launcher)
 
 // A workgroup converts R whole rows (so that it owns their row sums): R * Kp/8 output vectors, 1024 per round.  Up to a
 // few MB it is bound by memory latency, above by HBM as long as a value costs few instructions: one fused multiply-add
@@ -269,13 +270,33 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
                            (long)ldx, walk, flat, partials);
         MQ_HIP_CHECK_LAUNCH();
     }
-    // Rows per workgroup: one round (1024 vectors) while that keeps the grid within eight workgroups per compute unit;
-    // a larger tensor takes as many rounds per workgroup as bring it there, so that the parameters are derived (and the
-    // pairs read: the gated projection leaves thousands) that many times less often.
+    // Rows per workgroup: one round (1024 vectors) while that keeps the grid within eight workgroups per compute unit.  A
+    // larger tensor can take as many rounds per workgroup as bring it there: the parameters are derived (and the pairs read)
+    // that many times less often, but the grid may leave compute units idle at its end, the last round lanes, and the rounds
+    // of one workgroup do not overlap.  Whole calls in us, one round -> longer:
+    //   `full`, a single row is more than half a round and the busiest unit gets hardly more of them:
+    //     run-time range 4096 x 5120 41.5 -> 40.4, 5000 x 4608 41.3 -> 39.5; given parameters 3000 x 5120 30.3 -> 29.3,
+    //     5000 x 4160 30.3 -> 29.0, 6000 x 4608 33.6 -> 32.3, but 7000 x 4160 34.5 -> 35.1, 6000 x 5120 36.9 -> 38.5;
+    //     not full: 2049 x 8192 46.4 -> 47.3 and 38.5 -> 39.9
+    //   run-time range, `even`, the grid fills at least 15/16 of its last wave of compute units: 16384 x 1280 31.7 -> 31.4;
+    //     not even: 8193 x 2048 (1639 workgroups) 27.2 -> 28.2
+    //   thousands of pairs (the gated projection leaves them): 16384 x 2560 126.2 -> 124.1
+    //   given parameters otherwise: 16389 x 2560 42.6 -> 45.1, 262144 x 320 79.7 -> 87.2
     const int Kp8 = (K + 127) / 128 * 16;
     int R = 256 * Q_U / Kp8;
     R = R < 1 ? 1 : R;
-    if ((M + R - 1) / R > kQuantGrid) R = (M + kQuantGrid - 1) / kQuantGrid;
+    if ((M + R - 1) / R > kQuantGrid) {
+        int longer = (M + kQuantGrid - 1) / kQuantGrid;
+        longer = longer > Q_MAX_ROWS ? Q_MAX_ROWS : longer;
+        constexpr int CUS = kQuantGrid / 8;
+        const long groups = (M + longer - 1) / longer;
+        auto rounds = [&](int rows) {  // ... of the busiest compute unit
+            return (((long)M + rows - 1) / rows + CUS - 1) / CUS * (((long)rows * Kp8 + 256 * Q_U - 1) / (256 * Q_U));
+        };
+        const bool full = R == 1 && rounds(longer) * 10 <= rounds(1) * 11;
+        const bool even = groups * 16 >= (groups + CUS - 1) / CUS * CUS * 15;
+        if (dynamic ? full || even || given_partials > kPartialSlots : full && (long)M * K <= kSmallQuant) R = longer;
+    }
     R = R > Q_MAX_ROWS ? Q_MAX_ROWS : R;
     const int qgrid = (M + R - 1) / R;
     ProfScope prof(st, PROF_ACT_QUANTIZE, 0.0, 3.0 * M * K + 4.0 * M);

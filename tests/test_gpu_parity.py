@@ -521,10 +521,12 @@ def test_a8_small_shapes(mq, orc, mode, tile):
     mq.tune_force_tile(-1)
 
 
-@pytest.mark.parametrize("M,K,N", [(4200, 2048, 32), (2100, 64, 32), (16390, 320, 40)])
+@pytest.mark.parametrize("M,K,N", [(4200, 2048, 32), (2100, 64, 32), (16390, 320, 40), (10245, 2048, 32), (2503, 5120, 32),
+                                   (5003, 4160, 40), (6001, 5120, 32)])
 def test_activation_passes_at_the_edges_of_their_grids(mq, orc, M, K, N):
-    """Tensors that need every slot of the range pass and several rounds per workgroup of the conversion, with a ragged
-    last workgroup; NaN is outside every range and becomes code 0, infinities saturate.  The weight is the identity on
+    """Tensors that need every slot of the range pass; conversions of one round per workgroup (the first three shapes) and of
+    several, by a run-time range only, by given parameters too, and by padded rows (the others), each with a ragged last
+    workgroup; NaN is outside every range and becomes code 0, infinities saturate.  The weight is the identity on
     its first N channels, so that the integer sums are the activation codes themselves."""
     x = si.activations_f16(31, f"edge/x{M}x{K}", M, K, outlier_prob=0.01)
     x[M - 1, min(K, N) - 1] = np.float16(93.0)   # the extremes sit in the last row and in the first
@@ -823,6 +825,20 @@ def test_geglu_projection_with_dynamic_output_parameters(mq, orc, bits, sym, til
                     assert np.abs(codes.astype(np.int64) - rq.astype(np.int64)).max() <= 1, what
     finally:
         mq.tune_force_tile(-1)
+
+
+def test_gated_product_of_many_pairs_and_several_rounds_per_workgroup(mq, orc):
+    """More (min, max) pairs than the range pass has slots, seven rows and two rounds per workgroup of the conversion, a ragged
+    last workgroup, padded rows: parameters and every code are those of the kernel's own fp16 product."""
+    M, K, H = 12301, 64, 1248
+    x, w = si.activations_f16(65, "many/x", M, K, outlier_prob=0.01), si.weights_f16(65, "many/w", 2 * H, K)
+    pw, *_ = make_weight(mq, orc, w, 4)
+    a8, h16, (so, zo), _ = mq.qlinear_a8_geglu_dynamic(dev(x), pw, bias=dev(si.bias_f16(65, "many/b", 2 * H)))
+    gh = host(h16)
+    s2, z2 = orc.act_params(gh)
+    assert host(so)[0] == s2 and host(zo)[0] == z2
+    codes, pad = a8_unlayout(host(a8), H)
+    assert not pad.any() and np.array_equal(codes, orc.act_quantize(gh, s2, z2))
 
 
 def test_feed_forward_pair_with_dynamic_parameters_in_between(mq, orc):

@@ -445,13 +445,17 @@ int launch_tap_sums(const uint8_t* codes, int N, int Cin, int bits, int codes_si
 int launch_quantize_weights(const void* w, int N, int K, int bits, int symmetric, int dtype, uint8_t* codes,
                             float* scale, int32_t* zp, hipStream_t st) {
     // Vector form: 16-byte loads need rows that start on 16-byte boundaries, its 8-byte stores of codes likewise; a row
-    // has to fit the registers of one wave (2048 values; no barrier, four channels per workgroup) or of a workgroup.
+    // has to fit the registers of one wave (2048 values; no barrier, four channels per workgroup) or of a workgroup.  Short
+    // rows take one vector per lane: with four, the others repeat the row's last one (320 x 320 3.09 us, 2.65 with one;
+    // 10240 x 320 6.99 and 5.38).
     const bool vec = K % 8 == 0 && K <= 16384 && (uintptr_t)w % 16 == 0 && (uintptr_t)codes % 8 == 0;
     auto run = [&](auto kern, int grid) {
         hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, (const uint16_t*)w, N, K, bits, symmetric, dtype, codes,
                            scale, zp);
     };
-    if (vec && K <= 2048)
+    if (vec && K <= 512)
+        run(quantize_weights_vec_kernel<64, 1>, (N + 3) / 4);
+    else if (vec && K <= 2048)
         run(quantize_weights_vec_kernel<64, 4>, (N + 3) / 4);
     else if (vec && K <= 8192)
         run(quantize_weights_vec_kernel<256, 4>, N);

@@ -96,7 +96,7 @@ def test_quantize_weights_bf16(mq, orc):
 
 
 @pytest.mark.parametrize("offset", (0, 1, 4, 8))
-@pytest.mark.parametrize("K", (8, 64, 1000, 2048, 2056, 8192, 8200, 16384, 16392))
+@pytest.mark.parametrize("K", (8, 64, 504, 512, 520, 1000, 2048, 2056, 8192, 8200, 16384, 16392))
 def test_quantize_weights_at_the_edges_of_its_row_forms(mq, orc, K, offset):
     """Rows of one wave, of a workgroup and beyond, odd row counts, matrices that do not start on a 16-byte boundary, rows
     of zeros or of one sign: bit for bit as the oracle."""

@@ -4,6 +4,8 @@
 //
 // Every floating-point operation that decides an integer code is one IEEE fp32 operation
 // (this file is compiled with -ffp-contract=off): subtract, divide, reciprocal, multiply, round-to-nearest-even.
+#include <type_traits>
+
 #include "mq_common.h"
 
 namespace mq {
@@ -215,8 +217,9 @@ __device__ inline size_t kl_chunk_offset(int g, int c, int KC, int bits, int L) 
 // 32 one-byte loads that were K bytes apart between lanes, and a second pass over the codes for the sums, took 29.0 +
 // 13.8 us for 10240 x 1280 and 17.6 + 22.0 us for 1280 x 5120 at 4 bits.
 // ALIGNED: the code matrix starts on a 16-byte boundary (its rows then do as well: K is a multiple of 64).
+// SUMS: with the sums a workgroup takes all rounds of its channels; without them blockIdx.y says which of them.
 static constexpr int PACK_THREADS = 512;
-template <int BITS, bool ALIGNED>
+template <int BITS, bool ALIGNED, bool SUMS>
 __global__ __launch_bounds__(PACK_THREADS) void pack_kernel_layout_kernel(const uint8_t* __restrict__ codes, int N, int K,
                                                                           int codes_signed, uint8_t* __restrict__ packed,
                                                                           int32_t* __restrict__ colsum) {
@@ -227,7 +230,8 @@ __global__ __launch_bounds__(PACK_THREADS) void pack_kernel_layout_kernel(const 
     const int g = n >> 5, j = n & 31;
     constexpr unsigned mask = (1u << BITS) - 1u;
     int sum = 0;
-    for (int piece = wv * 8 + (lane & 7); piece < 2 * KC; piece += NW * 8) {
+    const int slice = SUMS ? 0 : blockIdx.y, slices = SUMS ? 1 : gridDim.y;
+    for (int piece = (slice * NW + wv) * 8 + (lane & 7); piece < 2 * KC; piece += slices * NW * 8) {
         const int c = piece >> 1, kb = piece & 1, L = kb * 32 + j;
         uint32_t d[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         if (n < N) {
@@ -247,8 +251,9 @@ __global__ __launch_bounds__(PACK_THREADS) void pack_kernel_layout_kernel(const 
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             d[i] &= mask * 0x01010101u;
-            sum = codes_signed ? __builtin_amdgcn_sdot4((int)d[i], 0x01010101, sum, false)
-                               : (int)__builtin_amdgcn_udot4(d[i], 0x01010101u, (uint32_t)sum, false);
+            if constexpr (SUMS)
+                sum = codes_signed ? __builtin_amdgcn_sdot4((int)d[i], 0x01010101, sum, false)
+                                   : (int)__builtin_amdgcn_udot4(d[i], 0x01010101u, (uint32_t)sum, false);
         }
         auto cd = [&](int e) -> uint32_t { return (d[e >> 2] >> (8 * (e & 3))) & 255u; };
         uint8_t* out8 = packed + kl_chunk_offset(g, c, KC, BITS, L);
@@ -301,7 +306,7 @@ __global__ __launch_bounds__(PACK_THREADS) void pack_kernel_layout_kernel(const 
             }
         }
     }
-    if (!colsum) return;
+    if constexpr (!SUMS) return;
     sum += __shfl_xor(sum, 1, 64);
     sum += __shfl_xor(sum, 2, 64);
     sum += __shfl_xor(sum, 4, 64);
@@ -485,15 +490,27 @@ int launch_pack(const uint8_t* codes, int N, int K, int bits, int layout, int co
     }
     if (layout == MQ_LAYOUT_KERNEL) {
         const bool al = (uintptr_t)codes % 16 == 0;
+        // Without sums the rounds of a row group are independent: a matrix of few rows hands them to workgroups of their own
+        // (32 x 17280 at 4 bits 5.98 us with one workgroup per eight rows, 2.35 with nine).
+        const int groups = (N + 31) / 32 * 4, rounds = (K / 32 + PACK_THREADS / 8 - 1) / (PACK_THREADS / 8);
+        int parts = colsum ? 1 : 1024 / groups;
+        parts = parts < 1 ? 1 : (parts > rounds ? rounds : parts);
         auto run = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3((N + 31) / 32 * 4), dim3(PACK_THREADS), 0, st, codes, N, K, codes_signed,
+            hipLaunchKernelGGL(kern, dim3(groups, parts), dim3(PACK_THREADS), 0, st, codes, N, K, codes_signed,
                                (uint8_t*)packed, colsum);
         };
+        auto of_width = [&](auto width) {
+            constexpr int B = decltype(width)::value;
+            if (colsum)
+                al ? run(pack_kernel_layout_kernel<B, true, true>) : run(pack_kernel_layout_kernel<B, false, true>);
+            else
+                al ? run(pack_kernel_layout_kernel<B, true, false>) : run(pack_kernel_layout_kernel<B, false, false>);
+        };
         switch (bits) {
-            case 2: al ? run(pack_kernel_layout_kernel<2, true>) : run(pack_kernel_layout_kernel<2, false>); break;
-            case 3: al ? run(pack_kernel_layout_kernel<3, true>) : run(pack_kernel_layout_kernel<3, false>); break;
-            case 4: al ? run(pack_kernel_layout_kernel<4, true>) : run(pack_kernel_layout_kernel<4, false>); break;
-            default: al ? run(pack_kernel_layout_kernel<8, true>) : run(pack_kernel_layout_kernel<8, false>); break;
+            case 2: of_width(std::integral_constant<int, 2>{}); break;
+            case 3: of_width(std::integral_constant<int, 3>{}); break;
+            case 4: of_width(std::integral_constant<int, 4>{}); break;
+            default: of_width(std::integral_constant<int, 8>{}); break;
         }
         MQ_HIP_CHECK_LAUNCH();
         return MQ_OK;

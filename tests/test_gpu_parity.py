@@ -119,7 +119,7 @@ def test_pack_and_sums_in_one_pass(mq, orc, bits, signed):
     """Channel counts that leave part of a workgroup or of a tile empty, one round and several, a code matrix that does
     not start on a 16-byte boundary, codes with bits above their width (masked off)."""
     rng = np.random.default_rng(40 + bits)
-    for (N, K) in ((1, 64), (9, 128), (33, 2048), (31, 2112), (40, 5120)):
+    for (N, K) in ((1, 64), (9, 128), (33, 2048), (31, 2112), (40, 5120), (5, 17344), (8200, 2112)):
         codes = rng.integers(0, 256, (N, K)).astype(np.uint8)
         low = codes & ((1 << bits) - 1)
         sums = orc.code_rowsum(codes, signed=True) if signed else low.astype(np.int64).sum(1)

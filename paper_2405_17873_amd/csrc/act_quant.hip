@@ -299,7 +299,7 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
     }
     R = R > Q_MAX_ROWS ? Q_MAX_ROWS : R;
     const int qgrid = (M + R - 1) / R;
-    ProfScope prof(st, PROF_ACT_QUANTIZE, 0.0, 3.0 * M * K + 4.0 * M);
+    ProfScope prof(st, PROF_ACT_QUANTIZE, 0.0, 3.0 * M * K + (rowsum ? 4.0 * M : 0.0));
     if (bos)
         hipLaunchKernelGGL(act_quantize_kernel<true>, dim3(qgrid + bos_blocks(*bos)), dim3(256), 0, st,
                            (const _Float16*)x, M, K, (long)ldx, walk, R, FastDiv::make(Kp8),

@@ -1202,6 +1202,32 @@ def test_conv_k_split_inside_the_workgroup(mq, orc, bits, sym, stride):
         mq.tune_force_tile(-1)
 
 
+def test_timed_bytes_of_the_conversion(mq, orc):
+    """The conversion is booked with the bytes it moves: the row sums only where it writes them, which the convolution and
+    the second half of the gated projection do not ask for."""
+    B, H, W, Cin, N = 1, 6, 11, 128, 40
+    pw, *_, tapsum = conv_weight(mq, orc, 74, N, Cin, 4)
+    x = dev(si.activations_f16(74, "pb/x", B * H * W, Cin))
+    act = (dev(np.array([0.05], np.float32)), dev(np.array([31], np.int32)))
+    lin, *_ = make_weight(mq, orc, si.weights_f16(74, "pb/w", N, Cin), 4)
+
+    def booked(call):
+        mq.prof_reset()
+        mq.prof_filter(-1, 1)
+        mq.prof_enable(True)
+        try:
+            call()
+        finally:
+            mq.prof_enable(False)
+        k = [k for k in mq.prof_read() if "act_quantize" in k["kernel"]]
+        assert len(k) == 1 and k[0]["launches"] == 1
+        return k[0]["bytes"]
+
+    M = B * H * W
+    assert booked(lambda: mq.qlinear_w4a8(x, lin, act=act)) == 3.0 * M * Cin + 4.0 * M
+    assert booked(lambda: mq.conv3x3_a8(x.view(B, H, W, Cin), pw, tapsum, act=act)) == 3.0 * M * Cin
+
+
 @pytest.mark.parametrize("tile", (-1, 0, 1, 2, 5))
 def test_conv_residual_and_split_shortcut(mq, orc, tile):
     """Residual block tail (conv + skip), and the first convolution of an up block whose input is the channel

@@ -70,7 +70,10 @@ void mq_tune_force_splits(int parts);
 
 /* Workspace that lets the weight-only and 8-bit-activation linears split the reduction of an [M,K] x [N,K] problem
  * over several workgroups per output tile (an upper bound over the tile choices; 0 for shapes that are never split:
- * more than 64 tiles of 128 x 128, or K < 1024).  It depends on the current mq_tune_force_splits setting. */
+ * more than 64 tiles of 128 x 128, or K < 1024).  It depends on the current mq_tune_force_splits setting.
+ * The contents of a workspace may be arbitrary: partial sums are written before they are read, and a tile's arrival
+ * counter counts only under a 44-bit tag of the launch, which is put in its place first; the last arrival leaves the
+ * word zero.  One stream at a time. */
 size_t mq_split_workspace_bytes(int M, int N, int K);
 
 /* Tuning and test hook: height, in row blocks, of the bands in which a GEMM's workgroups walk the output tiles
@@ -247,7 +250,8 @@ int mq_qlinear_w2a8(const void* x, int M, int K, int ldx, const void* packed, in
  *   (M * K up to about 50 M activations: every linear of the configured workloads fits); what the activation
  *   workspace leaves of the array serves the split of the reduction.
  *   Every call on a GPU uses that GPU's one array, which keeps the previous call's contents (nothing in it has to
- *   start at zero: every byte that is read is written first, the split counters by a clearing kernel).  Calls that
+ *   start at zero: whatever is used is written first, and the words that count the arrivals of a split reduction count
+ *   only under a tag of their launch and are left zero).  Calls that
  *   may overlap on one GPU - different streams, or a captured graph replayed while another call runs - race on it:
  *   keep them on one stream. */
 size_t mq_builtin_workspace_bytes(void);

@@ -43,7 +43,8 @@ struct A8Workspace {
 // smallest tile (64 x 64) plus `parts` partial accumulator sets over the output padded to the largest splitting tile
 // (128 x 128).  The automatic choice splits only where there are at most 64 tiles and at least 16 pipeline stages, into
 // at most min(16, stages / 4) parts; a forced part count (test hook) is taken as it is.  (64 counters of 8 bytes fit the
-// 512 that any shape gets; the larger tile counts of the test hook get theirs beside.)
+// 512 that any shape gets, and lie further apart where the parts leave room; the larger tile counts of the test hook get
+// theirs beside.)
 size_t split_workspace_bytes(long M, long N, long K) {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
     const long Mp = (M + 127) / 128 * 128, Np = (N + 127) / 128 * 128;
@@ -263,7 +264,8 @@ int mq_qlinear_a8_geglu(const void* x, int M, int K, int ldx, const void* packed
 
 // Dynamic output parameters: behind the input's workspace lie the parameters of the output pass, one (min, max)
 // pair per workgroup of the gated projection (at most one per 128 rows x 64 gated columns).  (The size counts four more
-// bytes per row, which nothing uses: the consumer takes the row sums inside its main loop.)
+// bytes per row, from when the output pass wrote row sums; the consumer takes them inside its main loop.  It stays, so that
+// the line between an accepted and a refused workspace does not move; likewise the row sums in the convolution's.)
 static size_t geglu_dynamic_pairs(long M, long H) { return (size_t)((M + 127) / 128) * (size_t)((H + 127) / 128 * 2); }
 
 size_t mq_qlinear_a8_geglu_dynamic_workspace_bytes(int M, int K, int H) {

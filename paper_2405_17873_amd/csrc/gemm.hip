@@ -312,7 +312,8 @@ __device__ __forceinline__ int4v widen_step(const WChunk<WBITS>& c, int s /*0..1
 // polynomial in its place costs twelve more instructions per element: the gated feed-forward pair runs 2 to 3 %
 // slower with it.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ float gelu32(float g) {
+// Returns 2 gelu(g) = g (1 + erf): the factor 1/2 rides in the value's constants (exact, a multiplication less).
+__device__ __forceinline__ float two_gelu32(float g) {
     const float x = fminf(__fmul_rn(fabsf(g), 0.70710678f), 4.3f);
     float p = -5.95750535e-05f;
     p = __fmaf_rn(p, x, 0.000253331062f);
@@ -323,7 +324,18 @@ __device__ __forceinline__ float gelu32(float g) {
     p = __fmaf_rn(p, x, 1.12838686f);
     const float e = __builtin_amdgcn_exp2f(__fmul_rn(__fmul_rn(p, x), -1.44269504f));  // v_exp_f32: 2^t, 1 ulp
     const float erf_g = copysignf(__fsub_rn(1.0f, e), g);
-    return __fmul_rn(__fmul_rn(0.5f, g), __fadd_rn(1.0f, erf_g));
+    return __fmul_rn(g, __fadd_rn(1.0f, erf_g));
+}
+
+// Four products a[r] * b[r] rounded to fp16, one instruction each: the mixed-precision multiply-add writes one half of its
+// destination (the compiler, where the results are used as a vector, multiplies in fp32 and packs in instructions of their own).
+__device__ __forceinline__ half4 mul_to_half4(const float (&a)[4], const float (&b)[4]) {
+    uint2v o;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(o[0]) : "v"(a[0]), "v"(b[0]));
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(o[1]) : "v"(a[2]), "v"(b[2]));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(o[0]) : "v"(a[1]), "v"(b[1]));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(o[1]) : "v"(a[3]), "v"(b[3]));
+    return __builtin_bit_cast(half4, o);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -471,6 +483,7 @@ void gemm_kernel(const GemmArgs g) {
     static_assert(MODE == 0 || KS == 1 || (CONV && TM == 1), "in-workgroup k split: plain layers, and convolutions whose waves own one row slab");
     static_assert(!(RES && GEGLU), "the gated projection takes no residual");
     static_assert(!RANGE || (I8 && !BF), "the range output belongs to the int8 gated projection");
+    static_assert(!GEGLU || !BF, "the gated projections write fp16 or codes");
     static_assert(!CODES16 || (!I8 && !BF), "MODE 6 is the fp16 weight-only gated projection with 8-bit output");
     static_assert((MODE != 2 && MODE != 4) || I8, "int8 modes");
     static_assert(MODE != 3 || !I8, "MODE 3 is the weight-only convolution");
@@ -881,10 +894,12 @@ void gemm_kernel(const GemmArgs g) {
             ch_dw[t] = dw;
             ch_cn[t] = dx * (c_colsum - g.K * g.w_off + g.K * dw);
         }
-        ch_mul[t] = c_scale * c_sx;
+        // (gated projection: half of the value channels, for two_gelu32)
+        const float half_v = GEGLU && !((t >> 5) & 1) ? 0.5f : 1.0f;
+        ch_mul[t] = half_v * (c_scale * c_sx);
         asm volatile("" : "+v"(c_bias_bits));  // (keeps the compiler from moving the conversion up to the load)
-        ch_add[t] = BF ? bf16_bits_to_float((uint16_t)c_bias_bits)
-                       : (float)__builtin_bit_cast(_Float16, (uint16_t)c_bias_bits);
+        ch_add[t] = half_v * (BF ? bf16_bits_to_float((uint16_t)c_bias_bits)
+                                 : (float)__builtin_bit_cast(_Float16, (uint16_t)c_bias_bits));
     }
 
     // k-split: the two groups' partial sums meet through LDS ([register quad][lane], 16 bytes per lane).  With an
@@ -1044,79 +1059,86 @@ void gemm_kernel(const GemmArgs g) {
         // Rows are staged through LDS (32 rows x 32 bytes per wave) and leave as 16-byte pieces.
         // (without output parameters the kernel only writes the product and its range: the codes follow in a pass of
         // their own once the range of the whole tensor is known)
+        // Vector instructions bound it (the pass of 16384 x 640 -> 2 x 2560 -> 640 with run-time ranges:
+        // 178 -> 167 us; waves of two row slabs, three workgroups per compute unit, 10 % slower), so the constants of a
+        // register quad are read once for all row slabs and the range is taken from pairs of fp16 values.
         constexpr bool want_codes = (I8 && !RANGE) || CODES16;
         float inv_o = 0.0f, zf_o = 0.0f;
         if constexpr (want_codes) {
             inv_o = __fdiv_rn(1.0f, *g.out_scale_p);
             zf_o = (float)*g.out_zp_p;
         }
-        float hmn = INFINITY, hmx = -INFINITY;
-        static_assert(P::NWG * 3072 <= S * STAGE_BYTES, "epilogue staging must fit the LDS stages");
-        uint8_t* ep8 = lds + wvg * 3072;
-        uint8_t* ep16 = ep8 + 1024;
-        const int col0 = n0 + wn * 32;  // first gated column of this wave
+        // range of the values as they are stored (fp16), per row slab: a row that does not exist is left out at the end
+        uint2v hmn4[TM], hmx4[TM];  // pairs of fp16 values
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
-            const int mt0 = m0 + (wm * TM + tm) * 32;
+            hmn4[tm] = uint2v{0x7C007C00u, 0x7C007C00u};  // infinity
+            hmx4[tm] = uint2v{0xFC00FC00u, 0xFC00FC00u};
+        }
+        constexpr int SLAB = 1024 + 2048;  // codes and fp16 image of 32 rows x 32 columns
+        static_assert(P::NWG * TM * SLAB <= S * STAGE_BYTES, "epilogue staging must fit the LDS stages");
+        uint8_t* const ep8 = lds + wvg * TM * SLAB;
+        uint8_t* const ep16 = ep8 + 1024;
+        const int col0 = n0 + wn * 32;  // first gated column of this wave
+        const bool real_cols = __builtin_amdgcn_readfirstlane(col0 < H ? 1 : 0);  // (all 32 or none: H is a multiple of 32)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int cl_v = (wn * TN) * 32 + 8 * q + 4 * kb, cl_g = cl_v + 32;
-                const float4v mul_v = *(const float4v*)(ch_mul + cl_v), add_v = *(const float4v*)(ch_add + cl_v);
-                const float4v mul_g = *(const float4v*)(ch_mul + cl_g), add_g = *(const float4v*)(ch_add + cl_g);
-                int4v dw_v = {0, 0, 0, 0}, cn_v = dw_v, dw_g = dw_v, cn_g = dw_v;
-                if constexpr (I8) {
-                    dw_v = *(const int4v*)(ch_dw + cl_v), cn_v = *(const int4v*)(ch_cn + cl_v);
-                    dw_g = *(const int4v*)(ch_dw + cl_g), cn_g = *(const int4v*)(ch_cn + cl_g);
-                }
+        for (int q = 0; q < 4; ++q) {
+            const int cl_v = (wn * TN) * 32 + 8 * q + 4 * kb, cl_g = cl_v + 32;
+            const float4v mul_v = *(const float4v*)(ch_mul + cl_v), add_v = *(const float4v*)(ch_add + cl_v);
+            const float4v mul_g = *(const float4v*)(ch_mul + cl_g), add_g = *(const float4v*)(ch_add + cl_g);
+            int4v dw_v = {0, 0, 0, 0}, cn_v = dw_v, dw_g = dw_v, cn_g = dw_v;
+            if constexpr (I8) {
+                dw_v = *(const int4v*)(ch_dw + cl_v), cn_v = *(const int4v*)(ch_cn + cl_v);
+                dw_g = *(const int4v*)(ch_dw + cl_g), cn_g = *(const int4v*)(ch_cn + cl_g);
+            }
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) {
                 uint32_t word = 0;
-                half4 hh;
+                float lv[4], tg[4];  // value / 2 and 2 gelu(gate)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    float lv, lg;
+                    float lg;
                     if constexpr (I8) {
                         const int av = acc[tm][0][4 * q + r] + __mul24(dw_v[r], rsum[tm]) + cn_v[r];
                         const int ag = acc[tm][1][4 * q + r] + __mul24(dw_g[r], rsum[tm]) + cn_g[r];
-                        lv = __fmaf_rn((float)av, mul_v[r], add_v[r]);
+                        lv[r] = __fmaf_rn((float)av, mul_v[r], add_v[r]);
                         lg = __fmaf_rn((float)ag, mul_g[r], add_g[r]);
                     } else {
-                        lv = __fmaf_rn(acc[tm][0][4 * q + r], mul_v[r], add_v[r]);
+                        lv[r] = __fmaf_rn(acc[tm][0][4 * q + r], mul_v[r], add_v[r]);
                         lg = __fmaf_rn(acc[tm][1][4 * q + r], mul_g[r], add_g[r]);
                     }
-                    const float h = __fmul_rn(lv, gelu32(lg));
-                    if constexpr (want_codes) {
-                        float t = __fadd_rn(rintf(__fmul_rn(h, inv_o)), zf_o);
-                        t = fminf(fmaxf(t, 0.0f), 255.0f);
-                        const int code = col0 + 8 * q + 4 * kb + r < H ? (int)t - 128 : 0;
-                        word |= ((uint32_t)code & 255u) << (8 * r);
-                    }
-                    if constexpr (BF)
-                        hh[r] = __builtin_bit_cast(_Float16, float_to_bf16_bits(h));
-                    else
-                        hh[r] = (_Float16)h;
+                    tg[r] = two_gelu32(lg);
+                    if constexpr (want_codes)  // (the conversion saturates to 0..255 and takes NaN to 0)
+                        word = __builtin_amdgcn_cvt_pk_u8_f32(__fadd_rn(rintf(__fmul_rn(__fmul_rn(lv[r], tg[r]), inv_o)), zf_o), r, word);
                 }
-                if constexpr (RANGE) {  // range of the values as they are stored (fp16), real rows and columns only
-                    const bool row_ok = mt0 + l31 < g.M;
+                const half4 hh = mul_to_half4(lv, tg);
+                if constexpr (RANGE) {
+                    const uint2v h2 = __builtin_bit_cast(uint2v, hh);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const bool ok = row_ok && col0 + 8 * q + 4 * kb + r < H;
-                        const float hv = (float)hh[r];
-                        hmn = fminf(hmn, ok ? hv : INFINITY);
-                        hmx = fmaxf(hmx, ok ? hv : -INFINITY);
+                    for (int p = 0; p < 2; ++p) {  // (written out: the compiler would first canonicalise both operands)
+                        asm("v_pk_min_f16 %0, %1, %2" : "=v"(hmn4[tm][p]) : "v"(hmn4[tm][p]), "v"(h2[p]));
+                        asm("v_pk_max_f16 %0, %1, %2" : "=v"(hmx4[tm][p]) : "v"(hmx4[tm][p]), "v"(h2[p]));
                     }
                 }
                 if constexpr (want_codes) {
+                    word = real_cols ? word ^ 0x80808080u : 0u;  // code - 128
                     const uint32_t other = (uint32_t)__shfl_xor((int)word, 32, 64);
                     const uint32_t lo = kb ? other : word, hi = kb ? word : other;  // columns 0..3 and 4..7 of the group
                     // v_perm_b32: selector bytes 0..3 pick bytes of the second source, 4..7 of the first
                     const uint32_t out = kb ? __builtin_amdgcn_perm(hi, lo, 0x07030602u) : __builtin_amdgcn_perm(hi, lo, 0x05010400u);
-                    *(uint32_t*)(ep8 + l31 * 32 + q * 8 + kb * 4) = out;
+                    *(uint32_t*)(ep8 + tm * SLAB + l31 * 32 + q * 8 + kb * 4) = out;
                 }
-                if (g.y) *(half4*)(ep16 + l31 * 64 + q * 16 + kb * 8) = hh;
+                // (16-byte chunks XOR-ed with the row bits above those that separate rows inside one turn of the banks)
+                if (g.y) *(half4*)(ep16 + tm * SLAB + l31 * 64 + ((q ^ (l31 >> 2)) & 3) * 16 + kb * 8) = hh;
             }
-            __builtin_amdgcn_wave_barrier();
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+            const int mt0 = m0 + (wm * TM + tm) * 32;
             if constexpr (want_codes) {
                 const int row = lane >> 1, half = lane & 1;
-                const uint4v v = *(const uint4v*)(ep8 + row * 32 + half * 16);
+                const uint4v v = *(const uint4v*)(ep8 + tm * SLAB + row * 32 + half * 16);
                 const int m = mt0 + row, col = col0 + half * 16;
                 if (m < g.M && col < g.ld8) __builtin_nontemporal_store(v, (uint4v*)(g.a8_out + (long)m * g.ld8 + col));
             }
@@ -1124,14 +1146,22 @@ void gemm_kernel(const GemmArgs g) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     const int idx = i * 64 + lane, row = idx >> 2, c = idx & 3;
-                    const uint4v v = *(const uint4v*)(ep16 + row * 64 + c * 16);
+                    const uint4v v = *(const uint4v*)(ep16 + tm * SLAB + row * 64 + ((c ^ (row >> 2)) & 3) * 16);
                     const int m = mt0 + row, col = col0 + c * 8;
                     if (m < g.M && col < H) __builtin_nontemporal_store(v, (uint4v*)(g.y + (long)m * g.ldy + col));
                 }
             }
-            __builtin_amdgcn_wave_barrier();
         }
         if constexpr (RANGE) {  // one pair per workgroup: waves meet through the (idle) sink of the padding loads
+            float hmn = INFINITY, hmx = -INFINITY;
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool ok = real_cols && m0 + (wm * TM + tm) * 32 + l31 < g.M;
+                    hmn = fminf(hmn, ok ? (float)__builtin_bit_cast(half4, hmn4[tm])[r] : INFINITY);
+                    hmx = fmaxf(hmx, ok ? (float)__builtin_bit_cast(half4, hmx4[tm])[r] : -INFINITY);
+                }
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) {
                 hmn = fminf(hmn, __shfl_xor(hmn, off, 64));

@@ -405,6 +405,7 @@ struct GemmArgs {
     int conv_stride;         // 1 or 2: output pixel (i, j) is centred on input pixel (stride * i, stride * j)
     int conv_cpt;            // 64-channel chunks per filter tap (Cin / 64)
     uint32_t conv_cpt_inv;   // ceil(2^32 / conv_cpt) for conv_cpt > 1
+    FastDiv fd_wo, fd_ho;    // divisors conv_wo and conv_ho
     const int32_t* w_tapsum; // MODE 4: [9][N] sums of the weight codes per filter tap
     // optional residual [M, ldr] (16-bit, the dtype of y; rows as the rows of y): added in fp32 before the rounding
     const uint16_t* res;
@@ -533,17 +534,22 @@ void gemm_kernel(const GemmArgs g) {
     int a_sub[KS == 2 ? P::DMA_A : 1];  // k-split tiles: which of the stage's two k steps the load belongs to
     int a_half[CONV ? P::DMA_A : 1];
     uint32_t a_taps[CONV ? P::DMA_A : 1];
-    // convolution: which of the 9 filter taps (bit r * 3 + s) of output pixel m read inside the image
-    auto tap_mask = [&](int m) -> uint32_t {
-        if (m >= g.M) return 0u;
-        const int j = (m % g.conv_wo) * g.conv_stride, i = ((m / g.conv_wo) % g.conv_ho) * g.conv_stride;
-        const uint32_t rows = (i > 0 ? 1u : 0u) | 2u | (i + 1 < g.conv_h ? 4u : 0u);
-        const uint32_t cols = (j > 0 ? 1u : 0u) | 2u | (j + 1 < g.conv_w ? 4u : 0u);
-        uint32_t mk = 0;
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-            if (rows >> r & 1u) mk |= cols << (3 * r);
-        return mk;
+    // convolution: the input pixel that output pixel m is centred on, and which rows and columns of the filter read inside the
+    // image there (3 bits each)
+    struct Centre {
+        int index;
+        uint32_t rows, cols;
+        __device__ uint32_t taps() const {  // bit r * 3 + s: filter tap (r, s) reads inside the image
+            return (rows & 1u ? cols : 0u) | cols << 3 | (rows & 4u ? cols << 6 : 0u);
+        }
+    };
+    auto centre_of = [&](int m) -> Centre {
+        uint32_t row, jo, bi, io;
+        g.fd_wo.divmod((uint32_t)m, row, jo);
+        g.fd_ho.divmod(row, bi, io);
+        const int i = (int)io * g.conv_stride, j = (int)jo * g.conv_stride;
+        return Centre{((int)bi * g.conv_h + i) * g.conv_w + j, (i > 0 ? 1u : 0u) | 2u | (i + 1 < g.conv_h ? 4u : 0u),
+                      (j > 0 ? 1u : 0u) | 2u | (j + 1 < g.conv_w ? 4u : 0u)};
     };
 #pragma unroll
     for (int i = 0; i < P::DMA_A; ++i) {
@@ -552,20 +558,17 @@ void gemm_kernel(const GemmArgs g) {
         const int row = row0 + (lane >> 3);
         const int piece = (lane & 7) ^ swz(row);
         a_voff[i] = m0 + row < g.M ? (int)((long)(m0 + row) * g.a_row_bytes + sub * 128 + piece * 16) : OOB;
-        if constexpr (KS == 2) a_sub[i] = sub;
+        if constexpr (KS == 2) a_sub[i] = __builtin_amdgcn_readfirstlane(sub);
         a_lds[i] = __builtin_amdgcn_readfirstlane((uint32_t)(sub * P::SUB_BYTES + row0 * 128));
         if constexpr (CONV) {
             // row = output pixel; the lane's 16 bytes of a stage lie in one 64-channel chunk (int8: piece / 4 says
             // which of the stage's two), i.e. in one filter tap: per stage it adds that tap's pixel offset, or
             // reads nothing (zero) where the tap falls outside the image
-            const int mo = m0 + row < g.M ? m0 + row : g.M - 1;  // (rows past M read nothing: their tap mask is empty)
-            const int per_image = g.conv_ho * g.conv_wo;
-            const int bi = mo / per_image, rem = mo - bi * per_image;
-            const int io = rem / g.conv_wo, jo = rem - io * g.conv_wo;
-            const long centre = ((long)bi * g.conv_h + io * g.conv_stride) * g.conv_w + jo * g.conv_stride;
-            a_voff[i] = (int)(centre * g.a_row_bytes) + (I8 ? (piece & 3) : piece) * 16;
+            const bool real = m0 + row < g.M;
+            const Centre c = centre_of(real ? m0 + row : g.M - 1);
+            a_voff[i] = (int)((long)c.index * g.a_row_bytes) + (I8 ? (piece & 3) : piece) * 16;
             a_half[i] = I8 ? piece >> 2 : 0;
-            a_taps[i] = tap_mask(m0 + row);
+            a_taps[i] = real ? c.taps() : 0u;  // (rows past M read nothing)
         }
     }
     // weight loads: instruction jj of a sub-stage copies piece jj % PCS of weight tile jj / PCS (tile = channel group,
@@ -650,10 +653,17 @@ void gemm_kernel(const GemmArgs g) {
         }
     }
     int rsum[TM];
+    // int8 convolution: the row's class of missing taps, first and last filter row in bits 2 and 3, column in bits 0 and 1
+    int border[MODE == 4 ? TM : 1];
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
-        const int m = m0 + (wm * TM + tm) * 32 + l31;
-        rsum[tm] = (I8 && !RS_INLINE) ? g.rowsum[m < g.M ? m : g.M - 1] : 0;
+        int m = m0 + (wm * TM + tm) * 32 + l31;
+        m = m < g.M ? m : g.M - 1;
+        rsum[tm] = (I8 && !RS_INLINE) ? g.rowsum[m] : 0;
+        if constexpr (MODE == 4) {
+            const Centre c = centre_of(m);
+            border[tm] = (int)((c.rows & 1u ? 0u : 4u) | (c.rows & 4u ? 0u : 8u) | (c.cols & 1u ? 0u : 1u) | (c.cols & 4u ? 0u : 2u));
+        }
     }
 
     // Every wave issues exactly OPS loads per stage (padding loads go to the sink), so that "at most n * OPS loads
@@ -683,19 +693,19 @@ void gemm_kernel(const GemmArgs g) {
                 const uint32_t t = g.conv_cpt > 1 ? __umulhi(ci, g.conv_cpt_inv) : ci;
                 const int cc = (int)(ci - t * g.conv_cpt);
                 tap[h] = ci < (uint32_t)KC ? (int)t : 31;  // past the end of K (padding of the last stage): no tap
-                delta[h] = (((int)t / 3 - 1) * g.conv_w + ((int)t % 3 - 1)) * (int)g.a_row_bytes + cc * (I8 ? 64 : 128);
+                // (one scalar: taken apart, its terms meet the lane's offset in vector multiplications, 20 instructions per load)
+                delta[h] = __builtin_amdgcn_readfirstlane((((int)t / 3 - 1) * g.conv_w + ((int)t % 3 - 1)) * (int)g.a_row_bytes +
+                                                          cc * (I8 ? 64 : 128));
             }
 #pragma unroll
             for (int i = 0; i < P::DMA_A; ++i) {
-                int t = CH == 2 && a_half[i] ? tap[CH - 1] : tap[0];
-                int d = CH == 2 && a_half[i] ? delta[CH - 1] : delta[0];
-                if constexpr (KS == 2) {
-                    if (a_sub[i]) {  // (the load belongs to the stage's second k step)
-                        t = CH == 2 && a_half[i] ? tap[2 * CH - 1] : tap[CH];
-                        d = CH == 2 && a_half[i] ? delta[2 * CH - 1] : delta[CH];
-                    }
-                }
-                const int voff = (a_taps[i] >> t) & 1u ? a_voff[i] + d : OOB;
+                // (KS == 2: a_sub says whether the load belongs to the stage's second k step)
+                const int h0 = KS == 2 ? (a_sub[i] ? CH : 0) : 0;
+                const int t0 = h0 ? tap[KS == 2 ? CH : 0] : tap[0], d0 = h0 ? delta[KS == 2 ? CH : 0] : delta[0];
+                const int t1 = h0 ? tap[KS * CH - 1] : tap[CH - 1], d1 = h0 ? delta[KS * CH - 1] : delta[CH - 1];
+                const int t = CH == 2 && a_half[i] ? t1 : t0, d = CH == 2 && a_half[i] ? d1 : d0;
+                const int in = (int)(a_taps[i] << (31 - t)) >> 31;  // all ones where the tap reads inside the image
+                const int voff = (in & (a_voff[i] + d)) | (~in & OOB);
                 dma_to_lds_b128(ra, __builtin_amdgcn_readfirstlane(sb + a_lds[i]), voff, 0);
             }
         } else if (tail_a) {
@@ -770,6 +780,7 @@ void gemm_kernel(const GemmArgs g) {
             if constexpr (BF && BITS != 16) wf[tn] = __builtin_bit_cast(half8, half8_to_bf16x8(wf[tn]));  // bf16 bits now
         }
     };
+    const int wn_u = __builtin_amdgcn_readfirstlane(wn);
     auto multiply = [&](const frag_t (&wf)[TN], int s, auto fresh_c) {
         constexpr bool FRESH = decltype(fresh_c)::value;  // the accumulators start here: C = 0
 #pragma unroll
@@ -791,12 +802,17 @@ void gemm_kernel(const GemmArgs g) {
                 else
                     acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[tn], xf[s][tm], c, 0, 0, 0);
             }
-        if constexpr (RS_INLINE) {  // this lane's share of the row sums of the stored activations (bytes a' = code - 128)
+        // Row sums of the stored activations (bytes a' = code - 128): the WGN waves that hold the same rows take the
+        // fragments of one k-step in WGN each.  (Four dot products per fragment, in every wave, were
+        // more vector instructions than the code widening: feed-forward pair 16384 x 640 162 -> 159 us a pass with the share.)
+        if constexpr (RS_INLINE) {
+            if (s % WGN == wn_u) {
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm) {
-                const int4v a = __builtin_bit_cast(int4v, xf[s][tm]);
+                for (int tm = 0; tm < TM; ++tm) {
+                    const int4v a = __builtin_bit_cast(int4v, xf[s][tm]);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) rsum[tm] = __builtin_amdgcn_sdot4(a[i], 0x01010101, rsum[tm], false);
+                    for (int i = 0; i < 4; ++i) rsum[tm] = __builtin_amdgcn_sdot4(a[i], 0x01010101, rsum[tm], false);
+                }
             }
         }
     };
@@ -868,9 +884,16 @@ void gemm_kernel(const GemmArgs g) {
     }
     __syncthreads();  // every wave is done reading the stages: what follows may overwrite them
 
-    if constexpr (RS_INLINE) {  // lanes l and l + 32 hold the two k-halves of row l's sum
+    // Row sums in parts: lanes l and l + 32 hold two shares of row l's, the waves (and wave groups) that hold the same rows
+    // one each.  They meet in the idle sink of the padding loads.
+    int* const rs_x = (int*)(lds + P::SINK) + wm * TM * 32 + l31;
+    if constexpr (RS_INLINE) {
+        static_assert((WGN == 2 || WGN == 4) && KS * WGN * BM * 4 <= 1024, "shares of the row sums fit the sink");
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) rsum[tm] += __shfl_xor(rsum[tm], 32, 64);
+        for (int tm = 0; tm < TM; ++tm) {
+            rsum[tm] += __shfl_xor(rsum[tm], 32, 64);
+            if (lane < 32) rs_x[(grp * WGN + wn) * BM + tm * 32] = rsum[tm];
+        }
     }
 
     // Park the per-channel constants in LDS behind the stages: multiplier, additive term and (int8) the two
@@ -883,6 +906,8 @@ void gemm_kernel(const GemmArgs g) {
     float* ch_add = ch_mul + BN;
     int* ch_dw = (int*)(ch_add + BN);
     int* ch_cn = ch_dw + BN;
+    // (int8 convolution: [16][BN], at the end of the idle stages, beyond what the epilogue puts there)
+    int* const ch_border = (int*)(lds + S * STAGE_BYTES) - 16 * BN;
     if (threadIdx.x < BN) {
         const int t = threadIdx.x;
         if constexpr (I8) {
@@ -892,7 +917,33 @@ void gemm_kernel(const GemmArgs g) {
             const int dx = 128 - c_zx;
             const int dw = g.w_off - c_zp;
             ch_dw[t] = dw;
-            ch_cn[t] = dx * (c_colsum - g.K * g.w_off + g.K * dw);
+            const int cn = dx * (c_colsum - g.K * g.w_off + g.K * dw);
+            ch_cn[t] = cn;
+            if constexpr (MODE == 4) {
+                // A filter tap outside the image reads zero bytes, which stand for the code 128, not for the value 0 (code
+                // z_x).  cn counts every tap; each class of border pixels takes back dx * sum_c (q_w - z_w) of the
+                // taps it does not have: a table of the classes, from which a lane reads its row's constants.  (With the
+                // per-tap sums read by the border lanes, the addresses of issue() in vector multiplications and the row sums in
+                // every wave, the block 2 x 128 x 128, 320 -> 320 with downsampler at 4 bits took 200 us, now 156.)
+                int n = group_of(t >> 5) * 32 + (t & 31);
+                n = n < g.N ? n : g.N - 1;
+                int tap[9];
+#pragma unroll
+                for (int i = 0; i < 9; ++i) tap[i] = g.w_tapsum[i * g.N + n];
+#pragma unroll
+                for (int cls = 0; cls < 16; ++cls) {
+                    int missing = 0, taps_missing = 0;
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) {
+                        const int r = i / 3, c = i % 3;
+                        if ((r == 0 && (cls & 4)) || (r == 2 && (cls & 8)) || (c == 0 && (cls & 1)) || (c == 2 && (cls & 2))) {
+                            missing += tap[i];
+                            ++taps_missing;
+                        }
+                    }
+                    ch_border[cls * BN + t] = cn - dx * (missing - taps_missing * (g.conv_cpt * 64) * c_zp);
+                }
+            }
         }
         // (gated projection: half of the value channels, for two_gelu32)
         const float half_v = GEGLU && !((t >> 5) & 1) ? 0.5f : 1.0f;
@@ -911,7 +962,7 @@ void gemm_kernel(const GemmArgs g) {
     if constexpr (KS == 2) {
         using quad_t = typename std::conditional<I8, int4v, float4v>::type;
         constexpr int XW = TMX * TN * 4 * 1024;  // bytes one wave sends
-        static_assert(P::NWG * (SPLIT_EPI ? 2 : 1) * XW <= S * STAGE_BYTES, "accumulator exchange must fit the stages");
+        static_assert(P::NWG * (SPLIT_EPI ? 2 : 1) * XW + (MODE == 4 ? 64 * BN : 0) <= S * STAGE_BYTES, "accumulator exchange must fit the stages");
         auto area = [&](int writer) { return lds + (SPLIT_EPI ? wvg * 2 + writer : wvg) * XW + lane * 16; };
         uint8_t* out = area(grp);
 #pragma unroll
@@ -927,12 +978,7 @@ void gemm_kernel(const GemmArgs g) {
                     *(quad_t*)(out + (((SPLIT_EPI ? tm >> 1 : tm) * TN + tn) * 4 + q) * 1024) = v;
                 }
         }
-        // (row sums taken in the main loop cover one group's k steps: group 1 hands its own over in the idle sink)
-        static_assert(!RS_INLINE || (!SPLIT_EPI && P::NWG * 32 * 4 <= 1024), "row sums of one slab per wave fit the sink");
-        int* const rs_x = (int*)(lds + P::SINK) + wvg * 32 + l31;
-        if (RS_INLINE && grp == 1 && lane < 32) *rs_x = rsum[0];
         __syncthreads();
-        if (RS_INLINE && grp == 0) rsum[0] += *rs_x;
         const uint8_t* in = area(1 - grp);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
@@ -950,6 +996,14 @@ void gemm_kernel(const GemmArgs g) {
     }
 
     if constexpr (KS == 1) __syncthreads();  // constants visible (the k-split exchange above has its own barriers)
+    if constexpr (RS_INLINE) {
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+            rsum[tm] = 0;
+#pragma unroll
+            for (int i = 0; i < KS * WGN; ++i) rsum[tm] += rs_x[i * BM + tm * 32];
+        }
+    }
 
     // Reduction split over workgroups: every workgroup stores its partial sums (register order, one 4-byte value per
     // lane per store: fully coalesced; rows past M skipped), then takes a ticket; the one that draws the last ticket
@@ -1191,9 +1245,9 @@ void gemm_kernel(const GemmArgs g) {
     // Where the idle stages have the room, a wave stages all its slabs at once: the per-channel constants of a
     // register quad are then read from LDS once and serve every slab (a wave that reads them again for each slab
     // spends most of its epilogue waiting for LDS), and one pass of stores follows one pass of conversions.
-    constexpr bool ALL_SLABS = KS == 1 && !RES && EW * TM * EP_BYTES <= S * STAGE_BYTES;
+    constexpr bool ALL_SLABS = KS == 1 && !RES && EW * TM * EP_BYTES + (MODE == 4 ? 64 * BN : 0) <= S * STAGE_BYTES;
     constexpr int WAVE_EP = ALL_SLABS ? TM * EP_BYTES : EP_BYTES;
-    static_assert(EW * WAVE_EP <= S * STAGE_BYTES, "epilogue staging must fit the LDS stages");
+    static_assert(EW * WAVE_EP + (MODE == 4 ? 64 * BN : 0) <= S * STAGE_BYTES, "epilogue staging must fit the LDS stages");
     uint8_t* ep = lds + (SPLIT_EPI ? wv : wvg) * WAVE_EP;
     const int nw0 = n0 + wn * TN * 32;  // first channel of this wave
     constexpr int CPR = TN * 4;              // 16-byte chunks per staged row
@@ -1239,7 +1293,7 @@ void gemm_kernel(const GemmArgs g) {
         k.add = *(const float4v*)(ch_add + cl);
         if constexpr (I8) {
             k.dw = *(const int4v*)(ch_dw + cl);
-            k.cn = *(const int4v*)(ch_cn + cl);
+            if constexpr (MODE != 4) k.cn = *(const int4v*)(ch_cn + cl);
         }
         return k;
     };
@@ -1247,30 +1301,13 @@ void gemm_kernel(const GemmArgs g) {
     auto int_quad = [&](int tm, int tn, int q, const QuadConst& k) {
         int4v a = {0, 0, 0, 0};
         if constexpr (I8) {
-            int4v border = {0, 0, 0, 0};
-            if constexpr (MODE == 4) {
-                // Convolution: a filter tap outside the image reads zero bytes, which stand for the code
-                // 128, not for the value 0 (code z_x).  The constant term cn counts every tap; take back
-                // dx * sum_c (q_w - z_w) of the taps this pixel does not have.
-                const uint32_t have = tap_mask(m0 + (wm * TM + tm) * 32 + l31);
-                if (have != 0x1FFu) {
-                    const int n_real = n0 + (wn * TN + tn) * 32 + 8 * q + 4 * kb;
-                    const int dxv = 128 - *g.act_zp_p;
-                    const int cin = g.conv_cpt * 64;
-                    for (int t = 0; t < 9; ++t) {
-                        if (have >> t & 1u) continue;
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int n = n_real + r < g.N ? n_real + r : g.N - 1;
-                            border[r] += dxv * (g.w_tapsum[t * g.N + n] - cin * (g.w_off - k.dw[r]));
-                        }
-                    }
-                }
-            }
+            int4v cn = k.cn;
+            if constexpr (MODE == 4)  // the constants of the row's class of border pixels
+                cn = *(const int4v*)(ch_border + border[tm] * BN + (wn * TN + tn) * 32 + 8 * q + 4 * kb);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 // |dw| <= 255 and |rowsum| <= 128 * K < 2^23: a 24-bit multiply (full rate) is exact
-                a[r] = acc[tm][tn][4 * q + r] + __mul24(k.dw[r], rsum[tm]) + k.cn[r] - border[r];
+                a[r] = acc[tm][tn][4 * q + r] + __mul24(k.dw[r], rsum[tm]) + cn[r];
         }
         return a;
     };
@@ -1869,6 +1906,8 @@ static void conv_args(GemmArgs& g, int B, int H, int W, int Cin, int stride, lon
     g.K = 9 * Cin;
     g.conv_h = H;
     g.conv_w = W;
+    g.fd_wo = FastDiv::make((uint32_t)g.conv_wo);
+    g.fd_ho = FastDiv::make((uint32_t)g.conv_ho);
     g.conv_cpt = Cin / 64;
     g.conv_cpt_inv = g.conv_cpt > 1 ? (uint32_t)(((1ull << 32) + g.conv_cpt - 1) / g.conv_cpt) : 0u;
 }

@@ -1859,8 +1859,11 @@ int launch_gemm_a8_codes(const int8_t* a8, long lda, const float* act_scale, con
     // serves, the output linears of feed-forward blocks, are narrow); the half-height tile 5 in place of tile 1
     int t = pick_tile(M, N, K, true);
     t = t == 6 ? 1 : (t >= 3 ? t - 2 : t);
-    // (tile 5 doubles the row-sum work per MFMA: measured 8 % faster at K = 1280, 5 % at 2560, 9 % slower at 5120)
-    const bool half_height = g_force_tile == 5 || (g_force_tile < 0 && K < 4096);
+    // Tile 5 (16384 x 2560 x 640 at 4 bits 40 us against 48; 4096 x 5120 x 1280 37.5 against 44.6, at 8 bits 42.4 against 44.5),
+    // except for many tiles over weights that an XCD's 4 MB L2 does not hold and half the height fetches twice as often
+    // (16384 x 5120 x 1280 at 8 bits 145 against 134; at 4 bits, 3.3 MB, 122 against 128).
+    const bool many = (long)((M + 127) / 128) * ((N + 127) / 128) >= 512 && (long)N * K * w_bits / 8 > (4L << 20);
+    const bool half_height = g_force_tile == 5 || (g_force_tile < 0 && !many);
     if (w_bits == 4) {
         g.w_off = 0;
         switch (t) {

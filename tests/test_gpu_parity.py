@@ -887,6 +887,21 @@ def test_a8_linear_on_codes(mq, orc, bits, sym, tile):
         mq.tune_force_tile(-1)
 
 
+@pytest.mark.parametrize("M,K,N,bits", [(2051, 4160, 1032, 8), (8200, 4160, 1032, 8), (8200, 4160, 1032, 4)])
+def test_a8_linear_on_codes_long_reductions(mq, orc, M, K, N, bits):
+    """Long reductions on both sides of the tile rule: few tiles, many tiles over weights beyond 4 MB, and below."""
+    rng = np.random.default_rng(66)
+    qx = rng.integers(0, 256, (M, K)).astype(np.uint8)
+    act = (np.float32(0.0123), 97)
+    pw, oc, os_, oz = make_weight(mq, orc, si.weights_f16(66, "cdl/w", N, K), bits)
+    d_act = (dev(np.array([act[0]], np.float32)), dev(np.array([act[1]], np.int32)))
+    y, acc = mq.qlinear_a8_codes(dev(a8_layout(qx)), K, d_act, pw, want_acc=True)
+    rows = np.array([0, 63, 64, 127, 128, M // 2, M - 2, M - 1])
+    ry, racc = orc.linear_a8_codes(qx[rows], act, oc, os_, oz)
+    assert np.array_equal(host(acc)[rows], racc)
+    assert_close16(host(y)[rows], ry, f"codes {M}x{K}x{N} b{bits}")
+
+
 @pytest.mark.parametrize("bits", ALL_BITS)
 @pytest.mark.parametrize("tile", (-1, 0, 1))
 def test_w_only_geglu_projection(mq, orc, bits, tile):

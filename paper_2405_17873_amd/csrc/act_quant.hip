@@ -31,7 +31,7 @@ __device__ inline T wave_reduce(T v, Op op) {
 // vectors (8 values; vector i is piece i % (K/8) of row i / (K/8)), every lane requests several vectors before it
 // touches one, and the grids are sized so that every compute unit holds a few workgroups.
 static constexpr int MM_U = 8;  // vectors per lane per round, pass 1
-static constexpr int Q_U = 4;   // vectors per lane per round, pass 2
+static constexpr int Q_U = 4;   // vectors per lane per round, pass 2 (at most: see the launcher)
 
 // Physical row of logical row r (RowMap::phys with its division prepared by the host).
 struct RowWalk {
@@ -126,9 +126,10 @@ static constexpr long kSmallQuant = 28L * 1000 * 1000;  // values: between 6000 
 // that widens it, one rounding, one addition and one saturating conversion into its byte (the conversion also takes NaN
 // to code 0, as the clamp of the formula does), with the division of a vector index by the row length prepared by the
 // host.  rowsum == nullptr: the caller's GEMM takes the sums itself, they are left out here.
-// BOS: workgroups from index qgrid on compute the BOS rows of a BOS-aware K/V projection instead (they depend on
-// nothing this kernel produces; one launch less on a path whose kernels are all bound by launch latency).
-template <bool BOS>
+// BOS: the first `nbos` workgroups compute the BOS rows of a BOS-aware K/V projection instead (they depend on nothing this
+// kernel produces; one launch less on a path whose kernels are all bound by launch latency).  They take longest, so they
+// come first.
+template <bool BOS, int U>
 __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __restrict__ x, int M, int K, long ldx,
                                                            RowWalk map, int R, FastDiv Kp8d, const float* __restrict__ partials,
                                                            int n_partials, const float* __restrict__ act_scale,
@@ -136,31 +137,31 @@ __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __res
                                                            int8_t* __restrict__ a8, int32_t* __restrict__ rowsum,
                                                            ActParams* __restrict__ params,
                                                            float* __restrict__ act_scale_out,
-                                                           int32_t* __restrict__ act_zp_out, int qgrid, BosWork bw) {
+                                                           int32_t* __restrict__ act_zp_out, int nbos, BosWork bw) {
+    int blk = (int)blockIdx.x;
     if constexpr (BOS) {
-        if ((int)blockIdx.x >= qgrid) {  // (whole workgroups: none of them reaches a barrier below)
-            if (bw.bos_out)
-                bos_copy_block((int)blockIdx.x - qgrid, (int)threadIdx.x, bw);
-            else
-                bos_rows_block<4>((int)blockIdx.x - qgrid, (int)threadIdx.x, bw);
+        __shared__ float part[4][256];
+        if (blk < nbos) {  // (whole workgroups: none of them reaches a barrier below)
+            bos_block(blk, (int)threadIdx.x, bw, part);
             return;
         }
+        blk -= nbos;
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     __shared__ float smn[4], smx[4];
     __shared__ int lsum[Q_MAX_ROWS];
-    const int r0 = blockIdx.x * R;
+    const int r0 = blk * R;
     const int Rr = M - r0 < R ? M - r0 : R;
     if (threadIdx.x < Q_MAX_ROWS) lsum[threadIdx.x] = 0;
     const uint32_t K8 = K >> 3;
     const uint32_t Kp = (K + 127) / 128 * 128;  // row stride of the int8 copy; the padding is zero
     const uint32_t Kp8 = Kp8d.d;                // Kp / 8, a multiple of 16: an aligned group of 8 lanes never straddles rows
     const uint32_t nvo = (uint32_t)Rr * Kp8;
-    half8 v[Q_U];
-    uint32_t lr[Q_U], pp[Q_U];
+    half8 v[U];
+    uint32_t lr[U], pp[U];
     auto request = [&](uint32_t base) {
 #pragma unroll
-        for (int u = 0; u < Q_U; ++u) {
+        for (int u = 0; u < U; ++u) {
             const uint32_t i = base + u * 256u + threadIdx.x;
             Kp8d.divmod(i, lr[u], pp[u]);
             if (i < nvo && pp[u] < K8) v[u] = ((const half8*)(x + map.phys(r0 + lr[u]) * ldx))[pp[u]];
@@ -208,16 +209,16 @@ __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __res
         __syncthreads();
     }
     const float inv = 1.0f / s;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (blk == 0 && threadIdx.x == 0) {
         params->scale = s;
         params->zp = (int)zf;
         if (act_scale_out) *act_scale_out = s;
         if (act_zp_out) *act_zp_out = (int)zf;
     }
-    for (uint32_t base = 0; base < nvo; base += 256u * Q_U) {
+    for (uint32_t base = 0; base < nvo; base += 256u * U) {
         if (base) request(base);
 #pragma unroll
-        for (int u = 0; u < Q_U; ++u) {
+        for (int u = 0; u < U; ++u) {
             const uint32_t i = base + u * 256u + threadIdx.x;
             const bool valid = i < nvo;
             uint32_t w0 = 0, w1 = 0;
@@ -270,8 +271,14 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
                            (long)ldx, walk, flat, partials);
         MQ_HIP_CHECK_LAUNCH();
     }
-    // Rows per workgroup: one round (1024 vectors) while that keeps the grid within eight workgroups per compute unit.  A
-    // larger tensor can take as many rounds per workgroup as bring it there: the parameters are derived (and the pairs read)
+    // Vectors per lane: as few as keep a row in one round and the grid within eight workgroups per compute unit, so that
+    // small tensors have more wavefronts to request them.  Whole calls with 64 output channels in us, four -> two -> one vector:
+    //   given parameters 77 x 2048 10.0 -> 9.5 -> 9.3, 256 x 320 7.1 -> 6.5 -> 6.4, 616 x 2048 10.7 -> 10.3 -> 10.1,
+    //     4096 x 640 9.5 -> 9.1 -> 8.9, 4096 x 320 8.0 -> 7.6 -> 7.4; 2964 x 1280 (one: 2964 workgroups) 10.5 -> 10.3
+    //   run-time range, every workgroup reads the pairs, so one vector only up to a workgroup per compute unit:
+    //     77 x 2048 13.4 -> 12.4 -> 12.3, 256 x 320 10.3 -> 9.5 -> 9.4, 616 x 2048 14.3 -> 14.0 -> 14.2, 1024 x 640 12.2 -> 11.5 -> 11.6
+    // Beyond that grid, rows per workgroup: one round (1024 vectors) while that keeps it within eight workgroups per compute
+    // unit.  A larger tensor can take as many rounds per workgroup as bring it there: the parameters are derived (and the pairs read)
     // that many times less often, but the grid may leave compute units idle at its end, the last round lanes, and the rounds
     // of one workgroup do not overlap.  Whole calls in us, one round -> longer:
     //   `full`, a single row is more than half a round and the busiest unit gets hardly more of them:
@@ -283,8 +290,15 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
     //   thousands of pairs (the gated projection leaves them): 16384 x 2560 126.2 -> 124.1
     //   given parameters otherwise: 16389 x 2560 42.6 -> 45.1, 262144 x 320 79.7 -> 87.2
     const int Kp8 = (K + 127) / 128 * 16;
-    int R = 256 * Q_U / Kp8;
+    int U = Q_U, R = 256 * Q_U / Kp8;
     R = R < 1 ? 1 : R;
+    for (int u = 1; u < Q_U && given_partials <= kPartialSlots; u *= 2) {
+        const int rows = 256 * u / Kp8;
+        if (rows < 1 || (M + rows - 1) / rows > (dynamic && u == 1 ? kQuantGrid / 8 : kQuantGrid)) continue;
+        U = u;
+        R = rows;
+        break;
+    }
     if ((M + R - 1) / R > kQuantGrid) {
         int longer = (M + kQuantGrid - 1) / kQuantGrid;
         longer = longer > Q_MAX_ROWS ? Q_MAX_ROWS : longer;
@@ -300,15 +314,12 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
     R = R > Q_MAX_ROWS ? Q_MAX_ROWS : R;
     const int qgrid = (M + R - 1) / R;
     ProfScope prof(st, PROF_ACT_QUANTIZE, 0.0, 3.0 * M * K + (rowsum ? 4.0 * M : 0.0));
-    if (bos)
-        hipLaunchKernelGGL(act_quantize_kernel<true>, dim3(qgrid + bos_blocks(*bos)), dim3(256), 0, st,
-                           (const _Float16*)x, M, K, (long)ldx, walk, R, FastDiv::make(Kp8),
-                           dynamic ? partials : (const float*)nullptr, grid, act_scale, act_zp, a8, rowsum, params,
-                           act_scale_out, act_zp_out, qgrid, *bos);
-    else
-        hipLaunchKernelGGL(act_quantize_kernel<false>, dim3(qgrid), dim3(256), 0, st, (const _Float16*)x, M, K,
-                           (long)ldx, walk, R, FastDiv::make(Kp8), dynamic ? partials : (const float*)nullptr, grid,
-                           act_scale, act_zp, a8, rowsum, params, act_scale_out, act_zp_out, qgrid, BosWork{});
+    auto kern = bos ? (U == 1 ? act_quantize_kernel<true, 1> : U == 2 ? act_quantize_kernel<true, 2> : act_quantize_kernel<true, 4>)
+                    : (U == 1 ? act_quantize_kernel<false, 1> : U == 2 ? act_quantize_kernel<false, 2> : act_quantize_kernel<false, 4>);
+    const int nbos = bos ? bos_blocks(*bos) : 0;
+    hipLaunchKernelGGL(kern, dim3(nbos + qgrid), dim3(256), 0, st, (const _Float16*)x, M, K, (long)ldx,
+                       walk, R, FastDiv::make(Kp8), dynamic ? partials : (const float*)nullptr, grid, act_scale, act_zp, a8,
+                       rowsum, params, act_scale_out, act_zp_out, nbos, bos ? *bos : BosWork{});
     MQ_HIP_CHECK_LAUNCH();
     return MQ_OK;
 }

@@ -5,21 +5,17 @@
 
 namespace mq {
 
-template <int BCHUNK>
 __global__ __launch_bounds__(256) void bos_rows_kernel(BosWork bw) {
-    bos_rows_block<BCHUNK>((int)blockIdx.x, (int)threadIdx.x, bw);
-}
-
-__global__ __launch_bounds__(256) void bos_copy_kernel(BosWork bw) {
-    bos_copy_block((int)blockIdx.x, (int)threadIdx.x, bw);
+    __shared__ float part[4][256];
+    bos_block((int)blockIdx.x, (int)threadIdx.x, bw, part);
 }
 
 int launch_bos_rows(const BosWork& bw, hipStream_t st) {
     if (bw.bos_out) {
-        hipLaunchKernelGGL(bos_copy_kernel, dim3(bos_blocks(bw)), dim3(256), 0, st, bw);
+        hipLaunchKernelGGL(bos_rows_kernel, dim3(bos_blocks(bw)), dim3(256), 0, st, bw);
     } else {
         ProfScope prof(st, PROF_BOS_ROWS, 2.0 * bw.B * bw.N * bw.K, 2.0 * bw.N * bw.K + 2.0 * bw.B * bw.K + 2.0 * bw.B * bw.N);
-        hipLaunchKernelGGL(bos_rows_kernel<8>, dim3(bos_blocks(bw)), dim3(256), 0, st, bw);
+        hipLaunchKernelGGL(bos_rows_kernel, dim3(bos_blocks(bw)), dim3(256), 0, st, bw);
     }
     MQ_HIP_CHECK_LAUNCH();
     return MQ_OK;

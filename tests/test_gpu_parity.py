@@ -555,6 +555,14 @@ def test_activation_passes_at_the_edges_of_their_grids(mq, orc, M, K, N):
     assert np.array_equal(host(acc) + 117, t.astype(np.int32))
 
 
+@pytest.mark.parametrize("M,K", [(256, 2048), (257, 2048), (2048, 2048), (2049, 2048), (2050, 2112), (2047, 4096), (2049, 4096), (4097, 64),
+                                 (33, 2176)])
+def test_conversion_at_the_edges_of_its_vectors_per_lane(mq, orc, M, K):
+    """One, two and four vectors per lane on both sides of each line: workgroups per compute unit (run-time range and given
+    parameters), rows that one vector per lane does not cover, many rows per workgroup."""
+    test_activation_passes_at_the_edges_of_their_grids(mq, orc, M, K, 32)
+
+
 @pytest.mark.parametrize("M,K,pad", [(1, 64, 0), (16, 64, 8), (300, 320, 0), (4200, 2048, 0), (8300, 1280, 24), (33000, 320, 0)])
 def test_range_pass_ignores_nan(mq, M, K, pad):
     """Quiet, signalling and negative NaN in the first vector, in the last one (which short workgroups read repeatedly) and a
@@ -1342,6 +1350,24 @@ def test_bos_aware_kv_projection_static_parameters_and_bias(mq, orc, N, bits, sy
     y3, _ = mq.bos_aware_kv_proj(dev(ctx), pw, act=d_act, bias=dev(b), naive_all_rows=True)
     ry3, _ = orc.bos_aware_kv_proj(ctx, oc, os_, oz, w_signed=sym, act=act, bias=b, naive_all_rows=True)
     assert_close16(host(y3), ry3, "naive all rows, static + bias")
+
+
+@pytest.mark.parametrize("B,T,K,N", [(1, 2, 64, 8), (15, 3, 192, 24), (16, 2, 1088, 40), (17, 3, 2048, 16), (33, 1, 320, 48)])
+def test_bos_rows_at_the_edges_of_their_tiles(mq, orc, B, T, K, N):
+    """Prompts and channels below, at and beyond 16, reductions that do not fill a round of the four waves, T = 1 (a launch of
+    their own); weights and activations with subnormal values."""
+    ctx = si.activations_f16(81, f"bt/x{B}x{T}x{K}", B * T, K).reshape(B, T, K)
+    w = si.weights_f16(81, f"bt/w{N}x{K}", N, K)
+    w[:, ::3] = np.float16(2.0 ** -20) * (1 + np.arange(N, dtype=np.float16)[:, None] % 7)
+    ctx[:, 0, 1::5] = np.float16(2.0 ** -18)
+    b = si.bias_f16(81, f"bt/b{N}", N)
+    pw, *_ = make_weight(mq, orc, w, 8)
+    y, _ = mq.bos_aware_kv_proj(dev(ctx), pw, w_f16=dev(w), bias=dev(b))
+    assert_close16(host(y)[:, 0], orc.linear_fp(np.ascontiguousarray(ctx[:, 0]), w, b), f"BOS rows {B}x{T}x{K}x{N}")
+    tiny = np.full((N, K), 2.0 ** -20, np.float16)  # sums of subnormal weights alone: exact
+    ones = np.ones((B, T, K), np.float16)
+    y, _ = mq.bos_aware_kv_proj(dev(ones), pw, w_f16=dev(tiny))
+    assert np.array_equal(host(y)[:, 0], np.full((B, N), K * 2.0 ** -20, np.float16))
 
 
 def test_bos_distinct_rows_small_and_degenerate(mq, orc):

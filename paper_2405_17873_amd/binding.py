@@ -37,6 +37,14 @@ class MixdqError(RuntimeError):
 
 
 _lib = None
+_native = None  # csrc/host.cpp: the eager calls of small layers, see there
+
+
+def _done(r, what: str):
+    """The result of a native call; it returns an error code in its place."""
+    if r.__class__ is int:
+        raise MixdqError(r, what)
+    return r
 
 
 def lib_path() -> str:
@@ -44,15 +52,20 @@ def lib_path() -> str:
 
 
 def load():
-    """Loads the HIP library; raises if it has not been built (there is no fallback path)."""
-    global _lib
+    """Loads the HIP library and the native marshalling; raises if they have not been built (there is no fallback path)."""
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(_LIB_PATH):
             raise RuntimeError(f"{_LIB_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'`")
-        _lib = C.CDLL(_LIB_PATH)
+        from . import _mqhost as _native  # (raises ImportError if it has not been built)
+        lib = C.CDLL(_LIB_PATH)
         for name in ("mq_a8_row_bytes", "mq_split_workspace_bytes", "mq_builtin_workspace_bytes", "mq_conv3x3_a8_workspace_bytes", "mq_packed_bytes", "mq_qlinear_a8_workspace_bytes", "mq_qlinear_a8_geglu_dynamic_workspace_bytes", "mq_bos_aware_kv_proj_workspace_bytes"):
-            getattr(_lib, name).restype = C.c_size_t
-        _lib.mq_prof_bracket_overhead_us.restype = C.c_double
+            getattr(lib, name).restype = C.c_size_t
+        lib.mq_prof_bracket_overhead_us.restype = C.c_double
+        _native.bind(*(C.cast(getattr(lib, name), C.c_void_p).value for name in (
+            "mq_qlinear_w_only", "mq_qlinear_w8a8", "mq_qlinear_w4a8", "mq_qlinear_w2a8", "mq_quantize_weights", "mq_pack_weights",
+            "mq_split_workspace_bytes", "mq_qlinear_a8_workspace_bytes", "mq_packed_bytes")))
+        _lib = lib
     return _lib
 
 
@@ -203,13 +216,17 @@ def stack_weights(parts) -> PackedWeight:
 
 def quantize_weights(w: torch.Tensor, bits: int, symmetric: bool = False):
     """W [N,K] fp16/bf16 -> (codes uint8 [N,K], scale float32 [N], zp int32 [N])."""
+    lib = load()
+    r = _native.quantize_weights(w, bits, int(symmetric))
+    if r is not None:
+        return _done(r, "mq_quantize_weights")
     assert w.is_cuda and w.dim() == 2 and w.is_contiguous()
     N, K = w.shape
     codes = torch.empty((N, K), dtype=torch.uint8, device=w.device)
     scale = torch.empty(N, dtype=torch.float32, device=w.device)
     zp = torch.empty(N, dtype=torch.int32, device=w.device)
-    _check(load().mq_quantize_weights(_ptr(w), N, K, bits, int(symmetric), _dtype_code(w), _ptr(codes), _ptr(scale),
-                                      _ptr(zp), _stream()), "mq_quantize_weights")
+    _check(lib.mq_quantize_weights(_ptr(w), N, K, bits, int(symmetric), _dtype_code(w), _ptr(codes), _ptr(scale),
+                                  _ptr(zp), _stream()), "mq_quantize_weights")
     return codes, scale, zp
 
 
@@ -221,14 +238,18 @@ def pack_weights(codes: torch.Tensor, bits: int, layout: int = LAYOUT_KERNEL, co
                  want_colsum: bool = True):
     """codes uint8 [N,K] -> (packed uint8 [bytes], colsum int32 [N] or None).  bits = 16: `codes` is the fp16/bf16
     weight matrix itself and there is no colsum."""
+    lib = load()
+    r = _native.pack_weights(codes, bits, layout, int(codes_signed), int(want_colsum))
+    if r is not None:
+        return _done(r, "mq_pack_weights")
     assert codes.is_cuda and codes.dim() == 2 and codes.is_contiguous()
     assert codes.dtype == torch.uint8 if bits != 16 else codes.dtype in (torch.float16, torch.bfloat16)
     N, K = codes.shape
     nbytes = packed_bytes(N, K, bits, layout)
     packed = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=codes.device)
     colsum = torch.empty(N, dtype=torch.int32, device=codes.device) if (want_colsum and bits != 16) else None
-    _check(load().mq_pack_weights(_ptr(codes), N, K, bits, layout, int(codes_signed), _ptr(packed), _ptr(colsum),
-                                  _stream()), "mq_pack_weights")
+    _check(lib.mq_pack_weights(_ptr(codes), N, K, bits, layout, int(codes_signed), _ptr(packed), _ptr(colsum), _stream()),
+           "mq_pack_weights")
     return packed, colsum
 
 
@@ -261,6 +282,10 @@ def qlinear_w_only(x: torch.Tensor, w: PackedWeight, bias: Optional[torch.Tensor
                    ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Y = X . dequant(W)^T + bias (+ residual) with 16-bit floating-point compute (weight-only quantisation).
     ws: optional uint8 workspace of split_workspace_bytes(M, N, K) bytes; allocated here when the shape can use one."""
+    lib = load()
+    r = _native.qlinear_w_only(x, w.packed, w.N, w.K, w.bits, w.layout, w.scale, w.zp, bias, out, residual, ws)
+    if r is not None:
+        return _done(r, "mq_qlinear_w_only")
     assert x.is_cuda and x.dim() == 2 and x.stride(1) == 1
     M, K = x.shape
     assert K == w.K
@@ -269,9 +294,9 @@ def qlinear_w_only(x: torch.Tensor, w: PackedWeight, bias: Optional[torch.Tensor
     if ws is None:
         need = split_workspace_bytes(M, w.N, K)
         ws = torch.empty(need, dtype=torch.uint8, device=x.device) if need else None
-    _check(load().mq_qlinear_w_only(_ptr(x), M, K, x.stride(0), _ptr(w.packed), w.N, w.bits, w.layout, _ptr(w.scale),
-                                    _ptr(w.zp), _ptr(bias), _ptr(y), y.stride(0), _dtype_code(x), rp, ldr, *_ws_args(ws),
-                                    _stream()), "mq_qlinear_w_only")
+    _check(lib.mq_qlinear_w_only(_ptr(x), M, K, x.stride(0), _ptr(w.packed), w.N, w.bits, w.layout, _ptr(w.scale), _ptr(w.zp),
+                                 _ptr(bias), _ptr(y), y.stride(0), _dtype_code(x), rp, ldr, *_ws_args(ws), _stream()),
+           "mq_qlinear_w_only")
     return y
 
 
@@ -286,6 +311,13 @@ def _workspace(nbytes: int, device, ws: Optional[torch.Tensor]):
 
 
 def _qlinear_a8(fn_name, x, w: PackedWeight, act, bias, out, ws, want_acc, want_act, residual=None):
+    L = load()
+    if not (want_acc or want_act):
+        a_s, a_z = (None, None) if act is None else act
+        r = _native.qlinear_a8(x, w.packed, w.N, w.K, w.bits, w.layout, int(w.signed), w.scale, w.zp, w.colsum, a_s, a_z, bias,
+                               out, residual, ws)
+        if r is not None:
+            return _done(r, fn_name), None, (None, None)
     assert x.is_cuda and x.dim() == 2 and x.stride(1) == 1 and x.dtype == torch.float16
     M, K = x.shape
     assert K == w.K
@@ -297,7 +329,6 @@ def _qlinear_a8(fn_name, x, w: PackedWeight, act, bias, out, ws, want_acc, want_
     z_out = torch.empty(1, dtype=torch.int32, device=dev) if want_act else None
     a_s, a_z = (None, None) if act is None else act
     rp, ldr = _res(residual, M, w.N, torch.float16)
-    L = load()
     if fn_name == "mq_qlinear_w8a8":
         rc = L.mq_qlinear_w8a8(_ptr(x), M, K, x.stride(0), _ptr(w.packed), w.N, w.layout, int(w.signed), _ptr(w.scale),
                                _ptr(w.zp), _ptr(w.colsum), _ptr(a_s), _ptr(a_z), _ptr(bias), _ptr(y), y.stride(0),

@@ -1,16 +1,18 @@
-"""Builds libmixdq.so (gfx950) in-tree with hipcc.  Object files are cached per source; pass force=True to
-rebuild everything."""
+"""Builds libmixdq.so (gfx950) in-tree with hipcc, and _mqhost.so (host code over torch's C++ interface) with g++.  Object
+files are cached per source; pass force=True to rebuild everything."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.environ.get("MQ_CSRC_DIR", os.path.join(HERE, "csrc"))
 OBJ = os.environ.get("MQ_OBJ_DIR", os.path.join(HERE, "_build"))
 LIB = os.environ.get("MQ_LIB_OUT", os.path.join(HERE, "libmixdq.so"))
+HOST = os.path.join(os.path.dirname(LIB), "_mqhost.so")
 EXTRA = os.environ.get("MQ_EXTRA_FLAGS", "").split()
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -47,10 +49,31 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def _build_host(force: bool) -> None:
+    src = os.path.join(CSRC, "host.cpp")
+    if not force and os.path.exists(HOST) and all(os.path.getmtime(HOST) >= os.path.getmtime(d) for d in (src, __file__)):
+        return
+    import torch
+    from torch.utils import cpp_extension
+
+    tmp = f"{HOST}.{os.getpid()}"
+    inc = [f"-I{d}" for d in (*cpp_extension.include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"])]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", *inc, src, "-o", tmp,
+           *(f"-L{d}" for d in cpp_extension.library_paths()), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(r.stdout + r.stderr)
+        raise RuntimeError("g++ failed on host.cpp")
+    os.replace(tmp, HOST)
+
+
 def build(force: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        host = ex.submit(_build_host, force)
         objs = list(ex.map(lambda s: _compile(s, force), SOURCES))
+        host.result()
     if force or not os.path.exists(LIB) or any(os.path.getmtime(o) > os.path.getmtime(LIB) for o in objs):
         cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
         r = subprocess.run(cmd, capture_output=True, text=True)

@@ -1475,6 +1475,65 @@ def test_stacked_layers_that_share_their_input(mq, orc):
                 assert torch.equal(acc[:, i * N:(i + 1) * N], acci) and torch.equal(y[:, i * N:(i + 1) * N], yi)
 
 
+def test_eager_calls_natively_marshalled_and_by_the_general_way(mq, orc):
+    """A mode that intercepts operators (here one that changes nothing) sends the eager calls the general way: same results, same
+    refusals, with outputs given and allocated, residuals, parameters, strided rows and no tensors where they are optional."""
+    class Pass(torch.overrides.TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    def same(call):
+        a = call()
+        with Pass():
+            b = call()
+        flat = lambda r: [t for t in (r if isinstance(r, tuple) else (r,)) if isinstance(t, torch.Tensor)]
+        assert type(a) is type(b) and len(flat(a)) == len(flat(b))
+        for u, v in zip(flat(a), flat(b)):
+            assert u.dtype == v.dtype and u.shape == v.shape and u.device == v.device and np.array_equal(host(u), host(v))
+        return a
+
+    def refused(call):
+        errors = []
+        for mode in (None, Pass()):
+            with pytest.raises((AssertionError, TypeError, mq.MixdqError)) as e:
+                if mode is None:
+                    call()
+                else:
+                    with mode:
+                        call()
+            errors.append((e.type, getattr(e.value, "code", None), str(e.value)))
+        assert errors[0] == errors[1]
+
+    M, K, N = 33, 128, 72
+    w, b = dev(si.weights_f16(90, "ng/w", N, K)), dev(si.bias_f16(90, "ng/b", N))
+    wide = torch.zeros(M, K + 8, dtype=torch.float16, device="cuda")
+    wide[:, :K] = dev(si.activations_f16(90, "ng/x", M, K))
+    x, res = wide[:, :K], dev(si.activations_f16(90, "ng/r", M, N))
+    codes, scale, zp = same(lambda: mq.quantize_weights(torch.nn.Parameter(w), 4, False))
+    packed, colsum = same(lambda: mq.pack_weights(codes, 4))
+    assert same(lambda: mq.pack_weights(codes, 4, want_colsum=False))[1] is None
+    pw = mq.PackedWeight(packed, scale, zp, colsum, N, K, 4, mq.LAYOUT_KERNEL, False)
+    out = torch.empty(M, N, dtype=torch.float16, device="cuda")
+    act = (dev(np.array([0.04], np.float32)), dev(np.array([120], np.int32)))
+    for bias, residual in ((b, None), (None, res)):
+        same(lambda: mq.qlinear_w_only(x, pw, bias, residual=residual))
+        assert same(lambda: mq.qlinear_w_only(x, pw, bias, out=out, residual=residual)) is out
+        for a in (None, act):
+            same(lambda: mq.qlinear_w4a8(x, pw, act=a, bias=bias, residual=residual))
+            assert same(lambda: mq.qlinear_w4a8(x, pw, act=a, bias=bias, out=out, residual=residual))[0] is out
+    refused(lambda: mq.qlinear_w_only(x.cpu(), pw))
+    refused(lambda: mq.qlinear_w_only(x.float(), pw))
+    refused(lambda: mq.qlinear_w_only(x[:, :64], pw))
+    refused(lambda: mq.qlinear_w_only(x, pw, residual=res[:, :64]))
+    refused(lambda: mq.qlinear_w4a8(x.bfloat16(), pw))
+    refused(lambda: mq.qlinear_w4a8(x, pw, act=(act[0], None)))
+    refused(lambda: mq.qlinear_w4a8(x, pw, ws=torch.empty(256, dtype=torch.uint8, device="cuda")))
+    refused(lambda: mq.quantize_weights(w.t(), 4))
+    refused(lambda: mq.quantize_weights(w, 5))
+    refused(lambda: mq.pack_weights(codes.to(torch.int8), 4))
+    refused(lambda: mq.pack_weights(codes, 8, codes_signed=True, layout=7))
+
+
 def test_side_streams_and_two_streams_at_once(mq, orc):
     """The library launches on the stream it is handed and keeps no state that two streams could trample: the results
     on a side stream, and on two streams that run different layers at the same time (each call with a workspace of its

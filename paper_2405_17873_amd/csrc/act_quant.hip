@@ -275,8 +275,9 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
     // small tensors have more wavefronts to request them.  Whole calls with 64 output channels in us, four -> two -> one vector:
     //   given parameters 77 x 2048 10.0 -> 9.5 -> 9.3, 256 x 320 7.1 -> 6.5 -> 6.4, 616 x 2048 10.7 -> 10.3 -> 10.1,
     //     4096 x 640 9.5 -> 9.1 -> 8.9, 4096 x 320 8.0 -> 7.6 -> 7.4; 2964 x 1280 (one: 2964 workgroups) 10.5 -> 10.3
-    //   run-time range, every workgroup reads the pairs, so one vector only up to a workgroup per compute unit:
-    //     77 x 2048 13.4 -> 12.4 -> 12.3, 256 x 320 10.3 -> 9.5 -> 9.4, 616 x 2048 14.3 -> 14.0 -> 14.2, 1024 x 640 12.2 -> 11.5 -> 11.6
+    //   run-time range, every workgroup reads the pairs, so one vector only up to a workgroup per compute unit, two up to four:
+    //     77 x 2048 13.4 -> 12.4 -> 12.3, 256 x 320 10.3 -> 9.5 -> 9.4, 616 x 2048 14.3 -> 14.0 -> 14.2, 1024 x 640 12.2 -> 11.5 -> 11.6,
+    //     4096 x 1280 (two: 1366 workgroups) 17.6 -> 17.6
     // Beyond that grid, rows per workgroup: one round (1024 vectors) while that keeps it within eight workgroups per compute
     // unit.  A larger tensor can take as many rounds per workgroup as bring it there: the parameters are derived (and the pairs read)
     // that many times less often, but the grid may leave compute units idle at its end, the last round lanes, and the rounds
@@ -294,7 +295,7 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
     R = R < 1 ? 1 : R;
     for (int u = 1; u < Q_U && given_partials <= kPartialSlots; u *= 2) {
         const int rows = 256 * u / Kp8;
-        if (rows < 1 || (M + rows - 1) / rows > (dynamic && u == 1 ? kQuantGrid / 8 : kQuantGrid)) continue;
+        if (rows < 1 || (M + rows - 1) / rows > (dynamic ? kQuantGrid / (u == 1 ? 8 : 2) : kQuantGrid)) continue;
         U = u;
         R = rows;
         break;

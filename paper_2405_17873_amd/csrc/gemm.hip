@@ -401,11 +401,10 @@ struct GemmArgs {
     // MODE 3 / 4 (3x3 convolution, stride 1, zero padding 1, channels-last): a is the [B*H*W, Cin] activation tensor
     // (a_row_bytes per pixel), K = 9 * Cin, row m is output pixel m; the k order is (filter row, filter column, c)
     int conv_h, conv_w;      // input image
-    int conv_ho, conv_wo;    // output image: (H - 1) / stride + 1, likewise W; M = B * conv_ho * conv_wo
     int conv_stride;         // 1 or 2: output pixel (i, j) is centred on input pixel (stride * i, stride * j)
     int conv_cpt;            // 64-channel chunks per filter tap (Cin / 64)
     uint32_t conv_cpt_inv;   // ceil(2^32 / conv_cpt) for conv_cpt > 1
-    FastDiv fd_wo, fd_ho;    // divisors conv_wo and conv_ho
+    FastDiv fd_ho, fd_wo;    // output image ho x wo: (H - 1) / stride + 1, likewise W; M = B * ho * wo
     const int32_t* w_tapsum; // MODE 4: [9][N] sums of the weight codes per filter tap
     // optional residual [M, ldr] (16-bit, the dtype of y; rows as the rows of y): added in fp32 before the rounding
     const uint16_t* res;
@@ -1447,7 +1446,9 @@ void gemm_kernel(const GemmArgs g) {
 //   0: 128x256, 4 waves (1x4) of 128x64     1: 128x128, 4 waves (2x2) of 64x64     2: 64x64, 4 waves of 32x32
 //   3: as 1 and 4: as 2, with a second wave group splitting k inside the workgroup (8 waves)
 //   5: 64x128, 4 waves (1x4) of 64x32, two or three LDS stages: the form of tile 1 that puts more workgroups on a
-//      compute unit
+//      compute unit     6: 96x256, 4 waves (1x4) of 96x64
+//   (int8, plain layers) 7: as 5 with three stages   8, 9: 128x128, 8 waves (2x4) of 64x32, with stages for one or for two
+//      workgroups per compute unit
 // A tall wave tile pays: every widened weight fragment then feeds 4 MFMAs (measured: an MFMA hides about five vector
 // ALU instructions on its SIMD; what a wave needs beyond that costs time of its own).  256x256 tiles with one wave per
 // SIMD and 128x128 tiles with two-wave workgroups were measured slower on every configured shape.
@@ -1516,13 +1517,41 @@ static int pick_tile(int M, int N, int K, bool wide_weights = false) {
 // stages instead of three, and eight waves on 64x256, were measured slower.
 // Weights that do not fit an XCD's L2 by a wide margin are streamed from the last-level cache once per row block,
 // twice as often with the half height: 8-bit 1280 -> 10240 (13 MB) on the int8 path took 121 us against 88; they
-// keep the full height.
+// keep the full height (that layer has a form of its own now, int8_tile).
 template <bool I8, int BITS>
 static int narrow_tile(int t, long N, long K) {
     if (g_force_tile == 5) return 5;
     if (g_force_tile >= 0 || (t != 1 && t != 3)) return t;
     if (BITS == 16 || N * K * BITS / 8 > (8L << 20)) return t;
     return 5;  // (also in place of tile 3: 5 to 7 % faster on its one regime, 4096 x 2560 x 640)
+}
+
+// The int8 path has more forms of tile 1, by how many workgroups a compute unit gets: with few of them the wait for loads
+// counts (more stages, or the eight waves of one 128x128 workgroup over half the L2 -> LDS traffic per operation), with many
+// the number of waves.  8-bit weights move twice the bytes, so that the L2 -> LDS path bounds the half height there (96 bytes
+// per clock and compute unit at the full MFMA rate, of 55): they have a form of their own for many tiles.  Whole calls with given
+// parameters in us, tile 5 / 7 / 8 (/ 9):
+//   4-bit weights: 2048 x 5120 x 1280 (320 workgroups of tile 5) 36.9 / 29.9 / 31.3, 2400 x 1280 x 1280 (380) 14.7 / 13.8 / 13.7,
+//     2560 x 2560 x 1280 (400) 23.0 / 19.9 / 20.3, 6000 x 2560 x 640 (470) 28.6 / 27.5 / 25.7, 3200 x 5120 x 1280 (500) 44.3 / 40.8 / 38.2,
+//     4096 x 1280 x 1280 (640, 320 of 128x128) 16.8 / 17.8 / 18.9
+//   8-bit weights: 2048 x 5120 x 1280 39.5 / 32.7 / 36.1, 2400 x 1280 x 1280 15.7 / 14.8 / 14.9, 2964 x 1280 x 1280 (470) 15.9 / 17.3 / 15.9, 3200 x 2560 x 1280 25.3 / 26.3 / 23.2,
+//     3200 x 5120 x 1280 46.8 / 48.1 / 42.1, 4096 x 1280 x 1280 19.2 / 21.2 / 23.9 / 19.7, 16384 x 2560 x 640 (640 of 128x128) 67.2 / - / - / 71.4,
+//     9000 x 1280 x 1280 (710) 32.4 / 34.5 / 33.9 / 30.8, 16384 x 640 x 5120 105.8 / - / - / 92.5, 4096 x 1280 x 10240 84.9 / - / - / 74.9
+// Fewer tiles than that: the wave groups of tile 4 leave 8-bit weights two stages, tile 2 has four: 616 x 2048 x 1280 13.3 / 11.7,
+// 700 x 5120 x 1280 24.6 / 20.2, 700 x 1280 x 1280 10.9 / 10.0 (tile 4 with twice the LDS 12.0, 20.3, 10.3); at 4 bits tile 4 is
+// the better one, 11.0 / 11.6 and 18.0 / 20.7.  Long reductions
+// that are split over workgroups stay with tile 4, whose parts are fewer: 64 x 5120 x 1280 14.3 / 16.0.
+template <int BITS>
+static int int8_tile(int t, long M, long N, long K) {
+    if (g_force_tile >= 7) return g_force_tile;
+    if (BITS == 8 && t == 4 && g_force_tile < 0) return K >= 4096 && ((M + 63) / 64) * ((N + 63) / 64) <= 64 ? 4 : 2;
+    const int narrow = narrow_tile<true, BITS>(t, N, K);
+    if (g_force_tile >= 0 || (t != 1 && t != 3)) return narrow;
+    const long t1 = ((M + 127) / 128) * ((N + 127) / 128), t5 = ((M + 63) / 64) * ((N + 127) / 128);
+    if (t5 <= 384) return 7;
+    if (t1 <= 256 && K >= 1536) return 8;
+    if (BITS == 8) return t1 > 640 ? 9 : 5;
+    return narrow;
 }
 
 template <bool I8, int BITS, int WGM, int WGN, int TM, int TN, int S, int KS>
@@ -1563,7 +1592,9 @@ static int run_gemm_r(GemmArgs& g, int tile_index, hipStream_t st) {
     int splits = 1;
     if (g_force_splits > 1) {
         splits = g_force_splits < KT ? g_force_splits : KT;
-    } else if (g_force_splits == 0 && tiles <= 64 && KT >= 16) {
+    } else if (g_force_splits == 0 && tiles <= 64 && KT >= 16 && !(I8 && BITS == 8 && KS == 1 && tiles > 32 && KT < 32)) {
+        // (8-bit weights, 77 x 2048 x 320 (10 tiles) 15.5 whole -> 15.2 us split, 640 16.0 -> 15.9, but 1280 (40) 17.3 -> 18.0,
+        // 152 x 2048 x 1280 (60) 17.5 -> 19.4, 308 x 2048 x 640 (50) 16.9 -> 18.5; 64 x 3392 x 1280 (20) 17.7 whole, 12.6 split)
         // (measured: handing the sums over costs about as much as eight pipeline stages)
         splits = (int)(512 / tiles);
         if (splits > KT / 4) splits = KT / 4;
@@ -1646,7 +1677,19 @@ static int dispatch_gemm(GemmArgs& g, hipStream_t st) {
     // large tile two workgroups per compute unit would not fit, so it runs one per compute unit with a deeper
     // pipeline (and is not chosen automatically)
     constexpr bool WIDE = (I8 && BITS == 8) || BITS == 16;
-    switch (narrow_tile<I8, BITS>(pick_tile(g.M, g.N, g.K, WIDE), g.N, g.K)) {
+    int t = pick_tile(g.M, g.N, g.K, WIDE);
+    if constexpr (I8) {
+        t = int8_tile<BITS>(t, g.M, g.N, g.K);
+        switch (t) {
+            case 7: return run_gemm<I8, BITS, 1, 4, 2, 1, 1, 76 * 1024, 3>(g, 7, st);
+            case 8: return run_gemm<I8, BITS, 2, 4, 2, 1, 1, BITS == 8 ? 160 * 1024 : 80 * 1024, 4>(g, 8, st);
+            case 9:
+                if constexpr (BITS == 8) return run_gemm<I8, BITS, 2, 4, 2, 1, 1, 80 * 1024, 4>(g, 9, st);
+        }
+    } else {
+        t = narrow_tile<I8, BITS>(t, g.N, g.K);
+    }
+    switch (t) {
         case 0: return run_gemm<I8, BITS, 1, 4, 4, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4>(g, 0, st);
         case 1: return run_gemm<I8, BITS, 2, 2, 2, 2, 1, 80 * 1024, 4>(g, 1, st);
         case 2: return run_gemm<I8, BITS, 2, 2, 1, 1, 1, 80 * 1024, 8>(g, 2, st);
@@ -1903,14 +1946,13 @@ static void conv_args(GemmArgs& g, int B, int H, int W, int Cin, int stride, lon
     g.a_row_bytes = pix_bytes;
     g.a_bytes = (uint32_t)((long)B * H * W * pix_bytes);
     g.conv_stride = stride;
-    g.conv_ho = (H - 1) / stride + 1;
-    g.conv_wo = (W - 1) / stride + 1;
-    g.M = B * g.conv_ho * g.conv_wo;
+    const int ho = (H - 1) / stride + 1, wo = (W - 1) / stride + 1;
+    g.M = B * ho * wo;
     g.K = 9 * Cin;
     g.conv_h = H;
     g.conv_w = W;
-    g.fd_wo = FastDiv::make((uint32_t)g.conv_wo);
-    g.fd_ho = FastDiv::make((uint32_t)g.conv_ho);
+    g.fd_ho = FastDiv::make((uint32_t)ho);
+    g.fd_wo = FastDiv::make((uint32_t)wo);
     g.conv_cpt = Cin / 64;
     g.conv_cpt_inv = g.conv_cpt > 1 ? (uint32_t)(((1ull << 32) + g.conv_cpt - 1) / g.conv_cpt) : 0u;
 }

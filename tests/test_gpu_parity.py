@@ -622,6 +622,32 @@ def test_a8_transformer_block_shapes_sampled_rows(mq, orc, K, N):
         assert_close16(host(y)[rows], ry, f"c3 W{bits}A8 {K}->{N}")
 
 
+@pytest.mark.parametrize("mode", ("w8s", "w8a", "w4", "w2"))
+@pytest.mark.parametrize("tile", (7, 8, 9))
+def test_a8_tiles_for_few_and_many_workgroups(mq, orc, mode, tile):
+    """Remainders of rows, channels and k-stages, a residual, and the split of the reduction over workgroups."""
+    test_a8_small_shapes(mq, orc, mode, tile)
+    if mode in ("w8s", "w4"):
+        test_residual_a8(mq, orc, mode, tile)
+    if mode == "w4":
+        test_every_splitting_kernel_takes_a_workspace_with_any_contents(mq, orc, "a8", tile)
+
+
+@pytest.mark.parametrize("M", (3072, 3073, 4096, 4097, 10240, 10241))
+def test_a8_both_sides_of_the_tile_rule(mq, orc, M):
+    """The automatic choice at 384, 392 and 512 workgroups of 64 x 128, 256, 264, 640 and 648 of 128 x 128."""
+    K, N = 192, 1024
+    x = si.activations_f16(14, f"tr/x{M}", M, K, outlier_prob=0.01)
+    w = si.weights_f16(14, "tr/w", N, K)
+    rows = sample_rows(x, 128, M)
+    for bits, fn in ((8, mq.qlinear_w8a8), (4, mq.qlinear_w4a8)):
+        pw, oc, os_, oz = make_weight(mq, orc, w, bits)
+        y, acc, _ = fn(dev(x), pw, want_acc=True, want_act=True)
+        ry, racc, _ = orc.linear_a8(x, oc, os_, oz, rows=rows)
+        assert np.array_equal(host(acc)[rows], racc)
+        assert_close16(host(y)[rows], ry, f"W{bits}A8 {M}x{K}x{N}")
+
+
 def test_a8_longest_reduction_and_extreme_codes(mq, orc):
     """K = 33024 is the longest reduction the int32 accumulator is guaranteed to hold (255 * 255 * K < 2^31).  All
     activation codes and all weight codes are 0 or 255 with zero points 0; row 0 against channel 0 is 255 * 255 in

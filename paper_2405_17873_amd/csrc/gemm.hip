@@ -459,7 +459,7 @@ struct GemmPlan {
     static constexpr int DMA_B = (NBI + NW - 1) / NW;         // per wave (padded with loads into the sink)
     static constexpr int OPS = DMA_A + DMA_B;                 // vector-memory operations per wave per stage
     static constexpr int SINK = S * STAGE_BYTES;
-    static constexpr int CONSTS = SINK + 1024;
+    static constexpr int CONSTS = SINK + (TM == 3 && TN == 1 ? 1536 : 1024);  // (the shares of 96 row sums, see rs_x)
     static constexpr int LDS_BYTES = CONSTS + BN * 16;
     static_assert(NAI % NW == 0, "tile rows must split over the waves");
 };
@@ -501,7 +501,7 @@ void gemm_kernel(const GemmArgs g) {
     int bm, bn;
     // (the large wave tile has no registers to spare for the split of the reduction over workgroups, and no use
     // for it: its problems have hundreds of tiles)
-    constexpr bool CAN_SPLIT = TM * TN <= 4 && MODE == 0;
+    constexpr bool CAN_SPLIT = TM * TN <= 4 && TM != 3 && MODE == 0;
     const int splits = CAN_SPLIT ? g.splits : 1;
     uint32_t tile_u = blockIdx.x, sp_u = 0;  // sp: which part of the reduction this workgroup takes
     if (splits > 1) g.fd_splits.divmod(blockIdx.x, tile_u, sp_u);
@@ -887,7 +887,7 @@ void gemm_kernel(const GemmArgs g) {
     // one each.  They meet in the idle sink of the padding loads.
     int* const rs_x = (int*)(lds + P::SINK) + wm * TM * 32 + l31;
     if constexpr (RS_INLINE) {
-        static_assert((WGN == 2 || WGN == 4) && KS * WGN * BM * 4 <= 1024, "shares of the row sums fit the sink");
+        static_assert((WGN == 2 || WGN == 4) && KS * WGN * BM * 4 <= P::CONSTS - P::SINK, "shares of the row sums fit the sink");
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             rsum[tm] += __shfl_xor(rsum[tm], 32, 64);
@@ -1446,9 +1446,10 @@ void gemm_kernel(const GemmArgs g) {
 //   0: 128x256, 4 waves (1x4) of 128x64     1: 128x128, 4 waves (2x2) of 64x64     2: 64x64, 4 waves of 32x32
 //   3: as 1 and 4: as 2, with a second wave group splitting k inside the workgroup (8 waves)
 //   5: 64x128, 4 waves (1x4) of 64x32, two or three LDS stages: the form of tile 1 that puts more workgroups on a
-//      compute unit     6: 96x256, 4 waves (1x4) of 96x64
+//      compute unit     6 (16-bit activations, linear layers): 96x256, 4 waves (1x4) of 96x64
 //   (int8, plain layers) 7: as 5 with three stages   8, 9: 128x128, 8 waves (2x4) of 64x32, with stages for one or for two
 //      workgroups per compute unit
+//   10: 96x128, 4 waves (1x4) of 96x32   11 (16-bit activations, plain layers): as 5 with a second wave group splitting k
 // A tall wave tile pays: every widened weight fragment then feeds 4 MFMAs (measured: an MFMA hides about five vector
 // ALU instructions on its SIMD; what a wave needs beyond that costs time of its own).  256x256 tiles with one wave per
 // SIMD and 128x128 tiles with two-wave workgroups were measured slower on every configured shape.
@@ -1493,7 +1494,7 @@ static inline size_t split_counter_bytes(long tiles, int step) { return ((size_t
 // k-split variants only pay where tiles are few and k is long (FF-out at the 640 level, the K/V projections).
 static int pick_tile(int M, int N, int K, bool wide_weights = false) {
     if ((g_force_tile >= 0 && g_force_tile <= 4) || g_force_tile == 6) return g_force_tile;
-    if (g_force_tile == 5) return 1;  // the half-height form of tile 1: the linear layers' dispatch decides (narrow_tile)
+    if (g_force_tile == 5) return 1;  // the half-height form of tile 1: the linear layers' dispatch decides
     const long t0 = (long)((M + 127) / 128) * ((N + 255) / 256);
     // One row block of 65 to 96 rows over very many column tiles (one prompt's 77 text tokens through all K/V
     // projections of the UNet, stacked): the 96x256 tile does three quarters of the large tile's MFMA and widening work
@@ -1515,15 +1516,43 @@ static int pick_tile(int M, int N, int K, bool wide_weights = false) {
 // slower on the 16-bit-activation path).  Measured on operands that are not cached: 8 to 19 % faster on every such
 // shape of both paths, except with unquantised 16-bit weights (4 KB per weight tile), which keep tile 1.  Two
 // stages instead of three, and eight waves on 64x256, were measured slower.
-// Weights that do not fit an XCD's L2 by a wide margin are streamed from the last-level cache once per row block,
-// twice as often with the half height: 8-bit 1280 -> 10240 (13 MB) on the int8 path took 121 us against 88; they
-// keep the full height (that layer has a form of its own now, int8_tile).
-template <bool I8, int BITS>
-static int narrow_tile(int t, long N, long K) {
-    if (g_force_tile == 5) return 5;
-    if (g_force_tile >= 0 || (t != 1 && t != 3)) return t;
-    if (BITS == 16 || N * K * BITS / 8 > (8L << 20)) return t;
-    return 5;  // (also in place of tile 3: 5 to 7 % faster on its one regime, 4096 x 2560 x 640)
+// The linear layers of the 16-bit-activation path and the convolutions have a third form, 96x128 (tile 10): three MFMAs per
+// widened weight fragment instead of two, for fewer workgroups.  A kernel lasts as long as its busiest compute unit, so the form
+// is chosen by what that unit multiplies: its number of workgroups times their height (UNITS: compute units).  At equal
+// height the taller form is faster, and mostly so where it takes an eighth more.  us, tile 5 / 10 (rows of the busiest unit):
+//   4-bit weights, fp16: 4096 x 1280 x 1280 (192 / 192) 17.6 / 16.5, 4096 x 5120 x 1280 59.1 / 55.4, 7293 x 1280 x 1280 (320 / 288) 29.9 / 25.8,
+//     7402 x 1280 x 320 (128 / 96) 13.0 / 12.1, 6362 x 5120 x 1280 (256 / 288) 84.6 / 83.3, but 2964 x 1280 x 1280 (128 / 192) 13.3 / 15.4,
+//     16384 x 640 x 640 (320 / 384) 16.4 / 17.7; bf16 4096 x 2560 x 640 (128 / 96) 25.3 / 23.9, 3896 x 5120 x 1280 (192 / 192) 70.9 / 61.8
+//   convolutions, 16-bit activations, 4-bit weights: 4 x 32 x 32, 1280 -> 1280 (192 / 192) 138 / 129, 3 x 100 x 128, 320 -> 320 (512 / 480)
+//     93.8 / 86.2, 4 x 64 x 64 x 640 (320 / 384) 126 / 135
+static constexpr long UNITS = 256;
+static bool taller(long M, long N, long num, long den) {  // busiest unit: rows of tile 10 <= num / den of tile 5's
+    const long cols = (N + 127) / 128;
+    const long t5 = (M + 63) / 64 * cols, t10 = (M + 95) / 96 * cols;
+    return 96 * den * ((t10 + UNITS - 1) / UNITS) <= 64 * num * ((t5 + UNITS - 1) / UNITS);
+}
+
+// Linear layers on 16-bit activations (unquantised weights keep tile 1).
+// Where the 64x64 tiles are more than one round of workgroups but those of 64x128 are not, a compute unit would get one wave
+// per SIMD of the latter; with a second wave group on the other half of the reduction (tile 11) it gets two.  us, 64x64 form / tile 5 / tile 11,
+// fp16: 4-bit weights 1024 x 1280 x 1280 10.4 / 9.9 / 9.3, 1024 x 5120 x 1280 30.8 / 31.1 / 25.7, 2048 x 2560 x 640 17.3 / 17.1 / 14.7, 2048 x 640 x 640
+// 7.0 / 6.4 / 6.3, 4096 x 448 x 320 6.0 / 5.8 / 6.1; 8-bit (twice the weight pieces per stage) 1536 x 1280 x 1280 11.4 / 10.7 / 10.3, 900 x 960 x 1280 8.9 / 8.4 / 8.4,
+// 4096 x 640 x 320 7.2 / 6.6 / 6.8; bf16 1024 x 5120 x 1280 42.4 / 36.8 / 29.8, 2048 x 640 x 640 8.4 / 7.3 / 6.9.
+// A handful of rows with 1024 to 2047 k: tile 4 has too few stages to split over workgroups, tile 2 has not.  us, tile 4 / 2: fp16
+// 4 x 1920 x 1280 9.8 / 8.0, 32 x 1280 x 640 7.6 / 7.0, 32 x 1280 x 1280 7.6 / 7.4, but 64 x 1280 x 1280 7.5 / 8.3 and 16 x 1280 x 2560 7.5 / 8.8; bf16 4 x 1920 x 1280
+// 12.0 / 8.4, 64 x 1280 x 1280 9.0 / 8.6, 77 x 1280 x 1280 9.0 / 9.8.
+// Two row blocks of 96 over very many columns, tile 0 / 10: 154 x 2048 x 166400 at 2, 4, 8 bits 134 / 113, 141 / 122, 168 / 146, 83200 71 / 61, 74 / 65, 79 / 70
+// (one such block keeps tile 6: 64.6 / 66.8 at 4 bits and 166400 columns, 38.7 / 34.0 at 83200).
+template <int BITS>
+static int float_tile(int t, long M, long N, long K, bool bf16) {
+    if (g_force_tile >= 0) return g_force_tile == 5 || (BITS != 16 && g_force_tile >= 10) ? g_force_tile : t;
+    if (BITS == 16 || t == 6) return t;
+    if (t == 0) return M > 128 && M <= 192 ? 10 : 0;
+    const long t2 = ((M + 63) / 64) * ((N + 63) / 64), t5 = ((M + 63) / 64) * ((N + 127) / 128);
+    if (t2 > UNITS && t5 <= UNITS) return K >= (BITS == 8 ? 1280 : 640) ? 11 : 5;
+    if (t == 1 || t == 3) return taller(M, N, 9, 8) ? 10 : 5;
+    if (t == 4 && M <= (bf16 ? 64 : 32) && K < 2048 && t2 <= 32) return 2;
+    return t;
 }
 
 // The int8 path has more forms of tile 1, by how many workgroups a compute unit gets: with few of them the wait for loads
@@ -1541,17 +1570,26 @@ static int narrow_tile(int t, long N, long K) {
 // 700 x 5120 x 1280 24.6 / 20.2, 700 x 1280 x 1280 10.9 / 10.0 (tile 4 with twice the LDS 12.0, 20.3, 10.3); at 4 bits tile 4 is
 // the better one, 11.0 / 11.6 and 18.0 / 20.7.  Long reductions
 // that are split over workgroups stay with tile 4, whose parts are fewer: 64 x 5120 x 1280 14.3 / 16.0.
+// One or two row blocks of 96 over very many columns (the K/V projections of all layers for one or two prompts of 77 tokens, stacked)
+// stream their weights: several workgroups per compute unit whose loads cover each other's epilogues, at three quarters of the rows
+// (tile 10).  Whole calls, 96x256 with one workgroup per unit (one prompt) or 128x256 and 128x128 (two) / tile 10: 8-bit weights
+// 77 x 2048 x 166400 79.8 / 76.3, 83200 47.6 / 40.0, 40960 25.7 / 24.7, 30720 20.7 / 22.2, 154 x 2048 x 166400 125.4 / 112.7, 20480 20.6 / 22.1; 4-bit 77 x 2048 x 166400
+// 46.0 / 44.3, 65280 25.7 / 22.8, 154 x 2048 x 166400 86.2 / 73.5, 40960 36.2 / 27.4.
+// Weights that do not fit an XCD's L2 by a wide margin are streamed from the last-level cache once per row block, so tall problems
+// keep the full height (4-bit 1536 x 2560 x 10240 49.8 / 50.9 with tile 1 / 5); of few row blocks each is better read twice by more
+// workgroups: 154 x 2048 x 20480 24.8 / 18.8, 308 x 2048 x 40960 42.9 / 40.0, 512 x 2560 x 10240 24.2 / 21.6, 1024 x 5120 x 5120 41.2 / 37.4.
 template <int BITS>
 static int int8_tile(int t, long M, long N, long K) {
-    if (g_force_tile >= 7) return g_force_tile;
+    if (g_force_tile >= 7) return g_force_tile == 11 ? 5 : g_force_tile;
     if (BITS == 8 && t == 4 && g_force_tile < 0) return K >= 4096 && ((M + 63) / 64) * ((N + 63) / 64) <= 64 ? 4 : 2;
-    const int narrow = narrow_tile<true, BITS>(t, N, K);
-    if (g_force_tile >= 0 || (t != 1 && t != 3)) return narrow;
+    if (g_force_tile >= 0) return g_force_tile == 5 ? 5 : t;
+    if (((M > 64 && M <= 96) || (M > 128 && M <= 192)) && (N + 127) / 128 >= 320) return 10;
+    if (t != 1 && t != 3) return t;
     const long t1 = ((M + 127) / 128) * ((N + 127) / 128), t5 = ((M + 63) / 64) * ((N + 127) / 128);
     if (t5 <= 384) return 7;
     if (t1 <= 256 && K >= 1536) return 8;
     if (BITS == 8) return t1 > 640 ? 9 : 5;
-    return narrow;
+    return M > 1024 && N * K * BITS / 8 > (8L << 20) ? t : 5;
 }
 
 template <bool I8, int BITS, int WGM, int WGN, int TM, int TN, int S, int KS>
@@ -1601,7 +1639,7 @@ static int run_gemm_r(GemmArgs& g, int tile_index, hipStream_t st) {
         if (splits > 16) splits = 16;
     }
     g.splits = 1;
-    if (MODE == 0 && TM * TN <= 4 && splits > 1) {
+    if (MODE == 0 && TM * TN <= 4 && TM != 3 && splits > 1) {
         // as many parts as the caller's workspace holds (forced part counts are for tests: they must fit)
         size_t cbytes = split_counter_bytes(tiles, 1);
         const size_t part_bytes = (size_t)tiles * P::BM * P::BN * 4;
@@ -1687,25 +1725,37 @@ static int dispatch_gemm(GemmArgs& g, hipStream_t st) {
                 if constexpr (BITS == 8) return run_gemm<I8, BITS, 2, 4, 2, 1, 1, 80 * 1024, 4>(g, 9, st);
         }
     } else {
-        t = narrow_tile<I8, BITS>(t, g.N, g.K);
+        t = float_tile<BITS>(t, g.M, g.N, g.K, false);
+        if constexpr (BITS != 16)
+            if (t == 11) return run_gemm<I8, BITS, 1, 4, 2, 1, 2, BITS == 8 ? 160 * 1024 : 80 * 1024, 4>(g, 11, st);
     }
+    if constexpr (BITS != 16)
+        if (t == 10 || (I8 && t == 6)) return run_gemm<I8, BITS, 1, 4, 3, 1, 1, 53 * 1024, 3>(g, 10, st);
     switch (t) {
         case 0: return run_gemm<I8, BITS, 1, 4, 4, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4>(g, 0, st);
         case 1: return run_gemm<I8, BITS, 2, 2, 2, 2, 1, 80 * 1024, 4>(g, 1, st);
         case 2: return run_gemm<I8, BITS, 2, 2, 1, 1, 1, 80 * 1024, 8>(g, 2, st);
         case 3: return run_gemm<I8, BITS, 2, 2, 2, 2, 2, 160 * 1024, 4>(g, 3, st);
         case 5: return run_gemm<I8, BITS, 1, 4, 2, 1, 1, I8 ? 40 * 1024 : 52 * 1024, 3>(g, 5, st);
-        case 6: return run_gemm<I8, BITS, 1, 4, 3, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4>(g, 6, st);
+        case 6:
+            if constexpr (!I8) return run_gemm<I8, BITS, 1, 4, 3, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4>(g, 6, st);
         default: return run_gemm<I8, BITS, 2, 2, 1, 1, 2, 80 * 1024, 8>(g, 4, st);
     }
 }
 
-// bfloat16 activations: the three plain tiles (the k-split variants fall back to their plain counterparts).
+// bfloat16 activations: tile 3 and, with unquantised weights, tile 4 fall back to their plain counterparts.  (Tile 4 in place of tile 2 in us:
+// 77 x 2048 x 640 9.8 -> 8.7, 77 x 2048 x 1280 15.2 -> 9.7, 308 x 2048 x 640 19 -> 11.2, 616 x 2048 x 1280 14.5 -> 13.1.)
 template <int BITS>
 static int dispatch_gemm_bf16(GemmArgs& g, hipStream_t st) {
     constexpr bool WIDE = BITS == 16;
     int t = pick_tile(g.M, g.N, g.K, WIDE);
-    t = narrow_tile<false, BITS>(t == 6 ? 0 : (t >= 3 ? t - 2 : t), g.N, g.K);
+    t = float_tile<BITS>(t == 6 ? 0 : (t == 3 || BITS == 16 && t == 4 ? t - 2 : t), g.M, g.N, g.K, true);
+    if constexpr (BITS != 16)
+        switch (t) {
+            case 4: return run_gemm<false, BITS, 2, 2, 1, 1, 2, 80 * 1024, 8, true>(g, 4, st);
+            case 10: return run_gemm<false, BITS, 1, 4, 3, 1, 1, 53 * 1024, 3, true>(g, 10, st);
+            case 11: return run_gemm<false, BITS, 1, 4, 2, 1, 2, BITS == 8 ? 160 * 1024 : 80 * 1024, 4, true>(g, 11, st);
+        }
     switch (t) {
         case 0: return run_gemm<false, BITS, 1, 4, 4, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4, true>(g, 0, st);
         case 1: return run_gemm<false, BITS, 2, 2, 2, 2, 1, 80 * 1024, 4, true>(g, 1, st);
@@ -1978,6 +2028,8 @@ static int dispatch_conv_w_only(GemmArgs& g, hipStream_t st) {
     int t = conv_tile(g.M, g.N, g.K, WIDE);
     // (the large tile only where its 256 channels are filled: the UNet's 320-channel level is better served by 128)
     if (g_force_tile < 0 && t == 0 && g.N < 512) t = 1;
+    if (g_force_tile == 10 || (g_force_tile < 0 && t == 1 && taller(g.M, g.N, 9, 8)))
+        return run_gemm<false, BITS, 1, 4, 3, 1, 1, 53 * 1024, 3, false, 3>(g, 10, st);
     if (g_force_tile == 5 || (g_force_tile < 0 && t == 1))
         return run_gemm<false, BITS, 1, 4, 2, 1, 1, 52 * 1024, 3, false, 3>(g, 5, st);
     switch (t) {
@@ -2029,8 +2081,15 @@ int launch_conv3x3_a8(const int8_t* a8, const ActParams* params, int B, int H, i
     g.acc_debug = acc_debug;
     // (not the large tile: no registers to spare for the row sums and the tap masks; tile 5 in place of tile 1)
     int t = conv_tile(g.M, N, g.K, true);
+    // Or tile 10, see taller(); it has two stages only, so not where a compute unit gets just one workgroup of it (2 x 32 x 32,
+    // 1280 -> 1280 at 4 bits 64.2 us with tile 5, 69.9), and 8-bit weights leave room for fewer of them: 4-bit 4 x 32 x 32, 1280 -> 1280
+    // 88.6 / 84.2, 3 x 64 x 64 x 640 (an eighth more rows) 65.2 / 63.9, 8-bit 98.4 / 89.1 and 79.0 / 84.6.
+    if ((t <= 1 && g_force_tile < 0 && (long)((g.M + 95) / 96) * ((N + 127) / 128) > UNITS &&
+         taller(g.M, N, w_bits == 8 ? 1 : 9, w_bits == 8 ? 1 : 8)) || g_force_tile == 10)
+        t = 10;
     if (w_bits == 4) {
         g.w_off = 0;
+        if (t == 10) return run_gemm<true, 4, 1, 4, 3, 1, 1, 53 * 1024, 3, false, 4>(g, 10, st);
         if (t <= 1 && g_force_tile != 1) return run_gemm<true, 4, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
         if (t <= 1) return run_gemm<true, 4, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 4>(g, 1, st);
         if (t == 4) return run_gemm<true, 4, 2, 2, 1, 1, 2, 80 * 1024, 8, false, 4>(g, 4, st);
@@ -2038,6 +2097,7 @@ int launch_conv3x3_a8(const int8_t* a8, const ActParams* params, int B, int H, i
     }
     if (w_bits == 2) {
         g.w_off = 0;
+        if (t == 10) return run_gemm<true, 2, 1, 4, 3, 1, 1, 53 * 1024, 3, false, 4>(g, 10, st);
         if (t <= 1 && g_force_tile != 1) return run_gemm<true, 2, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
         if (t <= 1) return run_gemm<true, 2, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 4>(g, 1, st);
         if (t == 4) return run_gemm<true, 2, 2, 2, 1, 1, 2, 80 * 1024, 8, false, 4>(g, 4, st);
@@ -2045,6 +2105,7 @@ int launch_conv3x3_a8(const int8_t* a8, const ActParams* params, int B, int H, i
     }
     if (w_bits == 8) {
         g.w_off = w_signed ? 0 : 128;
+        if (t == 10) return run_gemm<true, 8, 1, 4, 3, 1, 1, 53 * 1024, 3, false, 4>(g, 10, st);
         if (t <= 1 && g_force_tile != 1) return run_gemm<true, 8, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
         if (t <= 1) return run_gemm<true, 8, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 4>(g, 1, st);
         if (t == 4) return run_gemm<true, 8, 2, 2, 1, 1, 2, 80 * 1024, 8, false, 4>(g, 4, st);

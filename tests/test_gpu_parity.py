@@ -214,7 +214,11 @@ def test_w_only_exact_integer_case(mq, orc):
 
 def test_w_only_bf16(mq, orc):
     """bfloat16 activations, bias and output (fp32 accumulate); weights quantised from bf16 as well."""
-    for (M, K, N, tile) in ((256, 320, 320, -1), (300, 640, 640, 1), (77, 128, 40, 2), (513, 2048, 264, 0), (300, 640, 264, 5)):
+    check_w_only_bf16(mq, orc, ((256, 320, 320, -1), (300, 640, 640, 1), (77, 128, 40, 2), (513, 2048, 264, 0), (300, 640, 264, 5)))
+
+
+def check_w_only_bf16(mq, orc, shapes):
+    for (M, K, N, tile) in shapes:
         mq.tune_force_tile(tile)
         xb = torch.from_numpy(si.normal(21, f"bf/x{M}", (M, K)).astype(np.float32)).to(torch.bfloat16)
         wb = torch.from_numpy(si.normal(21, f"bf/w{N}", (N, K), 0.02).astype(np.float32)).to(torch.bfloat16)
@@ -646,6 +650,79 @@ def test_a8_both_sides_of_the_tile_rule(mq, orc, M):
         ry, racc, _ = orc.linear_a8(x, oc, os_, oz, rows=rows)
         assert np.array_equal(host(acc)[rows], racc)
         assert_close16(host(y)[rows], ry, f"W{bits}A8 {M}x{K}x{N}")
+
+
+@pytest.mark.parametrize("tile", (10, 11))
+def test_tiles_of_96_rows_and_of_two_k_groups(mq, orc, tile):
+    """Remainders of rows, channels and k steps (an odd number of them for two k groups), residuals, bfloat16, and the split of the
+    reduction over workgroups; tile 10 on both convolutions too."""
+    for bits in ALL_BITS:
+        test_w_only_small_shapes(mq, orc, bits, tile)
+    test_residual_weight_only(mq, orc, tile)
+    check_w_only_bf16(mq, orc, ((95, 192, 40, tile), (97, 320, 136, tile), (300, 704, 264, tile)))
+    if tile == 11:
+        for kind in ("f16", "bf16"):
+            test_every_splitting_kernel_takes_a_workspace_with_any_contents(mq, orc, kind, tile)
+        return
+    for mode in ("w8s", "w8a", "w4", "w2"):
+        test_a8_small_shapes(mq, orc, mode, tile)
+    test_residual_a8(mq, orc, "w4", tile)
+    for bits in ALL_BITS:
+        test_conv_w_only(mq, orc, bits, tile)
+    for bits, sym in ((4, False), (8, True), (8, False), (2, False)):
+        test_conv_a8(mq, orc, bits, sym, tile)
+    test_conv_stride_two(mq, orc, tile)
+
+
+@pytest.mark.parametrize("M,K,N", [(1056, 640, 1024), (2048, 640, 1024), (2049, 576, 1024), (2049, 640, 1024), (4096, 192, 512), (4097, 192, 512),
+                                   (6144, 192, 512), (6145, 192, 512), (32, 1280, 256), (33, 1280, 256), (64, 1984, 256), (65, 1984, 256), (64, 2048, 256)])
+def test_w_only_both_sides_of_the_tile_rule(mq, orc, M, K, N):
+    """The automatic choice at and beyond one round of workgroups of each tile, and where a handful of rows is split over workgroups,
+    in both 16-bit types."""
+    x = si.activations_f16(15, f"wr/x{M}x{K}", M, K, outlier_prob=0.01)
+    w = si.weights_f16(15, f"wr/w{N}x{K}", N, K)
+    rows = sample_rows(x, 128, M)
+    for bits in (8, 4):
+        pw, oc, os_, oz = make_weight(mq, orc, w, bits)
+        ref = orc.linear_w_only(x, oc, os_, oz, rows=rows)
+        assert_close16(host(mq.qlinear_w_only(dev(x), pw))[rows], ref, f"w{bits} {M}x{K}x{N}")
+        # bfloat16: integers up to 256 are exact in it, so the codes are the weights (scale 1) and the sums are exact in fp32
+        xi = np.random.default_rng(M).integers(-8, 9, (M, K))
+        pi = mq.PackedWeight(pw.packed, dev(np.ones(N, np.float32)), dev(oz), pw.colsum, N, K, bits, mq.LAYOUT_KERNEL, False)
+        y = mq.qlinear_w_only(dev(xi.astype(np.float32)).to(torch.bfloat16), pi)
+        want = torch.from_numpy(xi[rows] @ (oc.astype(np.int64) - oz[:, None]).T).to(torch.float32).to(torch.bfloat16)
+        assert torch.equal(y.cpu()[torch.from_numpy(rows)], want), f"bf16 w{bits} {M}x{K}x{N}"
+
+
+@pytest.mark.parametrize("M,K,N", [(64, 64, 40960), (65, 64, 40832), (77, 192, 40960), (96, 64, 40840), (97, 64, 40960), (129, 64, 40960), (192, 64, 40960),
+                                   (193, 64, 40960), (1024, 832, 10248), (1025, 1664, 10248)])
+def test_a8_over_many_columns(mq, orc, M, K, N):
+    """Both sides of the rules for one or two row blocks over very many columns, and for weights beyond 8 MB."""
+    x = si.activations_f16(16, f"mc/x{M}x{K}", M, K, outlier_prob=0.01)
+    w = si.weights_f16(16, f"mc/w{N}x{K}", N, K)
+    rows = sample_rows(x, 8, M)
+    for bits, fn in ((8, mq.qlinear_w8a8), (4, mq.qlinear_w4a8)):
+        pw, oc, os_, oz = make_weight(mq, orc, w, bits)
+        y, acc, _ = fn(dev(x), pw, want_acc=True)
+        ry, racc, _ = orc.linear_a8(x, oc, os_, oz, rows=rows)
+        assert np.array_equal(host(acc)[rows], racc)
+        assert_close16(host(y)[rows], ry, f"W{bits}A8 {M}x{K}x{N}")
+
+
+@pytest.mark.parametrize("H,N", [(171, 640), (192, 320), (192, 640)])
+def test_conv_both_sides_of_the_tile_rule(mq, orc, H, N):
+    """48-pixel rows of one 64-channel image: one workgroup of 96 rows per compute unit, an eighth more rows on the busiest one, equal rows."""
+    W, Cin = 48, 64
+    x = si.activations_f16(17, f"cr/x{H}", H * W, Cin, outlier_prob=0.01).reshape(1, H, W, Cin)
+    b = si.bias_f16(17, f"cr/b{N}", N)
+    for bits in (8, 4):
+        pw, oc, os_, oz, tapsum = conv_weight(mq, orc, 17, N, Cin, bits)
+        y = mq.conv3x3_w_only(dev(x), pw, dev(b))
+        assert_close16(host(y).reshape(-1, N), orc.conv3x3_w_only(x, oc, os_, oz, b), f"conv w{bits} {H}x{W}->{N}")
+        y, acc, _ = mq.conv3x3_a8(dev(x), pw, tapsum, bias=dev(b), want_acc=True)
+        ry, racc, _ = orc.conv3x3_a8(x, oc, os_, oz, bias=b)
+        assert np.array_equal(host(acc), racc)
+        assert_close16(host(y).reshape(-1, N), ry, f"conv a8 b{bits} {H}x{W}->{N}")
 
 
 def test_a8_longest_reduction_and_extreme_codes(mq, orc):

@@ -1,7 +1,7 @@
 // Per-tensor 8-bit activation quantisation (paper Sec. 4.1 "Quantization Scheme": one scale and
 // zero point per activation tensor; Sec. 4.3: the FP16->INT8 conversion that precedes the integer GEMM).
 //
-//   pass 1 (dynamic only): every workgroup reduces the min/max of its rows with wavefront shuffles and
+//   pass 1 (dynamic only; small tensors do without, see act_quantize_kernel): every workgroup reduces the min/max of its rows with wavefront shuffles and
 //           writes one partial pair; no atomics, no pre-cleared memory, order independent.
 //   pass 2: every workgroup re-reduces the partials (a few KB, L2 resident), derives (scale, zp) with the
 //           same fp32 operations as the weight quantiser, then converts its rows:
@@ -49,25 +49,23 @@ struct RowWalk {
     }
 };
 
-// The extremes are found in pairs of fp16 values (a minimum or maximum of fp16 values is one of them: nothing is lost)
-// and widened once at the end; NaN is ignored as by fminf / fmaxf.  Bound by memory latency up to a few MB and by HBM above.
-// (Workgroups of 1024 threads for tensors that need every partial slot left up to half of the slots without work and were
-// slower at every size: 8192 x 1280 whole call 21.4 us against 20.4, 16384 x 2560 57.1 against 55.7.)
-__global__ __launch_bounds__(256) void act_minmax_kernel(const _Float16* __restrict__ x, uint32_t nv, FastDiv K8,
-                                                         long ldx, RowWalk map, int flat, float* __restrict__ partials) {
-    constexpr uint32_t STEP = 256 * MM_U;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+// This thread's share of the extremes of the tensor's vectors: U at a time, NT lanes side by side, from `base` on in steps of `step`.
+// They are found in pairs of fp16 values (a minimum or maximum of fp16 values is one of them: nothing is lost) and widened
+// once at the end; NaN is ignored as by fminf / fmaxf.
+template <int U, int NT>
+__device__ inline void extremes(const _Float16* __restrict__ x, uint32_t nv, FastDiv K8, long ldx, const RowWalk& map, int flat, uint32_t base,
+                                uint32_t step, float& mn, float& mx) {
     half8 mn8, mx8;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         mn8[e] = (_Float16)INFINITY;
         mx8[e] = -(_Float16)INFINITY;
     }
-    for (uint32_t base = blockIdx.x * STEP; base < nv; base += gridDim.x * STEP) {
-        half8 v[MM_U];
+    for (; base < nv; base += step) {
+        half8 v[U];
 #pragma unroll
-        for (uint32_t u = 0; u < MM_U; ++u) {
-            uint32_t i = base + u * 256u + threadIdx.x;
+        for (uint32_t u = 0; u < U; ++u) {
+            uint32_t i = base + u * (uint32_t)NT + threadIdx.x;
             i = i < nv ? i : nv - 1;  // a repeated vector does not change a min or a max
             if (flat) {
                 v[u] = ((const half8*)x)[i];
@@ -78,17 +76,28 @@ __global__ __launch_bounds__(256) void act_minmax_kernel(const _Float16* __restr
             }
         }
 #pragma unroll
-        for (uint32_t u = 0; u < MM_U; ++u) {
+        for (uint32_t u = 0; u < U; ++u) {
             mn8 = __builtin_elementwise_min(mn8, v[u]);
             mx8 = __builtin_elementwise_max(mx8, v[u]);
         }
     }
-    float mn = INFINITY, mx = -INFINITY;
+    mn = INFINITY, mx = -INFINITY;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         mn = fminf(mn, (float)mn8[e]);
         mx = fmaxf(mx, (float)mx8[e]);
     }
+}
+
+// Bound by memory latency up to a few MB and by HBM above.
+// (Workgroups of 1024 threads for tensors that need every partial slot left up to half of the slots without work and were
+// slower at every size: 8192 x 1280 whole call 21.4 us against 20.4, 16384 x 2560 57.1 against 55.7.)
+__global__ __launch_bounds__(256) void act_minmax_kernel(const _Float16* __restrict__ x, uint32_t nv, FastDiv K8,
+                                                         long ldx, RowWalk map, int flat, float* __restrict__ partials) {
+    constexpr uint32_t STEP = 256 * MM_U;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    float mn, mx;
+    extremes<MM_U, 256>(x, nv, K8, ldx, map, flat, blockIdx.x * STEP, gridDim.x * STEP, mn, mx);
     mn = wave_reduce(mn, [](float a, float b) { return fminf(a, b); });
     mx = wave_reduce(mx, [](float a, float b) { return fmaxf(a, b); });
     __shared__ float smn[4], smx[4];
@@ -129,8 +138,15 @@ static constexpr long kSmallQuant = 28L * 1000 * 1000;  // values: between 6000 
 // BOS: the first `nbos` workgroups compute the BOS rows of a BOS-aware K/V projection instead (they depend on nothing this
 // kernel produces; one launch less on a path whose kernels are all bound by launch latency).  They take longest, so they
 // come first.
-template <bool BOS, int U>
-__global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __restrict__ x, int M, int K, long ldx,
+// NT == 1024: a small tensor with a run-time range.  A launch of the range pass costs more than reading such a tensor again, so every
+// workgroup finds the range of all of it by itself, with SELF_U vectors per lane on their way at once (see the launcher).
+// Whole calls in us, range pass and conversion -> one launch: 1 x 320 -> 64 12.2 -> 8.8, 4 x 1280 -> 1280 12.7 -> 10.7, 64 x 1280 -> 1280 13.5 -> 11.7, 256 x 320 -> 320
+// 12.5 -> 10.6, 100 x 1280 -> 1280 13.7 -> 12.8, 128 x 1280 -> 64 13.9 -> 13.1; with four rounds in place of two 250 x 1280 -> 64 14.0 -> 16.0, 154 x 2048 -> 64
+// 15.1 -> 17.3, with the BOS rows beside it (four blocks of theirs per workgroup) 77 x 2048 -> 1280 16.7 -> 17.5.
+static constexpr int SELF_NT = 1024, SELF_U = 10;
+static constexpr uint32_t SELF_VECTORS = 2 * SELF_U * SELF_NT;
+template <bool BOS, int U, int NT = 256>
+__global__ __launch_bounds__(NT) void act_quantize_kernel(const _Float16* __restrict__ x, int M, int K, long ldx, int flat, FastDiv K8d,
                                                            RowWalk map, int R, FastDiv Kp8d, const float* __restrict__ partials,
                                                            int n_partials, const float* __restrict__ act_scale,
                                                            const int32_t* __restrict__ act_zp,
@@ -139,6 +155,8 @@ __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __res
                                                            float* __restrict__ act_scale_out,
                                                            int32_t* __restrict__ act_zp_out, int nbos, BosWork bw) {
     int blk = (int)blockIdx.x;
+    constexpr bool SELF = NT == SELF_NT;
+    static_assert(!(BOS && SELF), "the BOS rows take workgroups of 256 threads");
     if constexpr (BOS) {
         __shared__ float part[4][256];
         if (blk < nbos) {  // (whole workgroups: none of them reaches a barrier below)
@@ -148,7 +166,7 @@ __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __res
         blk -= nbos;
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    __shared__ float smn[4], smx[4];
+    __shared__ float smn[NT / 64], smx[NT / 64];
     __shared__ int lsum[Q_MAX_ROWS];
     const int r0 = blk * R;
     const int Rr = M - r0 < R ? M - r0 : R;
@@ -162,17 +180,18 @@ __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __res
     auto request = [&](uint32_t base) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t i = base + u * 256u + threadIdx.x;
+            const uint32_t i = base + u * (uint32_t)NT + threadIdx.x;
             Kp8d.divmod(i, lr[u], pp[u]);
             if (i < nvo && pp[u] < K8) v[u] = ((const half8*)(x + map.phys(r0 + lr[u]) * ldx))[pp[u]];
         }
     };
     request(0);  // on its way while the parameters are derived (most workgroups have a single round)
     float s, zf;
-    if (partials) {
+    if (SELF || partials) {
         float mn = INFINITY, mx = -INFINITY;
         constexpr int PU = 4;  // pairs requested together
-        for (int i0 = threadIdx.x; i0 < n_partials; i0 += 256 * PU) {
+        if constexpr (SELF) extremes<SELF_U, NT>(x, (uint32_t)M * K8, K8d, ldx, map, flat, 0, SELF_U * NT, mn, mx);
+        for (int i0 = threadIdx.x; !SELF && i0 < n_partials; i0 += 256 * PU) {
             float2 pr[PU];
 #pragma unroll
             for (int u = 0; u < PU; ++u) {
@@ -192,8 +211,11 @@ __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __res
             smx[wv] = mx;
         }
         __syncthreads();
-        mn = fminf(fminf(smn[0], smn[1]), fminf(smn[2], smn[3]));
-        mx = fmaxf(fmaxf(smx[0], smx[1]), fmaxf(smx[2], smx[3]));
+#pragma unroll
+        for (int i = 0; i < NT / 64; ++i) {
+            mn = fminf(mn, smn[i]);
+            mx = fmaxf(mx, smx[i]);
+        }
         const float lo = fminf(mn, 0.0f), hi = fmaxf(mx, 0.0f);
         s = 1.0f;
         if (hi != lo) {
@@ -215,11 +237,11 @@ __global__ __launch_bounds__(256) void act_quantize_kernel(const _Float16* __res
         if (act_scale_out) *act_scale_out = s;
         if (act_zp_out) *act_zp_out = (int)zf;
     }
-    for (uint32_t base = 0; base < nvo; base += 256u * U) {
+    for (uint32_t base = 0; base < nvo; base += (uint32_t)NT * U) {
         if (base) request(base);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t i = base + u * 256u + threadIdx.x;
+            const uint32_t i = base + u * (uint32_t)NT + threadIdx.x;
             const bool valid = i < nvo;
             uint32_t w0 = 0, w1 = 0;
             if (valid && pp[u] < K8) {
@@ -260,12 +282,24 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
     int grid = (int)(g1 > kPartialSlots ? kPartialSlots : g1);
     const RowWalk walk = RowWalk::make(in_map);
     const bool dynamic = act_scale == nullptr;
+    const int flat = in_map.rows_per_group <= 0 && ldx == K;
+    const int Kp8 = (K + 127) / 128 * 16;
+    if (dynamic && given_partials == 0 && nv <= SELF_VECTORS && !bos) {
+        int R = SELF_NT / Kp8;
+        R = R < 1 ? 1 : R > Q_MAX_ROWS ? Q_MAX_ROWS : R;
+        ProfScope prof(st, PROF_ACT_QUANTIZE, 0.0, 3.0 * M * K + (rowsum ? 4.0 * M : 0.0));
+        auto kern = act_quantize_kernel<false, 1, SELF_NT>;
+        hipLaunchKernelGGL(kern, dim3((M + R - 1) / R), dim3(SELF_NT), 0, st, (const _Float16*)x, M, K, (long)ldx, flat, FastDiv::make(K8), walk, R,
+                           FastDiv::make(Kp8), (const float*)nullptr, 0, act_scale, act_zp, a8, rowsum, params, act_scale_out, act_zp_out, 0,
+                           BosWork{});
+        MQ_HIP_CHECK_LAUNCH();
+        return MQ_OK;
+    }
     // given_partials > 0: the producer of x has left that many (min, max) pairs in `partials` already (the gated
     // projection's epilogue does), so the pass over x that would find them is skipped
     if (dynamic && given_partials > 0) {
         grid = given_partials;
     } else if (dynamic) {
-        const int flat = in_map.rows_per_group <= 0 && ldx == K;
         ProfScope prof(st, PROF_ACT_MINMAX, 0.0, 2.0 * M * K);
         hipLaunchKernelGGL(act_minmax_kernel, dim3(grid), dim3(256), 0, st, (const _Float16*)x, nv, FastDiv::make(K8),
                            (long)ldx, walk, flat, partials);
@@ -290,7 +324,6 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
     //     not even: 8193 x 2048 (1639 workgroups) 27.2 -> 28.2
     //   thousands of pairs (the gated projection leaves them): 16384 x 2560 126.2 -> 124.1
     //   given parameters otherwise: 16389 x 2560 42.6 -> 45.1, 262144 x 320 79.7 -> 87.2
-    const int Kp8 = (K + 127) / 128 * 16;
     int U = Q_U, R = 256 * Q_U / Kp8;
     R = R < 1 ? 1 : R;
     for (int u = 1; u < Q_U && given_partials <= kPartialSlots; u *= 2) {
@@ -318,7 +351,7 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
     auto kern = bos ? (U == 1 ? act_quantize_kernel<true, 1> : U == 2 ? act_quantize_kernel<true, 2> : act_quantize_kernel<true, 4>)
                     : (U == 1 ? act_quantize_kernel<false, 1> : U == 2 ? act_quantize_kernel<false, 2> : act_quantize_kernel<false, 4>);
     const int nbos = bos ? bos_blocks(*bos) : 0;
-    hipLaunchKernelGGL(kern, dim3(nbos + qgrid), dim3(256), 0, st, (const _Float16*)x, M, K, (long)ldx,
+    hipLaunchKernelGGL(kern, dim3(nbos + qgrid), dim3(256), 0, st, (const _Float16*)x, M, K, (long)ldx, flat, FastDiv::make(K8),
                        walk, R, FastDiv::make(Kp8), dynamic ? partials : (const float*)nullptr, grid, act_scale, act_zp, a8,
                        rowsum, params, act_scale_out, act_zp_out, nbos, bos ? *bos : BosWork{});
     MQ_HIP_CHECK_LAUNCH();

@@ -567,6 +567,12 @@ def test_conversion_at_the_edges_of_its_vectors_per_lane(mq, orc, M, K):
     test_activation_passes_at_the_edges_of_their_grids(mq, orc, M, K, 32)
 
 
+@pytest.mark.parametrize("M,K", [(2, 64), (1279, 64), (1281, 64), (2559, 64), (2560, 64), (2561, 64), (63, 64), (65, 64), (17, 8128), (4, 33024), (5, 33024)])
+def test_conversion_that_finds_the_range_itself(mq, orc, M, K):
+    """One and two rounds over the tensor and the first size beyond, one row more than a workgroup converts, rows longer than a round."""
+    test_activation_passes_at_the_edges_of_their_grids(mq, orc, M, K, 32)
+
+
 @pytest.mark.parametrize("M,K,pad", [(1, 64, 0), (16, 64, 8), (300, 320, 0), (4200, 2048, 0), (8300, 1280, 24), (33000, 320, 0)])
 def test_range_pass_ignores_nan(mq, M, K, pad):
     """Quiet, signalling and negative NaN in the first vector, in the last one (which short workgroups read repeatedly) and a

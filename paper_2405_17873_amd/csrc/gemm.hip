@@ -1566,6 +1566,9 @@ static int float_tile(int t, long M, long N, long K, bool bf16) {
 //   8-bit weights: 2048 x 5120 x 1280 39.5 / 32.7 / 36.1, 2400 x 1280 x 1280 15.7 / 14.8 / 14.9, 2964 x 1280 x 1280 (470) 15.9 / 17.3 / 15.9, 3200 x 2560 x 1280 25.3 / 26.3 / 23.2,
 //     3200 x 5120 x 1280 46.8 / 48.1 / 42.1, 4096 x 1280 x 1280 19.2 / 21.2 / 23.9 / 19.7, 16384 x 2560 x 640 (640 of 128x128) 67.2 / - / - / 71.4,
 //     9000 x 1280 x 1280 (710) 32.4 / 34.5 / 33.9 / 30.8, 16384 x 640 x 5120 105.8 / - / - / 92.5, 4096 x 1280 x 10240 84.9 / - / - / 74.9
+// In between, 8-bit weights with long reductions take tile 10 or, where it gives the busiest unit fewer rows, 9; tile 5 / 9 / 10: 4096 x 5120 x 1280
+// (192 / 256 / 192 rows) 52.3 / 51.0 / 48.6, 4800 x 5120 x 1280 59.1 / 55.7 / 52.9, 6000 x 5120 x 1280 (256 / 256 / 288) 81.5 / 64.8 / 81.9, 7300 x 5120 x 1280 (320 / 384 / 384)
+// 94.5 / 93.4 / 87.7, 7300 x 2560 x 640 34.7 / 32.8 / 31.0, 8192 x 2560 x 640 34.1 / 34.1 / 32.8; with 1280 k 4096 x 1280 x 1280 18.7 / 19.7 / 18.8.
 // Fewer tiles than that: the wave groups of tile 4 leave 8-bit weights two stages, tile 2 has four: 616 x 2048 x 1280 13.3 / 11.7,
 // 700 x 5120 x 1280 24.6 / 20.2, 700 x 1280 x 1280 10.9 / 10.0 (tile 4 with twice the LDS 12.0, 20.3, 10.3); at 4 bits tile 4 is
 // the better one, 11.0 / 11.6 and 18.0 / 20.7.  Long reductions
@@ -1588,6 +1591,10 @@ static int int8_tile(int t, long M, long N, long K) {
     const long t1 = ((M + 127) / 128) * ((N + 127) / 128), t5 = ((M + 63) / 64) * ((N + 127) / 128);
     if (t5 <= 384) return 7;
     if (t1 <= 256 && K >= 1536) return 8;
+    if (BITS == 8 && t1 <= 640 && K >= 2560) {
+        const long t10 = (M + 95) / 96 * ((N + 127) / 128);
+        return 128 * ((t1 + UNITS - 1) / UNITS) < 96 * ((t10 + UNITS - 1) / UNITS) ? 9 : 10;
+    }
     if (BITS == 8) return t1 > 640 ? 9 : 5;
     return M > 1024 && N * K * BITS / 8 > (8L << 20) ? t : 5;
 }

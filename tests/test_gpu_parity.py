@@ -701,9 +701,9 @@ def test_w_only_both_sides_of_the_tile_rule(mq, orc, M, K, N):
 
 
 @pytest.mark.parametrize("M,K,N", [(64, 64, 40960), (65, 64, 40832), (77, 192, 40960), (96, 64, 40840), (97, 64, 40960), (129, 64, 40960), (192, 64, 40960),
-                                   (193, 64, 40960), (1024, 832, 10248), (1025, 1664, 10248)])
+                                   (193, 64, 40960), (1024, 832, 10248), (1025, 1664, 10248), (3300, 2496, 1280), (3300, 2560, 1280), (6000, 2560, 1280)])
 def test_a8_over_many_columns(mq, orc, M, K, N):
-    """Both sides of the rules for one or two row blocks over very many columns, and for weights beyond 8 MB."""
+    """Both sides of the rules for one or two row blocks over very many columns, for weights beyond 8 MB and for long reductions."""
     x = si.activations_f16(16, f"mc/x{M}x{K}", M, K, outlier_prob=0.01)
     w = si.weights_f16(16, f"mc/w{N}x{K}", N, K)
     rows = sample_rows(x, 8, M)

@@ -1538,20 +1538,24 @@ static bool taller(long M, long N, long num, long den) {  // busiest unit: rows 
 // fp16: 4-bit weights 1024 x 1280 x 1280 10.4 / 9.9 / 9.3, 1024 x 5120 x 1280 30.8 / 31.1 / 25.7, 2048 x 2560 x 640 17.3 / 17.1 / 14.7, 2048 x 640 x 640
 // 7.0 / 6.4 / 6.3, 4096 x 448 x 320 6.0 / 5.8 / 6.1; 8-bit (twice the weight pieces per stage) 1536 x 1280 x 1280 11.4 / 10.7 / 10.3, 900 x 960 x 1280 8.9 / 8.4 / 8.4,
 // 4096 x 640 x 320 7.2 / 6.6 / 6.8; bf16 1024 x 5120 x 1280 42.4 / 36.8 / 29.8, 2048 x 640 x 640 8.4 / 7.3 / 6.9.
-// A handful of rows with 1024 to 2047 k: tile 4 has too few stages to split over workgroups, tile 2 has not.  us, tile 4 / 2: fp16
+// A handful of rows with 1024 to 2047 k: tile 4 has too few stages to split over workgroups, tile 2 has enough (where the workspace
+// holds the parts: unsplit its chain is twice as long).  us, tile 4 / 2: fp16
 // 4 x 1920 x 1280 9.8 / 8.0, 32 x 1280 x 640 7.6 / 7.0, 32 x 1280 x 1280 7.6 / 7.4, but 64 x 1280 x 1280 7.5 / 8.3 and 16 x 1280 x 2560 7.5 / 8.8; bf16 4 x 1920 x 1280
 // 12.0 / 8.4, 64 x 1280 x 1280 9.0 / 8.6, 77 x 1280 x 1280 9.0 / 9.8.
 // Two row blocks of 96 over very many columns, tile 0 / 10: 154 x 2048 x 166400 at 2, 4, 8 bits 134 / 113, 141 / 122, 168 / 146, 83200 71 / 61, 74 / 65, 79 / 70
 // (one such block keeps tile 6: 64.6 / 66.8 at 4 bits and 166400 columns, 38.7 / 34.0 at 83200).
 template <int BITS>
-static int float_tile(int t, long M, long N, long K, bool bf16) {
+static int float_tile(int t, const GemmArgs& g, bool bf16) {
+    const long M = g.M, N = g.N, K = g.K;
     if (g_force_tile >= 0) return g_force_tile == 5 || (BITS != 16 && g_force_tile >= 10) ? g_force_tile : t;
     if (BITS == 16 || t == 6) return t;
     if (t == 0) return M > 128 && M <= 192 ? 10 : 0;
     const long t2 = ((M + 63) / 64) * ((N + 63) / 64), t5 = ((M + 63) / 64) * ((N + 127) / 128);
     if (t2 > UNITS && t5 <= UNITS) return K >= (BITS == 8 ? 1280 : 640) ? 11 : 5;
     if (t == 1 || t == 3) return taller(M, N, 9, 8) ? 10 : 5;
-    if (t == 4 && M <= (bf16 ? 64 : 32) && K < 2048 && t2 <= 32) return 2;
+    if (t == 4 && M <= (bf16 ? 64 : 32) && K < 2048 && t2 <= 32 && g.split_ws &&
+        g.split_ws_bytes >= split_counter_bytes(t2, 1) + (size_t)(K / 256) * t2 * (64 * 64 * 4))
+        return 2;
     return t;
 }
 
@@ -1732,7 +1736,7 @@ static int dispatch_gemm(GemmArgs& g, hipStream_t st) {
                 if constexpr (BITS == 8) return run_gemm<I8, BITS, 2, 4, 2, 1, 1, 80 * 1024, 4>(g, 9, st);
         }
     } else {
-        t = float_tile<BITS>(t, g.M, g.N, g.K, false);
+        t = float_tile<BITS>(t, g, false);
         if constexpr (BITS != 16)
             if (t == 11) return run_gemm<I8, BITS, 1, 4, 2, 1, 2, BITS == 8 ? 160 * 1024 : 80 * 1024, 4>(g, 11, st);
     }
@@ -1756,7 +1760,7 @@ template <int BITS>
 static int dispatch_gemm_bf16(GemmArgs& g, hipStream_t st) {
     constexpr bool WIDE = BITS == 16;
     int t = pick_tile(g.M, g.N, g.K, WIDE);
-    t = float_tile<BITS>(t == 6 ? 0 : (t == 3 || BITS == 16 && t == 4 ? t - 2 : t), g.M, g.N, g.K, true);
+    t = float_tile<BITS>(t == 6 ? 0 : (t == 3 || (BITS == 16 && t == 4) ? t - 2 : t), g, true);
     if constexpr (BITS != 16)
         switch (t) {
             case 4: return run_gemm<false, BITS, 2, 2, 1, 1, 2, 80 * 1024, 8, true>(g, 4, st);

@@ -692,6 +692,11 @@ def test_w_only_both_sides_of_the_tile_rule(mq, orc, M, K, N):
         pw, oc, os_, oz = make_weight(mq, orc, w, bits)
         ref = orc.linear_w_only(x, oc, os_, oz, rows=rows)
         assert_close16(host(mq.qlinear_w_only(dev(x), pw))[rows], ref, f"w{bits} {M}x{K}x{N}")
+        if M <= 65:  # without a workspace, and with one that holds too few parts
+            for ws in (None, torch.full((256 + 64 * N * 4,), 0xA5, dtype=torch.uint8, device="cuda")):
+                y = torch.empty(M, N, dtype=torch.float16, device="cuda")
+                mq.plan_qlinear_w_only(dev(x), pw, None, y, ws=ws)()
+                assert_close16(host(y)[rows], ref, f"w{bits} {M}x{K}x{N}, workspace {None if ws is None else ws.numel()}")
         # bfloat16: integers up to 256 are exact in it, so the codes are the weights (scale 1) and the sums are exact in fp32
         xi = np.random.default_rng(M).integers(-8, 9, (M, K))
         pi = mq.PackedWeight(pw.packed, dev(np.ones(N, np.float32)), dev(oz), pw.colsum, N, K, bits, mq.LAYOUT_KERNEL, False)

@@ -327,8 +327,10 @@ __device__ __forceinline__ float two_gelu32(float g) {
     return __fmul_rn(g, __fadd_rn(1.0f, erf_g));
 }
 
-// Four products a[r] * b[r] rounded to fp16, one instruction each: the mixed-precision multiply-add writes one half of its
-// destination (the compiler, where the results are used as a vector, multiplies in fp32 and packs in instructions of their own).
+// Four products a[r] * b[r] rounded once, to fp16, one instruction each: the mixed-precision multiply-add writes one half of
+// its destination (the compiler, where the results are used as a vector, multiplies in fp32 and packs in instructions of their
+// own).  A zero product is stored as +0.  For the run-time-range form, whose product is needed in fp16 only; the forms with given
+// output parameters have the fp32 product in hand and convert that.
 __device__ __forceinline__ half4 mul_to_half4(const float (&a)[4], const float (&b)[4]) {
     uint2v o;
     asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(o[0]) : "v"(a[0]), "v"(b[0]));
@@ -1148,6 +1150,7 @@ void gemm_kernel(const GemmArgs g) {
             for (int tm = 0; tm < TM; ++tm) {
                 uint32_t word = 0;
                 float lv[4], tg[4];  // value / 2 and 2 gelu(gate)
+                half4 hh;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     float lg;
@@ -1161,10 +1164,17 @@ void gemm_kernel(const GemmArgs g) {
                         lg = __fmaf_rn(acc[tm][1][4 * q + r], mul_g[r], add_g[r]);
                     }
                     tg[r] = two_gelu32(lg);
-                    if constexpr (want_codes)  // (the conversion saturates to 0..255 and takes NaN to 0)
-                        word = __builtin_amdgcn_cvt_pk_u8_f32(__fadd_rn(rintf(__fmul_rn(__fmul_rn(lv[r], tg[r]), inv_o)), zf_o), r, word);
+                    if constexpr (!RANGE) {
+                        // the fp32 product, rounded once more where it is stored as fp16 (kept apart from that conversion, which
+                        // the compiler may otherwise fuse with it: one rounding, and a zero product loses its sign)
+                        float h = __fmul_rn(lv[r], tg[r]);
+                        asm("" : "+v"(h));
+                        if constexpr (want_codes)  // (the conversion saturates to 0..255 and takes NaN to 0)
+                            word = __builtin_amdgcn_cvt_pk_u8_f32(__fadd_rn(rintf(__fmul_rn(h, inv_o)), zf_o), r, word);
+                        hh[r] = (_Float16)h;
+                    }
                 }
-                const half4 hh = mul_to_half4(lv, tg);
+                if constexpr (RANGE) hh = mul_to_half4(lv, tg);
                 if constexpr (RANGE) {
                     const uint2v h2 = __builtin_bit_cast(uint2v, hh);
 #pragma unroll

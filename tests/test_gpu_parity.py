@@ -1024,6 +1024,42 @@ def test_a8_linear_on_codes_long_reductions(mq, orc, M, K, N, bits):
     assert_close16(host(y)[rows], ry, f"codes {M}x{K}x{N} b{bits}")
 
 
+@pytest.mark.parametrize("tile", (0, 1))
+def test_gated_product_is_rounded_to_fp32_then_to_fp16(mq, tile):
+    """The stored product of the gated projections with given output parameters, bit for bit: value * gate in fp32, that in fp16 (gates
+    beyond 6.1, where the activation is the identity, against values whose two roundings differ from a single one), and the sign of
+    a product that is zero (gates below -6.1, where the activation is -0)."""
+    rng = np.random.default_rng(8)
+    M, K, H = 40, 64, 96
+    v = rng.uniform(1, 64, 1 << 22).astype(np.float32) * rng.choice(np.float32([-1, 1]), 1 << 22)
+    g = rng.uniform(8, 16, 1 << 22).astype(np.float16)
+    twice = (v * g.astype(np.float32)).astype(np.float16)
+    once = (v.astype(np.float64) * g).astype(np.float16)
+    pick = np.flatnonzero(twice != once)[:H]
+    assert len(pick) == H
+    v, g, want = v[pick], g[pick], twice[pick]
+    g[::3] = np.float16(-12)  # these products are zero
+    want[::3] = np.copysign(np.float16(0), -v[::3])
+    codes = np.zeros((2 * H, K), np.uint8)
+    codes[:H, 5] = 1  # value channel n: scale[n] * x[5]; gate channel: its bias alone
+    scale = np.concatenate([v, np.ones(H, np.float32)])
+    bias = dev(np.concatenate([np.zeros(H, np.float16), g]))
+    x = np.zeros((M, K), np.float16)
+    x[:, 5] = 1
+    one = (dev(np.array([1.0], np.float32)), dev(np.array([0], np.int32)))  # activation codes are the values themselves
+    mq.tune_force_tile(tile)
+    try:
+        for bits in (2, 4, 8):
+            packed, colsum = mq.pack_weights(dev(codes), bits)
+            pw = mq.PackedWeight(packed, dev(scale), dev(np.zeros(2 * H, np.int32)), colsum, 2 * H, K, bits, mq.LAYOUT_KERNEL, False)
+            outs = (mq.qlinear_w_only_geglu(dev(x), pw, bias=bias), mq.qlinear_w_only_geglu_a8(dev(x), pw, one, bias=bias, want_h16=True)[1],
+                    mq.qlinear_a8_geglu(dev(x), pw, one, act=one, bias=bias, want_h16=True)[1])
+            for i, h in enumerate(outs):
+                assert np.array_equal(host(h).view(np.uint16), np.broadcast_to(want.view(np.uint16), (M, H))), (bits, i)
+    finally:
+        mq.tune_force_tile(-1)
+
+
 @pytest.mark.parametrize("bits", ALL_BITS)
 @pytest.mark.parametrize("tile", (-1, 0, 1))
 def test_w_only_geglu_projection(mq, orc, bits, tile):

@@ -781,6 +781,7 @@ void gemm_kernel(const GemmArgs g) {
             if constexpr (BF && BITS != 16) wf[tn] = __builtin_bit_cast(half8, half8_to_bf16x8(wf[tn]));  // bf16 bits now
         }
     };
+    constexpr int RS_SHARES = WGN == 4 ? 4 : 1;  // waves that share the row sums of the rows they hold
     const int wn_u = __builtin_amdgcn_readfirstlane(wn);
     auto multiply = [&](const frag_t (&wf)[TN], int s, auto fresh_c) {
         constexpr bool FRESH = decltype(fresh_c)::value;  // the accumulators start here: C = 0
@@ -803,11 +804,13 @@ void gemm_kernel(const GemmArgs g) {
                 else
                     acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[tn], xf[s][tm], c, 0, 0, 0);
             }
-        // Row sums of the stored activations (bytes a' = code - 128): the WGN waves that hold the same rows take the
-        // fragments of one k-step in WGN each.  (Four dot products per fragment, in every wave, were
-        // more vector instructions than the code widening: feed-forward pair 16384 x 640 162 -> 159 us a pass with the share.)
+        // Row sums of the stored activations (bytes a' = code - 128).  Where four waves hold the same rows each takes the
+        // fragments of one k-step in four: four dot products per fragment, in every wave, were more vector instructions than the
+        // code widening (feed-forward pair 16384 x 640 162 -> 159 us a pass with the share).  Two such waves take all: the turns
+        // cut the loop into branches, which costs more than half the sums (1024 x 2560 x 640 at 4 bits, tile 2: 11.35 us with turns,
+        // 10.46 without; convolutions of few tiles, tile 4: 2 %; 8-bit tile 1 2 %).
         if constexpr (RS_INLINE) {
-            if (s % WGN == wn_u) {
+            if (RS_SHARES == 1 || s % RS_SHARES == wn_u) {
 #pragma unroll
                 for (int tm = 0; tm < TM; ++tm) {
                     const int4v a = __builtin_bit_cast(int4v, xf[s][tm]);
@@ -885,15 +888,16 @@ void gemm_kernel(const GemmArgs g) {
     }
     __syncthreads();  // every wave is done reading the stages: what follows may overwrite them
 
-    // Row sums in parts: lanes l and l + 32 hold two shares of row l's, the waves (and wave groups) that hold the same rows
-    // one each.  They meet in the idle sink of the padding loads.
+    // Row sums in parts: lanes l and l + 32 hold two shares of row l's, the waves that share them and the wave groups one each.
+    // They meet in the idle sink of the padding loads.
+    constexpr int RS_PARTS = KS * RS_SHARES;
     int* const rs_x = (int*)(lds + P::SINK) + wm * TM * 32 + l31;
     if constexpr (RS_INLINE) {
-        static_assert((WGN == 2 || WGN == 4) && KS * WGN * BM * 4 <= P::CONSTS - P::SINK, "shares of the row sums fit the sink");
+        static_assert(RS_PARTS == 1 || RS_PARTS * BM * 4 <= P::CONSTS - P::SINK, "shares of the row sums fit the sink");
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             rsum[tm] += __shfl_xor(rsum[tm], 32, 64);
-            if (lane < 32) rs_x[(grp * WGN + wn) * BM + tm * 32] = rsum[tm];
+            if (RS_PARTS > 1 && lane < 32 && (RS_SHARES > 1 || wn == 0)) rs_x[(grp * RS_SHARES + (RS_SHARES > 1 ? wn : 0)) * BM + tm * 32] = rsum[tm];
         }
     }
 
@@ -997,12 +1001,12 @@ void gemm_kernel(const GemmArgs g) {
     }
 
     if constexpr (KS == 1) __syncthreads();  // constants visible (the k-split exchange above has its own barriers)
-    if constexpr (RS_INLINE) {
+    if constexpr (RS_INLINE && RS_PARTS > 1) {
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             rsum[tm] = 0;
 #pragma unroll
-            for (int i = 0; i < KS * WGN; ++i) rsum[tm] += rs_x[i * BM + tm * 32];
+            for (int i = 0; i < RS_PARTS; ++i) rsum[tm] += rs_x[i * BM + tm * 32];
         }
     }
 

@@ -1540,10 +1540,11 @@ static int pick_tile(int M, int N, int K, bool wide_weights = false) {
 //   convolutions, 16-bit activations, 4-bit weights: 4 x 32 x 32, 1280 -> 1280 (192 / 192) 138 / 129, 3 x 100 x 128, 320 -> 320 (512 / 480)
 //     93.8 / 86.2, 4 x 64 x 64 x 640 (320 / 384) 126 / 135
 static constexpr long UNITS = 256;
+static long busiest(long M, long N, long rows) {  // rows that the busiest unit multiplies with tiles of rows x 128
+    return rows * (((M + rows - 1) / rows * ((N + 127) / 128) + UNITS - 1) / UNITS);
+}
 static bool taller(long M, long N, long num, long den) {  // busiest unit: rows of tile 10 <= num / den of tile 5's
-    const long cols = (N + 127) / 128;
-    const long t5 = (M + 63) / 64 * cols, t10 = (M + 95) / 96 * cols;
-    return 96 * den * ((t10 + UNITS - 1) / UNITS) <= 64 * num * ((t5 + UNITS - 1) / UNITS);
+    return den * busiest(M, N, 96) <= num * busiest(M, N, 64);
 }
 
 // Linear layers on 16-bit activations (unquantised weights keep tile 1).
@@ -1977,37 +1978,31 @@ int launch_gemm_a8_codes(const int8_t* a8, long lda, const float* act_scale, con
     // serves, the output linears of feed-forward blocks, are narrow); the half-height tile 5 in place of tile 1
     int t = pick_tile(M, N, K, true);
     t = t == 6 ? 1 : (t >= 3 ? t - 2 : t);
-    // Tile 5 (16384 x 2560 x 640 at 4 bits 40 us against 48; 4096 x 5120 x 1280 37.5 against 44.6, at 8 bits 42.4 against 44.5),
-    // except for many tiles over weights that an XCD's 4 MB L2 does not hold and half the height fetches twice as often
-    // (16384 x 5120 x 1280 at 8 bits 145 against 134; at 4 bits, 3.3 MB, 122 against 128).
-    const bool many = (long)((M + 127) / 128) * ((N + 127) / 128) >= 512 && (long)N * K * w_bits / 8 > (4L << 20);
-    const bool half_height = g_force_tile == 5 || (g_force_tile < 0 && !many);
+    // Tile 5 (16384 x 2560 x 640 at 4 bits 40 us against 48; 4096 x 5120 x 1280 37.5 against 44.6; at 2 and 4 bits 0 to 30 % faster
+    // over 1000 shapes).  8-bit weights move twice the bytes: there tile 1 where two of its workgroups on the busiest compute
+    // unit are no more rows than four of the half height (4928 x 5120 x 1280 45.8 us against 58.5; of more rows, 4096 x 5120 x
+    // 1280, 44.5 against 42.4), and for many tiles over weights that an XCD's 4 MB L2 does not hold and half the height fetches twice as
+    // often (16384 x 5120 x 1280 134 against 145).
+    const long t1 = (long)((M + 127) / 128) * ((N + 127) / 128);
+    const bool full_height = g_force_tile >= 0 ? g_force_tile != 5
+                             : t1 <= 2 * UNITS ? t1 > UNITS && busiest(M, N, 128) <= busiest(M, N, 64)
+                                               : t1 > 3 * UNITS && (long)N * K > (4L << 20);
     if (w_bits == 4) {
         g.w_off = 0;
-        switch (t) {
-            case 0:
-            case 1:
-                if (half_height) return run_gemm<true, 4, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 2>(g, 5, st);
-                return run_gemm<true, 4, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 2>(g, 1, st);
-            default: return run_gemm<true, 4, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 2>(g, 2, st);
-        }
+        if (t <= 1) return run_gemm<true, 4, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 2>(g, 5, st);
+        return run_gemm<true, 4, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 2>(g, 2, st);
     }
     if (w_bits == 2) {
         g.w_off = 0;
-        switch (t) {
-            case 0:
-            case 1:
-                if (half_height) return run_gemm<true, 2, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 2>(g, 5, st);
-                return run_gemm<true, 2, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 2>(g, 1, st);
-            default: return run_gemm<true, 2, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 2>(g, 2, st);
-        }
+        if (t <= 1) return run_gemm<true, 2, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 2>(g, 5, st);
+        return run_gemm<true, 2, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 2>(g, 2, st);
     }
     if (w_bits == 8) {
         g.w_off = w_signed ? 0 : 128;
         switch (t) {
             case 0:
             case 1:
-                if (half_height) return run_gemm<true, 8, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 2>(g, 5, st);
+                if (!full_height) return run_gemm<true, 8, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 2>(g, 5, st);
                 return run_gemm<true, 8, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 2>(g, 1, st);
             default: return run_gemm<true, 8, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 2>(g, 2, st);
         }

@@ -1024,6 +1024,44 @@ def test_a8_linear_on_codes_long_reductions(mq, orc, M, K, N, bits):
     assert_close16(host(y)[rows], ry, f"codes {M}x{K}x{N} b{bits}")
 
 
+def chosen_tile(mq, call):
+    """The GEMM tile (numbered as for mq_tune_force_tile) that a call runs, from its profiling slot."""
+    mq.prof_reset()
+    mq.prof_filter(-1, 1)
+    mq.prof_enable(True)
+    try:
+        out = call()
+        torch.cuda.synchronize()
+    finally:
+        mq.prof_enable(False)
+    (slot,) = [k["slot"] for k in mq.prof_read() if "gemm_kernel" in k["kernel"]]
+    return slot % 12, out
+
+
+@pytest.mark.parametrize("bits,M,K,N,tile", [
+    (8, 4928, 320, 1280, 1),    # 390 tiles of 128 x 128: two on the busiest unit, or four of half the height
+    (8, 4096, 320, 1280, 5),    # 320: two, or three of half the height
+    (8, 3276, 320, 1280, 5),    # 256: one, or two
+    (8, 8200, 4160, 1032, 5),   # 585
+    (8, 11000, 4160, 1032, 1),  # 774 over 4.3 MB of weights
+    (8, 11000, 4032, 1032, 5),  # ... over 4.2 MB
+    (4, 4928, 320, 1280, 5),
+    (4, 11000, 8320, 1032, 5),
+    (2, 11000, 16640, 1032, 5)])
+def test_a8_linear_on_codes_tile_rule(mq, orc, bits, M, K, N, tile):
+    rng = np.random.default_rng(67)
+    qx = rng.integers(0, 256, (M, K)).astype(np.uint8)
+    act = (np.float32(0.0123), 97)
+    pw, oc, os_, oz = make_weight(mq, orc, si.weights_f16(67, "cdr/w", N, K), bits)
+    d_act = (dev(np.array([act[0]], np.float32)), dev(np.array([act[1]], np.int32)))
+    ran, (y, acc) = chosen_tile(mq, lambda: mq.qlinear_a8_codes(dev(a8_layout(qx)), K, d_act, pw, want_acc=True))
+    assert ran == tile
+    rows = np.array([0, 63, 64, 127, 128, M // 2, M - 2, M - 1])
+    ry, racc = orc.linear_a8_codes(qx[rows], act, oc, os_, oz)
+    assert np.array_equal(host(acc)[rows], racc)
+    assert_close16(host(y)[rows], ry, f"codes {M}x{K}x{N} b{bits}")
+
+
 @pytest.mark.parametrize("tile", (0, 1))
 def test_gated_product_is_rounded_to_fp32_then_to_fp16(mq, tile):
     """The stored product of the gated projections with given output parameters, bit for bit: value * gate in fp32, that in fp16 (gates

@@ -1533,12 +1533,9 @@ static int pick_tile(int M, int N, int K, bool wide_weights = false) {
 // The linear layers of the 16-bit-activation path and the convolutions have a third form, 96x128 (tile 10): three MFMAs per
 // widened weight fragment instead of two, for fewer workgroups.  A kernel lasts as long as its busiest compute unit, so the form
 // is chosen by what that unit multiplies: its number of workgroups times their height (UNITS: compute units).  At equal
-// height the taller form is faster, and mostly so where it takes an eighth more.  us, tile 5 / 10 (rows of the busiest unit):
-//   4-bit weights, fp16: 4096 x 1280 x 1280 (192 / 192) 17.6 / 16.5, 4096 x 5120 x 1280 59.1 / 55.4, 7293 x 1280 x 1280 (320 / 288) 29.9 / 25.8,
-//     7402 x 1280 x 320 (128 / 96) 13.0 / 12.1, 6362 x 5120 x 1280 (256 / 288) 84.6 / 83.3, but 2964 x 1280 x 1280 (128 / 192) 13.3 / 15.4,
-//     16384 x 640 x 640 (320 / 384) 16.4 / 17.7; bf16 4096 x 2560 x 640 (128 / 96) 25.3 / 23.9, 3896 x 5120 x 1280 (192 / 192) 70.9 / 61.8
-//   convolutions, 16-bit activations, 4-bit weights: 4 x 32 x 32, 1280 -> 1280 (192 / 192) 138 / 129, 3 x 100 x 128, 320 -> 320 (512 / 480)
-//     93.8 / 86.2, 4 x 64 x 64 x 640 (320 / 384) 126 / 135
+// height the taller form is faster, and where the widening costs most also where it takes an eighth more.  Convolutions in us, tile 5 / 10
+// (rows of the busiest unit), 16-bit activations, 4-bit weights: 4 x 32 x 32, 1280 -> 1280 (192 / 192) 138 / 129, 3 x 100 x 128, 320 -> 320
+// (512 / 480) 93.8 / 86.2, 4 x 64 x 64 x 640 (320 / 384) 126 / 135.
 static constexpr long UNITS = 256;
 static long busiest(long M, long N, long rows) {  // rows that the busiest unit multiplies with tiles of rows x 128
     return rows * (((M + rows - 1) / rows * ((N + 127) / 128) + UNITS - 1) / UNITS);
@@ -1548,6 +1545,19 @@ static bool taller(long M, long N, long num, long den) {  // busiest unit: rows 
 }
 
 // Linear layers on 16-bit activations (unquantised weights keep tile 1).
+// Tile 5 or 10, time of tile 10 over tile 5's (3000 shapes, geometric means; rows of the busiest unit, tile 10 / tile 5):
+//   bf16 (widening costs most) fewer rows 0.71 to 0.9, equal 0.88 to 0.95, an eighth more 0.88 to 0.97.
+//   fp16, 8-bit weights fewer 0.87, equal 0.95, an eighth more 0.91; but with one workgroup of tile 10 or less per unit, which has two
+//     stages only, 1.02 to 1.07 (4096 x 2560 x 640 20.9 -> 22.7 us).
+//   fp16, 3 bits 0.85 / 0.92 / 0.98; 2 and 4 bits 0.87 / 0.98 / 1.01 to 1.03 (fp16 widens these in fewer instructions).
+//   Short reductions leave the stores of the output to bound it, in more and smaller workgroups the faster ones, fp16 with less than 640 k and
+//   equal rows 1.0 to 1.04.  All the more where a row starts inside a 64-byte sector (ldy is no multiple of 32) and the pieces of
+//   two workgroups meet in it: 2291 x 384 x 5480 at 2 bits 16.6 -> 20.9 us, 12530 x 384 x 808 14.7 -> 17.9, in bf16 2877 x 384 x 4728
+//   18.1 -> 22.1; fp16 with up to 1280 k and one workgroup per unit 1.01, 2 bits up to 1.09.
+// fp16 weights beyond 8 MB are streamed once per row block: tile 1, where neither of the lower forms gives the busiest unit
+// fewer rows (1024 x 3584 x 6352 at 8 bits, 256 / 256 / 288 rows, tile 1 / 5 / 10 52.6 / 64.5 / 57.3; 1024 x 4224 x 6336 at 4 bits 59.6 /
+// 61.7 / 62.4; at equal rows of tile 10, 1766 x 4736 x 6080 at 4 bits, 112 / 107.5 / 106.3).  With one 128x128 workgroup per unit
+// or less its reduction has nothing beside it: 616 x 4992 x 4832 at 3 bits 52.0 / 40.7.  (In bf16 it is never the fastest.)
 // Where the 64x64 tiles are more than one round of workgroups but those of 64x128 are not, a compute unit would get one wave
 // per SIMD of the latter; with a second wave group on the other half of the reduction (tile 11) it gets two.  us, 64x64 form / tile 5 / tile 11,
 // fp16: 4-bit weights 1024 x 1280 x 1280 10.4 / 9.9 / 9.3, 1024 x 5120 x 1280 30.8 / 31.1 / 25.7, 2048 x 2560 x 640 17.3 / 17.1 / 14.7, 2048 x 640 x 640
@@ -1567,7 +1577,16 @@ static int float_tile(int t, const GemmArgs& g, bool bf16) {
     if (t == 0) return M > 128 && M <= 192 ? 10 : 0;
     const long t2 = ((M + 63) / 64) * ((N + 63) / 64), t5 = ((M + 63) / 64) * ((N + 127) / 128);
     if (t2 > UNITS && t5 <= UNITS) return K >= (BITS == 8 ? 1280 : 640) ? 11 : 5;
-    if (t == 1 || t == 3) return taller(M, N, 9, 8) ? 10 : 5;
+    if (t == 1 || t == 3) {
+        const bool ragged = g.ldy % 32 != 0;
+        if (bf16) return (K >= 640 || !ragged) && taller(M, N, 9, 8) ? 10 : 5;
+        const long r1 = busiest(M, N, 128), r5 = busiest(M, N, 64), r10 = busiest(M, N, 96);
+        if (N * K * BITS / 8 > (8L << 20) && r1 > 128 && r1 <= r5 && r1 < r10) return 1;
+        const bool one_each = r10 <= 96;
+        if (BITS == 8 && one_each) return 5;
+        if (K < (ragged && BITS != 8 ? 1280 : 640)) return r10 < r5 && !(ragged && (K < 640 || one_each)) ? 10 : 5;
+        return taller(M, N, BITS == 3 || BITS == 8 ? 9 : 8, 8) ? 10 : 5;
+    }
     if (t == 4 && M <= (bf16 ? 64 : 32) && K < 2048 && t2 <= 32 && g.split_ws &&
         g.split_ws_bytes >= split_counter_bytes(t2, 1) + (size_t)(K / 256) * t2 * (64 * 64 * 4))
         return 2;

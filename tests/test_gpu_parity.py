@@ -212,6 +212,20 @@ def test_w_only_exact_integer_case(mq, orc):
         assert np.array_equal(y.astype(np.float64), ref.astype(np.float16).astype(np.float64)), bits
 
 
+def chosen_tile(mq, call):
+    """The GEMM tile (numbered as for mq_tune_force_tile) that a call runs, from its profiling slot."""
+    mq.prof_reset()
+    mq.prof_filter(-1, 1)
+    mq.prof_enable(True)
+    try:
+        out = call()
+        torch.cuda.synchronize()
+    finally:
+        mq.prof_enable(False)
+    (slot,) = [k["slot"] for k in mq.prof_read() if "gemm_kernel" in k["kernel"]]
+    return slot % 12, out
+
+
 def test_w_only_bf16(mq, orc):
     """bfloat16 activations, bias and output (fp32 accumulate); weights quantised from bf16 as well."""
     check_w_only_bf16(mq, orc, ((256, 320, 320, -1), (300, 640, 640, 1), (77, 128, 40, 2), (513, 2048, 264, 0), (300, 640, 264, 5)))
@@ -705,6 +719,40 @@ def test_w_only_both_sides_of_the_tile_rule(mq, orc, M, K, N):
         assert torch.equal(y.cpu()[torch.from_numpy(rows)], want), f"bf16 w{bits} {M}x{K}x{N}"
 
 
+@pytest.mark.parametrize("dtype,bits,M,K,N,tile", [
+    ("f16", 8, 4096, 1280, 640, 5),     # 215 workgroups of 96 x 128
+    ("f16", 8, 8256, 640, 640, 10),     # 430, rows of the busiest unit: 192 of either form
+    ("f16", 4, 4096, 1280, 640, 10),    # one workgroup each, 96 rows for 128
+    ("f16", 4, 4096, 704, 616, 5),      # ... and rows that start inside a 64-byte sector
+    ("f16", 4, 4096, 1280, 616, 10),
+    ("f16", 4, 8256, 576, 640, 5),      # equal rows: short reductions
+    ("f16", 4, 8256, 640, 640, 10),
+    ("f16", 3, 16384, 640, 640, 5),     # 384 rows for 320
+    ("f16", 3, 10240, 640, 640, 10),    # 288 for 256
+    ("f16", 4, 10240, 640, 640, 5),
+    ("f16", 8, 1024, 1664, 7040, 1),    # 256 rows, 256 and 288, weights beyond 8 MB
+    ("f16", 8, 1024, 1152, 7040, 10),   # ... below
+    ("f16", 8, 1024, 1664, 5376, 10),   # 192 rows of 96
+    ("bf16", 8, 1024, 1664, 7040, 10),
+    ("bf16", 4, 2880, 384, 4728, 5),    # ragged rows, short reduction
+    ("bf16", 4, 2880, 640, 4728, 10),
+    ("bf16", 4, 2880, 384, 4736, 10)])
+def test_w_only_tile_rule_96_rows(mq, orc, dtype, bits, M, K, N, tile):
+    """The half height or 96 rows on both sides of each line of the rule, and what the chosen kernel computes: small integers, exact in
+    both types."""
+    dt = torch.float16 if dtype == "f16" else torch.bfloat16
+    rng = np.random.default_rng(M + K)
+    codes, x = rng.integers(0, 1 << bits, (N, K)).astype(np.uint8), rng.integers(-2, 3, (M, K))
+    zp = rng.integers(0, 1 << bits, N).astype(np.int32)
+    packed, colsum = mq.pack_weights(dev(codes), bits)
+    pw = mq.PackedWeight(packed, dev(np.full(N, 2.0 ** -6, np.float32)), dev(zp), colsum, N, K, bits, mq.LAYOUT_KERNEL, False)
+    ran, y = chosen_tile(mq, lambda: mq.qlinear_w_only(dev(x.astype(np.float32)).to(dt), pw))
+    assert ran == tile
+    rows = np.array([0, 63, 64, 95, 96, 127, 128, M // 2, M - 2, M - 1])
+    want = torch.from_numpy(x[rows] @ (codes.astype(np.int64) - zp[:, None]).T * 2.0 ** -6).to(torch.float32).to(dt)
+    assert torch.equal(y.cpu()[torch.from_numpy(rows)], want)
+
+
 @pytest.mark.parametrize("M,K,N", [(64, 64, 40960), (65, 64, 40832), (77, 192, 40960), (96, 64, 40840), (97, 64, 40960), (129, 64, 40960), (192, 64, 40960),
                                    (193, 64, 40960), (1024, 832, 10248), (1025, 1664, 10248), (3300, 2496, 1280), (3300, 2560, 1280), (6000, 2560, 1280)])
 def test_a8_over_many_columns(mq, orc, M, K, N):
@@ -1022,20 +1070,6 @@ def test_a8_linear_on_codes_long_reductions(mq, orc, M, K, N, bits):
     ry, racc = orc.linear_a8_codes(qx[rows], act, oc, os_, oz)
     assert np.array_equal(host(acc)[rows], racc)
     assert_close16(host(y)[rows], ry, f"codes {M}x{K}x{N} b{bits}")
-
-
-def chosen_tile(mq, call):
-    """The GEMM tile (numbered as for mq_tune_force_tile) that a call runs, from its profiling slot."""
-    mq.prof_reset()
-    mq.prof_filter(-1, 1)
-    mq.prof_enable(True)
-    try:
-        out = call()
-        torch.cuda.synchronize()
-    finally:
-        mq.prof_enable(False)
-    (slot,) = [k["slot"] for k in mq.prof_read() if "gemm_kernel" in k["kernel"]]
-    return slot % 12, out
 
 
 @pytest.mark.parametrize("bits,M,K,N,tile", [

@@ -1563,10 +1563,13 @@ static bool taller(long M, long N, long num, long den) {  // busiest unit: rows 
 // fp16: 4-bit weights 1024 x 1280 x 1280 10.4 / 9.9 / 9.3, 1024 x 5120 x 1280 30.8 / 31.1 / 25.7, 2048 x 2560 x 640 17.3 / 17.1 / 14.7, 2048 x 640 x 640
 // 7.0 / 6.4 / 6.3, 4096 x 448 x 320 6.0 / 5.8 / 6.1; 8-bit (twice the weight pieces per stage) 1536 x 1280 x 1280 11.4 / 10.7 / 10.3, 900 x 960 x 1280 8.9 / 8.4 / 8.4,
 // 4096 x 640 x 320 7.2 / 6.6 / 6.8; bf16 1024 x 5120 x 1280 42.4 / 36.8 / 29.8, 2048 x 640 x 640 8.4 / 7.3 / 6.9.
-// A handful of rows with 1024 to 2047 k: tile 4 has too few stages to split over workgroups, tile 2 has enough (where the workspace
-// holds the parts: unsplit its chain is twice as long).  us, tile 4 / 2: fp16
-// 4 x 1920 x 1280 9.8 / 8.0, 32 x 1280 x 640 7.6 / 7.0, 32 x 1280 x 1280 7.6 / 7.4, but 64 x 1280 x 1280 7.5 / 8.3 and 16 x 1280 x 2560 7.5 / 8.8; bf16 4 x 1920 x 1280
-// 12.0 / 8.4, 64 x 1280 x 1280 9.0 / 8.6, 77 x 1280 x 1280 9.0 / 9.8.
+// Few tiles with 1024 k and more: tile 4 splits its reduction over workgroups from 16 of its stages on (1984 k), tile 2, of twice as
+// many stages, from 1024 k on, where the workspace holds the parts (unsplit its chain is twice as long).  Tile 2 over tile 4 (2000
+// shapes of up to 64 tiles, 1024 to 1920 k): fp16 with up to 32 rows 0.78 to 0.90 at 10 tiles, 0.89 to 1.01 at 24, 0.95 to 1.05 at 30, 1.07 to
+// 1.15 at 40 (4 x 1920 x 1280 8.0 us / 9.8; 32 x 1984 x 2040, where tile 4 splits too, 9.9 / 8.9); bf16 0.69 to 0.78 at 10 tiles, 0.79 to 0.94 at
+// 28, 0.91 to 1.01 at 40 and 1.0 at 48, with more than 32 rows 0.94 to 1.06 at 36 (77 x 1920 x 504 9.2 / 13.2, 32 x 1600 x 2560 10.0 / 10.8).
+// With up to 8 tiles bf16 is better off with tile 2 up to 3071 k, both split (0.93 to 1.0), and with 53 to 64 from 4096 k on (0.90 to 1.01:
+// 4 x 4224 x 3792 20.0 us / 21.8).
 // Two row blocks of 96 over very many columns, tile 0 / 10: 154 x 2048 x 166400 at 2, 4, 8 bits 134 / 113, 141 / 122, 168 / 146, 83200 71 / 61, 74 / 65, 79 / 70
 // (one such block keeps tile 6: 64.6 / 66.8 at 4 bits and 166400 columns, 38.7 / 34.0 at 83200).
 template <int BITS>
@@ -1587,9 +1590,9 @@ static int float_tile(int t, const GemmArgs& g, bool bf16) {
         if (K < (ragged && BITS != 8 ? 1280 : 640)) return r10 < r5 && !(ragged && (K < 640 || one_each)) ? 10 : 5;
         return taller(M, N, BITS == 3 || BITS == 8 ? 9 : 8, 8) ? 10 : 5;
     }
-    if (t == 4 && M <= (bf16 ? 64 : 32) && K < 2048 && t2 <= 32 && g.split_ws &&
-        g.split_ws_bytes >= split_counter_bytes(t2, 1) + (size_t)(K / 256) * t2 * (64 * 64 * 4))
-        return 2;
+    const bool few = bf16 ? (K < 1984 && t2 <= (M <= 32 ? 48 : 36)) || (K < 3072 && t2 <= 8) || (K >= 4096 && t2 > 52 && t2 <= 64)
+                          : K < 1984 && M <= 32 && t2 <= 24;
+    if (t == 4 && few && g.split_ws && g.split_ws_bytes >= split_counter_bytes(t2, 1) + (size_t)(K / 256) * t2 * (64 * 64 * 4)) return 2;
     return t;
 }
 

@@ -719,6 +719,21 @@ def test_w_only_both_sides_of_the_tile_rule(mq, orc, M, K, N):
         assert torch.equal(y.cpu()[torch.from_numpy(rows)], want), f"bf16 w{bits} {M}x{K}x{N}"
 
 
+def check_w_only_tile(mq, dtype, bits, M, K, N, tile):
+    """Which tile runs, and what it computes: small integers, exact in both types."""
+    dt = torch.float16 if dtype == "f16" else torch.bfloat16
+    rng = np.random.default_rng(M + K)
+    codes, x = rng.integers(0, 1 << bits, (N, K)).astype(np.uint8), rng.integers(-2, 3, (M, K))
+    zp = rng.integers(0, 1 << bits, N).astype(np.int32)
+    packed, colsum = mq.pack_weights(dev(codes), bits)
+    pw = mq.PackedWeight(packed, dev(np.full(N, 2.0 ** -6, np.float32)), dev(zp), colsum, N, K, bits, mq.LAYOUT_KERNEL, False)
+    ran, y = chosen_tile(mq, lambda: mq.qlinear_w_only(dev(x.astype(np.float32)).to(dt), pw))
+    assert ran == tile
+    rows = np.unique(np.clip([0, 63, 64, 95, 96, 127, 128, M // 2, M - 2, M - 1], 0, M - 1))
+    want = torch.from_numpy(x[rows] @ (codes.astype(np.int64) - zp[:, None]).T * 2.0 ** -6).to(torch.float32).to(dt)
+    assert torch.equal(y.cpu()[torch.from_numpy(rows)], want)
+
+
 @pytest.mark.parametrize("dtype,bits,M,K,N,tile", [
     ("f16", 8, 4096, 1280, 640, 5),     # 215 workgroups of 96 x 128
     ("f16", 8, 8256, 640, 640, 10),     # 430, rows of the busiest unit: 192 of either form
@@ -738,19 +753,18 @@ def test_w_only_both_sides_of_the_tile_rule(mq, orc, M, K, N):
     ("bf16", 4, 2880, 640, 4728, 10),
     ("bf16", 4, 2880, 384, 4736, 10)])
 def test_w_only_tile_rule_96_rows(mq, orc, dtype, bits, M, K, N, tile):
-    """The half height or 96 rows on both sides of each line of the rule, and what the chosen kernel computes: small integers, exact in
-    both types."""
-    dt = torch.float16 if dtype == "f16" else torch.bfloat16
-    rng = np.random.default_rng(M + K)
-    codes, x = rng.integers(0, 1 << bits, (N, K)).astype(np.uint8), rng.integers(-2, 3, (M, K))
-    zp = rng.integers(0, 1 << bits, N).astype(np.int32)
-    packed, colsum = mq.pack_weights(dev(codes), bits)
-    pw = mq.PackedWeight(packed, dev(np.full(N, 2.0 ** -6, np.float32)), dev(zp), colsum, N, K, bits, mq.LAYOUT_KERNEL, False)
-    ran, y = chosen_tile(mq, lambda: mq.qlinear_w_only(dev(x.astype(np.float32)).to(dt), pw))
-    assert ran == tile
-    rows = np.array([0, 63, 64, 95, 96, 127, 128, M // 2, M - 2, M - 1])
-    want = torch.from_numpy(x[rows] @ (codes.astype(np.int64) - zp[:, None]).T * 2.0 ** -6).to(torch.float32).to(dt)
-    assert torch.equal(y.cpu()[torch.from_numpy(rows)], want)
+    """The half height or 96 rows on both sides of each line of the rule."""
+    check_w_only_tile(mq, dtype, bits, M, K, N, tile)
+
+
+@pytest.mark.parametrize("dtype,M,K,N,tile", [
+    ("f16", 4, 1280, 1536, 2), ("f16", 4, 1280, 1600, 4), ("f16", 32, 1920, 1280, 2), ("f16", 32, 1984, 1280, 4), ("f16", 33, 1280, 640, 4),
+    ("bf16", 32, 1280, 3072, 2), ("bf16", 32, 1280, 3136, 4), ("bf16", 33, 1280, 2304, 2), ("bf16", 33, 1280, 2368, 4), ("bf16", 77, 1920, 1152, 2),
+    ("bf16", 77, 1984, 320, 4), ("bf16", 77, 2048, 256, 2), ("bf16", 77, 2048, 320, 4), ("bf16", 4, 3008, 512, 2), ("bf16", 4, 3072, 512, 4),
+    ("bf16", 4, 4096, 3392, 2), ("bf16", 4, 4096, 3328, 4), ("bf16", 4, 4032, 3392, 4)])
+def test_w_only_tile_rule_few_tiles(mq, orc, dtype, M, K, N, tile):
+    """Few tiles over long reductions, both sides of each line, with the workspace that the split needs."""
+    check_w_only_tile(mq, dtype, 4, M, K, N, tile)
 
 
 @pytest.mark.parametrize("M,K,N", [(64, 64, 40960), (65, 64, 40832), (77, 192, 40960), (96, 64, 40840), (97, 64, 40960), (129, 64, 40960), (192, 64, 40960),

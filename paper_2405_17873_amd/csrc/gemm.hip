@@ -1597,47 +1597,52 @@ static int float_tile(int t, const GemmArgs& g, bool bf16) {
 }
 
 // The int8 path has more forms of tile 1, by how many workgroups a compute unit gets: with few of them the wait for loads
-// counts (more stages, or the eight waves of one 128x128 workgroup over half the L2 -> LDS traffic per operation), with many
+// counts (more stages, 7, or the eight waves of one 128x128 workgroup over half the L2 -> LDS traffic per operation, 8), with many
 // the number of waves.  8-bit weights move twice the bytes, so that the L2 -> LDS path bounds the half height there (96 bytes
-// per clock and compute unit at the full MFMA rate, of 55): they have a form of their own for many tiles.  Whole calls with given
+// per clock and compute unit at the full MFMA rate, of 55): they have a form of their own for many tiles, 9.  Whole calls with given
 // parameters in us, tile 5 / 7 / 8 (/ 9):
-//   4-bit weights: 2048 x 5120 x 1280 (320 workgroups of tile 5) 36.9 / 29.9 / 31.3, 2400 x 1280 x 1280 (380) 14.7 / 13.8 / 13.7,
-//     2560 x 2560 x 1280 (400) 23.0 / 19.9 / 20.3, 6000 x 2560 x 640 (470) 28.6 / 27.5 / 25.7, 3200 x 5120 x 1280 (500) 44.3 / 40.8 / 38.2,
-//     4096 x 1280 x 1280 (640, 320 of 128x128) 16.8 / 17.8 / 18.9
-//   8-bit weights: 2048 x 5120 x 1280 39.5 / 32.7 / 36.1, 2400 x 1280 x 1280 15.7 / 14.8 / 14.9, 2964 x 1280 x 1280 (470) 15.9 / 17.3 / 15.9, 3200 x 2560 x 1280 25.3 / 26.3 / 23.2,
-//     3200 x 5120 x 1280 46.8 / 48.1 / 42.1, 4096 x 1280 x 1280 19.2 / 21.2 / 23.9 / 19.7, 16384 x 2560 x 640 (640 of 128x128) 67.2 / - / - / 71.4,
-//     9000 x 1280 x 1280 (710) 32.4 / 34.5 / 33.9 / 30.8, 16384 x 640 x 5120 105.8 / - / - / 92.5, 4096 x 1280 x 10240 84.9 / - / - / 74.9
-// In between, 8-bit weights with long reductions take tile 10 or, where it gives the busiest unit fewer rows, 9; tile 5 / 9 / 10: 4096 x 5120 x 1280
-// (192 / 256 / 192 rows) 52.3 / 51.0 / 48.6, 4800 x 5120 x 1280 59.1 / 55.7 / 52.9, 6000 x 5120 x 1280 (256 / 256 / 288) 81.5 / 64.8 / 81.9, 7300 x 5120 x 1280 (320 / 384 / 384)
-// 94.5 / 93.4 / 87.7, 7300 x 2560 x 640 34.7 / 32.8 / 31.0, 8192 x 2560 x 640 34.1 / 34.1 / 32.8; with 1280 k 4096 x 1280 x 1280 18.7 / 19.7 / 18.8.
+//   4-bit weights: 2048 x 5120 x 1280 (320 workgroups of tile 5) 36.9 / 29.9 / 31.3, 2560 x 2560 x 1280 (400) 23.0 / 19.9 / 20.3,
+//     3200 x 5120 x 1280 (500) 44.3 / 40.8 / 38.2, 4096 x 1280 x 1280 (640, 320 of 128x128) 16.8 / 17.8 / 18.9
+//   8-bit weights: 2048 x 5120 x 1280 39.5 / 32.7 / 36.1, 2964 x 1280 x 1280 (470) 15.9 / 17.3 / 15.9, 3200 x 5120 x 1280 46.8 / 48.1 / 42.1,
+//     4096 x 1280 x 1280 19.2 / 21.2 / 23.9 / 19.7, 9000 x 1280 x 1280 (710 of 128x128) 32.4 / 34.5 / 33.9 / 30.8, 16384 x 640 x 5120 105.8 / - / - / 92.5
+// 8-bit weights in between take the form that gives the busiest unit fewest rows.  Tile 9 over tile 5 where it gives no more 0.78 to 0.92 (1619 x 2048
+// x 4504 27.6 us / 32.8, 1024 x 1984 x 7752 31.6 / 36.3), where it gives more 1.02 to 1.06; from 2560 k on tile 10 comes in (tile 5 / 9 / 10: 4096 x 5120 x
+// 1280, 192 / 256 / 192 rows, 52.3 / 51.0 / 48.6; 6000 x 5120 x 1280, 256 / 256 / 288, 81.5 / 64.8 / 81.9; 16384 x 2560 x 640, 320 / 384 / 384, 67.2 / 71.4 / 68.5).
+// Below 640 k the output's stores bound it, and the smaller workgroups are the faster ones: 8192 x 384 x 6216 71.2 us / 78.6, 2964 x 384 x 5624 29.4 / 33.2.
+// Weights beyond the last-level cache (256 MB) come from memory once per row block: tile 1, with the fewest loads in flight per byte of
+// LDS, 231 x 2048 x 147456 113 us / 119 with tile 9.
 // Fewer tiles than that: the wave groups of tile 4 leave 8-bit weights two stages, tile 2 has four: 616 x 2048 x 1280 13.3 / 11.7,
-// 700 x 5120 x 1280 24.6 / 20.2, 700 x 1280 x 1280 10.9 / 10.0 (tile 4 with twice the LDS 12.0, 20.3, 10.3); at 4 bits tile 4 is
-// the better one, 11.0 / 11.6 and 18.0 / 20.7.  Long reductions
-// that are split over workgroups stay with tile 4, whose parts are fewer: 64 x 5120 x 1280 14.3 / 16.0.
+// 700 x 5120 x 1280 24.6 / 20.2; at 4 bits tile 4 is the better one, 11.0 / 11.6 and 18.0 / 20.7.  Few tiles that tile 4 splits over workgroups
+// stay with it, whose parts are fewer (500 x 4032 x 336 14.8 / 19.9, 64 x 5120 x 1280 14.3 / 16.0), and nearly two rounds of tile 2 over a narrow
+// output take tile 7 (2964 x 2560 x 640, tile 4 / 2 / 7 19.3 / 20.4 / 18.7; wide, 616 x 2560 x 2928 16.5 / 15.8 / 16.0).
 // One or two row blocks of 96 over very many columns (the K/V projections of all layers for one or two prompts of 77 tokens, stacked)
 // stream their weights: several workgroups per compute unit whose loads cover each other's epilogues, at three quarters of the rows
 // (tile 10).  Whole calls, 96x256 with one workgroup per unit (one prompt) or 128x256 and 128x128 (two) / tile 10: 8-bit weights
-// 77 x 2048 x 166400 79.8 / 76.3, 83200 47.6 / 40.0, 40960 25.7 / 24.7, 30720 20.7 / 22.2, 154 x 2048 x 166400 125.4 / 112.7, 20480 20.6 / 22.1; 4-bit 77 x 2048 x 166400
-// 46.0 / 44.3, 65280 25.7 / 22.8, 154 x 2048 x 166400 86.2 / 73.5, 40960 36.2 / 27.4.
-// Weights that do not fit an XCD's L2 by a wide margin are streamed from the last-level cache once per row block, so tall problems
-// keep the full height (4-bit 1536 x 2560 x 10240 49.8 / 50.9 with tile 1 / 5); of few row blocks each is better read twice by more
-// workgroups: 154 x 2048 x 20480 24.8 / 18.8, 308 x 2048 x 40960 42.9 / 40.0, 512 x 2560 x 10240 24.2 / 21.6, 1024 x 5120 x 5120 41.2 / 37.4.
+// 77 x 2048 x 166400 79.8 / 76.3, 83200 47.6 / 40.0, 40960 25.7 / 24.7, 154 x 2048 x 166400 125.4 / 112.7; 4-bit 77 x 2048 x 166400 46.0 / 44.3,
+// 65280 25.7 / 22.8, 154 x 2048 x 166400 86.2 / 73.5, 40960 36.2 / 27.4.
+// 2- and 4-bit weights that do not fit an XCD's L2 by a wide margin are streamed from the last-level cache once per row block, so tall problems
+// keep the full height (1536 x 2560 x 10240 49.8 / 50.9 with tile 1 / 5); of few row blocks each is better read twice by more
+// workgroups (512 x 2560 x 10240 24.2 / 21.6, 1024 x 5120 x 5120 41.2 / 37.4), unless the busiest unit gets no fewer rows by it (1024 x 2304 x 7512
+// 26.6 / 28.1).
 template <int BITS>
 static int int8_tile(int t, long M, long N, long K) {
     if (g_force_tile >= 7) return g_force_tile == 11 ? 5 : g_force_tile;
-    if (BITS == 8 && t == 4 && g_force_tile < 0) return K >= 4096 && ((M + 63) / 64) * ((N + 63) / 64) <= 64 ? 4 : 2;
+    const long cols = (N + 127) / 128, t2 = ((M + 63) / 64) * ((N + 63) / 64);
+    if (BITS == 8 && t == 4 && g_force_tile < 0) return t2 <= 64 ? (K > 3840 ? 4 : 2) : t2 > 448 && M >= 4 * N ? 7 : 2;
     if (g_force_tile >= 0) return g_force_tile == 5 ? 5 : t;
-    if (((M > 64 && M <= 96) || (M > 128 && M <= 192)) && (N + 127) / 128 >= 320) return 10;
+    if (((M > 64 && M <= 96) || (M > 128 && M <= 192)) && cols >= 320) return 10;
     if (t != 1 && t != 3) return t;
-    const long t1 = ((M + 127) / 128) * ((N + 127) / 128), t5 = ((M + 63) / 64) * ((N + 127) / 128);
+    const long t1 = ((M + 127) / 128) * cols, t5 = ((M + 63) / 64) * cols;
     if (t5 <= 384) return 7;
-    if (t1 <= 256 && K >= 1536) return 8;
-    if (BITS == 8 && t1 <= 640 && K >= 2560) {
-        const long t10 = (M + 95) / 96 * ((N + 127) / 128);
-        return 128 * ((t1 + UNITS - 1) / UNITS) < 96 * ((t10 + UNITS - 1) / UNITS) ? 9 : 10;
-    }
-    if (BITS == 8) return t1 > 640 ? 9 : 5;
-    return M > 1024 && N * K * BITS / 8 > (8L << 20) ? t : 5;
+    if (t1 <= UNITS && K >= 1536) return 8;
+    const long r1 = busiest(M, N, 128), r5 = busiest(M, N, 64), r10 = busiest(M, N, 96);
+    const bool big = N * K * BITS / 8 > (8L << 20);
+    if (BITS != 8) return big && (M > 1024 || (t1 <= 2 * UNITS && r1 <= r5)) ? 1 : 5;
+    if (N * K > (256L << 20)) return 1;
+    if (K < 640 && !big) return 5;
+    if (t1 > 640) return 9;
+    if (K >= 2560) return r1 < r10 ? 9 : 8 * r10 <= 9 * r5 ? 10 : 5;
+    return t1 > UNITS && r1 <= r5 ? 9 : 5;
 }
 
 template <bool I8, int BITS, int WGM, int WGN, int TM, int TN, int S, int KS>

@@ -798,6 +798,49 @@ def test_conv_both_sides_of_the_tile_rule(mq, orc, H, N):
         assert_close16(host(y).reshape(-1, N), ry, f"conv a8 b{bits} {H}x{W}->{N}")
 
 
+@pytest.mark.parametrize("bits,M,K,N,tile", [
+    # few tiles of 64 x 64: what is split over workgroups, and a second round over a narrow output
+    (8, 500, 3840, 336, 2), (8, 500, 3904, 336, 4), (8, 577, 3904, 392, 2), (8, 2816, 1024, 640, 2), (8, 2964, 1024, 640, 7), (8, 1500, 1024, 1280, 2),
+    # up to one workgroup of 128 x 128 per compute unit
+    (8, 3072, 192, 1024, 7), (8, 3073, 192, 1024, 5), (8, 4096, 1472, 1024, 5), (8, 4096, 1536, 1024, 8), (8, 4097, 1536, 1024, 5),
+    (4, 4096, 1472, 1024, 5), (4, 4096, 1536, 1024, 8), (4, 4097, 1536, 1024, 5),
+    # 8-bit weights beyond, by the rows of the busiest unit (128 x 128, 64 x 128, 96 x 128)
+    (8, 4096, 640, 1792, 9), (8, 4096, 576, 1792, 5),      # 256, 256
+    (8, 690, 1664, 7040, 5), (8, 1024, 1664, 7040, 9),     # 256, 192; 256, 256
+    (8, 4096, 2560, 1280, 10), (8, 4096, 2496, 1280, 5),   # 256, 192, 192
+    (8, 4928, 2560, 1280, 9),                              # 256, 256, 288
+    (8, 16384, 2560, 640, 5),                              # 384, 320, 384
+    (8, 10240, 640, 1024, 5), (8, 10241, 640, 1024, 9), (8, 10241, 576, 1024, 5),
+    # 2- and 4-bit weights beyond 8 MB
+    (4, 1024, 2368, 7040, 5), (4, 1024, 2432, 7040, 1), (4, 600, 2432, 7040, 5), (4, 1088, 2432, 7040, 1), (2, 1024, 4800, 7040, 1)])
+def test_a8_tile_rule(mq, orc, bits, M, K, N, tile):
+    """The form that runs on both sides of each line of the rule, and what it computes: small integers as codes of scale 1."""
+    rng = np.random.default_rng(M + K)
+    codes, x = rng.integers(0, 1 << bits, (N, K)).astype(np.uint8), rng.integers(0, 4, (M, K))
+    zp = rng.integers(0, 1 << bits, N).astype(np.int32)
+    packed, colsum = mq.pack_weights(dev(codes), bits)
+    pw = mq.PackedWeight(packed, dev(np.full(N, 2.0 ** -8, np.float32)), dev(zp), colsum, N, K, bits, mq.LAYOUT_KERNEL, False)
+    one = (dev(np.array([1.0], np.float32)), dev(np.array([0], np.int32)))
+    fn = {8: mq.qlinear_w8a8, 4: mq.qlinear_w4a8, 2: mq.qlinear_w2a8}[bits]
+    ran, (y, *_) = chosen_tile(mq, lambda: fn(dev(x.astype(np.float16)), pw, act=one))
+    assert ran == tile
+    rows = np.array([0, 63, 64, 95, 96, 127, 128, M // 2, M - 2, M - 1])
+    want = (x[rows] @ (codes.astype(np.int64) - zp[:, None]).T * 2.0 ** -8).astype(np.float32).astype(np.float16)
+    assert np.array_equal(host(y)[rows], want)
+
+
+def test_a8_weights_beyond_the_last_level_cache_take_the_full_height(mq):
+    """231 rows over 8-bit weights on both sides of 256 MB (the choice alone: the forms are compared with the oracle elsewhere)."""
+    M, K = 231, 2048
+    x = torch.zeros(M, K, dtype=torch.float16, device="cuda")
+    one = (dev(np.array([1.0], np.float32)), dev(np.array([0], np.int32)))
+    for N, tile in ((131072, 9), (131200, 1)):
+        pw = mq.PackedWeight(torch.zeros(mq.packed_bytes(N, K, 8, mq.LAYOUT_KERNEL), dtype=torch.uint8, device="cuda"), torch.ones(N, device="cuda"),
+                             torch.zeros(N, dtype=torch.int32, device="cuda"), torch.zeros(N, dtype=torch.int32, device="cuda"), N, K, 8, mq.LAYOUT_KERNEL, False)
+        ran, (y, *_) = chosen_tile(mq, lambda: mq.qlinear_w8a8(x, pw, act=one))
+        assert ran == tile and not y.any()
+
+
 def test_a8_longest_reduction_and_extreme_codes(mq, orc):
     """K = 33024 is the longest reduction the int32 accumulator is guaranteed to hold (255 * 255 * K < 2^31).  All
     activation codes and all weight codes are 0 or 255 with zero points 0; row 0 against channel 0 is 255 * 255 in

@@ -1460,7 +1460,7 @@ void gemm_kernel(const GemmArgs g) {
 //   0: 128x256, 4 waves (1x4) of 128x64     1: 128x128, 4 waves (2x2) of 64x64     2: 64x64, 4 waves of 32x32
 //   3: as 1 and 4: as 2, with a second wave group splitting k inside the workgroup (8 waves)
 //   5: 64x128, 4 waves (1x4) of 64x32, two or three LDS stages: the form of tile 1 that puts more workgroups on a
-//      compute unit     6 (16-bit activations, linear layers): 96x256, 4 waves (1x4) of 96x64
+//      compute unit     6 (linear layers, not 8-bit weights under 8-bit activations): 96x256, 4 waves (1x4) of 96x64
 //   (int8, plain layers) 7: as 5 with three stages   8, 9: 128x128, 8 waves (2x4) of 64x32, with stages for one or for two
 //      workgroups per compute unit
 //   10: 96x128, 4 waves (1x4) of 96x32   11 (16-bit activations, plain layers): as 5 with a second wave group splitting k
@@ -1619,7 +1619,9 @@ static int float_tile(int t, const GemmArgs& g, bool bf16) {
 // stream their weights: several workgroups per compute unit whose loads cover each other's epilogues, at three quarters of the rows
 // (tile 10).  Whole calls, 96x256 with one workgroup per unit (one prompt) or 128x256 and 128x128 (two) / tile 10: 8-bit weights
 // 77 x 2048 x 166400 79.8 / 76.3, 83200 47.6 / 40.0, 40960 25.7 / 24.7, 154 x 2048 x 166400 125.4 / 112.7; 4-bit 77 x 2048 x 166400 46.0 / 44.3,
-// 65280 25.7 / 22.8, 154 x 2048 x 166400 86.2 / 73.5, 40960 36.2 / 27.4.
+// 65280 25.7 / 22.8, 154 x 2048 x 166400 86.2 / 73.5, 40960 36.2 / 27.4.  2- and 4-bit weights leave room for three workgroups of tile 10 per unit
+// or two of 96x256: where 96x128 is just more than three rounds of workgroups, 96x256 (tile 6) is two (77 x 2048 x 99840 at 4 bits 33.4 / 43.3,
+// 118400 35.3 / 45.1, at 2 bits 33.7 / 35.9).
 // 2- and 4-bit weights that do not fit an XCD's L2 by a wide margin are streamed from the last-level cache once per row block, so tall problems
 // keep the full height (1536 x 2560 x 10240 49.8 / 50.9 with tile 1 / 5); of few row blocks each is better read twice by more
 // workgroups (512 x 2560 x 10240 24.2 / 21.6, 1024 x 5120 x 5120 41.2 / 37.4), unless the busiest unit gets no fewer rows by it (1024 x 2304 x 7512
@@ -1630,6 +1632,7 @@ static int int8_tile(int t, long M, long N, long K) {
     const long cols = (N + 127) / 128, t2 = ((M + 63) / 64) * ((N + 63) / 64);
     if (BITS == 8 && t == 4 && g_force_tile < 0) return t2 <= 64 ? (K > 3840 ? 4 : 2) : t2 > 448 && M >= 4 * N ? 7 : 2;
     if (g_force_tile >= 0) return g_force_tile == 5 ? 5 : t;
+    if (BITS != 8 && M > 64 && M <= 96 && cols > 3 * UNITS && cols <= 4 * UNITS) return 6;
     if (((M > 64 && M <= 96) || (M > 128 && M <= 192)) && cols >= 320) return 10;
     if (t != 1 && t != 3) return t;
     const long t1 = ((M + 127) / 128) * cols, t5 = ((M + 63) / 64) * cols;
@@ -1783,7 +1786,7 @@ static int dispatch_gemm(GemmArgs& g, hipStream_t st) {
             if (t == 11) return run_gemm<I8, BITS, 1, 4, 2, 1, 2, BITS == 8 ? 160 * 1024 : 80 * 1024, 4>(g, 11, st);
     }
     if constexpr (BITS != 16)
-        if (t == 10 || (I8 && t == 6)) return run_gemm<I8, BITS, 1, 4, 3, 1, 1, 53 * 1024, 3>(g, 10, st);
+        if (t == 10 || (I8 && BITS == 8 && t == 6)) return run_gemm<I8, BITS, 1, 4, 3, 1, 1, 53 * 1024, 3>(g, 10, st);
     switch (t) {
         case 0: return run_gemm<I8, BITS, 1, 4, 4, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4>(g, 0, st);
         case 1: return run_gemm<I8, BITS, 2, 2, 2, 2, 1, 80 * 1024, 4>(g, 1, st);
@@ -1791,7 +1794,7 @@ static int dispatch_gemm(GemmArgs& g, hipStream_t st) {
         case 3: return run_gemm<I8, BITS, 2, 2, 2, 2, 2, 160 * 1024, 4>(g, 3, st);
         case 5: return run_gemm<I8, BITS, 1, 4, 2, 1, 1, I8 ? 40 * 1024 : 52 * 1024, 3>(g, 5, st);
         case 6:
-            if constexpr (!I8) return run_gemm<I8, BITS, 1, 4, 3, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4>(g, 6, st);
+            if constexpr (!(I8 && BITS == 8)) return run_gemm<I8, BITS, 1, 4, 3, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4>(g, 6, st);
         default: return run_gemm<I8, BITS, 2, 2, 1, 1, 2, 80 * 1024, 8>(g, 4, st);
     }
 }

@@ -811,6 +811,8 @@ def test_conv_both_sides_of_the_tile_rule(mq, orc, H, N):
     (8, 4928, 2560, 1280, 9),                              # 256, 256, 288
     (8, 16384, 2560, 640, 5),                              # 384, 320, 384
     (8, 10240, 640, 1024, 5), (8, 10241, 640, 1024, 9), (8, 10241, 576, 1024, 5),
+    # one row block over very many columns: rounds of workgroups of 96 x 128 (three per compute unit) and of 96 x 256
+    (4, 77, 192, 98304, 10), (4, 77, 192, 98312, 6), (4, 96, 128, 131072, 6), (2, 65, 128, 131072, 6), (4, 77, 128, 131080, 10), (8, 77, 128, 131072, 10),
     # 2- and 4-bit weights beyond 8 MB
     (4, 1024, 2368, 7040, 5), (4, 1024, 2432, 7040, 1), (4, 600, 2432, 7040, 5), (4, 1088, 2432, 7040, 1), (2, 1024, 4800, 7040, 1)])
 def test_a8_tile_rule(mq, orc, bits, M, K, N, tile):
@@ -824,7 +826,7 @@ def test_a8_tile_rule(mq, orc, bits, M, K, N, tile):
     fn = {8: mq.qlinear_w8a8, 4: mq.qlinear_w4a8, 2: mq.qlinear_w2a8}[bits]
     ran, (y, *_) = chosen_tile(mq, lambda: fn(dev(x.astype(np.float16)), pw, act=one))
     assert ran == tile
-    rows = np.array([0, 63, 64, 95, 96, 127, 128, M // 2, M - 2, M - 1])
+    rows = np.unique(np.clip([0, 63, 64, 95, 96, 127, 128, M // 2, M - 2, M - 1], 0, M - 1))
     want = (x[rows] @ (codes.astype(np.int64) - zp[:, None]).T * 2.0 ** -8).astype(np.float32).astype(np.float16)
     assert np.array_equal(host(y)[rows], want)
 

@@ -1609,8 +1609,6 @@ static int float_tile(int t, const GemmArgs& g, bool bf16) {
 // x 4504 27.6 us / 32.8, 1024 x 1984 x 7752 31.6 / 36.3), where it gives more 1.02 to 1.06; from 2560 k on tile 10 comes in (tile 5 / 9 / 10: 4096 x 5120 x
 // 1280, 192 / 256 / 192 rows, 52.3 / 51.0 / 48.6; 6000 x 5120 x 1280, 256 / 256 / 288, 81.5 / 64.8 / 81.9; 16384 x 2560 x 640, 320 / 384 / 384, 67.2 / 71.4 / 68.5).
 // Below 640 k the output's stores bound it, and the smaller workgroups are the faster ones: 8192 x 384 x 6216 71.2 us / 78.6, 2964 x 384 x 5624 29.4 / 33.2.
-// Weights beyond the last-level cache (256 MB) come from memory once per row block: tile 1, with the fewest loads in flight per byte of
-// LDS, 231 x 2048 x 147456 113 us / 119 with tile 9.
 // Fewer tiles than that: the wave groups of tile 4 leave 8-bit weights two stages, tile 2 has four: 616 x 2048 x 1280 13.3 / 11.7,
 // 700 x 5120 x 1280 24.6 / 20.2; at 4 bits tile 4 is the better one, 11.0 / 11.6 and 18.0 / 20.7.  Few tiles that tile 4 splits over workgroups
 // stay with it, whose parts are fewer (500 x 4032 x 336 14.8 / 19.9, 64 x 5120 x 1280 14.3 / 16.0), and nearly two rounds of tile 2 over a narrow
@@ -1641,7 +1639,6 @@ static int int8_tile(int t, long M, long N, long K) {
     const long r1 = busiest(M, N, 128), r5 = busiest(M, N, 64), r10 = busiest(M, N, 96);
     const bool big = N * K * BITS / 8 > (8L << 20);
     if (BITS != 8) return big && (M > 1024 || (t1 <= 2 * UNITS && r1 <= r5)) ? 1 : 5;
-    if (N * K > (256L << 20)) return 1;
     if (K < 640 && !big) return 5;
     if (t1 > 640) return 9;
     if (K >= 2560) return r1 < r10 ? 9 : 8 * r10 <= 9 * r5 ? 10 : 5;

@@ -831,18 +831,6 @@ def test_a8_tile_rule(mq, orc, bits, M, K, N, tile):
     assert np.array_equal(host(y)[rows], want)
 
 
-def test_a8_weights_beyond_the_last_level_cache_take_the_full_height(mq):
-    """231 rows over 8-bit weights on both sides of 256 MB (the choice alone: the forms are compared with the oracle elsewhere)."""
-    M, K = 231, 2048
-    x = torch.zeros(M, K, dtype=torch.float16, device="cuda")
-    one = (dev(np.array([1.0], np.float32)), dev(np.array([0], np.int32)))
-    for N, tile in ((131072, 9), (131200, 1)):
-        pw = mq.PackedWeight(torch.zeros(mq.packed_bytes(N, K, 8, mq.LAYOUT_KERNEL), dtype=torch.uint8, device="cuda"), torch.ones(N, device="cuda"),
-                             torch.zeros(N, dtype=torch.int32, device="cuda"), torch.zeros(N, dtype=torch.int32, device="cuda"), N, K, 8, mq.LAYOUT_KERNEL, False)
-        ran, (y, *_) = chosen_tile(mq, lambda: mq.qlinear_w8a8(x, pw, act=one))
-        assert ran == tile and not y.any()
-
-
 def test_a8_longest_reduction_and_extreme_codes(mq, orc):
     """K = 33024 is the longest reduction the int32 accumulator is guaranteed to hold (255 * 255 * K < 2^31).  All
     activation codes and all weight codes are 0 or 255 with zero points 0; row 0 against channel 0 is 255 * 255 in

@@ -1626,7 +1626,7 @@ static int float_tile(int t, const GemmArgs& g, bool bf16) {
 // 26.6 / 28.1).
 template <int BITS>
 static int int8_tile(int t, long M, long N, long K) {
-    if (g_force_tile >= 7) return g_force_tile == 11 ? 5 : g_force_tile;
+    if (g_force_tile >= 7) return g_force_tile == 11 ? 5 : BITS != 8 && g_force_tile == 9 ? 8 : g_force_tile;
     const long cols = (N + 127) / 128, t2 = ((M + 63) / 64) * ((N + 63) / 64);
     if (BITS == 8 && t == 4 && g_force_tile < 0) return t2 <= 64 ? (K > 3840 ? 4 : 2) : t2 > 448 && M >= 4 * N ? 7 : 2;
     if (g_force_tile >= 0) return g_force_tile == 5 ? 5 : t;

@@ -424,18 +424,22 @@ def test_split_reduction_takes_a_workspace_with_any_contents(mq, orc, fill):
 @pytest.mark.parametrize("kind", ("f16", "bf16", "a8"))
 @pytest.mark.parametrize("tile", (1, 2, 3, 4, 5))
 def test_every_splitting_kernel_takes_a_workspace_with_any_contents(mq, orc, kind, tile):
+    check_workspace_with_any_contents(mq, orc, kind, tile, 4)
+
+
+def check_workspace_with_any_contents(mq, orc, kind, tile, bits):
     """Each tile form that splits, several tiles, a ragged last row block: the first call on a workspace full of garbage, the
     second on what it left, and one on cleared memory give the same bits."""
     M, K, N = 140, 2048, 200
     x, w = dev(si.activations_f16(35, "anyk/x", M, K)), si.weights_f16(35, "anyk/w", N, K)
-    pw, *_ = make_weight(mq, orc, w, 4)
+    pw, *_ = make_weight(mq, orc, w, bits)
     mq.tune_force_tile(tile)
     mq.tune_force_splits(4)
     try:
         base = mq.qlinear_a8_workspace_bytes(M, K) if kind == "a8" else 0
         ws = torch.zeros(base + mq.split_workspace_bytes(M, N, K), dtype=torch.uint8, device="cuda")
         if kind == "a8":
-            go = lambda: mq.qlinear_w4a8(x, pw, ws=ws)[0]
+            go = lambda: {8: mq.qlinear_w8a8, 4: mq.qlinear_w4a8, 2: mq.qlinear_w2a8}[bits](x, pw, ws=ws)[0]
         else:
             xk = x if kind == "f16" else x.to(torch.bfloat16)
             go = lambda: mq.qlinear_w_only(xk, pw, ws=ws)
@@ -653,8 +657,19 @@ def test_a8_tiles_for_few_and_many_workgroups(mq, orc, mode, tile):
     test_a8_small_shapes(mq, orc, mode, tile)
     if mode in ("w8s", "w4"):
         test_residual_a8(mq, orc, mode, tile)
-    if mode == "w4":
-        test_every_splitting_kernel_takes_a_workspace_with_any_contents(mq, orc, "a8", tile)
+    if mode != "w8a":
+        check_workspace_with_any_contents(mq, orc, "a8", tile, int(mode[1]))
+
+
+@pytest.mark.parametrize("bits,tile,ran", [(8, 9, 9), (4, 9, 8), (2, 9, 8), (4, 8, 8)])
+def test_a_forced_form_that_the_width_lacks_gives_way_to_the_nearest(mq, orc, bits, tile, ran):
+    pw, *_ = make_weight(mq, orc, si.weights_f16(14, "ff/w", 136, 192), bits)
+    x = dev(si.activations_f16(14, "ff/x", 130, 192))
+    mq.tune_force_tile(tile)
+    try:
+        assert chosen_tile(mq, lambda: {8: mq.qlinear_w8a8, 4: mq.qlinear_w4a8, 2: mq.qlinear_w2a8}[bits](x, pw))[0] == ran
+    finally:
+        mq.tune_force_tile(-1)
 
 
 @pytest.mark.parametrize("M", (3072, 3073, 4096, 4097, 10240, 10241))

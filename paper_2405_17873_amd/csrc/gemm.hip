@@ -1458,7 +1458,8 @@ void gemm_kernel(const GemmArgs g) {
 // ---------------------------------------------------------------------------------------------
 // Tile table.  index -> workgroup tile (rows x channels), waves, wave tile:
 //   0: 128x256, 4 waves (1x4) of 128x64     1: 128x128, 4 waves (2x2) of 64x64     2: 64x64, 4 waves of 32x32
-//   3: as 1 and 4: as 2, with a second wave group splitting k inside the workgroup (8 waves)
+//      (linear layers, not 8-bit weights under 8-bit activations, nor quantised ones in bf16)
+//   3 (unquantised fp16 weights): as 1 and 4: as 2, with a second wave group splitting k inside the workgroup (8 waves)
 //   5: 64x128, 4 waves (1x4) of 64x32, two or three LDS stages: the form of tile 1 that puts more workgroups on a
 //      compute unit     6 (linear layers, not 8-bit weights under 8-bit activations): 96x256, 4 waves (1x4) of 96x64
 //   (int8, plain layers) 7: as 5 with three stages   8, 9: 128x128, 8 waves (2x4) of 64x32, with stages for one or for two
@@ -1575,7 +1576,8 @@ static bool taller(long M, long N, long num, long den) {  // busiest unit: rows 
 template <int BITS>
 static int float_tile(int t, const GemmArgs& g, bool bf16) {
     const long M = g.M, N = g.N, K = g.K;
-    if (g_force_tile >= 0) return g_force_tile == 5 || (BITS != 16 && g_force_tile >= 10) ? g_force_tile : t;
+    if (g_force_tile >= 0 && (g_force_tile == 5 || (BITS != 16 && g_force_tile >= 10))) return g_force_tile;
+    if (g_force_tile >= 0) return BITS == 16 ? t : t == 1 && bf16 ? 5 : t == 3 ? 11 : t;
     if (BITS == 16 || t == 6) return t;
     if (t == 0) return M > 128 && M <= 192 ? 10 : 0;
     const long t2 = ((M + 63) / 64) * ((N + 63) / 64), t5 = ((M + 63) / 64) * ((N + 127) / 128);
@@ -1629,7 +1631,7 @@ static int int8_tile(int t, long M, long N, long K) {
     if (g_force_tile >= 7) return g_force_tile == 11 ? 5 : BITS != 8 && g_force_tile == 9 ? 8 : g_force_tile;
     const long cols = (N + 127) / 128, t2 = ((M + 63) / 64) * ((N + 63) / 64);
     if (BITS == 8 && t == 4 && g_force_tile < 0) return t2 <= 64 ? (K > 3840 ? 4 : 2) : t2 > 448 && M >= 4 * N ? 7 : 2;
-    if (g_force_tile >= 0) return g_force_tile == 5 ? 5 : t;
+    if (g_force_tile >= 0) return g_force_tile == 5 ? 5 : t == 1 || t == 3 ? (BITS == 8 ? 9 : 1) : t;
     if (BITS != 8 && M > 64 && M <= 96 && cols > 3 * UNITS && cols <= 4 * UNITS) return 6;
     if (((M > 64 && M <= 96) || (M > 128 && M <= 192)) && cols >= 320) return 10;
     if (t != 1 && t != 3) return t;
@@ -1786,9 +1788,11 @@ static int dispatch_gemm(GemmArgs& g, hipStream_t st) {
         if (t == 10 || (I8 && BITS == 8 && t == 6)) return run_gemm<I8, BITS, 1, 4, 3, 1, 1, 53 * 1024, 3>(g, 10, st);
     switch (t) {
         case 0: return run_gemm<I8, BITS, 1, 4, 4, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4>(g, 0, st);
-        case 1: return run_gemm<I8, BITS, 2, 2, 2, 2, 1, 80 * 1024, 4>(g, 1, st);
+        case 1:
+            if constexpr (!(I8 && BITS == 8)) return run_gemm<I8, BITS, 2, 2, 2, 2, 1, 80 * 1024, 4>(g, 1, st);
         case 2: return run_gemm<I8, BITS, 2, 2, 1, 1, 1, 80 * 1024, 8>(g, 2, st);
-        case 3: return run_gemm<I8, BITS, 2, 2, 2, 2, 2, 160 * 1024, 4>(g, 3, st);
+        case 3:
+            if constexpr (BITS == 16) return run_gemm<I8, BITS, 2, 2, 2, 2, 2, 160 * 1024, 4>(g, 3, st);
         case 5: return run_gemm<I8, BITS, 1, 4, 2, 1, 1, I8 ? 40 * 1024 : 52 * 1024, 3>(g, 5, st);
         case 6:
             if constexpr (!(I8 && BITS == 8)) return run_gemm<I8, BITS, 1, 4, 3, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4>(g, 6, st);
@@ -1811,7 +1815,8 @@ static int dispatch_gemm_bf16(GemmArgs& g, hipStream_t st) {
         }
     switch (t) {
         case 0: return run_gemm<false, BITS, 1, 4, 4, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4, true>(g, 0, st);
-        case 1: return run_gemm<false, BITS, 2, 2, 2, 2, 1, 80 * 1024, 4, true>(g, 1, st);
+        case 1:
+            if constexpr (BITS == 16) return run_gemm<false, BITS, 2, 2, 2, 2, 1, 80 * 1024, 4, true>(g, 1, st);
         case 5: return run_gemm<false, BITS, 1, 4, 2, 1, 1, 52 * 1024, 3, true>(g, 5, st);
         default: return run_gemm<false, BITS, 2, 2, 1, 1, 1, 80 * 1024, 8, true>(g, 2, st);
     }
@@ -2077,11 +2082,9 @@ static int dispatch_conv_w_only(GemmArgs& g, hipStream_t st) {
     if (g_force_tile < 0 && t == 0 && g.N < 512) t = 1;
     if (g_force_tile == 10 || (g_force_tile < 0 && t == 1 && taller(g.M, g.N, 9, 8)))
         return run_gemm<false, BITS, 1, 4, 3, 1, 1, 53 * 1024, 3, false, 3>(g, 10, st);
-    if (g_force_tile == 5 || (g_force_tile < 0 && t == 1))
-        return run_gemm<false, BITS, 1, 4, 2, 1, 1, 52 * 1024, 3, false, 3>(g, 5, st);
     switch (t) {
         case 0: return run_gemm<false, BITS, 1, 4, 4, 2, 1, 80 * 1024, 4, false, 3>(g, 0, st);
-        case 1: return run_gemm<false, BITS, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 3>(g, 1, st);
+        case 1: return run_gemm<false, BITS, 1, 4, 2, 1, 1, 52 * 1024, 3, false, 3>(g, 5, st);
         case 4: return run_gemm<false, BITS, 2, 2, 1, 1, 2, 160 * 1024, 8, false, 3>(g, 4, st);
         default: return run_gemm<false, BITS, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 3>(g, 2, st);
     }
@@ -2137,24 +2140,21 @@ int launch_conv3x3_a8(const int8_t* a8, const ActParams* params, int B, int H, i
     if (w_bits == 4) {
         g.w_off = 0;
         if (t == 10) return run_gemm<true, 4, 1, 4, 3, 1, 1, 53 * 1024, 3, false, 4>(g, 10, st);
-        if (t <= 1 && g_force_tile != 1) return run_gemm<true, 4, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
-        if (t <= 1) return run_gemm<true, 4, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 4>(g, 1, st);
+        if (t <= 1) return run_gemm<true, 4, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
         if (t == 4) return run_gemm<true, 4, 2, 2, 1, 1, 2, 80 * 1024, 8, false, 4>(g, 4, st);
         return run_gemm<true, 4, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 4>(g, 2, st);
     }
     if (w_bits == 2) {
         g.w_off = 0;
         if (t == 10) return run_gemm<true, 2, 1, 4, 3, 1, 1, 53 * 1024, 3, false, 4>(g, 10, st);
-        if (t <= 1 && g_force_tile != 1) return run_gemm<true, 2, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
-        if (t <= 1) return run_gemm<true, 2, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 4>(g, 1, st);
+        if (t <= 1) return run_gemm<true, 2, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
         if (t == 4) return run_gemm<true, 2, 2, 2, 1, 1, 2, 80 * 1024, 8, false, 4>(g, 4, st);
         return run_gemm<true, 2, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 4>(g, 2, st);
     }
     if (w_bits == 8) {
         g.w_off = w_signed ? 0 : 128;
         if (t == 10) return run_gemm<true, 8, 1, 4, 3, 1, 1, 53 * 1024, 3, false, 4>(g, 10, st);
-        if (t <= 1 && g_force_tile != 1) return run_gemm<true, 8, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
-        if (t <= 1) return run_gemm<true, 8, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 4>(g, 1, st);
+        if (t <= 1) return run_gemm<true, 8, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
         if (t == 4) return run_gemm<true, 8, 2, 2, 1, 1, 2, 80 * 1024, 8, false, 4>(g, 4, st);
         return run_gemm<true, 8, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 4>(g, 2, st);
     }

@@ -52,21 +52,37 @@ def lib_path() -> str:
 
 
 def load():
-    """Loads the HIP library and the native marshalling; raises if they have not been built (there is no fallback path)."""
-    global _lib, _native
+    """Loads the HIP library; raises if it has not been built (there is no fallback path)."""
+    global _lib
     if _lib is None:
         if not os.path.exists(_LIB_PATH):
             raise RuntimeError(f"{_LIB_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'`")
-        from . import _mqhost as _native  # (raises ImportError if it has not been built)
         lib = C.CDLL(_LIB_PATH)
         for name in ("mq_a8_row_bytes", "mq_split_workspace_bytes", "mq_builtin_workspace_bytes", "mq_conv3x3_a8_workspace_bytes", "mq_packed_bytes", "mq_qlinear_a8_workspace_bytes", "mq_qlinear_a8_geglu_dynamic_workspace_bytes", "mq_bos_aware_kv_proj_workspace_bytes"):
             getattr(lib, name).restype = C.c_size_t
         lib.mq_prof_bracket_overhead_us.restype = C.c_double
-        _native.bind(*(C.cast(getattr(lib, name), C.c_void_p).value for name in (
-            "mq_qlinear_w_only", "mq_qlinear_w8a8", "mq_qlinear_w4a8", "mq_qlinear_w2a8", "mq_quantize_weights", "mq_pack_weights",
-            "mq_split_workspace_bytes", "mq_qlinear_a8_workspace_bytes", "mq_packed_bytes")))
         _lib = lib
     return _lib
+
+
+def _load_native():
+    """The native marshalling, bound to the library's entry points; raises if it has not been built, or not for this torch and
+    Python.  Only the calls that go through it need it."""
+    global _native
+    if _native is None:
+        from .build import _host_made_for
+        try:
+            from . import _mqhost
+        except ImportError as e:
+            raise RuntimeError("_mqhost.so is missing or stale: run `python -c 'import __graft_entry__ as g; g.build()'`") from e
+        if _mqhost.made_for != _host_made_for():
+            raise RuntimeError(f"_mqhost.so was built for {_mqhost.made_for}, this is {_host_made_for()}: build again")
+        lib = load()
+        _mqhost.bind(*(C.cast(getattr(lib, name), C.c_void_p).value for name in (
+            "mq_qlinear_w_only", "mq_qlinear_w8a8", "mq_qlinear_w4a8", "mq_qlinear_w2a8", "mq_quantize_weights", "mq_pack_weights",
+            "mq_split_workspace_bytes", "mq_qlinear_a8_workspace_bytes", "mq_packed_bytes")))
+        _native = _mqhost
+    return _native
 
 
 def version() -> int:
@@ -217,7 +233,7 @@ def stack_weights(parts) -> PackedWeight:
 def quantize_weights(w: torch.Tensor, bits: int, symmetric: bool = False):
     """W [N,K] fp16/bf16 -> (codes uint8 [N,K], scale float32 [N], zp int32 [N])."""
     lib = load()
-    r = _native.quantize_weights(w, bits, int(symmetric))
+    r = (_native or _load_native()).quantize_weights(w, bits, int(symmetric))
     if r is not None:
         return _done(r, "mq_quantize_weights")
     assert w.is_cuda and w.dim() == 2 and w.is_contiguous()
@@ -239,7 +255,7 @@ def pack_weights(codes: torch.Tensor, bits: int, layout: int = LAYOUT_KERNEL, co
     """codes uint8 [N,K] -> (packed uint8 [bytes], colsum int32 [N] or None).  bits = 16: `codes` is the fp16/bf16
     weight matrix itself and there is no colsum."""
     lib = load()
-    r = _native.pack_weights(codes, bits, layout, int(codes_signed), int(want_colsum))
+    r = (_native or _load_native()).pack_weights(codes, bits, layout, int(codes_signed), int(want_colsum))
     if r is not None:
         return _done(r, "mq_pack_weights")
     assert codes.is_cuda and codes.dim() == 2 and codes.is_contiguous()
@@ -283,7 +299,7 @@ def qlinear_w_only(x: torch.Tensor, w: PackedWeight, bias: Optional[torch.Tensor
     """Y = X . dequant(W)^T + bias (+ residual) with 16-bit floating-point compute (weight-only quantisation).
     ws: optional uint8 workspace of split_workspace_bytes(M, N, K) bytes; allocated here when the shape can use one."""
     lib = load()
-    r = _native.qlinear_w_only(x, w.packed, w.N, w.K, w.bits, w.layout, w.scale, w.zp, bias, out, residual, ws)
+    r = (_native or _load_native()).qlinear_w_only(x, w.packed, w.N, w.K, w.bits, w.layout, w.scale, w.zp, bias, out, residual, ws)
     if r is not None:
         return _done(r, "mq_qlinear_w_only")
     assert x.is_cuda and x.dim() == 2 and x.stride(1) == 1
@@ -314,7 +330,7 @@ def _qlinear_a8(fn_name, x, w: PackedWeight, act, bias, out, ws, want_acc, want_
     L = load()
     if not (want_acc or want_act):
         a_s, a_z = (None, None) if act is None else act
-        r = _native.qlinear_a8(x, w.packed, w.N, w.K, w.bits, w.layout, int(w.signed), w.scale, w.zp, w.colsum, a_s, a_z, bias,
+        r = (_native or _load_native()).qlinear_a8(x, w.packed, w.N, w.K, w.bits, w.layout, int(w.signed), w.scale, w.zp, w.colsum, a_s, a_z, bias,
                                out, residual, ws)
         if r is not None:
             return _done(r, fn_name), None, (None, None)

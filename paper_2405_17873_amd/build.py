@@ -49,23 +49,35 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def _host_made_for() -> str:
+    """What _mqhost.so is compiled against, beside its source: it reads torch's and Python's object layouts."""
+    import torch
+
+    return f"torch {torch.__version__}, hip {torch.version.hip}, {sysconfig.get_config_var('SOABI')}"
+
+
 def _build_host(force: bool) -> None:
-    src = os.path.join(CSRC, "host.cpp")
-    if not force and os.path.exists(HOST) and all(os.path.getmtime(HOST) >= os.path.getmtime(d) for d in (src, __file__)):
+    src, stamp, made_for = os.path.join(CSRC, "host.cpp"), os.path.join(OBJ, "mqhost.made_for"), _host_made_for()
+    if not force and os.path.exists(HOST) and os.path.exists(stamp) and open(stamp).read() == made_for and \
+            all(os.path.getmtime(HOST) >= os.path.getmtime(d) for d in (src, __file__)):
         return
     import torch
     from torch.utils import cpp_extension
 
     tmp = f"{HOST}.{os.getpid()}"
-    inc = [f"-I{d}" for d in (*cpp_extension.include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"])]
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    inc = [a for d in (*cpp_extension.include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"]) for a in ("-isystem", d)]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-missing-field-initializers",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f'-DMQ_MADE_FOR="{made_for}"',
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", *inc, src, "-o", tmp,
            *(f"-L{d}" for d in cpp_extension.library_paths()), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
+    if r.stderr:
         sys.stderr.write(r.stdout + r.stderr)
+    if r.returncode != 0:
         raise RuntimeError("g++ failed on host.cpp")
     os.replace(tmp, HOST)
+    with open(stamp, "w") as f:
+        f.write(made_for)
 
 
 def build(force: bool = False) -> str:

@@ -290,4 +290,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_mqhost", nullptr, -1, methods, nu
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__mqhost(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__mqhost(void) {
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "made_for", MQ_MADE_FOR) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -165,3 +165,61 @@ def test_product_package_does_not_import_the_oracle():
             if f.endswith((".py", ".hip", ".h", ".cpp")):
                 text = open(os.path.join(dirpath, f)).read()
                 assert "oracle" not in text.lower().replace("no cpu fallback", ""), f
+
+
+def test_host_only_calls_do_without_the_native_marshalling(tmp_path):
+    """A package whose _mqhost.so is missing still answers size queries and solves allocations; the calls that need the module say so."""
+    import shutil
+    import subprocess
+    import sys
+
+    from paper_2405_17873_amd import binding
+    pkg = tmp_path / "mqcopy"
+    pkg.mkdir()
+    here = os.path.dirname(os.path.abspath(binding.__file__))
+    for name in ("__init__.py", "binding.py", "build.py"):
+        shutil.copy(os.path.join(here, name), pkg)
+    os.symlink(os.path.join(here, "libmixdq.so"), pkg / "libmixdq.so")
+    code = ("import numpy as np, torch, mqcopy as mq\n"
+            "assert mq.packed_bytes(320, 320, 4, mq.LAYOUT_KERNEL) == 320 * 160 and mq.split_workspace_bytes(4, 1280, 1280) > 0\n"
+            "choice, _, used = mq.alloc_solve(np.array([[1.0, 0.0]]), np.array([[1, 2]]), 2)\n"
+            "assert choice[0] in (0, 1) and used <= 2\n"
+            "try:\n    mq.quantize_weights(torch.zeros(8, 64), 4)\n"
+            "except RuntimeError as e:\n    assert '_mqhost' in str(e)\n"
+            "else:\n    raise SystemExit('not refused')\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_native_marshalling_is_built_again_for_another_torch(tmp_path, monkeypatch):
+    import subprocess
+
+    import torch
+
+    from paper_2405_17873_amd import build as b
+    ran = []
+
+    def compiler(cmd, **kw):
+        ran.append(cmd)
+        open(cmd[cmd.index("-o") + 1], "w").close()
+        return subprocess.CompletedProcess(cmd, 0, "", "")
+
+    monkeypatch.setattr(b, "HOST", str(tmp_path / "_mqhost.so"))
+    monkeypatch.setattr(b, "OBJ", str(tmp_path))
+    monkeypatch.setattr(b.subprocess, "run", compiler)
+    b._build_host(False)
+    b._build_host(False)
+    assert len(ran) == 1
+    monkeypatch.setattr(torch, "__version__", "0.0.0+other")
+    b._build_host(False)
+    b._build_host(False)
+    assert len(ran) == 2
+
+
+def test_native_marshalling_made_for_another_torch_is_refused(monkeypatch):
+    from paper_2405_17873_amd import binding, build
+    binding._load_native()
+    monkeypatch.setattr(binding, "_native", None)
+    monkeypatch.setattr(build, "_host_made_for", lambda: "torch 0.0.0")
+    with pytest.raises(RuntimeError, match="built for"):
+        binding._load_native()

@@ -73,10 +73,19 @@ bool fits(int64_t v) { return v >= 0 && v <= INT32_MAX; }
 // Nothing between the caller and the operators that would want to see the allocations.
 bool plain_calls() { return !at::impl::torch_function_mode_enabled() && !c10::impl::TorchDispatchModeTLS::any_modes_set(); }
 
+// Gives the interpreter lock up for as long as it lives: for allocations, which wait for the device when the pool has to
+// grow, and for the launch.
+struct Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked&) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 void* stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
 
-at::Tensor empty(at::IntArrayRef size, at::ScalarType type, const at::Tensor& like) {
-    return at::empty(size, at::TensorOptions().dtype(type).device(like.device()));
+at::Tensor empty(at::IntArrayRef size, at::ScalarType type, at::Device device) {
+    return at::empty(size, at::TensorOptions().dtype(type).device(device));
 }
 
 // [M, N] residual of x's type: its address and row stride.
@@ -112,30 +121,28 @@ PyObject* qlinear_w_only(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (type != at::kHalf && type != at::kBFloat16) return general();
         const int64_t M = x->size(0);
         if (!residual_of(a[10], M, N, type, res, ldr)) return general();
-        at::Tensor y, own_ws;
-        if (a[9] == Py_None) {
-            y = empty({M, N}, type, *x);
-        } else {
-            if (!(out = gpu_tensor(a[9])) || out->dim() < 1 || !fits(out->stride(0))) return general();
-            y = *out;
-        }
+        if (a[9] != Py_None && (!(out = gpu_tensor(a[9])) || out->dim() < 1 || !fits(out->stride(0)))) return general();
         if (!optional_ptr(a[11], ws, &wst)) return general();
         size_t ws_bytes = wst ? wst->nbytes() : 0;
-        if (!wst) {
-            ws_bytes = entry.split_bytes((int)M, N, K);
-            if (ws_bytes) {
-                own_ws = empty({(int64_t)ws_bytes}, at::kByte, *x);
+        const void* xp = x->data_ptr();
+        void* yp = out ? out->data_ptr() : nullptr;
+        const int ldx = (int)x->stride(0), ldy = out ? (int)out->stride(0) : N, dt = type == at::kHalf ? 0 : 1;
+        const at::Device device = x->device();
+        at::Tensor y, own_ws;
+        int rc;
+        {
+            Unlocked unlocked;
+            if (!out) {
+                y = empty({M, N}, type, device);
+                yp = y.data_ptr();
+            }
+            if (!wst && (ws_bytes = entry.split_bytes((int)M, N, K)) != 0) {
+                own_ws = empty({(int64_t)ws_bytes}, at::kByte, device);
                 ws = own_ws.data_ptr();
             }
+            rc = entry.w_only(xp, (int)M, K, ldx, packed, N, bits, layout, (const float*)scale, (const int32_t*)zp, bias, yp, ldy, dt, res,
+                              ldr, ws, ws_bytes, stream());
         }
-        const void* xp = x->data_ptr();
-        void *yp = y.data_ptr(), *st = stream();
-        const int ldx = (int)x->stride(0), ldy = (int)y.stride(0), dt = type == at::kHalf ? 0 : 1;
-        int rc;
-        Py_BEGIN_ALLOW_THREADS;
-        rc = entry.w_only(xp, (int)M, K, ldx, packed, N, bits, layout, (const float*)scale, (const int32_t*)zp, bias, yp, ldy, dt, res,
-                          ldr, ws, ws_bytes, st);
-        Py_END_ALLOW_THREADS;
         if (rc) return PyLong_FromLong(rc);
         if (a[9] != Py_None) return Py_NewRef(a[9]);
         return THPVariable_Wrap(std::move(y));
@@ -158,36 +165,36 @@ PyObject* qlinear_a8(PyObject*, PyObject* const* a, Py_ssize_t n) {
             return general();
         const int64_t M = x->size(0);
         if (!residual_of(a[14], M, N, at::kHalf, res, ldr)) return general();
-        at::Tensor y, own_ws;
-        if (a[13] == Py_None) {
-            y = empty({M, N}, at::kHalf, *x);
-        } else {
-            if (!(out = gpu_tensor(a[13])) || out->dim() < 1 || !fits(out->stride(0))) return general();
-            y = *out;
-        }
+        if (a[13] != Py_None && (!(out = gpu_tensor(a[13])) || out->dim() < 1 || !fits(out->stride(0)))) return general();
         if (!optional_ptr(a[15], ws, &wst)) return general();
-        size_t ws_bytes;
-        if (wst) {
-            ws_bytes = (size_t)wst->numel();
-        } else {
-            ws_bytes = entry.a8_bytes((int)M, K) + entry.split_bytes((int)M, N, K);
-            own_ws = empty({(int64_t)ws_bytes}, at::kByte, *x);
-            ws = own_ws.data_ptr();
-        }
+        size_t ws_bytes = wst ? (size_t)wst->numel() : 0;
         const void* xp = x->data_ptr();
-        void *yp = y.data_ptr(), *st = stream();
-        const int ldx = (int)x->stride(0), ldy = (int)y.stride(0);
+        void* yp = out ? out->data_ptr() : nullptr;
+        const int ldx = (int)x->stride(0), ldy = out ? (int)out->stride(0) : N;
+        const at::Device device = x->device();
+        at::Tensor y, own_ws;
         int rc;
-        Py_BEGIN_ALLOW_THREADS;
-        if (bits == 8)
-            rc = entry.w8a8(xp, (int)M, K, ldx, packed, N, layout, sgn, (const float*)scale, (const int32_t*)zp, (const int32_t*)colsum,
-                            (const float*)act_s, (const int32_t*)act_z, bias, yp, ldy, nullptr, res, ldr, nullptr, nullptr, ws,
-                            ws_bytes, st);
-        else
-            rc = (bits == 4 ? entry.w4a8 : entry.w2a8)(xp, (int)M, K, ldx, packed, N, layout, (const float*)scale, (const int32_t*)zp,
-                                                       (const int32_t*)colsum, (const float*)act_s, (const int32_t*)act_z, bias, yp,
-                                                       ldy, nullptr, res, ldr, nullptr, nullptr, ws, ws_bytes, st);
-        Py_END_ALLOW_THREADS;
+        {
+            Unlocked unlocked;
+            if (!out) {
+                y = empty({M, N}, at::kHalf, device);
+                yp = y.data_ptr();
+            }
+            if (!wst) {
+                ws_bytes = entry.a8_bytes((int)M, K) + entry.split_bytes((int)M, N, K);
+                own_ws = empty({(int64_t)ws_bytes}, at::kByte, device);
+                ws = own_ws.data_ptr();
+            }
+            void* st = stream();
+            if (bits == 8)
+                rc = entry.w8a8(xp, (int)M, K, ldx, packed, N, layout, sgn, (const float*)scale, (const int32_t*)zp, (const int32_t*)colsum,
+                                (const float*)act_s, (const int32_t*)act_z, bias, yp, ldy, nullptr, res, ldr, nullptr, nullptr, ws,
+                                ws_bytes, st);
+            else
+                rc = (bits == 4 ? entry.w4a8 : entry.w2a8)(xp, (int)M, K, ldx, packed, N, layout, (const float*)scale, (const int32_t*)zp,
+                                                           (const int32_t*)colsum, (const float*)act_s, (const int32_t*)act_z, bias, yp,
+                                                           ldy, nullptr, res, ldr, nullptr, nullptr, ws, ws_bytes, st);
+        }
         if (rc) return PyLong_FromLong(rc);
         if (a[13] != Py_None) return Py_NewRef(a[13]);
         return THPVariable_Wrap(std::move(y));
@@ -208,13 +215,16 @@ PyObject* quantize_weights(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::ScalarType type = w->scalar_type();
         if (type != at::kHalf && type != at::kBFloat16) return general();
         const int64_t N = w->size(0), K = w->size(1);
-        at::Tensor codes = empty({N, K}, at::kByte, *w), scale = empty({N}, at::kFloat, *w), zp = empty({N}, at::kInt, *w);
         const void* wp = w->data_ptr();
-        void *cp = codes.data_ptr(), *sp = scale.data_ptr(), *zpp = zp.data_ptr(), *st = stream();
+        const at::Device device = w->device();
+        at::Tensor codes, scale, zp;
         int rc;
-        Py_BEGIN_ALLOW_THREADS;
-        rc = entry.quantize(wp, (int)N, (int)K, bits, sym, type == at::kHalf ? 0 : 1, (uint8_t*)cp, (float*)sp, (int32_t*)zpp, st);
-        Py_END_ALLOW_THREADS;
+        {
+            Unlocked unlocked;
+            codes = empty({N, K}, at::kByte, device), scale = empty({N}, at::kFloat, device), zp = empty({N}, at::kInt, device);
+            rc = entry.quantize(wp, (int)N, (int)K, bits, sym, type == at::kHalf ? 0 : 1, (uint8_t*)codes.data_ptr(), (float*)scale.data_ptr(),
+                                (int32_t*)zp.data_ptr(), stream());
+        }
         if (rc) return PyLong_FromLong(rc);
         PyObject *c = THPVariable_Wrap(std::move(codes)), *s = THPVariable_Wrap(std::move(scale)), *z = THPVariable_Wrap(std::move(zp));
         PyObject* t = c && s && z ? PyTuple_Pack(3, c, s, z) : nullptr;
@@ -239,14 +249,17 @@ PyObject* pack_weights(PyObject*, PyObject* const* a, Py_ssize_t n) {
             return general();
         const int64_t N = codes->size(0), K = codes->size(1);
         const size_t nbytes = entry.packed_bytes((int)N, (int)K, bits, layout);
-        at::Tensor packed = empty({(int64_t)(nbytes ? nbytes : 1)}, at::kByte, *codes), colsum;
-        if (want) colsum = empty({N}, at::kInt, *codes);
         const void* cp = codes->data_ptr();
-        void *pp = packed.data_ptr(), *sp = want ? colsum.data_ptr() : nullptr, *st = stream();
+        const at::Device device = codes->device();
+        at::Tensor packed, colsum;
         int rc;
-        Py_BEGIN_ALLOW_THREADS;
-        rc = entry.pack((const uint8_t*)cp, (int)N, (int)K, bits, layout, sgn, pp, (int32_t*)sp, st);
-        Py_END_ALLOW_THREADS;
+        {
+            Unlocked unlocked;
+            packed = empty({(int64_t)(nbytes ? nbytes : 1)}, at::kByte, device);
+            if (want) colsum = empty({N}, at::kInt, device);
+            rc = entry.pack((const uint8_t*)cp, (int)N, (int)K, bits, layout, sgn, packed.data_ptr(),
+                            want ? (int32_t*)colsum.data_ptr() : nullptr, stream());
+        }
         if (rc) return PyLong_FromLong(rc);
         PyObject *p = THPVariable_Wrap(std::move(packed)), *s = want ? THPVariable_Wrap(std::move(colsum)) : Py_NewRef(Py_None);
         PyObject* t = p && s ? PyTuple_Pack(2, p, s) : nullptr;

@@ -1818,6 +1818,51 @@ def test_eager_calls_natively_marshalled_and_by_the_general_way(mq, orc):
     refused(lambda: mq.pack_weights(codes, 8, codes_signed=True, layout=7))
 
 
+def test_eager_calls_allocate_without_the_interpreter_lock(mq, tmp_path):
+    """An allocator that notes whether its caller holds Python's lock, under the eager calls that allocate their results."""
+    import ctypes
+    import subprocess
+    src, so = tmp_path / "note.c", tmp_path / "note.so"
+    src.write_text("""
+#include <stddef.h>
+extern int PyGILState_Check(void);
+int (*device_malloc)(void**, size_t);
+int (*device_free)(void*);
+int allocations, locked;
+void* note_alloc(ptrdiff_t bytes, int device, void* stream) {
+    void* p = NULL;
+    ++allocations;
+    locked += PyGILState_Check();
+    return device_malloc(&p, (size_t)bytes) ? NULL : p;
+}
+void note_free(void* p, ptrdiff_t bytes, int device, void* stream) { device_free(p); }
+""")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(so), str(src)], check=True)
+    note = ctypes.CDLL(str(so))
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    for name, fn in (("device_malloc", hip.hipMalloc), ("device_free", hip.hipFree)):
+        ctypes.c_void_p.in_dll(note, name).value = ctypes.cast(fn, ctypes.c_void_p).value
+    count = lambda name: ctypes.c_int.in_dll(note, name).value
+    w = torch.randn(72, 1024, device="cuda").half()
+    codes, scale, zp = mq.quantize_weights(w, 4)
+    packed, colsum = mq.pack_weights(codes, 4)
+    pw = mq.PackedWeight(packed, scale, zp, colsum, 72, 1024, 4, mq.LAYOUT_KERNEL, False)
+    x = torch.randn(33, 1024, device="cuda").half()
+    allocator = torch.cuda.memory.CUDAPluggableAllocator(str(so), "note_alloc", "note_free")
+    ctypes.pythonapi.Py_IncRef(ctypes.py_object(allocator.allocator()))  # (a pool calls it when it goes, at the latest with the process)
+    seen = []
+    for call in (lambda: torch.empty(64, device="cuda"), lambda: mq.qlinear_w_only(x, pw), lambda: mq.qlinear_w4a8(x, pw)[0],
+                 lambda: mq.quantize_weights(w, 4), lambda: mq.pack_weights(codes, 4)):
+        before = count("allocations"), count("locked")
+        pool = torch.cuda.MemPool(allocator.allocator())
+        with torch.cuda.use_mem_pool(pool):
+            result = call()
+        torch.cuda.synchronize()
+        del result, pool  # (gives the memory back while its allocator is there)
+        seen.append((count("allocations") - before[0] > 0, count("locked") - before[1]))
+    assert seen == [(True, 0)] * 5
+
+
 def test_side_streams_and_two_streams_at_once(mq, orc):
     """The library launches on the stream it is handed and keeps no state that two streams could trample: the results
     on a side stream, and on two streams that run different layers at the same time (each call with a workspace of its

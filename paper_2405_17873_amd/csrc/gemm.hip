@@ -1458,7 +1458,6 @@ void gemm_kernel(const GemmArgs g) {
 // ---------------------------------------------------------------------------------------------
 // Tile table.  index -> workgroup tile (rows x channels), waves, wave tile:
 //   0: 128x256, 4 waves (1x4) of 128x64     1: 128x128, 4 waves (2x2) of 64x64     2: 64x64, 4 waves of 32x32
-//      (linear layers, not 8-bit weights under 8-bit activations, nor quantised ones in bf16)
 //   3 (unquantised fp16 weights): as 1 and 4: as 2, with a second wave group splitting k inside the workgroup (8 waves)
 //   5: 64x128, 4 waves (1x4) of 64x32, two or three LDS stages: the form of tile 1 that puts more workgroups on a
 //      compute unit     6 (linear layers, not 8-bit weights under 8-bit activations): 96x256, 4 waves (1x4) of 96x64
@@ -1470,6 +1469,8 @@ void gemm_kernel(const GemmArgs g) {
 // SIMD and 128x128 tiles with two-wave workgroups were measured slower on every configured shape.
 // The number of LDS stages is the largest (<= 4; <= 8 for tile 2, whose problems are latency bound) that lets two
 // workgroups share a compute unit and keeps the hand-counted loads within the 6-bit vmcnt.
+// 8-bit weights under 8-bit activations, 2 KB per weight tile, leave room for three workgroups of tile 5 and two of tile 10 on a unit (the
+// other widths for four and three), with two stages: 1300 tiles of 96x128 (K/V projections of all layers, one prompt) are 512 + 512 + 276.
 static int g_force_tile = -1;
 static long long* g_phase_clk = nullptr;
 static long g_phase_cap = 0;
@@ -1571,8 +1572,9 @@ static bool taller(long M, long N, long num, long den) {  // busiest unit: rows 
 // 28, 0.91 to 1.01 at 40 and 1.0 at 48, with more than 32 rows 0.94 to 1.06 at 36 (77 x 1920 x 504 9.2 / 13.2, 32 x 1600 x 2560 10.0 / 10.8).
 // With up to 8 tiles bf16 is better off with tile 2 up to 3071 k, both split (0.93 to 1.0), and with 53 to 64 from 4096 k on (0.90 to 1.01:
 // 4 x 4224 x 3792 20.0 us / 21.8).
-// Two row blocks of 96 over very many columns, tile 0 / 10: 154 x 2048 x 166400 at 2, 4, 8 bits 134 / 113, 141 / 122, 168 / 146, 83200 71 / 61, 74 / 65, 79 / 70
-// (one such block keeps tile 6: 64.6 / 66.8 at 4 bits and 166400 columns, 38.7 / 34.0 at 83200).
+// Two row blocks of 96 over very many columns, tile 0 / 10: 154 x 2048 x 166400 at 2, 4, 8 bits 134 / 113, 141 / 122, 168 / 146, 83200 71 / 61, 74 / 65, 79 / 70.
+// One such block keeps tile 6 (fp16) or 0: at 769 to 1024 column tiles, the third round of tile 10, it is the faster one in fp16 (tile 10 over it 1.1, 8 bits
+// 1.3); elsewhere tile 10 measures 0.83 to 0.96 of it, in bf16 0.66 to 0.94 but at 8 bits there (1.06), which no rule takes up.
 template <int BITS>
 static int float_tile(int t, const GemmArgs& g, bool bf16) {
     const long M = g.M, N = g.N, K = g.K;
@@ -1666,7 +1668,7 @@ template <bool I8, int BITS, int WGM, int WGN, int TM, int TN, int KS, int BUDGE
 static int run_gemm_r(GemmArgs& g, int tile_index, hipStream_t st) {
     constexpr int S = pick_stages<I8, BITS, WGM, WGN, TM, TN, KS>(BUDGET, MAXS);
     using P = GemmPlan<I8, BITS, WGM, WGN, TM, TN, S, KS>;
-    static_assert(P::LDS_BYTES <= 160 * 1024, "LDS plan exceeds the compute unit");
+    static_assert(P::LDS_BYTES <= BUDGET && BUDGET <= 160 * 1024, "the plan of the fewest stages exceeds the budget that was asked for");
     g.tiles_m = (g.M + P::BM - 1) / P::BM;
     g.tiles_n = (g.N + P::BN - 1) / P::BN;
     if (MODE == 1 || MODE == 5 || MODE == 6) g.tiles_n = (int)((g.ld8 + P::BN / 2 - 1) / (P::BN / 2));  // gated columns up to the padded row end
@@ -1785,7 +1787,7 @@ static int dispatch_gemm(GemmArgs& g, hipStream_t st) {
             if (t == 11) return run_gemm<I8, BITS, 1, 4, 2, 1, 2, BITS == 8 ? 160 * 1024 : 80 * 1024, 4>(g, 11, st);
     }
     if constexpr (BITS != 16)
-        if (t == 10 || (I8 && BITS == 8 && t == 6)) return run_gemm<I8, BITS, 1, 4, 3, 1, 1, 53 * 1024, 3>(g, 10, st);
+        if (t == 10 || (I8 && BITS == 8 && t == 6)) return run_gemm<I8, BITS, 1, 4, 3, 1, 1, I8 && BITS == 8 ? 60 * 1024 : 53 * 1024, 3>(g, 10, st);
     switch (t) {
         case 0: return run_gemm<I8, BITS, 1, 4, 4, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4>(g, 0, st);
         case 1:
@@ -1793,7 +1795,7 @@ static int dispatch_gemm(GemmArgs& g, hipStream_t st) {
         case 2: return run_gemm<I8, BITS, 2, 2, 1, 1, 1, 80 * 1024, 8>(g, 2, st);
         case 3:
             if constexpr (BITS == 16) return run_gemm<I8, BITS, 2, 2, 2, 2, 2, 160 * 1024, 4>(g, 3, st);
-        case 5: return run_gemm<I8, BITS, 1, 4, 2, 1, 1, I8 ? 40 * 1024 : 52 * 1024, 3>(g, 5, st);
+        case 5: return run_gemm<I8, BITS, 1, 4, 2, 1, 1, I8 && BITS != 8 ? 40 * 1024 : 52 * 1024, 3>(g, 5, st);
         case 6:
             if constexpr (!(I8 && BITS == 8)) return run_gemm<I8, BITS, 1, 4, 3, 2, 1, WIDE ? 160 * 1024 : 80 * 1024, 4>(g, 6, st);
         default: return run_gemm<I8, BITS, 2, 2, 1, 1, 2, 80 * 1024, 8>(g, 4, st);
@@ -2034,7 +2036,7 @@ int launch_gemm_a8_codes(const int8_t* a8, long lda, const float* act_scale, con
         switch (t) {
             case 0:
             case 1:
-                if (!full_height) return run_gemm<true, 8, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 2>(g, 5, st);
+                if (!full_height) return run_gemm<true, 8, 1, 4, 2, 1, 1, 52 * 1024, 3, false, 2>(g, 5, st);
                 return run_gemm<true, 8, 2, 2, 2, 2, 1, 80 * 1024, 4, false, 2>(g, 1, st);
             default: return run_gemm<true, 8, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 2>(g, 2, st);
         }
@@ -2153,8 +2155,8 @@ int launch_conv3x3_a8(const int8_t* a8, const ActParams* params, int B, int H, i
     }
     if (w_bits == 8) {
         g.w_off = w_signed ? 0 : 128;
-        if (t == 10) return run_gemm<true, 8, 1, 4, 3, 1, 1, 53 * 1024, 3, false, 4>(g, 10, st);
-        if (t <= 1) return run_gemm<true, 8, 1, 4, 2, 1, 1, 40 * 1024, 3, false, 4>(g, 5, st);
+        if (t == 10) return run_gemm<true, 8, 1, 4, 3, 1, 1, 60 * 1024, 3, false, 4>(g, 10, st);
+        if (t <= 1) return run_gemm<true, 8, 1, 4, 2, 1, 1, 52 * 1024, 3, false, 4>(g, 5, st);
         if (t == 4) return run_gemm<true, 8, 2, 2, 1, 1, 2, 80 * 1024, 8, false, 4>(g, 4, st);
         return run_gemm<true, 8, 2, 2, 1, 1, 1, 80 * 1024, 8, false, 4>(g, 2, st);
     }

@@ -674,7 +674,8 @@ def test_a_forced_form_that_the_width_lacks_gives_way_to_the_nearest(mq, orc, bi
 
 @pytest.mark.parametrize("M", (3072, 3073, 4096, 4097, 10240, 10241))
 def test_a8_both_sides_of_the_tile_rule(mq, orc, M):
-    """The automatic choice at 384, 392 and 512 workgroups of 64 x 128, 256, 264, 640 and 648 of 128 x 128."""
+    """The automatic choice at 384, 392 and 512 workgroups of 64 x 128, 640 and 648 of 128 x 128 (test_a8_tile_rule names the forms, and
+    reaches the lines that need a longer reduction)."""
     K, N = 192, 1024
     x = si.activations_f16(14, f"tr/x{M}", M, K, outlier_prob=0.01)
     w = si.weights_f16(14, "tr/w", N, K)
@@ -1816,6 +1817,28 @@ def test_eager_calls_natively_marshalled_and_by_the_general_way(mq, orc):
     refused(lambda: mq.quantize_weights(w, 5))
     refused(lambda: mq.pack_weights(codes.to(torch.int8), 4))
     refused(lambda: mq.pack_weights(codes, 8, codes_signed=True, layout=7))
+
+
+def test_ordinary_eager_calls_are_marshalled_natively(mq):
+    """The native functions take the ordinary case themselves, outputs given and allocated, and decline it under a mode that intercepts
+    operators (a default device is one): without this, comparing the two ways could compare the general one with itself."""
+    from paper_2405_17873_amd import binding
+    native = binding._load_native()
+    w = torch.randn(72, 128, device="cuda").half()
+    codes, scale, zp = mq.quantize_weights(w, 4)
+    packed, colsum = mq.pack_weights(codes, 4)
+    x, out = torch.randn(33, 128, device="cuda").half(), torch.empty(33, 72, dtype=torch.float16, device="cuda")
+    act = (torch.ones(1, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    calls = [lambda o=o, r=r: native.qlinear_w_only(x, packed, 72, 128, 4, mq.LAYOUT_KERNEL, scale, zp, None, o, r, None) for o in (None, out) for r in (None, out)]
+    calls += [lambda o=o, a=a: native.qlinear_a8(x, packed, 72, 128, 4, mq.LAYOUT_KERNEL, 0, scale, zp, colsum, *a, None, o, None, None)
+              for o in (None, out) for a in ((None, None), act)]
+    calls += [lambda: native.quantize_weights(w, 4, 0), lambda: native.quantize_weights(torch.nn.Parameter(w), 4, 0),
+              lambda: native.pack_weights(codes, 4, mq.LAYOUT_KERNEL, 0, 1)]
+    for i, call in enumerate(calls):
+        assert isinstance(call(), (torch.Tensor, tuple)), i
+        with torch.device("cuda"):
+            assert call() is None, i
+    torch.cuda.synchronize()
 
 
 def test_eager_calls_allocate_without_the_interpreter_lock(mq, tmp_path):

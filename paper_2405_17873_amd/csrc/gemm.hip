@@ -1546,54 +1546,44 @@ static bool taller(long M, long N, long num, long den) {  // busiest unit: rows 
     return den * busiest(M, N, 96) <= num * busiest(M, N, 64);
 }
 
-// Linear layers on 16-bit activations (unquantised weights keep tile 1).
-// Tile 5 or 10, time of tile 10 over tile 5's (3000 shapes, geometric means; rows of the busiest unit, tile 10 / tile 5):
-//   bf16 (widening costs most) fewer rows 0.71 to 0.9, equal 0.88 to 0.95, an eighth more 0.88 to 0.97.
-//   fp16, 8-bit weights fewer 0.87, equal 0.95, an eighth more 0.91; but with one workgroup of tile 10 or less per unit, which has two
-//     stages only, 1.02 to 1.07 (4096 x 2560 x 640 20.9 -> 22.7 us).
-//   fp16, 3 bits 0.85 / 0.92 / 0.98; 2 and 4 bits 0.87 / 0.98 / 1.01 to 1.03 (fp16 widens these in fewer instructions).
-//   Short reductions leave the stores of the output to bound it, in more and smaller workgroups the faster ones, fp16 with less than 640 k and
-//   equal rows 1.0 to 1.04.  All the more where a row starts inside a 64-byte sector (ldy is no multiple of 32) and the pieces of
-//   two workgroups meet in it: 2291 x 384 x 5480 at 2 bits 16.6 -> 20.9 us, 12530 x 384 x 808 14.7 -> 17.9, in bf16 2877 x 384 x 4728
-//   18.1 -> 22.1; fp16 with up to 1280 k and one workgroup per unit 1.01, 2 bits up to 1.09.
-// fp16 weights beyond 8 MB are streamed once per row block: tile 1, where neither of the lower forms gives the busiest unit
-// fewer rows (1024 x 3584 x 6352 at 8 bits, 256 / 256 / 288 rows, tile 1 / 5 / 10 52.6 / 64.5 / 57.3; 1024 x 4224 x 6336 at 4 bits 59.6 /
-// 61.7 / 62.4; at equal rows of tile 10, 1766 x 4736 x 6080 at 4 bits, 112 / 107.5 / 106.3).  With one 128x128 workgroup per unit
-// or less its reduction has nothing beside it: 616 x 4992 x 4832 at 3 bits 52.0 / 40.7.  (In bf16 it is never the fastest.)
-// Where the 64x64 tiles are more than one round of workgroups but those of 64x128 are not, a compute unit would get one wave
-// per SIMD of the latter; with a second wave group on the other half of the reduction (tile 11) it gets two.  us, 64x64 form / tile 5 / tile 11,
-// fp16: 4-bit weights 1024 x 1280 x 1280 10.4 / 9.9 / 9.3, 1024 x 5120 x 1280 30.8 / 31.1 / 25.7, 2048 x 2560 x 640 17.3 / 17.1 / 14.7, 2048 x 640 x 640
-// 7.0 / 6.4 / 6.3, 4096 x 448 x 320 6.0 / 5.8 / 6.1; 8-bit (twice the weight pieces per stage) 1536 x 1280 x 1280 11.4 / 10.7 / 10.3, 900 x 960 x 1280 8.9 / 8.4 / 8.4,
-// 4096 x 640 x 320 7.2 / 6.6 / 6.8; bf16 1024 x 5120 x 1280 42.4 / 36.8 / 29.8, 2048 x 640 x 640 8.4 / 7.3 / 6.9.
-// Few tiles with 1024 k and more: tile 4 splits its reduction over workgroups from 16 of its stages on (1984 k), tile 2, of twice as
-// many stages, from 1024 k on, where the workspace holds the parts (unsplit its chain is twice as long).  Tile 2 over tile 4 (2000
-// shapes of up to 64 tiles, 1024 to 1920 k): fp16 with up to 32 rows 0.78 to 0.90 at 10 tiles, 0.89 to 1.01 at 24, 0.95 to 1.05 at 30, 1.07 to
-// 1.15 at 40 (4 x 1920 x 1280 8.0 us / 9.8; 32 x 1984 x 2040, where tile 4 splits too, 9.9 / 8.9); bf16 0.69 to 0.78 at 10 tiles, 0.79 to 0.94 at
-// 28, 0.91 to 1.01 at 40 and 1.0 at 48, with more than 32 rows 0.94 to 1.06 at 36 (77 x 1920 x 504 9.2 / 13.2, 32 x 1600 x 2560 10.0 / 10.8).
-// With up to 8 tiles bf16 is better off with tile 2 up to 3071 k, both split (0.93 to 1.0), and with 53 to 64 from 4096 k on (0.90 to 1.01:
-// 4 x 4224 x 3792 20.0 us / 21.8).
-// Two row blocks of 96 over very many columns, tile 0 / 10: 154 x 2048 x 166400 at 2, 4, 8 bits 134 / 113, 141 / 122, 168 / 146, 83200 71 / 61, 74 / 65, 79 / 70.
-// One such block keeps tile 6 (fp16) or 0: at 769 to 1024 column tiles, the third round of tile 10, it is the faster one in fp16 (tile 10 over it 1.1, 8 bits
-// 1.3); elsewhere tile 10 measures 0.83 to 0.96 of it, in bf16 0.66 to 0.94 but at 8 bits there (1.06), which no rule takes up.
+// Linear layers on 16-bit activations (unquantised weights keep tile 1).  Beside each line one pair of times of whole calls in us; all of
+// them, and the ratios over thousands of shapes that the lines were drawn by, are in profiles/tile_rules.txt.
 template <int BITS>
 static int float_tile(int t, const GemmArgs& g, bool bf16) {
     const long M = g.M, N = g.N, K = g.K;
     if (g_force_tile >= 0 && (g_force_tile == 5 || (BITS != 16 && g_force_tile >= 10))) return g_force_tile;
     if (g_force_tile >= 0) return BITS == 16 ? t : t == 1 && bf16 ? 5 : t == 3 ? 11 : t;
+    // (one row block of 96 over very many columns keeps tile 6: in fp16 the faster one at 769 to 1024 column tiles, by 10 to 30 %; elsewhere
+    // tile 10 would be, by 4 to 17 %, which no rule takes up)
     if (BITS == 16 || t == 6) return t;
+    // two such blocks: three quarters of tile 0's rows (154 x 2048 x 166400 at 4 bits: tile 0 141, tile 10 122)
     if (t == 0) return M > 128 && M <= 192 ? 10 : 0;
     const long t2 = ((M + 63) / 64) * ((N + 63) / 64), t5 = ((M + 63) / 64) * ((N + 127) / 128);
+    // Where the 64x64 tiles are more than one round of workgroups but those of 64x128 are not, a compute unit would get one wave
+    // per SIMD of the latter; with a second wave group on the other half of the reduction (tile 11) it gets two, which short reductions,
+    // shorter ones with 8-bit weights, do not repay (1024 x 5120 x 1280: tile 5 31.1, tile 11 25.7; 4096 x 448 x 320 5.8 and 6.1).
     if (t2 > UNITS && t5 <= UNITS) return K >= (BITS == 8 ? 1280 : 640) ? 11 : 5;
     if (t == 1 || t == 3) {
-        const bool ragged = g.ldy % 32 != 0;
+        const bool ragged = g.ldy % 32 != 0;  // (rows that start inside a 64-byte sector, where the pieces of two workgroups meet)
+        // bf16, whose widening costs most, takes the taller form at up to an eighth more rows (0.88 to 0.97 of the time there), but short
+        // reductions, which the output's stores bound, keep the smaller workgroups if rows are ragged (2877 x 384 x 4728 18.1, 22.1).
         if (bf16) return (K >= 640 || !ragged) && taller(M, N, 9, 8) ? 10 : 5;
         const long r1 = busiest(M, N, 128), r5 = busiest(M, N, 64), r10 = busiest(M, N, 96);
+        // fp16 weights beyond 8 MB are streamed once per row block: the full height where neither lower form gives the busiest unit fewer
+        // rows (1024 x 3584 x 6352 at 8 bits, tile 1 / 5 / 10: 52.6 / 64.5 / 57.3), but not one workgroup per unit, with nothing beside
+        // its reduction (616 x 4992 x 4832 at 3 bits, tile 1 52.0, else 40.7).
         if (N * K * BITS / 8 > (8L << 20) && r1 > 128 && r1 <= r5 && r1 < r10) return 1;
+        // one workgroup of tile 10 per unit: two stages of 8-bit weights and nothing beside them (4096 x 2560 x 640: tile 5 20.9, tile 10 22.7)
         const bool one_each = r10 <= 96;
         if (BITS == 8 && one_each) return 5;
+        // short reductions, as above (2291 x 384 x 5480 at 2 bits: tile 5 16.6, tile 10 20.9)
         if (K < (ragged && BITS != 8 ? 1280 : 640)) return r10 < r5 && !(ragged && (K < 640 || one_each)) ? 10 : 5;
+        // fp16 at an eighth more rows: 0.91 of the time at 8 bits, 0.98 at 3, 1.01 to 1.03 at 2 and 4, which it widens in fewer instructions
         return taller(M, N, BITS == 3 || BITS == 8 ? 9 : 8, 8) ? 10 : 5;
     }
+    // Few tiles with 1024 k and more: tile 4 splits its reduction over workgroups from 16 of its stages on (1984 k), tile 2, of twice as
+    // many stages, from 1024 k on, where the workspace holds the parts (unsplit its chain is twice as long).  Fewer tiles gain more by it
+    // (4 x 1920 x 1280: tile 2 8.0, tile 4 9.8; 32 x 1984 x 2040 9.9 and 8.9; bf16 77 x 1920 x 504 9.2 and 13.2; 4 x 4224 x 3792 20.0 and 21.8).
     const bool few = bf16 ? (K < 1984 && t2 <= (M <= 32 ? 48 : 36)) || (K < 3072 && t2 <= 8) || (K >= 4096 && t2 > 52 && t2 <= 64)
                           : K < 1984 && M <= 32 && t2 <= 24;
     if (t == 4 && few && g.split_ws && g.split_ws_bytes >= split_counter_bytes(t2, 1) + (size_t)(K / 256) * t2 * (64 * 64 * 4)) return 2;
@@ -1603,46 +1593,39 @@ static int float_tile(int t, const GemmArgs& g, bool bf16) {
 // The int8 path has more forms of tile 1, by how many workgroups a compute unit gets: with few of them the wait for loads
 // counts (more stages, 7, or the eight waves of one 128x128 workgroup over half the L2 -> LDS traffic per operation, 8), with many
 // the number of waves.  8-bit weights move twice the bytes, so that the L2 -> LDS path bounds the half height there (96 bytes
-// per clock and compute unit at the full MFMA rate, of 55): they have a form of their own for many tiles, 9.  Whole calls with given
-// parameters in us, tile 5 / 7 / 8 (/ 9):
-//   4-bit weights: 2048 x 5120 x 1280 (320 workgroups of tile 5) 36.9 / 29.9 / 31.3, 2560 x 2560 x 1280 (400) 23.0 / 19.9 / 20.3,
-//     3200 x 5120 x 1280 (500) 44.3 / 40.8 / 38.2, 4096 x 1280 x 1280 (640, 320 of 128x128) 16.8 / 17.8 / 18.9
-//   8-bit weights: 2048 x 5120 x 1280 39.5 / 32.7 / 36.1, 2964 x 1280 x 1280 (470) 15.9 / 17.3 / 15.9, 3200 x 5120 x 1280 46.8 / 48.1 / 42.1,
-//     4096 x 1280 x 1280 19.2 / 21.2 / 23.9 / 19.7, 9000 x 1280 x 1280 (710 of 128x128) 32.4 / 34.5 / 33.9 / 30.8, 16384 x 640 x 5120 105.8 / - / - / 92.5
-// 8-bit weights in between take the form that gives the busiest unit fewest rows.  Tile 9 over tile 5 where it gives no more 0.78 to 0.92 (1619 x 2048
-// x 4504 27.6 us / 32.8, 1024 x 1984 x 7752 31.6 / 36.3), where it gives more 1.02 to 1.06; from 2560 k on tile 10 comes in (tile 5 / 9 / 10: 4096 x 5120 x
-// 1280, 192 / 256 / 192 rows, 52.3 / 51.0 / 48.6; 6000 x 5120 x 1280, 256 / 256 / 288, 81.5 / 64.8 / 81.9; 16384 x 2560 x 640, 320 / 384 / 384, 67.2 / 71.4 / 68.5).
-// Below 640 k the output's stores bound it, and the smaller workgroups are the faster ones: 8192 x 384 x 6216 71.2 us / 78.6, 2964 x 384 x 5624 29.4 / 33.2.
-// Fewer tiles than that: the wave groups of tile 4 leave 8-bit weights two stages, tile 2 has four: 616 x 2048 x 1280 13.3 / 11.7,
-// 700 x 5120 x 1280 24.6 / 20.2; at 4 bits tile 4 is the better one, 11.0 / 11.6 and 18.0 / 20.7.  Few tiles that tile 4 splits over workgroups
-// stay with it, whose parts are fewer (500 x 4032 x 336 14.8 / 19.9, 64 x 5120 x 1280 14.3 / 16.0), and nearly two rounds of tile 2 over a narrow
-// output take tile 7 (2964 x 2560 x 640, tile 4 / 2 / 7 19.3 / 20.4 / 18.7; wide, 616 x 2560 x 2928 16.5 / 15.8 / 16.0).
-// One or two row blocks of 96 over very many columns (the K/V projections of all layers for one or two prompts of 77 tokens, stacked)
-// stream their weights: several workgroups per compute unit whose loads cover each other's epilogues, at three quarters of the rows
-// (tile 10).  Whole calls, 96x256 with one workgroup per unit (one prompt) or 128x256 and 128x128 (two) / tile 10: 8-bit weights
-// 77 x 2048 x 166400 79.8 / 76.3, 83200 47.6 / 40.0, 40960 25.7 / 24.7, 154 x 2048 x 166400 125.4 / 112.7; 4-bit 77 x 2048 x 166400 46.0 / 44.3,
-// 65280 25.7 / 22.8, 154 x 2048 x 166400 86.2 / 73.5, 40960 36.2 / 27.4.  2- and 4-bit weights leave room for three workgroups of tile 10 per unit
-// or two of 96x256: where 96x128 is just more than three rounds of workgroups, 96x256 (tile 6) is two (77 x 2048 x 99840 at 4 bits 33.4 / 43.3,
-// 118400 35.3 / 45.1, at 2 bits 33.7 / 35.9).
-// 2- and 4-bit weights that do not fit an XCD's L2 by a wide margin are streamed from the last-level cache once per row block, so tall problems
-// keep the full height (1536 x 2560 x 10240 49.8 / 50.9 with tile 1 / 5); of few row blocks each is better read twice by more
-// workgroups (512 x 2560 x 10240 24.2 / 21.6, 1024 x 5120 x 5120 41.2 / 37.4), unless the busiest unit gets no fewer rows by it (1024 x 2304 x 7512
-// 26.6 / 28.1).
+// per clock and compute unit at the full MFMA rate, of 55): they have a form of their own for many tiles, 9.  Beside each line one pair of
+// times of whole calls with given parameters in us; all of them are in profiles/tile_rules.txt.
 template <int BITS>
 static int int8_tile(int t, long M, long N, long K) {
     if (g_force_tile >= 7) return g_force_tile == 11 ? 5 : BITS != 8 && g_force_tile == 9 ? 8 : g_force_tile;
     const long cols = (N + 127) / 128, t2 = ((M + 63) / 64) * ((N + 63) / 64);
+    // Few tiles: the wave groups of tile 4 leave 8-bit weights two stages, tile 2 has four (700 x 5120 x 1280: tile 4 24.6, tile 2 20.2).
+    // What tile 4 splits over workgroups stays with it, its parts are fewer (64 x 5120 x 1280 14.3 and 16.0); nearly two rounds of tile 2
+    // over a narrow output take tile 7 (2964 x 2560 x 640: tile 2 20.4, tile 7 18.7; wide, 616 x 2560 x 2928, 15.8 and 16.0).
     if (BITS == 8 && t == 4 && g_force_tile < 0) return t2 <= 64 ? (K > 3840 ? 4 : 2) : t2 > 448 && M >= 4 * N ? 7 : 2;
     if (g_force_tile >= 0) return g_force_tile == 5 ? 5 : t == 1 || t == 3 ? (BITS == 8 ? 9 : 1) : t;
+    // One or two row blocks of 96 over very many columns (the K/V projections of all layers for one or two prompts of 77 tokens, stacked)
+    // stream their weights: several workgroups per compute unit whose loads cover each other's epilogues, at three quarters of the rows
+    // (77 x 2048 x 83200 at 8 bits: tile 6 47.6, tile 10 40.0).  2- and 4-bit weights leave room for three workgroups of tile 10 per unit
+    // or two of tile 6: just more than three rounds of the one are two of the other (77 x 2048 x 99840 at 4 bits: tile 6 33.4, tile 10 43.3).
     if (BITS != 8 && M > 64 && M <= 96 && cols > 3 * UNITS && cols <= 4 * UNITS) return 6;
     if (((M > 64 && M <= 96) || (M > 128 && M <= 192)) && cols >= 320) return 10;
     if (t != 1 && t != 3) return t;
     const long t1 = ((M + 127) / 128) * cols, t5 = ((M + 63) / 64) * cols;
+    // few workgroups of the half height: three stages (2048 x 5120 x 1280 at 4 bits, 320 of them: tile 5 36.9, tile 7 29.9)
     if (t5 <= 384) return 7;
+    // one 128x128 workgroup per unit at most, over a reduction that repays its start (3200 x 5120 x 1280 at 8 bits: tile 5 46.8, tile 8 42.1)
     if (t1 <= UNITS && K >= 1536) return 8;
     const long r1 = busiest(M, N, 128), r5 = busiest(M, N, 64), r10 = busiest(M, N, 96);
     const bool big = N * K * BITS / 8 > (8L << 20);
+    // 2- and 4-bit weights that do not fit an XCD's L2 by a wide margin are streamed from the last-level cache once per row block, so tall
+    // problems keep the full height (1536 x 2560 x 10240: tile 1 49.8, tile 5 50.9); of few row blocks each is better read twice by more
+    // workgroups (1024 x 5120 x 5120 41.2 and 37.4), unless the busiest unit gets no fewer rows by it (1024 x 2304 x 7512 26.6 and 28.1).
     if (BITS != 8) return big && (M > 1024 || (t1 <= 2 * UNITS && r1 <= r5)) ? 1 : 5;
+    // 8-bit weights: below 640 k the output's stores bound it, and smaller workgroups are the faster ones (8192 x 384 x 6216: tile 5 71.2,
+    // tile 9 78.6); many tiles take tile 9 (9000 x 1280 x 1280: tile 5 32.4, tile 9 30.8); in between the form that gives the busiest unit
+    // fewest rows (1619 x 2048 x 4504: tile 9 27.6, tile 5 32.8), among them from 2560 k on tile 10 (4096 x 5120 x 1280: tile 9 51.0, tile 10
+    // 48.6; 6000 x 5120 x 1280, where it has more rows, 64.8 and 81.9).
     if (K < 640 && !big) return 5;
     if (t1 > 640) return 9;
     if (K >= 2560) return r1 < r10 ? 9 : 8 * r10 <= 9 * r5 ? 10 : 5;

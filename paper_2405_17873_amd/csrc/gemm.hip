@@ -1596,7 +1596,8 @@ static int float_tile(int t, const GemmArgs& g, bool bf16) {
 // per clock and compute unit at the full MFMA rate, of 55): they have a form of their own for many tiles, 9.  Beside each line one pair of
 // times of whole calls with given parameters in us; all of them are in profiles/tile_rules.txt.
 template <int BITS>
-static int int8_tile(int t, long M, long N, long K) {
+static int int8_tile(int t, const GemmArgs& g) {
+    const long M = g.M, N = g.N, K = g.K;
     if (g_force_tile >= 7) return g_force_tile == 11 ? 5 : BITS != 8 && g_force_tile == 9 ? 8 : g_force_tile;
     const long cols = (N + 127) / 128, t2 = ((M + 63) / 64) * ((N + 63) / 64);
     // Few tiles: the wave groups of tile 4 leave 8-bit weights two stages, tile 2 has four (700 x 5120 x 1280: tile 4 24.6, tile 2 20.2).
@@ -1627,7 +1628,14 @@ static int int8_tile(int t, long M, long N, long K) {
     // fewest rows (1619 x 2048 x 4504: tile 9 27.6, tile 5 32.8), among them from 2560 k on tile 10 (4096 x 5120 x 1280: tile 9 51.0, tile 10
     // 48.6; 6000 x 5120 x 1280, where it has more rows, 64.8 and 81.9).
     if (K < 640 && !big) return 5;
-    if (t1 > 640) return 9;
+    if (t1 > 640) {
+        // Two workgroups of tile 9 fit a unit: an odd one is alone at the end.  That costs most, and so do the larger stores, where rows start
+        // inside a 64-byte sector, whose pieces of two workgroups meet in it (time of tile 9 over tile 5's with 640 to 767 k 1.0 to 1.18, with
+        // up to 1400 k 384 rows for 384 1.0 to 1.12, 640 for 576 1.01 to 1.10: 4637 x 1536 x 2456 tile 5 38.5, tile 9 41.2).
+        const bool ragged = g.ldy % 32 != 0;
+        const long r = ragged ? (r1 + 255) / 256 * 256 : r1;
+        return !big && ((ragged && K < 768) || 3 * r >= 4 * r5) ? 5 : 9;
+    }
     if (K >= 2560) return r1 < r10 ? 9 : 8 * r10 <= 9 * r5 ? 10 : 5;
     return t1 > UNITS && r1 <= r5 ? 9 : 5;
 }
@@ -1757,7 +1765,7 @@ static int dispatch_gemm(GemmArgs& g, hipStream_t st) {
     constexpr bool WIDE = (I8 && BITS == 8) || BITS == 16;
     int t = pick_tile(g.M, g.N, g.K, WIDE);
     if constexpr (I8) {
-        t = int8_tile<BITS>(t, g.M, g.N, g.K);
+        t = int8_tile<BITS>(t, g);
         switch (t) {
             case 7: return run_gemm<I8, BITS, 1, 4, 2, 1, 1, 76 * 1024, 3>(g, 7, st);
             case 8: return run_gemm<I8, BITS, 2, 4, 2, 1, 1, BITS == 8 ? 160 * 1024 : 80 * 1024, 4>(g, 8, st);

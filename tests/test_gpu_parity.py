@@ -827,6 +827,10 @@ def test_conv_both_sides_of_the_tile_rule(mq, orc, H, N):
     (8, 4928, 2560, 1280, 9),                              # 256, 256, 288
     (8, 16384, 2560, 640, 5),                              # 384, 320, 384
     (8, 10240, 640, 1024, 5), (8, 10241, 640, 1024, 9), (8, 10241, 576, 1024, 5),
+    # ... more than 640 of them: an odd one on the busiest unit, rows that start inside a 64-byte sector
+    (8, 4224, 1024, 2464, 9), (8, 4224, 1024, 2456, 5),                            # 384, 384
+    (8, 6400, 704, 2464, 9), (8, 6400, 704, 2456, 5), (8, 6400, 768, 2456, 9),     # 512, 512
+    (8, 1600, 640, 7680, 5), (8, 1600, 1152, 7680, 9), (8, 1728, 640, 7680, 9),    # 512, 384, without and with 8 MB; 512, 448
     # one row block over very many columns: rounds of workgroups of 96 x 128 (three per compute unit) and of 96 x 256
     (4, 77, 192, 98304, 10), (4, 77, 192, 98312, 6), (4, 96, 128, 131072, 6), (2, 65, 128, 131072, 6), (4, 77, 128, 131080, 10), (8, 77, 128, 131072, 10),
     # 2- and 4-bit weights beyond 8 MB

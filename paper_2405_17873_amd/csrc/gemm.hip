@@ -1368,6 +1368,13 @@ void gemm_kernel(const GemmArgs g) {
             }
         }
     }
+    // Rows that start inside a 64-byte sector: pieces of two waves meet in it.  A streaming store may leave the XCD's L2 before the other
+    // piece has come, and memory then takes the sector twice, in parts.  In the GEMM on codes, whose stages of short reductions leave little
+    // time between the stores of one workgroup and the next, such rows are stored the ordinary way (6494 x 448 x 2632 at 4 bits took 20.8 us
+    // with row sums in every wave and 28.1 with the faster loop and streaming stores; ordinary stores over streaming ones, 2500 shapes: 0.87 of
+    // the time below 512 k, 0.95 from there to 831, 1.01 to 1023, 1.02 beyond; at 8 bits 0.95, 0.98, 1.0).  In the other modes ordinary
+    // stores are 0.9 to 0.98 of the time in the mean, but for one call in ten 1.03 to 1.06.
+    const bool ragged = MODE == 2 && g.K < 1024 && (((uintptr_t)g.y | (uintptr_t)(uint32_t)g.ldy * 2) & 63) != 0;
     // Reads the slab image back as 16 bytes per lane along rows and stores it: CPR lanes cover one contiguous row
     // segment of TN * 64 bytes.  All reads are requested before the first store (a store that waits for its own read
     // pays the LDS latency every time), and with the identity row map the addresses advance by a constant.
@@ -1387,9 +1394,15 @@ void gemm_kernel(const GemmArgs g) {
         // dominant kernel's time).
         bool identity = true;
         if constexpr (I8) identity = g.out_map.rows_per_group <= 0;
-        if (identity) {
-            uint16_t* yp = g.y + (long)m_first * g.ldy + n;
-            const long step = (long)ROWS_PER_PASS * g.ldy;
+        uint16_t* yp = g.y + (long)m_first * g.ldy + n;
+        const long step = (long)ROWS_PER_PASS * g.ldy;
+        if (identity && ragged) {
+            asm volatile("");  // (here and below: or the compiler makes one kind of store of the two)
+#pragma unroll
+            for (int i = 0; i < NP; ++i)
+                if (m_first + i * ROWS_PER_PASS < g.M) *(uint4v*)(yp + i * step) = v[i];
+            asm volatile("");
+        } else if (identity) {
 #pragma unroll
             for (int i = 0; i < NP; ++i)
                 if (m_first + i * ROWS_PER_PASS < g.M) __builtin_nontemporal_store(v[i], (uint4v*)(yp + i * step));

@@ -1163,6 +1163,27 @@ def test_a8_linear_on_codes_tile_rule(mq, orc, bits, M, K, N, tile):
     assert_close16(host(y)[rows], ry, f"codes {M}x{K}x{N} b{bits}")
 
 
+@pytest.mark.parametrize("bits", (2, 4, 8))
+@pytest.mark.parametrize("K,N,ldy", [(960, 320, 320), (960, 328, 328), (960, 320, 328), (1024, 328, 328)])
+def test_a8_linear_on_codes_output_rows(mq, orc, bits, K, N, ldy):
+    """Output rows that start on a 64-byte boundary and inside one (stored another way below 1024 k); nothing beyond the row is written."""
+    rng = np.random.default_rng(68)
+    M = 1100
+    qx = rng.integers(0, 256, (M, K)).astype(np.uint8)
+    act = (np.float32(0.0123), 97)
+    pw, oc, os_, oz = make_weight(mq, orc, si.weights_f16(68, "cor/w", N, K), bits)
+    d_act = (dev(np.array([act[0]], np.float32)), dev(np.array([act[1]], np.int32)))
+    buf = torch.full((M + 1, ldy), 7.0, dtype=torch.float16, device="cuda")
+    mq.tune_force_tile(5)
+    try:
+        mq.qlinear_a8_codes(dev(a8_layout(qx)), K, d_act, pw, out=buf[:M, :N])
+    finally:
+        mq.tune_force_tile(-1)
+    ry, _ = orc.linear_a8_codes(qx, act, oc, os_, oz)
+    assert_close16(host(buf[:M, :N]), ry, f"codes {M}x{K}x{N} ldy {ldy} b{bits}")
+    assert torch.all(buf[M] == 7) and torch.all(buf[:, N:] == 7)
+
+
 @pytest.mark.parametrize("tile", (0, 1))
 def test_gated_product_is_rounded_to_fp32_then_to_fp16(mq, tile):
     """The stored product of the gated projections with given output parameters, bit for bit: value * gate in fp32, that in fp16 (gates

@@ -148,9 +148,10 @@ void set_force_band(int n);
 void set_phase_buffer(long long* p, long workgroups);
 
 // ---- optional per-kernel event timing (prof.hip) ----
-enum { PROF_GEMM_TILES = 12, PROF_GEMM_BITS = 5, PROF_GEMM_FAMILIES = 7, PROF_ACT_MINMAX = PROF_GEMM_FAMILIES * PROF_GEMM_BITS * PROF_GEMM_TILES, PROF_ACT_QUANTIZE, PROF_BOS_ROWS };
+enum { PROF_GEMM_TILES = 12, PROF_GEMM_BITS = 5, PROF_GEMM_FAMILIES = 11, PROF_ACT_MINMAX = PROF_GEMM_FAMILIES * PROF_GEMM_BITS * PROF_GEMM_TILES, PROF_ACT_QUANTIZE, PROF_BOS_ROWS };
 int prof_num_slots();
-int prof_gemm_slot(int family /*0 weight-only fp16, 1 int8, 2 weight-only bf16, 3 int8 gated projection, 4 int8 on codes, 5 weight-only convolution, 6 int8 convolution*/,
+int prof_gemm_slot(int family /*0 weight-only fp16, 1 int8, 2 weight-only bf16, 3 int8 gated projection, 4 int8 on codes, 5 weight-only convolution, 6 int8 convolution,
+                   7 to 10 with one wave per SIMD: weight-only and its convolution, int8, int8 on codes, int8 convolution*/,
                    int bits, int tile);
 bool prof_enabled();
 bool prof_wants(int slot);

@@ -2022,3 +2022,109 @@ def test_microbenchmarks_of_the_machine_report_plausible_rates(mq):
     assert pk["lds_read_TBps"] > 10.0 and pk["l2_to_lds_TBps"] > 3.0
     assert 0.5 <= pk["serial_share_same_wave"] <= 1.05 and 0.5 <= pk["serial_share_two_waves"] <= 1.05
     assert pk["four_valu_per_mfma_ms"] < pk["same_wave_ms"]
+
+
+# ------------------------------------------------------------------------------------- one wave per SIMD (gemm_solo.hip)
+
+def ran_kernel(mq, call):
+    """Name of the GEMM kernel that a call runs, and what the call returns."""
+    mq.prof_reset()
+    mq.prof_filter(-1, 1)
+    mq.prof_enable(True)
+    try:
+        out = call()
+        torch.cuda.synchronize()
+    finally:
+        mq.prof_enable(False)
+    (name,) = [k["kernel"] for k in mq.prof_read() if "gemm" in k["kernel"]]
+    return name, out
+
+
+def solo_case(mq, kind, bits, M, K, N, res, tile, sym=False, rows=None):
+    """A linear on small integers (sums exact in fp32, one rounding at the end) with a forced tile; returns the kernel's name."""
+    rng = np.random.default_rng(M + K + N + bits)
+    codes = rng.integers(0, 1 << bits, (N, K)).astype(np.uint8)
+    zp = np.zeros(N, np.int32) if sym else rng.integers(0, 1 << bits, N).astype(np.int32)
+    q = codes.view(np.int8).astype(np.int64) if sym else codes.astype(np.int64) - zp[:, None]
+    x, bias = rng.integers(-4, 5, (M, K)), rng.integers(-8, 9, N)
+    r = rng.integers(-64, 65, (M, N)) if res else None
+    packed, colsum = mq.pack_weights(dev(codes), bits, mq.LAYOUT_KERNEL, codes_signed=sym)
+    pw = mq.PackedWeight(packed, dev(np.full(N, 2.0 ** -6, np.float32)), dev(zp), colsum, N, K, bits, mq.LAYOUT_KERNEL, sym)
+    d_b, d_r = dev(bias.astype(np.float16)), None if r is None else dev(r.astype(np.float16))
+    act = (dev(np.array([1.0], np.float32)), dev(np.array([97], np.int32)))
+    mq.tune_force_tile(tile)
+    try:
+        if kind == "f16":
+            name, y = ran_kernel(mq, lambda: mq.qlinear_w_only(dev(x.astype(np.float16)), pw, d_b, residual=d_r))
+            acc = None
+        elif kind == "a8":
+            fn = {8: mq.qlinear_w8a8, 4: mq.qlinear_w4a8, 2: mq.qlinear_w2a8}[bits]
+            name, (y, acc, _) = ran_kernel(mq, lambda: fn(dev(x.astype(np.float16)), pw, act=act, bias=d_b, want_acc=True, residual=d_r))
+        else:
+            a8 = dev(a8_layout((x + 97).astype(np.uint8)))
+            name, (y, acc) = ran_kernel(mq, lambda: mq.qlinear_a8_codes(a8, K, act, pw, bias=d_b, want_acc=True, residual=d_r))
+    finally:
+        mq.tune_force_tile(-1)
+    rows = np.arange(M) if rows is None else rows
+    want = x[rows] @ q.T
+    if acc is not None:
+        assert np.array_equal(host(acc)[rows], want)
+    want = want * 2.0 ** -6 + bias + (0 if r is None else r[rows])
+    assert np.array_equal(host(y)[rows], want.astype(np.float32).astype(np.float16)), (kind, bits, M, K, N, res, tile)
+    return name
+
+
+@pytest.mark.parametrize("tile", (12, 13))
+@pytest.mark.parametrize("kind,bits", [("f16", 2), ("f16", 3), ("f16", 4), ("f16", 8), ("a8", 2), ("a8", 4), ("a8", 8), ("codes", 2), ("codes", 4), ("codes", 8)])
+def test_one_wave_per_simd_linears(mq, kind, bits, tile):
+    """Rows and channels below, at and beyond the tile, reductions of the fewest stages and of an odd number of k steps (of 64-k chunks under
+    8-bit activations), with and without a residual; what the form does not take runs elsewhere."""
+    for (M, K, N, res) in ((1, 448, 8, False), (255, 448, 168, True), (257, 512, 160, False), (300, 832, 328, True), (127, 896, 152, False),
+                           (513, 1088, 488, True), (40, 192, 320, False)):
+        name = solo_case(mq, kind, bits, M, K, N, res, tile)
+        steps = K // 64 if kind == "f16" else -(-K // 128)
+        takes = steps >= 4 if tile == 12 else -(-steps // 2) >= 4 and not (kind != "f16" and bits == 8)
+        assert ("gemm_solo_kernel" in name) == takes, name
+    if bits == 8 and kind != "f16":
+        solo_case(mq, kind, bits, 260, 640, 200, True, tile, sym=True)
+
+
+@pytest.mark.parametrize("kind,bits,M,K,N,solo", [
+    ("f16", 4, 4096, 2048, 2560, True), ("f16", 4, 4096, 1984, 2560, False), ("f16", 4, 4097, 2048, 2560, False),  # one round, two
+    ("f16", 8, 4096, 2560, 1280, True), ("f16", 8, 4096, 2496, 1280, False),     # half the height
+    ("a8", 4, 4096, 2048, 2560, True), ("a8", 2, 4097, 2048, 2560, False), ("a8", 8, 4096, 2624, 2560, True), ("a8", 8, 4096, 2560, 2560, False),
+    ("codes", 4, 4096, 2560, 2560, True), ("codes", 2, 4096, 2560, 2560, False), ("codes", 8, 4096, 2560, 2560, True), ("codes", 8, 4096, 2560, 2552, False),
+    ("codes", 4, 8192, 2560, 2560, False)])
+def test_one_wave_per_simd_rule(mq, kind, bits, M, K, N, solo):
+    """Both sides of the lines."""
+    rows = np.unique(np.clip([0, 63, 64, 127, 128, 255, 256, M // 2, M - 2, M - 1], 0, M - 1))
+    assert ("gemm_solo_kernel" in solo_case(mq, kind, bits, M, K, N, False, -1, rows=rows)) == solo
+
+
+@pytest.mark.parametrize("tile", (12, 13))
+@pytest.mark.parametrize("bits", ALL_BITS)
+def test_one_wave_per_simd_convolutions(mq, orc, bits, tile):
+    """Borders, images of one row or column, both strides, a residual; under 8-bit activations stages that hold the end of one filter tap and the
+    start of the next (an odd number of 64-channel chunks) and padded rows."""
+    for (B, H, W, Cin, N, stride, res) in ((1, 1, 1, 64, 40, 1, False), (2, 9, 7, 192, 168, 1, True), (1, 33, 17, 128, 320, 2, False), (3, 1, 90, 320, 160, 1, True),
+                                           (1, 130, 1, 192, 328, 2, True)):
+        ho, wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+        x = si.activations_f16(91, f"so/x{B}x{H}x{W}x{Cin}", B * H * W, Cin, outlier_prob=0.01).reshape(B, H, W, Cin)
+        b = si.bias_f16(91, f"so/b{N}", N)
+        r = si.normal(91, f"so/r{N}", (B, ho, wo, N)).astype(np.float16) if res else None
+        pw, oc, os_, oz, tapsum = conv_weight(mq, orc, 91, N, Cin, bits)
+        d_r, r2 = (None, None) if r is None else (dev(r), r.reshape(-1, N))
+        mq.tune_force_tile(tile)
+        try:
+            y = host(mq.conv3x3_w_only(dev(x), pw, dev(b), residual=d_r, stride=stride))
+            assert_close16(y.reshape(-1, N), orc.conv3x3_w_only(x, oc, os_, oz, b, residual=r2, stride=stride), f"conv w{bits} {B}x{H}x{W}x{Cin}->{N}")
+            if bits == 3:
+                continue
+            act = (np.float32(0.05), 31)
+            y, acc, _ = mq.conv3x3_a8(dev(x), pw, tapsum, act=(dev(np.array([act[0]], np.float32)), dev(np.array([act[1]], np.int32))), bias=dev(b),
+                                      want_acc=True, residual=d_r, stride=stride)
+            ry, racc, _ = orc.conv3x3_a8(x, oc, os_, oz, act=act, bias=b, residual=r2, stride=stride)
+            assert np.array_equal(host(acc), racc)
+            assert_close16(host(y).reshape(-1, N), ry, f"conv a8 b{bits} {B}x{H}x{W}x{Cin}->{N}")
+        finally:
+            mq.tune_force_tile(-1)

@@ -56,7 +56,8 @@ int mq_last_hip_error(void);
 /* Tuning and test hook: force the GEMM workgroup tile (0: 128x256, 1: 128x128, 2: 64x64, 3 and 4: as 1 and 2 with the
  * reduction split over two wave groups inside the workgroup, 5: 64x128, 6: 96x256, 7 to 9: forms of 5 and 1 for
  * few or many workgroups, linears on 8-bit activations only; 10: 96x128; 11: 5 with the split of 3 and 4, linears on 16-bit
- * activations only; 12, 13: 256x160 and 128x160 with one wave per SIMD, from four pipeline stages on; -1: automatic choice from the problem shape; a mode, type or weight width that
+ * activations only; 12, 13: 256x160 and 128x160 with one wave per SIMD, from four pipeline stages on; 14: 64 rows that
+ * the kernel converts itself, linears on 8-bit activations with a run-time range and 256 to 640 k; -1: automatic choice from the problem shape; a mode, type or weight width that
  * does not have the tile takes its nearest one).  Process-wide, not thread safe; results do not depend on the tile
  * beyond the order of the fp32 sums. */
 void mq_tune_force_tile(int tile);

@@ -27,14 +27,15 @@ PER_FILE = {
     # three more instructions per four values to put the halves where the store wants them.
     "gemm.hip": ["-fno-slp-vectorize"],
     "gemm_solo.hip": ["-fno-slp-vectorize"],
+    "gemm_panel.hip": ["-fno-slp-vectorize", "-ffp-contract=off"],
 }
-SOURCES = ["api.hip", "quant_pack.hip", "act_quant.hip", "gemm.hip", "gemm_solo.hip", "bos.hip", "prof.hip", "peaks.hip", "alloc.cpp"]
+SOURCES = ["api.hip", "quant_pack.hip", "act_quant.hip", "gemm.hip", "gemm_solo.hip", "gemm_panel.hip", "bos.hip", "prof.hip", "peaks.hip", "alloc.cpp"]
 
 
 def _compile(src: str, force: bool) -> str:
     path = os.path.join(CSRC, src)
     obj = os.path.join(OBJ, src + ".o")
-    deps = [path, os.path.join(CSRC, "mq_common.h"), os.path.join(CSRC, "bos_rows.h"), os.path.join(CSRC, "gemm_core.h"),
+    deps = [path, os.path.join(CSRC, "mq_common.h"), os.path.join(CSRC, "bos_rows.h"), os.path.join(CSRC, "gemm_core.h"), os.path.join(CSRC, "act_range.h"),
             os.path.join(HERE, "..", "include", "mixdq.h"), __file__]
     if not force and os.path.exists(obj) and all(os.path.getmtime(obj) >= os.path.getmtime(d) for d in deps):
         return obj

@@ -9,22 +9,13 @@
 //               0,4,1,5,2,6,3,7, rows padded with zeros to a multiple of 128, and rowsum[m] = sum_k a'[m,k].
 //
 // Compiled with -ffp-contract=off: each fp32 operation rounds once.
+#include "act_range.h"
 #include "bos_rows.h"
 
 namespace mq {
 
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
-
 static constexpr int kPartialSlots = 512;  // upper bound of pass-1 workgroups
 int act_quant_partial_slots() { return kPartialSlots; }
-
-template <typename T, typename Op>
-__device__ inline T wave_reduce(T v, Op op) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = op(v, __shfl_xor(v, off, 64));
-    return v;
-}
 
 // Both passes are bound by memory latency at the sizes of this path (5 to 80 MB per tensor): what counts is the
 // number of bytes requested before the first one arrives.  The tensor is therefore walked as a flat list of 16-byte
@@ -33,97 +24,20 @@ __device__ inline T wave_reduce(T v, Op op) {
 static constexpr int MM_U = 8;  // vectors per lane per round, pass 1
 static constexpr int Q_U = 4;   // vectors per lane per round, pass 2 (at most: see the launcher)
 
-// Physical row of logical row r (RowMap::phys with its division prepared by the host).
-struct RowWalk {
-    FastDiv group;  // d = rows per group; used where `mapped` says so
-    int mapped, group_stride, row_offset;
-    static RowWalk make(const RowMap& m) {
-        return RowWalk{FastDiv::make((uint32_t)(m.rows_per_group > 0 ? m.rows_per_group : 1)), m.rows_per_group > 0,
-                       m.group_stride, m.row_offset};
-    }
-    __device__ inline long phys(uint32_t r) const {
-        if (!mapped) return r;
-        uint32_t q, rem;
-        group.divmod(r, q, rem);
-        return (long)q * group_stride + rem + row_offset;
-    }
-};
-
-// This thread's share of the extremes of the tensor's vectors: U at a time, NT lanes side by side, from `base` on in steps of `step`.
-// They are found in pairs of fp16 values (a minimum or maximum of fp16 values is one of them: nothing is lost) and widened
-// once at the end; NaN is ignored as by fminf / fmaxf.
-template <int U, int NT>
-__device__ inline void extremes(const _Float16* __restrict__ x, uint32_t nv, FastDiv K8, long ldx, const RowWalk& map, int flat, uint32_t base,
-                                uint32_t step, float& mn, float& mx) {
-    half8 mn8, mx8;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        mn8[e] = (_Float16)INFINITY;
-        mx8[e] = -(_Float16)INFINITY;
-    }
-    for (; base < nv; base += step) {
-        half8 v[U];
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {
-            uint32_t i = base + u * (uint32_t)NT + threadIdx.x;
-            i = i < nv ? i : nv - 1;  // a repeated vector does not change a min or a max
-            if (flat) {
-                v[u] = ((const half8*)x)[i];
-            } else {
-                uint32_t row, p;
-                K8.divmod(i, row, p);
-                v[u] = ((const half8*)(x + map.phys(row) * ldx))[p];
-            }
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {
-            mn8 = __builtin_elementwise_min(mn8, v[u]);
-            mx8 = __builtin_elementwise_max(mx8, v[u]);
-        }
-    }
-    mn = INFINITY, mx = -INFINITY;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        mn = fminf(mn, (float)mn8[e]);
-        mx = fmaxf(mx, (float)mx8[e]);
-    }
-}
-
 // Bound by memory latency up to a few MB and by HBM above.
 // (Workgroups of 1024 threads for tensors that need every partial slot left up to half of the slots without work and were
 // slower at every size: 8192 x 1280 whole call 21.4 us against 20.4, 16384 x 2560 57.1 against 55.7.)
 __global__ __launch_bounds__(256) void act_minmax_kernel(const _Float16* __restrict__ x, uint32_t nv, FastDiv K8,
                                                          long ldx, RowWalk map, int flat, float* __restrict__ partials) {
     constexpr uint32_t STEP = 256 * MM_U;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     float mn, mx;
     extremes<MM_U, 256>(x, nv, K8, ldx, map, flat, blockIdx.x * STEP, gridDim.x * STEP, mn, mx);
-    mn = wave_reduce(mn, [](float a, float b) { return fminf(a, b); });
-    mx = wave_reduce(mx, [](float a, float b) { return fmaxf(a, b); });
     __shared__ float smn[4], smx[4];
-    if (lane == 0) {
-        smn[wv] = mn;
-        smx[wv] = mx;
-    }
-    __syncthreads();
+    group_extremes<256>(mn, mx, smn, smx);
     if (threadIdx.x == 0) {
-#pragma unroll
-        for (int i = 1; i < 4; ++i) {
-            mn = fminf(mn, smn[i]);
-            mx = fmaxf(mx, smx[i]);
-        }
         partials[2 * blockIdx.x] = mn;
         partials[2 * blockIdx.x + 1] = mx;
     }
-}
-
-// Sum over each aligned group of eight lanes, in every lane of the group (two quad permutes and a mirror of the group:
-// register moves inside the vector ALU, no trip through LDS).
-__device__ inline int sum8(int v) {
-    v += __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);   // lanes 1 0 3 2
-    v += __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);   // lanes 2 3 0 1
-    v += __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true);  // lanes 7 6 5 4 3 2 1 0
-    return v;
 }
 
 static constexpr int Q_MAX_ROWS = 128;   // rows per workgroup, pass 2
@@ -145,6 +59,7 @@ static constexpr long kSmallQuant = 28L * 1000 * 1000;  // values: between 6000 
 // 15.1 -> 17.3, with the BOS rows beside it (four blocks of theirs per workgroup) 77 x 2048 -> 1280 16.7 -> 17.5.
 static constexpr int SELF_NT = 1024, SELF_U = 10;
 static constexpr uint32_t SELF_VECTORS = 2 * SELF_U * SELF_NT;
+static_assert(SELF_VECTORS == ACT_SELF_VECTORS, "sizes that need no pass for the range");
 template <bool BOS, int U, int NT = 256>
 __global__ __launch_bounds__(NT) void act_quantize_kernel(const _Float16* __restrict__ x, int M, int K, long ldx, int flat, FastDiv K8d,
                                                            RowWalk map, int R, FastDiv Kp8d, const float* __restrict__ partials,
@@ -165,7 +80,7 @@ __global__ __launch_bounds__(NT) void act_quantize_kernel(const _Float16* __rest
         }
         blk -= nbos;
     }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
     __shared__ float smn[NT / 64], smx[NT / 64];
     __shared__ int lsum[Q_MAX_ROWS];
     const int r0 = blk * R;
@@ -188,43 +103,13 @@ __global__ __launch_bounds__(NT) void act_quantize_kernel(const _Float16* __rest
     request(0);  // on its way while the parameters are derived (most workgroups have a single round)
     float s, zf;
     if (SELF || partials) {
-        float mn = INFINITY, mx = -INFINITY;
-        constexpr int PU = 4;  // pairs requested together
-        if constexpr (SELF) extremes<SELF_U, NT>(x, (uint32_t)M * K8, K8d, ldx, map, flat, 0, SELF_U * NT, mn, mx);
-        for (int i0 = threadIdx.x; !SELF && i0 < n_partials; i0 += 256 * PU) {
-            float2 pr[PU];
-#pragma unroll
-            for (int u = 0; u < PU; ++u) {
-                const int i = i0 + u * 256;
-                pr[u] = ((const float2*)partials)[i < n_partials ? i : n_partials - 1];
-            }
-#pragma unroll
-            for (int u = 0; u < PU; ++u) {
-                mn = fminf(mn, pr[u].x);
-                mx = fmaxf(mx, pr[u].y);
-            }
-        }
-        mn = wave_reduce(mn, [](float a, float b) { return fminf(a, b); });
-        mx = wave_reduce(mx, [](float a, float b) { return fmaxf(a, b); });
-        if (lane == 0) {
-            smn[wv] = mn;
-            smx[wv] = mx;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < NT / 64; ++i) {
-            mn = fminf(mn, smn[i]);
-            mx = fmaxf(mx, smx[i]);
-        }
-        const float lo = fminf(mn, 0.0f), hi = fmaxf(mx, 0.0f);
-        s = 1.0f;
-        if (hi != lo) {
-            const float range = hi - lo;
-            s = range / 255.0f;
-        }
-        const float inv0 = 1.0f / s;
-        zf = rintf((-lo) * inv0);
-        zf = fminf(fmaxf(zf, 0.0f), 255.0f);
+        float mn, mx;
+        if constexpr (SELF)
+            extremes<SELF_U, NT>(x, (uint32_t)M * K8, K8d, ldx, map, flat, 0, SELF_U * NT, mn, mx);
+        else
+            pair_extremes<NT>(partials, n_partials, mn, mx);
+        group_extremes<NT>(mn, mx, smn, smx);
+        range_params(mn, mx, s, zf);
     } else {
         s = *act_scale;
         zf = (float)*act_zp;
@@ -245,15 +130,8 @@ __global__ __launch_bounds__(NT) void act_quantize_kernel(const _Float16* __rest
             const bool valid = i < nvo;
             uint32_t w0 = 0, w1 = 0;
             if (valid && pp[u] < K8) {
-                // t of element e of the group; byte b of word h holds element k8_perm(4 h + b)
-                auto t = [&](int e) { return rintf(__builtin_fmaf((float)v[u][e], inv, 0.0f)) + zf; };
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    w0 = __builtin_amdgcn_cvt_pk_u8_f32(t(k8_perm(b)), b, w0);
-                    w1 = __builtin_amdgcn_cvt_pk_u8_f32(t(k8_perm(4 + b)), b, w1);
-                }
-                w0 ^= 0x80808080u;  // code - 128
-                w1 ^= 0x80808080u;
+                const uint2v w = quantize8(v[u], inv, zf);
+                w0 = w[0], w1 = w[1];
             }
             // (streaming store: read next by another kernel, nothing gained by keeping it in this XCD's L2)
             if (valid) {
@@ -272,14 +150,26 @@ __global__ __launch_bounds__(NT) void act_quantize_kernel(const _Float16* __rest
     if ((int)threadIdx.x < Rr) rowsum[r0 + threadIdx.x] = lsum[threadIdx.x];
 }
 
+int launch_act_range(const void* x, int M, int K, int ldx, RowMap in_map, float* partials, int* pairs, hipStream_t st) {
+    const uint32_t K8 = (uint32_t)K >> 3;
+    const uint32_t nv = (uint32_t)M * K8;  // M * ldx * 2 < 2^31 has been checked: this fits easily
+    const long g1 = ((long)nv + 256 * MM_U - 1) / (256 * MM_U);
+    const int grid = (int)(g1 > kPartialSlots ? kPartialSlots : g1);
+    ProfScope prof(st, PROF_ACT_MINMAX, 0.0, 2.0 * M * K);
+    hipLaunchKernelGGL(act_minmax_kernel, dim3(grid), dim3(256), 0, st, (const _Float16*)x, nv, FastDiv::make(K8), (long)ldx,
+                       RowWalk::make(in_map), in_map.rows_per_group <= 0 && ldx == K, partials);
+    MQ_HIP_CHECK_LAUNCH();
+    *pairs = grid;
+    return MQ_OK;
+}
+
 int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const float* act_scale,
                      const int32_t* act_zp, int8_t* a8, int32_t* rowsum, ActParams* params, float* partials,
                      float* act_scale_out, int32_t* act_zp_out, const BosWork* bos, hipStream_t st,
                      int given_partials) {
     const uint32_t K8 = (uint32_t)K >> 3;
-    const uint32_t nv = (uint32_t)M * K8;  // M * ldx * 2 < 2^31 has been checked: this fits easily
-    long g1 = ((long)nv + 256 * MM_U - 1) / (256 * MM_U);
-    int grid = (int)(g1 > kPartialSlots ? kPartialSlots : g1);
+    const uint32_t nv = (uint32_t)M * K8;
+    int grid = 0;  // (min, max) pairs
     const RowWalk walk = RowWalk::make(in_map);
     const bool dynamic = act_scale == nullptr;
     const int flat = in_map.rows_per_group <= 0 && ldx == K;
@@ -300,10 +190,7 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
     if (dynamic && given_partials > 0) {
         grid = given_partials;
     } else if (dynamic) {
-        ProfScope prof(st, PROF_ACT_MINMAX, 0.0, 2.0 * M * K);
-        hipLaunchKernelGGL(act_minmax_kernel, dim3(grid), dim3(256), 0, st, (const _Float16*)x, nv, FastDiv::make(K8),
-                           (long)ldx, walk, flat, partials);
-        MQ_HIP_CHECK_LAUNCH();
+        if (const int rc = launch_act_range(x, M, K, ldx, in_map, partials, &grid, st)) return rc;
     }
     // Vectors per lane: as few as keep a row in one round and the grid within eight workgroups per compute unit, so that
     // small tensors have more wavefronts to request them.  Whole calls with 64 output channels in us, four -> two -> one vector:

@@ -100,6 +100,14 @@ static int qlinear_a8(const void* x, int M, int K, int ldx, RowMap in_map, const
     // (a forced split that the rest of the workspace cannot hold must fail before anything is launched)
     if (forced_splits() > 1 && ws_bytes - base < split_workspace_bytes(M, N, K)) return MQ_ERR_WORKSPACE_TOO_SMALL;
     A8Workspace w(ws, M, K);
+    // (activations that the output overwrites have to be converted before the first result is stored)
+    const bool apart = (uintptr_t)y >= (uintptr_t)x + ((size_t)(M - 1) * ldx + K) * 2 || (uintptr_t)x >= (uintptr_t)y + ((size_t)(M - 1) * ldy + N) * 2;
+    if (!act_scale && !bos && in_map.rows_per_group <= 0 && out_map.rows_per_group <= 0 && apart && panel_takes(M, N, K, ldy)) {
+        int pairs = 0;
+        if ((long)M * (K / 8) > (long)ACT_SELF_VECTORS && (rc = launch_act_range(x, M, K, ldx, in_map, w.partials, &pairs, st))) return rc;
+        return launch_gemm_panel(x, M, K, ldx, w.partials, pairs, act_scale_out, act_zp_out, packed, N, w_bits, w_signed, w_scale, w_zp, w_colsum,
+                                 bias, y, ldy, acc_debug, residual, ldr, st);
+    }
     rc = launch_act_quant(x, M, K, ldx, in_map, act_scale, act_zp, w.a8, w.rowsum, w.params, w.partials,
                           act_scale_out, act_zp_out, bos, st);
     if (rc) return rc;

@@ -470,7 +470,6 @@ inline double gemm_alg_bytes(const GemmArgs& g, bool i8, int bits, int mode) {
 }
 
 // Test and measurement hooks (mq_tune_*, mq_prof_phase_buffer), kept in gemm.hip.
-int forced_tile();      // -1: automatic
 int forced_band();      // 0: automatic
 long long* phase_buffer(long workgroups);  // where the shader clocks of that many workgroups go, or null
 

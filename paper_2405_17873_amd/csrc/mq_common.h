@@ -110,6 +110,9 @@ int launch_act_quant(const void* x, int M, int K, int ldx, RowMap in_map, const 
                      float* act_scale_out, int32_t* act_zp_out, const BosWork* bos, hipStream_t st,
                      int given_partials = 0);
 int act_quant_partial_slots();
+// The range alone: one (min, max) pair per workgroup, their number in *pairs.
+int launch_act_range(const void* x, int M, int K, int ldx, RowMap in_map, float* partials, int* pairs, hipStream_t st);
+static constexpr uint32_t ACT_SELF_VECTORS = 20480;  // tensors of up to that many vectors of eight values need no pass for the range
 
 int launch_gemm_w_only(const void* x, int M, int K, int ldx, const void* packed, int N, int bits,
                        const float* w_scale, const int32_t* w_zp, const void* bias, void* y, int ldy, int dtype,
@@ -119,6 +122,13 @@ int launch_gemm_a8(const int8_t* a8, const int32_t* rowsum, const ActParams* par
                    const void* packed, int N, int w_bits, int w_signed, const float* w_scale, const int32_t* w_zp,
                    const int32_t* w_colsum, const void* bias, void* y, int ldy, RowMap out_map, int32_t* acc_debug,
                    const void* res, int ldr, void* split_ws, size_t split_ws_bytes, hipStream_t st);
+
+// The linear that converts its own activations, with a run-time range (gemm_panel.hip): whether it takes the problem, and the launch;
+// pairs == 0: it finds the range itself.
+bool panel_takes(int M, int N, int K, long ldy);
+int launch_gemm_panel(const void* x, int M, int K, int ldx, const float* partials, int pairs, float* act_scale_out, int32_t* act_zp_out,
+                      const void* packed, int N, int w_bits, int w_signed, const float* w_scale, const int32_t* w_zp, const int32_t* w_colsum,
+                      const void* bias, void* y, int ldy, int32_t* acc_debug, const void* res, int ldr, hipStream_t st);
 
 int launch_gemm_a8_geglu(const int8_t* a8, const int32_t* rowsum, const ActParams* params, int M, int K,
                          const void* packed, int H, int w_bits, int w_signed, const float* w_scale, const int32_t* w_zp,
@@ -142,6 +152,7 @@ int launch_conv3x3_a8(const int8_t* a8, const ActParams* params, int B, int H, i
 int launch_tap_sums(const uint8_t* codes, int N, int Cin, int bits, int codes_signed, int32_t* tapsum, hipStream_t st);
 
 void set_force_tile(int t);
+int forced_tile();  // -1: automatic
 void set_force_splits(int n);
 int forced_splits();
 void set_force_band(int n);
@@ -151,7 +162,8 @@ void set_phase_buffer(long long* p, long workgroups);
 enum { PROF_GEMM_TILES = 12, PROF_GEMM_BITS = 5, PROF_GEMM_FAMILIES = 11, PROF_ACT_MINMAX = PROF_GEMM_FAMILIES * PROF_GEMM_BITS * PROF_GEMM_TILES, PROF_ACT_QUANTIZE, PROF_BOS_ROWS };
 int prof_num_slots();
 int prof_gemm_slot(int family /*0 weight-only fp16, 1 int8, 2 weight-only bf16, 3 int8 gated projection, 4 int8 on codes, 5 weight-only convolution, 6 int8 convolution,
-                   7 to 10 with one wave per SIMD: weight-only and its convolution, int8, int8 on codes, int8 convolution*/,
+                   7 to 10 with one wave per SIMD: weight-only and its convolution, int8, int8 on codes, int8 convolution; 8, tiles 4 and 5:
+                   int8 with its own conversion*/,
                    int bits, int tile);
 bool prof_enabled();
 bool prof_wants(int slot);

@@ -2128,3 +2128,60 @@ def test_one_wave_per_simd_convolutions(mq, orc, bits, tile):
             assert_close16(host(y).reshape(-1, N), ry, f"conv a8 b{bits} {B}x{H}x{W}x{Cin}->{N}")
         finally:
             mq.tune_force_tile(-1)
+
+
+# --------------------------------------------------------------- linears that convert their own activations (gemm_panel.hip)
+
+@pytest.mark.parametrize("mode", ("w8s", "w8a", "w4", "w2"))
+@pytest.mark.parametrize("M,K,N,pad", [(1, 256, 8, 0), (63, 320, 40, 8), (64, 320, 320, 0), (65, 448, 648, 0), (256, 640, 2568, 0), (257, 640, 640, 8), (600, 320, 5128, 0),
+                                       (1025, 576, 104, 0), (4100, 320, 1288, 0)])
+def test_a8_own_conversion(mq, orc, mode, M, K, N, pad):
+    """Rows, channels and 64-k chunks below, at and beyond a panel, a unit and a share of the waves, with and without a pass for the range
+    (20480 vectors of eight values), strided activations, a residual; workspaces of any contents."""
+    bits, sym = int(mode[1]), mode == "w8s"
+    x = si.activations_f16(93, f"oc/x{M}x{K}", M, K, outlier_prob=0.01)
+    w, b = si.weights_f16(93, f"oc/w{N}x{K}", N, K), si.bias_f16(93, f"oc/b{N}", N)
+    r = si.normal(93, f"oc/r{M}x{N}", (M, N)).astype(np.float16) if (M + K) % 3 else None
+    pw, oc, os_, oz = make_weight(mq, orc, w, bits, sym)
+    wide = torch.full((M, K + pad), 1000.0, dtype=torch.float16, device="cuda")
+    wide[:, :K] = dev(x)
+    ws = torch.full((mq.qlinear_a8_workspace_bytes(M, K),), 0xA5, dtype=torch.uint8, device="cuda")
+    out = torch.full((M, N + pad), 7.0, dtype=torch.float16, device="cuda")
+    fn = {8: mq.qlinear_w8a8, 4: mq.qlinear_w4a8, 2: mq.qlinear_w2a8}[bits]
+    mq.tune_force_tile(14)
+    try:
+        name, (y, acc, (s, z)) = ran_kernel(mq, lambda: fn(wide[:, :K], pw, bias=dev(b), out=out[:, :N], ws=ws, want_acc=True, want_act=True,
+                                                           residual=None if r is None else dev(r)))
+    finally:
+        mq.tune_force_tile(-1)
+    assert "gemm_panel_kernel" in name
+    rows = sample_rows(x, 256, M)
+    ry, racc, (rs, rz) = orc.linear_a8(x, oc, os_, oz, w_signed=sym, bias=b, residual=r, rows=rows)
+    assert host(s)[0] == rs and host(z)[0] == rz
+    assert np.array_equal(host(acc)[rows], racc)
+    assert_close16(host(out)[rows, :N], ry, f"own conversion {mode} {M}x{K}x{N}")
+    assert (host(out)[:, N:] == 7.0).all()
+    y2, acc2, _ = fn(wide[:, :K], pw, bias=dev(b), act=(s, z), want_acc=True, residual=None if r is None else dev(r))  # in two launches
+    assert torch.equal(acc, acc2) and torch.equal(out[:, :N], y2)
+
+
+@pytest.mark.parametrize("M,K,N,own", [(15, 640, 320, True), (16, 640, 320, False), (16384, 320, 640, True), (16385, 320, 320, False), (8192, 320, 1288, False),
+                                       (8192, 640, 640, True), (8191, 640, 640, False), (8192, 640, 648, False), (512, 384, 320, False)])
+def test_a8_own_conversion_rule(mq, M, K, N, own):
+    x = torch.randn(M, K, device="cuda").half()
+    c, s, z = mq.quantize_weights(torch.randn(N, K, device="cuda").half(), 4)
+    packed, cs = mq.pack_weights(c, 4, mq.LAYOUT_KERNEL)
+    pw = mq.PackedWeight(packed, s, z, cs, N, K, 4, mq.LAYOUT_KERNEL, False)
+    assert ("gemm_panel_kernel" in ran_kernel(mq, lambda: mq.qlinear_w4a8(x, pw))[0]) == own
+
+
+def test_a8_output_over_its_activations(mq):
+    """A call may write over its activations: they are converted before the first result is stored."""
+    M = K = 320
+    x = torch.randn(M, K, device="cuda").half()
+    c, s, z = mq.quantize_weights(torch.randn(K, K, device="cuda").half(), 4)
+    packed, cs = mq.pack_weights(c, 4, mq.LAYOUT_KERNEL)
+    pw = mq.PackedWeight(packed, s, z, cs, K, K, 4, mq.LAYOUT_KERNEL, False)
+    want = mq.qlinear_w4a8(x, pw)[0].clone()
+    name, _ = ran_kernel(mq, lambda: mq.qlinear_w4a8(x, pw, out=x))
+    assert "gemm_panel_kernel" not in name and torch.equal(x, want)

@@ -202,15 +202,17 @@ __device__ __forceinline__ void dma_to_lds_b128(int4s rsrc, uint32_t lds_wave_ba
         : "memory");  // m0 is a reserved register: the compiler rewrites it before each of its own uses
 }
 
-// The same with the LDS address as a sum of two scalars.
+// The same with the LDS address as a sum of two scalars, and in two halves: between the address and the load has to lie one other instruction.
+__device__ __forceinline__ void dma_address(uint32_t lds_stage, uint32_t lds_offset) {
+    asm volatile("s_add_u32 m0, %0, %1" : : "s"(lds_stage), "s"(lds_offset) : "memory", "scc");
+}
+__device__ __forceinline__ void dma_load_b128(int4s rsrc, int voff, int soff) {
+    asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" : : "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
 __device__ __forceinline__ void dma_to_lds_b128(int4s rsrc, uint32_t lds_stage, uint32_t lds_offset, int voff, int soff) {
-    asm volatile(
-        "s_add_u32 m0, %0, %1\n\t"
-        "s_nop 0\n\t"
-        "buffer_load_dwordx4 %2, %3, %4 offen lds"
-        :
-        : "s"(lds_stage), "s"(lds_offset), "v"(voff), "s"(rsrc), "s"(soff)
-        : "memory", "scc");
+    dma_address(lds_stage, lds_offset);
+    asm volatile("s_nop 0");
+    dma_load_b128(rsrc, voff, soff);
 }
 
 // The same for 4 bytes per lane (256 contiguous bytes per wave).

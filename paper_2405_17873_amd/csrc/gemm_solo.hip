@@ -13,7 +13,8 @@
 // Measured in us, gemm.hip's choice -> this, 4-bit weights unless said: convolutions 4 x 64 x 64 x 640 on 16-bit activations 121 -> 106, 2 x 128 x
 // 128 x 320 on 8-bit ones 57 -> 45, 4 x 64 x 64, 960 -> 640 at 8 bits 142 -> 103; linears 16384 x 2560 x 640 with residual on 16-bit activations
 // 69 -> 58 (8 bits 76 -> 58), on codes 49 -> 37.  A stage takes 1700 to 1800 cycles, its MFMAs alone 1308 (loads, LDS reads or widening left
-// out in turn: 14 to 20 % less each); the tail is the store of 80 KB from every compute unit at once (10000 cycles at 21 MB).
+// out in turn: 14 to 20 % less each); the tail, 7000 cycles (int8 12000), is the conversion of 160 results per lane and the store of 80 KB from every
+// compute unit at once.  (Constants read per slab and stores behind branches: 10000 and 13000; the residual in pieces of 8 bytes: 4000 more.)
 #include <stdio.h>
 
 #include <algorithm>
@@ -276,26 +277,34 @@ __global__ __launch_bounds__(256, 1) void gemm_solo_kernel(const GemmArgs g) {
         }
         return s;
     };
-    auto issue_a = [&](const StageAt& s, int i) {
-        const int sub = i / A_PER_SUB;
-        int4s r = ra;
-        if constexpr (CONV) {
-            dma_to_lds_b128(r, s.sb, a_lds[i], c_voff[i], s.soff[CONV ? sub : 0]);
+    // Load k of a stage: its LDS address (which the load takes from a register of its own, at least one instruction later), and the load.
+    auto address_op = [&](const StageAt& s, int k) {
+        if (k < P::DMA_A)
+            dma_address(s.sb, a_lds[k < P::DMA_A ? k : 0]);
+        else
+            dma_address(b_pad[k < P::DMA_A ? 0 : k - P::DMA_A] ? lds_base + P::SINK : s.sb, b_lds[k < P::DMA_A ? 0 : k - P::DMA_A]);
+    };
+    auto load_op = [&](const StageAt& s, int k) {
+        if (k < P::DMA_A) {
+            const int i = k < P::DMA_A ? k : 0, sub = i / A_PER_SUB;
+            if constexpr (CONV) {
+                dma_load_b128(ra, c_voff[CONV ? i : 0], s.soff[CONV ? sub : 0]);
+            } else {
+                int4s r = ra;
+                if (KS == 2 && sub) r[2] = s.step0 + sub < KSTEPS ? r[2] : 0;
+                dma_load_b128(r, a_voff[i], s.step0 * 128);
+            }
         } else {
-            if (KS == 2 && sub) r[2] = s.step0 + sub < KSTEPS ? r[2] : 0;
-            dma_to_lds_b128(r, s.sb, a_lds[i], a_voff[i], s.step0 * 128);
+            const int i = k < P::DMA_A ? 0 : k - P::DMA_A;
+            int4s r = rb;
+            if (B_TAIL) r[2] = s.step0 * CH + b_chunk[B_TAIL ? i : 0] < KC ? r[2] : 0;
+            dma_load_b128(r, b_voff[i], s.step0 * CH * TILE_B);
         }
     };
-    auto issue_b = [&](const StageAt& s, int i) {
-        int4s r = rb;
-        if (B_TAIL) r[2] = s.step0 * CH + b_chunk[B_TAIL ? i : 0] < KC ? r[2] : 0;
-        dma_to_lds_b128(r, b_pad[i] ? lds_base + P::SINK : s.sb, b_lds[i], b_voff[i], s.step0 * CH * TILE_B);
-    };
     auto issue_op = [&](const StageAt& s, int k) {
-        if (k < P::DMA_A)
-            issue_a(s, k);
-        else
-            issue_b(s, k - P::DMA_A);
+        address_op(s, k);
+        asm volatile("s_nop 0");
+        load_op(s, k);
     };
 
     const int sw = swz(l31);
@@ -375,10 +384,11 @@ __global__ __launch_bounds__(256, 1) void gemm_solo_kernel(const GemmArgs g) {
         for (int p = 0; p < TM; ++p) widen_part(wf[0][tn], tn, 0, p);
 
     constexpr int SLOTS = TM * TN;
-    static_assert(SLOTS % 2 == 0 && P::OPS <= 2 * SLOTS, "loads of a stage per slot");
-    // Residual of the slabs this wave finishes, in the accumulator layout; requested in the last stages but S - 1.
-    constexpr int RES_LOADS = RES ? TM / KS * TN * 4 : 0;
-    uint2v rs[RES ? TM / KS : 1][RES ? TN : 1][4];
+    static_assert(SLOTS % 2 == 0 && P::OPS <= 4 * SLOTS, "at most one load of a stage per slot");
+    // Residual of the slabs this wave finishes, requested in the last stages but S - 1: eight channels of its row per lane, 16 bytes; the two
+    // lanes of a row swap halves when they are used.
+    constexpr int RES_LOADS = RES ? TM / KS * TN * 2 : 0;
+    uint4v rs[RES ? TM / KS : 1][RES ? TN : 1][2];
     __amdgpu_buffer_rsrc_t rr;
     int r_voff[RES ? TM / KS : 1];
     if constexpr (RES) {
@@ -386,7 +396,7 @@ __global__ __launch_bounds__(256, 1) void gemm_solo_kernel(const GemmArgs g) {
         rr = __builtin_amdgcn_make_buffer_rsrc((void*)(g.res + (long)m0 * g.ldr), 0, (int)(((long)(rows - 1) * g.ldr + g.N) * 2), 0x00020000);
 #pragma unroll
         for (int i = 0; i < TM / KS; ++i)
-            r_voff[i] = (((wm * TM + (KS == 2 ? 2 * i + grp : i)) * 32 + l31) * (int)g.ldr + n0 + 4 * kb) * 2;
+            r_voff[i] = (((wm * TM + (KS == 2 ? 2 * i + grp : i)) * 32 + l31) * (int)g.ldr + n0 + 8 * kb) * 2;
     }
     int buf = 0, kt = 0;
     // One stage.  EARLY: the second half of the loads that the stage before began to request; LATE: the first half of the stage that takes
@@ -411,8 +421,22 @@ __global__ __launch_bounds__(256, 1) void gemm_solo_kernel(const GemmArgs g) {
 #pragma unroll
             for (int j = 0; j < SLOTS; ++j) {
                 const int tn = j / TM, tm = j % TM;
+                const bool loads = (s < 2 && EARLY) || (s >= 2 && LATE);
+                const int at_slot = ((s + 2) & 3) * SLOTS + j;  // from the hand-over to the next one
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (EARLY || LATE) {
+#pragma unroll
+                    for (int k = 0; k < P::OPS; ++k)
+                        if (loads && k * 4 * SLOTS / P::OPS == at_slot) address_op(at, k);
+                }
                 __builtin_amdgcn_sched_barrier(0);
                 mfma(tm, tn, wf[s & 1][tn], xf[s][tm]);
+                if constexpr (EARLY || LATE) {
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int k = 0; k < P::OPS; ++k)
+                        if (loads && k * 4 * SLOTS / P::OPS == at_slot) load_op(at, k);
+                }
                 if (j < TM) {
                     if (s < 2)
                         read_x(cur, s + 2, j);
@@ -424,19 +448,13 @@ __global__ __launch_bounds__(256, 1) void gemm_solo_kernel(const GemmArgs g) {
                     asm volatile("" : "+v"(wf[1][tn]));
                     read_w(next, tn);
                 }
-                if ((s < 2 && EARLY) || (s >= 2 && LATE)) {
-                    const int at_slot = ((s + 2) & 3) * SLOTS + j;  // from the hand-over to the next one
-#pragma unroll
-                    for (int k = 0; k < P::OPS; ++k)
-                        if (k * 4 * SLOTS / P::OPS == at_slot) issue_op(at, k);
-                }
                 if constexpr (RES && LAST == S - 1) {
                     if (s >= 2) {
 #pragma unroll
                         for (int k = 0; k < RES_LOADS; ++k)
                             if (k * 2 * SLOTS / RES_LOADS == (s - 2) * SLOTS + j) {
-                                const int slab = k / (TN * 4), rt = k / 4 % TN, q = k % 4;
-                                rs[RES ? slab : 0][RES ? rt : 0][q] = __builtin_amdgcn_raw_buffer_load_b64(rr, r_voff[RES ? slab : 0] + (rt * 32 + 8 * q) * 2, 0, 0);
+                                const int slab = k / (TN * 2), rt = k / 2 % TN, h = k % 2;
+                                rs[RES ? slab : 0][RES ? rt : 0][h] = __builtin_amdgcn_raw_buffer_load_b128(rr, r_voff[RES ? slab : 0] + (rt * 32 + 16 * h) * 2, 0, 0);
                             }
                     }
                 }
@@ -572,16 +590,30 @@ __global__ __launch_bounds__(256, 1) void gemm_solo_kernel(const GemmArgs g) {
     const int nw0 = n0;
     // 16-byte chunk of a staged row -> its place
     auto place = [](int row, int chunk) { return (chunk & ~3) | ((chunk ^ (row >> 2)) & 3); };
-    // int8 path: the exact integer sums of result quad q of tile (tm, tn) with both zero-point corrections
-    auto int_quad = [&](int tm, int tn, int q) {
-        const int cl = tn * 32 + 8 * q + 4 * kb;
-        const int4v dw = *(const int4v*)(ch_dw + cl);
-        const int4v cn = *(const int4v*)((MODE == 4 ? ch_border + border[MODE == 4 ? tm : 0] * BN : ch_cn) + cl);
-        int4v a;
+    // The constants of result quad q of channel tile tn: four consecutive channels.
+    struct QuadConst {
+        float4v mul, add;
+        int4v dw, cn;
+    };
+    auto quad_const = [&](int i) {
+        const int cl = (i >> 2) * 32 + 8 * (i & 3) + 4 * kb;
+        QuadConst k;
+        k.mul = *(const float4v*)(ch_mul + cl);
+        k.add = *(const float4v*)(ch_add + cl);
+        if constexpr (I8) {
+            k.dw = *(const int4v*)(ch_dw + cl);
+            if constexpr (MODE != 4) k.cn = *(const int4v*)(ch_cn + cl);
+        }
+        return k;
+    };
+    // int8 path: the exact integer sums of result quad i of slab tm with both zero-point corrections
+    auto int_quad = [&](int tm, int i, const QuadConst& k) {
+        int4v a, cn = k.cn;
+        if constexpr (MODE == 4) cn = *(const int4v*)(ch_border + border[MODE == 4 ? tm : 0] * BN + (i >> 2) * 32 + 8 * (i & 3) + 4 * kb);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             // |dw| <= 255 and |rowsum| <= 128 * K < 2^23: a 24-bit multiply (full rate) is exact
-            a[r] = (int)acc[tm][tn][4 * q + r] + __mul24(dw[r], rsum[tm]) + cn[r];
+            a[r] = (int)acc[tm][i >> 2][4 * (i & 3) + r] + __mul24(k.dw[r], rsum[tm]) + cn[r];
         return a;
     };
     if constexpr (I8) {
@@ -595,53 +627,77 @@ __global__ __launch_bounds__(256, 1) void gemm_solo_kernel(const GemmArgs g) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int n = n0 + tn * 32 + 8 * q + 4 * kb;
-                        const int4v a = int_quad(tm, tn, q);
+                        const int4v a = int_quad(tm, tn * 4 + q, quad_const(tn * 4 + q));
                         if (m < g.M && n < g.N) *(int4v*)(g.acc_debug + (long)m * g.N + n) = a;
                     }
             }
         }
     }
-    // Slab by slab: convert (eight-byte pieces into the staged rows), read back as 16 bytes per lane along rows, store rows of 320 bytes.
+    // Slabs [from, to): convert (eight-byte pieces into the staged rows; a quad's constants are read once for all slabs, one quad ahead of the
+    // conversions: there is no other wave to cover their latency), read back as 16 bytes per lane along rows, store rows of 320 bytes.
+    // Every store is issued, without a branch: what lies outside the output is dropped by the buffer's bounds.
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(g.y + (long)m0 * g.ldy), 0, (int)(((long)((g.M - m0 < BM ? g.M - m0 : BM) - 1) * g.ldy + g.N) * 2), 0x00020000);
+    auto finish = [&](auto from_c, auto to_c) {
+        constexpr int FROM = decltype(from_c)::value, TO = decltype(to_c)::value;
+        QuadConst k = quad_const(0);
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm) {
-        if (owner(tm) != grp) continue;
-        uint8_t* slab = ep + (KS == 2 ? tm >> 1 : tm) * EP_BYTES;
+        for (int i = 0; i < TN * 4; ++i) {
+            const QuadConst kn = quad_const(i + 1 < TN * 4 ? i + 1 : i);
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
+            for (int tm = FROM; tm < TO; ++tm) {
+                float4v add = k.add;
+                if constexpr (RES) {
+                    uint4v& pair = rs[tm - FROM][i >> 2][(i & 3) >> 1];  // the lane's channels of quads i and i + 1, once the halves are swapped
+                    if (i % 2 == 0) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int cl = tn * 32 + 8 * q + 4 * kb;
-                const float4v mul = *(const float4v*)(ch_mul + cl);
-                float4v add = *(const float4v*)(ch_add + cl);
-                if constexpr (RES)
+                        for (int d = 0; d < 2; ++d) {
+                            const auto sw2 = __builtin_amdgcn_permlane32_swap(pair[d], pair[2 + d], false, false);
+                            pair[d] = sw2[0], pair[2 + d] = sw2[1];
+                        }
+                    }
+                    const half4 rq = __builtin_bit_cast(half4, uint2v{pair[2 * (i & 1)], pair[2 * (i & 1) + 1]});
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) add[r] += (float)__builtin_bit_cast(half4, rs[KS == 2 ? 0 : tm][tn][q])[r];
+                    for (int r = 0; r < 4; ++r) add[r] += (float)rq[r];
+                }
                 half4 o;
                 if constexpr (I8) {
-                    const int4v a = int_quad(tm, tn, q);
+                    const int4v a = int_quad(tm, i, k);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) o[r] = (_Float16)((float)a[r] * mul[r] + add[r]);
+                    for (int r = 0; r < 4; ++r) o[r] = (_Float16)((float)a[r] * k.mul[r] + add[r]);
                 } else {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) o[r] = (_Float16)(acc[tm][tn][4 * q + r] * mul[r] + add[r]);
+                    for (int r = 0; r < 4; ++r) o[r] = (_Float16)(acc[tm][i >> 2][4 * (i & 3) + r] * k.mul[r] + add[r]);
                 }
-                *(half4*)(slab + l31 * (CPR * 16) + (place(l31, tn * 4 + q) << 4) + kb * 8) = o;
+                *(half4*)(ep + (tm - FROM) * EP_BYTES + l31 * (CPR * 16) + (place(l31, i) << 4) + kb * 8) = o;
             }
+            k = kn;
+        }
         __builtin_amdgcn_wave_barrier();
         constexpr int NP = 32 * CPR / 64;
-        const int m_first = m0 + (wm * TM + tm) * 32;
-        uint4v v[NP];
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            const int idx = i * 64 + lane, row = idx / CPR, c = idx % CPR;
-            v[i] = *(const uint4v*)(slab + row * (CPR * 16) + (place(row, c) << 4));
-        }
+        for (int tm = FROM; tm < TO; ++tm) {
+            uint4v v[NP];
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            const int idx = i * 64 + lane, row = idx / CPR, c = idx % CPR;
-            const int m = m_first + row, n = nw0 + c * 8;
-            if (m < g.M && n < g.N) __builtin_nontemporal_store(v[i], (uint4v*)(g.y + (long)m * g.ldy + n));
+            for (int i = 0; i < NP; ++i) {
+                const int idx = i * 64 + lane, row = idx / CPR, c = idx % CPR;
+                v[i] = *(const uint4v*)(ep + (tm - FROM) * EP_BYTES + row * (CPR * 16) + (place(row, c) << 4));
+            }
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const int idx = i * 64 + lane, row = (wm * TM + tm) * 32 + idx / CPR, n = nw0 + idx % CPR * 8;
+                const int voff = m0 + row < g.M && n < g.N ? (row * (int)g.ldy + n) * 2 : OOB;
+                __builtin_amdgcn_raw_buffer_store_b128(v[i], ry, voff, 0, 2 /* streaming */);
+            }
         }
+    };
+    if constexpr (KS == 1) {
+        finish(std::integral_constant<int, 0>{}, std::integral_constant<int, 2>{});
+    } else {
+        if (grp == 0)
+            finish(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+        else
+            finish(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
     }
     if (g.phase_clk && threadIdx.x == 0) {
         long long* o = g.phase_clk + (long)blockIdx.x * 4;
@@ -736,7 +792,7 @@ int solo_form(const GemmArgs& g, bool i8, int bits, int mode) {
     const int forced = forced_tile();
     if ((forced >= 0 && forced < 12) || bits == 16) return -1;
     if (g.out_map.rows_per_group > 0 || forced_splits() > 1) return -1;
-    if (g.res && g.ldr >= (1 << 21)) return -1;  // (offsets of a workgroup's residual rows are 32-bit)
+    if (g.ldy >= (1 << 21) || (g.res && g.ldr >= (1 << 21))) return -1;  // (offsets inside a workgroup's rows are 32-bit)
     const bool halves = !(i8 && bits == 8);      // form 1 exists
     // (the stages that are requested ahead of the loop have to exist)
     auto long_enough = [&](int form) { return (g.k_stages + form) / (form + 1) >= 4; };

@@ -348,9 +348,11 @@ void gemm_kernel(const GemmArgs g) {
         for (int tn = 0; tn < TN; ++tn) {
             if constexpr (I8)
                 wf[tn] = widen_step<BITS>(wq[tn][s >> 1], s & 1, xflip);
+            else if constexpr (BF && KS == 1)
+                wf[tn] = dequant_step_bf16<BITS>(wq[tn][0], s, zc[tn]);
             else
                 wf[tn] = dequant_step<BITS>(wq[tn][0], s, zc[tn]);
-            if constexpr (BF && BITS != 16) wf[tn] = __builtin_bit_cast(half8, half8_to_bf16x8(wf[tn]));  // bf16 bits now
+            if constexpr (BF && KS == 2 && BITS != 16) wf[tn] = half8_to_bf16x8(wf[tn]);  // bf16 bits now
         }
     };
     constexpr int RS_SHARES = WGN == 4 ? 4 : 1;  // waves that share the row sums of the rows they hold

@@ -149,17 +149,69 @@ __device__ __forceinline__ half8 dequant_step<16>(const WChunk<16>& c, int s, in
     return __builtin_bit_cast(half8, v);
 }
 
-// bfloat16 variant: the widened weights are small integers (|q - z| <= 255), exact in fp16 and in bf16 alike, so
-// the fp16 fragment is converted pair by pair: two fp16 -> fp32 conversions and one byte permute that keeps the
-// upper halves (which for these values is the exact bf16).
-__device__ __forceinline__ bf16x8 half8_to_bf16x8(half8 h) {
+// bfloat16 variant: the widened weights are small integers (|q - z| <= 255), exact in fp16, in fp32 and in bf16 alike.
+// Where two wave groups share a reduction: the fp16 fragment is converted pair by pair, two fp16 -> fp32 conversions and one byte permute that
+// keeps the upper halves (which for these values is the exact bf16), five instructions a pair in all.
+__device__ __forceinline__ half8 half8_to_bf16x8(half8 h) {  // (bf16 bits)
     uint4v o;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         const uint32_t f0 = __float_as_uint((float)h[2 * p]), f1 = __float_as_uint((float)h[2 * p + 1]);
         o[p] = __builtin_amdgcn_perm(f1, f0, 0x07060302u);
     }
-    return __builtin_bit_cast(bf16x8, o);
+    return __builtin_bit_cast(half8, o);
+}
+// Elsewhere the pair with the magic number in it, 1024 + 2^SHIFT q, becomes q - z in fp32 by one mixed-precision multiply-add a half: four
+// instructions a pair.  us, five -> four: 16384 x 640 x 640 20.8 -> 19.3 (2 bits), 21.2 -> 20.7 (4 bits), 4096 x 5120 x 1280 63.7 -> 60.7 (3 bits), 4096 x
+// 2560 x 640 25.1 -> 25.3; two wave groups, one wave per SIMD each: 535 x 3904 x 2520 (3 bits) 25.6 -> 26.5.
+template <int SHIFT>
+__device__ __forceinline__ uint32_t magic_to_bf16x2(uint32_t v, int z) {
+    const float c = -(float)((1024 >> SHIFT) + z);
+    float inv = 1.0f / (float)(1 << SHIFT);
+    asm("" : "+s"(inv));  // (a multiplication by a visible 1 would become a conversion and an addition)
+    const half2v h = as_h2(v);
+    const float f0 = __builtin_fmaf((float)h[0], inv, c), f1 = __builtin_fmaf((float)h[1], inv, c);
+    return __builtin_amdgcn_perm(__float_as_uint(f1), __float_as_uint(f0), 0x07060302u);
+}
+template <int SHIFT>
+__device__ __forceinline__ uint32_t field_to_bf16x2(uint32_t w, uint32_t mask, int z) {
+    uint32_t magic = 0x64006400u;
+    asm("" : "+s"(mask));  // (as and_or, but left to the compiler to schedule)
+    asm("" : "+v"(magic));
+    return magic_to_bf16x2<SHIFT>((w & mask) | magic, z);
+}
+template <int BITS>
+__device__ __forceinline__ half8 dequant_step_bf16(const WChunk<BITS>& c, int s, int z) {  // (bf16 bits)
+    uint4v o;
+    if constexpr (BITS == 4) {
+        const uint32_t w = c.w[s], v = w >> 8;
+        o = uint4v{field_to_bf16x2<0>(w, 0x000F000Fu, z), field_to_bf16x2<4>(w, 0x00F000F0u, z), field_to_bf16x2<0>(v, 0x000F000Fu, z),
+                   field_to_bf16x2<4>(v, 0x00F000F0u, z)};
+    } else if constexpr (BITS == 2) {
+        const uint32_t w = (s & 1) ? c.w[s >> 1] >> 8 : c.w[s >> 1];
+        o = uint4v{field_to_bf16x2<0>(w, 0x00030003u, z), field_to_bf16x2<2>(w, 0x000C000Cu, z), field_to_bf16x2<4>(w, 0x00300030u, z),
+                   field_to_bf16x2<6>(w, 0x00C000C0u, z)};
+    } else if constexpr (BITS == 3) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {  // as dequant_step<3>: pair 4 s + p is field % 5 of word / 5, the last one scattered
+            const int i = 4 * s + p, f = i % 5;
+            if (i == 15) {
+                const uint32_t t = ((c.w[0] >> 15) & 0x00010001u) | ((c.w[1] >> 14) & 0x00020002u) | ((c.w[2] >> 13) & 0x00040004u);
+                o[p] = field_to_bf16x2<0>(t, 0x00070007u, z);
+            } else {
+                const uint32_t w = f < 3 ? c.w[i / 5] : c.w[i / 5] >> 9;
+                o[p] = f == 0 || f == 3 ? field_to_bf16x2<0>(w, 0x00070007u, z) : f == 1 || f == 4 ? field_to_bf16x2<3>(w, 0x00380038u, z)
+                                                                                                   : field_to_bf16x2<6>(w, 0x01C001C0u, z);
+            }
+        }
+    } else if constexpr (BITS == 8) {
+        const uint32_t wa = c.w[(s >> 1) * 4 + (s & 1) * 2], wb = c.w[(s >> 1) * 4 + (s & 1) * 2 + 1];
+        o = uint4v{magic_to_bf16x2<0>(__builtin_amdgcn_perm(0x64646464u, wa, 0x04020400u), z), magic_to_bf16x2<0>(__builtin_amdgcn_perm(0x64646464u, wb, 0x04020400u), z),
+                   magic_to_bf16x2<0>(__builtin_amdgcn_perm(0x64646464u, wa, 0x04030401u), z), magic_to_bf16x2<0>(__builtin_amdgcn_perm(0x64646464u, wb, 0x04030401u), z)};
+    } else {
+        return dequant_step<BITS>(c, s, z);  // unquantised
+    }
+    return __builtin_bit_cast(half8, o);
 }
 
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }

@@ -787,7 +787,9 @@ int launch_gemm_solo(GemmArgs& g, int form, bool i8, int bits, int mode, hipStre
 //   ... 1.25                 1.0 to 1.15, but int8 convolutions at 8 bits 0.83 0.90 0.94
 //   form 1, fit up to 0.85   16-bit: linears 0.88 to 0.91 (3 bits 0.95), convolutions 0.83 to 0.90; at fit 1.0 1.0 to 1.1; int8: convolutions of
 //                            5760 k and more 0.83 to 0.95, of 2880 (22 stages, and the halves' sums have to meet) 1.03; linears 0.98, codes 0.96
-// Reductions below 2048 k (convolutions and codes: 2560) do not repay the store at the end, 16-bit 0.96 to 1.05 at fit 1.0.
+// Reductions below 2048 k (convolutions and codes: 2560) do not repay the store at the end, 0.96 to 1.05 at fit 1.0 and more with every round of
+// workgroups; 16-bit linears in one round do from 1280 k on at 4 bits (to 1407 0.97 1.00 1.01, from there 0.93 to 0.94) and 8 (0.92 and 0.88), not
+// at 2 (1.00 and 0.97).
 int solo_form(const GemmArgs& g, bool i8, int bits, int mode) {
     const int forced = forced_tile();
     if ((forced >= 0 && forced < 12) || bits == 16) return -1;
@@ -798,15 +800,17 @@ int solo_form(const GemmArgs& g, bool i8, int bits, int mode) {
     auto long_enough = [&](int form) { return (g.k_stages + form) / (form + 1) >= 4; };
     if (forced >= 12) return forced == 12 && long_enough(0) ? 0 : forced == 13 && halves && long_enough(1) ? 1 : -1;
     const bool conv = mode == 3 || mode == 4;
-    if (g.K < (mode == 0 ? 2048 : 2560)) return -1;
     const long now = std::min(busiest_area(g.M, g.N, 64, 128), busiest_area(g.M, g.N, 96, 128));
     const long full = busiest_area(g.M, g.N, 256, 160), half = busiest_area(g.M, g.N, 128, 160);
     auto fit = [&](long area, int percent) { return 100 * area <= percent * now; };
+    const bool one_round = full == 256 * 160;
+    const int shortest = mode != 0 ? 2560 : !i8 && (bits == 4 || bits == 8) && one_round ? 1280 : 2048;
+    if (g.K < shortest) return -1;
     if (mode == 2) {
         // On codes: 8 bits 0.85 0.90 1.00 (rows that start inside a 64-byte sector 0.90 0.99 1.00: left where they were), 4 bits 0.92 0.96 0.98 in
         // one round of workgroups but 1.04 in two, 2 bits 0.98 and 1.12.
         if (bits == 8) return fit(full, 115) && g.ldy % 32 == 0 ? 0 : -1;
-        return bits == 4 && fit(full, 115) && full == 256 * 160 ? 0 : -1;
+        return bits == 4 && fit(full, 115) && one_round ? 0 : -1;
     }
     // (int8 linears at 8 bits from 2624 k on: at 2560, the feed-forward outputs of the 640-channel level, 64 x 128 stays)
     if (mode == 0 && i8) return fit(full, 115) && (bits != 8 || g.K > 2560) ? 0 : -1;

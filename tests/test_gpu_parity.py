@@ -2090,7 +2090,8 @@ def test_one_wave_per_simd_linears(mq, kind, bits, tile):
 
 
 @pytest.mark.parametrize("kind,bits,M,K,N,solo", [
-    ("f16", 4, 4096, 2048, 2560, True), ("f16", 4, 4096, 1984, 2560, False), ("f16", 4, 4097, 2048, 2560, False),  # one round, two
+    ("f16", 4, 4096, 1280, 2560, True), ("f16", 4, 4096, 1216, 2560, False), ("f16", 4, 4097, 2048, 2560, False),  # one round, two
+    ("f16", 2, 4096, 1984, 2560, False), ("f16", 2, 4096, 2048, 2560, True), ("f16", 4, 8192, 1984, 2560, False), ("f16", 4, 8192, 2048, 2560, True),
     ("f16", 8, 4096, 2560, 1280, True), ("f16", 8, 4096, 2496, 1280, False),     # half the height
     ("a8", 4, 4096, 2048, 2560, True), ("a8", 2, 4097, 2048, 2560, False), ("a8", 8, 4096, 2624, 2560, True), ("a8", 8, 4096, 2560, 2560, False),
     ("codes", 4, 4096, 2560, 2560, True), ("codes", 2, 4096, 2560, 2560, False), ("codes", 8, 4096, 2560, 2560, True), ("codes", 8, 4096, 2560, 2552, False),

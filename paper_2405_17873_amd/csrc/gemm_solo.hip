@@ -789,7 +789,11 @@ int launch_gemm_solo(GemmArgs& g, int form, bool i8, int bits, int mode, hipStre
 //                            5760 k and more 0.83 to 0.95, of 2880 (22 stages, and the halves' sums have to meet) 1.03; linears 0.98, codes 0.96
 // Reductions below 2048 k (convolutions and codes: 2560) do not repay the store at the end, 0.96 to 1.05 at fit 1.0 and more with every round of
 // workgroups; 16-bit linears in one round do from 1280 k on at 4 bits (to 1407 0.97 1.00 1.01, from there 0.93 to 0.94) and 8 (0.92 and 0.88), not
-// at 2 (1.00 and 0.97).
+// at 2 (1.00 and 0.97).  Where at least 19/20 of that round is output, also shorter ones: with a residual, which this kernel has in registers by then,
+// from 640 k on (us: 16384 x 640 x 640 at 2, 3, 4, 8 bits 24.2 -> 22.3, 22.3 -> 21.7, 23.1 -> 21.0, 24.1 -> 21.7, int8 at 4 and 8 bits 26.4 -> 25.2 and
+// 27.3 -> 26.1; 32768 x 640 x 320 at 4 bits 27.9 -> 20.1; 14000 x 640 x 640, 0.85 of the round, 17.2 -> 18.2), without one 16-bit linears at 8 bits (16384 x 640 x
+// 640 18.3 -> 16.8, 2048 x 640 x 5120 18.5 -> 16.8; at 4 bits 16.9 -> 16.7 and 16.7 -> 16.8) and from 960 k on at 4 bits (16384 x 960 x 640 22.8 -> 21.8; at 2
+// bits 23.1 -> 22.7 and 22.5 -> 22.0, left); int8 without a residual 0.93 to 1.1.
 int solo_form(const GemmArgs& g, bool i8, int bits, int mode) {
     const int forced = forced_tile();
     if ((forced >= 0 && forced < 12) || bits == 16) return -1;
@@ -804,7 +808,9 @@ int solo_form(const GemmArgs& g, bool i8, int bits, int mode) {
     const long full = busiest_area(g.M, g.N, 256, 160), half = busiest_area(g.M, g.N, 128, 160);
     auto fit = [&](long area, int percent) { return 100 * area <= percent * now; };
     const bool one_round = full == 256 * 160;
-    const int shortest = mode != 0 ? 2560 : !i8 && (bits == 4 || bits == 8) && one_round ? 1280 : 2048;
+    const bool filled = one_round && 20L * g.M * g.N >= 19 * UNITS * full;  // ... and hardly any of it padding
+    const int shortest = mode != 0 ? 2560 : filled && g.res ? 640 : filled && !i8 && bits == 8 ? 640 : filled && !i8 && bits == 4 ? 960
+                         : one_round && !i8 && (bits == 4 || bits == 8) ? 1280 : 2048;
     if (g.K < shortest) return -1;
     if (mode == 2) {
         // On codes: 8 bits 0.85 0.90 1.00 (rows that start inside a 64-byte sector 0.90 0.99 1.00: left where they were), 4 bits 0.92 0.96 0.98 in
@@ -813,7 +819,7 @@ int solo_form(const GemmArgs& g, bool i8, int bits, int mode) {
         return bits == 4 && fit(full, 115) && one_round ? 0 : -1;
     }
     // (int8 linears at 8 bits from 2624 k on: at 2560, the feed-forward outputs of the 640-channel level, 64 x 128 stays)
-    if (mode == 0 && i8) return fit(full, 115) && (bits != 8 || g.K > 2560) ? 0 : -1;
+    if (mode == 0 && i8) return fit(full, 115) && (bits != 8 || g.K > 2560 || (filled && g.res)) ? 0 : -1;
     if (fit(full, i8 && bits == 8 ? 125 : 105)) return 0;
     return halves && fit(half, 85) && (!i8 || g.K >= 5120) && (conv || g.K >= 2560) ? 1 : -1;
 }

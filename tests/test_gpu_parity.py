@@ -2090,7 +2090,7 @@ def test_one_wave_per_simd_linears(mq, kind, bits, tile):
 
 
 @pytest.mark.parametrize("kind,bits,M,K,N,solo", [
-    ("f16", 4, 4096, 1280, 2560, True), ("f16", 4, 4096, 1216, 2560, False), ("f16", 4, 4097, 2048, 2560, False),  # one round, two
+    ("f16", 4, 3888, 1280, 2560, True), ("f16", 4, 3888, 1216, 2560, False), ("f16", 4, 4097, 2048, 2560, False),  # one round, two
     ("f16", 2, 4096, 1984, 2560, False), ("f16", 2, 4096, 2048, 2560, True), ("f16", 4, 8192, 1984, 2560, False), ("f16", 4, 8192, 2048, 2560, True),
     ("f16", 8, 4096, 2560, 1280, True), ("f16", 8, 4096, 2496, 1280, False),     # half the height
     ("a8", 4, 4096, 2048, 2560, True), ("a8", 2, 4097, 2048, 2560, False), ("a8", 8, 4096, 2624, 2560, True), ("a8", 8, 4096, 2560, 2560, False),
@@ -2100,6 +2100,16 @@ def test_one_wave_per_simd_rule(mq, kind, bits, M, K, N, solo):
     """Both sides of the lines."""
     rows = np.unique(np.clip([0, 63, 64, 127, 128, 255, 256, M // 2, M - 2, M - 1], 0, M - 1))
     assert ("gemm_solo_kernel" in solo_case(mq, kind, bits, M, K, N, False, -1, rows=rows)) == solo
+
+
+@pytest.mark.parametrize("kind,bits,M,K,N,res,solo", [
+    ("f16", 2, 4096, 640, 2560, True, True), ("f16", 2, 4096, 576, 2560, True, False), ("f16", 3, 3889, 640, 2560, True, False), ("f16", 3, 3892, 640, 2560, True, True),
+    ("f16", 8, 4096, 640, 2560, False, True), ("f16", 8, 3888, 640, 2560, False, False), ("f16", 4, 4096, 960, 2560, False, True), ("f16", 4, 4096, 896, 2560, False, False),
+    ("a8", 8, 4096, 640, 2560, True, True), ("a8", 8, 4096, 640, 2560, False, False), ("a8", 2, 4096, 704, 2560, True, True)])
+def test_one_wave_per_simd_rule_for_short_reductions(mq, kind, bits, M, K, N, res, solo):
+    """One round of workgroups that is nearly all output (3892 x 2560 is 19/20 of it): with a residual, and without."""
+    rows = np.unique(np.clip([0, 63, 64, 127, 128, 255, 256, M // 2, M - 2, M - 1], 0, M - 1))
+    assert ("gemm_solo_kernel" in solo_case(mq, kind, bits, M, K, N, res, -1, rows=rows)) == solo
 
 
 @pytest.mark.parametrize("tile", (12, 13))

@@ -343,7 +343,7 @@ void gemm_kernel(const GemmArgs g) {
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) xf[0][tm] = *(const frag_t*)(abuf + rd[0] + tm * 32 * 128);
     };
-    auto widen_from = [&](const WChunk<BITS> (&wq)[TN][CH], frag_t (&wf)[TN], int s) {
+    auto widen = [&](frag_t (&wf)[TN], int s) {
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
             if constexpr (I8)
@@ -355,10 +355,9 @@ void gemm_kernel(const GemmArgs g) {
             if constexpr (BF && KS == 2 && BITS != 16) wf[tn] = half8_to_bf16x8(wf[tn]);  // bf16 bits now
         }
     };
-    auto widen = [&](frag_t (&wf)[TN], int s) { widen_from(wq, wf, s); };
     constexpr int RS_SHARES = WGN == 4 ? 4 : 1;  // waves that share the row sums of the rows they hold
     const int wn_u = __builtin_amdgcn_readfirstlane(wn);
-    auto multiply_frags = [&](const frag_t (&wf)[TN], const frag_t (&x)[TM], int s, auto fresh_c) {
+    auto multiply = [&](const frag_t (&wf)[TN], int s, auto fresh_c) {
         constexpr bool FRESH = decltype(fresh_c)::value;  // the accumulators start here: C = 0
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
@@ -372,12 +371,12 @@ void gemm_kernel(const GemmArgs g) {
                     c = acc[tm][tn];
                 }
                 if constexpr (I8)
-                    acc[tm][tn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[tn], x[tm], c, 0, 0, 0);
+                    acc[tm][tn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[tn], xf[s][tm], c, 0, 0, 0);
                 else if constexpr (BF)
                     acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(bf16x8, wf[tn]), __builtin_bit_cast(bf16x8, x[tm]), c, 0, 0, 0);
+                        __builtin_bit_cast(bf16x8, wf[tn]), __builtin_bit_cast(bf16x8, xf[s][tm]), c, 0, 0, 0);
                 else
-                    acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[tn], x[tm], c, 0, 0, 0);
+                    acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[tn], xf[s][tm], c, 0, 0, 0);
             }
         // Row sums of the stored activations (bytes a' = code - 128).  Where four waves hold the same rows each takes the
         // fragments of one k-step in four: four dot products per fragment, in every wave, were more vector instructions than the
@@ -388,15 +387,13 @@ void gemm_kernel(const GemmArgs g) {
             if (RS_SHARES == 1 || s % RS_SHARES == wn_u) {
 #pragma unroll
                 for (int tm = 0; tm < TM; ++tm) {
-                    const int4v a = __builtin_bit_cast(int4v, x[tm]);
+                    const int4v a = __builtin_bit_cast(int4v, xf[s][tm]);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) rsum[tm] = __builtin_amdgcn_sdot4(a[i], 0x01010101, rsum[tm], false);
                 }
             }
         }
     };
-
-    auto multiply = [&](const frag_t (&wf)[TN], int s, auto fresh_c) { multiply_frags(wf, xf[s], s, fresh_c); };
 
     // stage 0 must have landed; the younger stages stay in flight
     constexpr int W_FIRST = (S - 1) * P::OPS <= 63 ? (S - 1) * P::OPS : (S > 2 ? (S - 2) * P::OPS : 0);
@@ -409,53 +406,52 @@ void gemm_kernel(const GemmArgs g) {
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) zc[tn] = *(const int*)(lds + ZP_SLOT + ((wn * TN + tn) * 32 + l31) * 4);
     }
-    int buf = 0;
-    // Hand-over from stage kt to the next: it must have landed (the S-2 stages behind it may stay in flight while they exist); the barrier also
-    // says that every wave holds its last fragments of stage kt, so its buffer is refilled.
-    auto hand_over = [&](int kt) {
-        if (S > 2 && kt + S - 1 < KT)
-            wait_vmcnt<(S > 2 ? (S - 2) * P::OPS : 0)>();
-        else
-            wait_vmcnt<0>();
-        __syncthreads();
-        if (kt + S < KT) issue(kt + S, buf);
-    };
     if constexpr (TM == 1 && TN == 1 && MODE != 0) {
         // One MFMA a step covers neither the LDS round trip of the next step's fragment nor the widening: a stage of the small tile was a chain
         // of four such trips, 600 cycles for 128 of MFMAs.  Its fragments are few, so a wave holds those of two stages: all of the next
         // stage's are requested at the hand-over, the current one's are widened ahead of it and multiplied behind it.  us: convolutions 1 x 20 x 20 x 1280
         // at 4 bits on 16-bit activations 57.4 -> 54.7, on 8-bit ones 45.4 -> 41.8 (8 bits 46.4 -> 43.5), 2 x 32 x 32 x 640 with stride 2 26.9 -> 25.2; on
         // codes 500 x 5120 x 1280 17.2 -> 16.5.  Not plain linears, whose reductions are split further: 0.97 to 1.02, at 8 bits 1.0 to 1.16.
-        WChunk<BITS> wq2[2][TN][CH];
-        frag_t xf2[2][4][TM];
+        int buf = 0;
+        WChunk<BITS> wq2[2][CH];
+        frag_t xf2[2][4];
         auto request = [&](int set, const uint8_t* abuf) {
 #pragma unroll
-            for (int c = 0; c < CH; ++c) read_chunk<BITS>(wq2[set][0][c], abuf + P::A_BYTES + (wn * CH + c) * P::BSLOT, lane);
+            for (int c = 0; c < CH; ++c) read_chunk<BITS>(wq2[set][c], abuf + P::A_BYTES + (wn * CH + c) * P::BSLOT, lane);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) xf2[set][s][0] = *(const frag_t*)(abuf + rd[s]);
+            for (int s = 0; s < 4; ++s) xf2[set][s] = *(const frag_t*)(abuf + rd[s]);
         };
         auto stage = [&](int set, int kt) {
             const bool live = KS == 1 || (kt0 + kt) * KS + grp < KSTEPS;
             frag_t wf[4][TN];
 #pragma unroll
+            for (int c = 0; c < CH; ++c) wq[0][c] = wq2[set][c];
+#pragma unroll
             for (int s = 0; s < 4; ++s) {
-                widen_from(wq2[set], wf[s], s);
-                asm volatile("" : "+v"(wf[s][0]), "+v"(xf2[set][s][0]));  // here, not behind the requests below
+                widen(wf[s], s);
+                asm volatile("" : "+v"(wf[s][0]), "+v"(xf2[set][s]));  // here, not behind the requests below
+                xf[s][0] = xf2[set][s];
             }
             __builtin_amdgcn_sched_barrier(0);
             const int nb = buf + 1 == S ? 0 : buf + 1;
             if (kt + 1 < KT) {
-                hand_over(kt);
+                // hand-over, as in the loop below
+                if (S > 2 && kt + S - 1 < KT)
+                    wait_vmcnt<(S > 2 ? (S - 2) * P::OPS : 0)>();
+                else
+                    wait_vmcnt<0>();
+                __syncthreads();
+                if (kt + S < KT) issue(kt + S, buf);
                 request(set ^ 1, lds + nb * STAGE_BYTES + grp * P::SUB_BYTES);
             }
             __builtin_amdgcn_sched_barrier(0);
             if (ZERO_C && kt == 0)
-                multiply_frags(wf[0], xf2[set][0], 0, std::true_type{});
+                multiply(wf[0], 0, std::true_type{});
             else if (live)
-                multiply_frags(wf[0], xf2[set][0], 0, std::false_type{});
+                multiply(wf[0], 0, std::false_type{});
             if (live) {
 #pragma unroll
-                for (int s = 1; s < 4; ++s) multiply_frags(wf[s], xf2[set][s], s, std::false_type{});
+                for (int s = 1; s < 4; ++s) multiply(wf[s], s, std::false_type{});
             }
             __builtin_amdgcn_sched_barrier(0);
             buf = nb;
@@ -467,6 +463,8 @@ void gemm_kernel(const GemmArgs g) {
         }
     } else {
     request_first(lds + grp * P::SUB_BYTES);
+
+    int buf = 0;
     for (int kt = 0; kt < KT; ++kt) {
         const uint8_t* abuf = lds + buf * STAGE_BYTES + grp * P::SUB_BYTES;
         // odd tail of a k-split: the last k step of group 1 does not exist (it still takes part in the barriers)
@@ -500,7 +498,14 @@ void gemm_kernel(const GemmArgs g) {
         __builtin_amdgcn_sched_barrier(0);
         int nb = buf + 1 == S ? 0 : buf + 1;
         if (kt + 1 < KT) {
-            hand_over(kt);
+            // hand-over: stage kt+1 must have landed (the S-2 stages behind it may stay in flight while they exist);
+            // the barrier also says that every wave holds its last fragments of stage kt, so its buffer is refilled
+            if (S > 2 && kt + S - 1 < KT)
+                wait_vmcnt<(S > 2 ? (S - 2) * P::OPS : 0)>();
+            else
+                wait_vmcnt<0>();
+            __syncthreads();
+            if (kt + S < KT) issue(kt + S, buf);
             request_first(lds + nb * STAGE_BYTES + grp * P::SUB_BYTES);
         }
         __builtin_amdgcn_sched_barrier(0);

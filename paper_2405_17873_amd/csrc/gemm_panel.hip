@@ -179,12 +179,12 @@ __global__ __launch_bounds__(PANEL_NT) void gemm_panel_kernel(const PanelArgs g)
     int rsum[2];
 #pragma unroll
     for (int tm = 0; tm < 2; ++tm) rsum[tm] = lsum[tm * 32 + l31];
+    // Pieces of the two k-steps of an even 64-k tile (two tiles per 128-byte row, two pieces a step); those of an odd one are four pieces on,
+    // one bit under the swizzle.  (Four offsets indexed by the tile lie in scratch memory, and every read of that waits for all loads in flight.)
     const int sw = swz(l31);  // (the same for row l31 + 32)
-    uint32_t rd[4];           // piece of k-step s (two per 64 k; two 64-k tiles per 128-byte row)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) rd[i] = (uint32_t)(l31 * 128 + ((((i >> 1) * 4 + kb * 2 + (i & 1)) ^ sw) << 4));
+    const uint32_t rd0 = (uint32_t)(l31 * 128 + (((kb * 2) ^ sw) << 4)), rd1 = (uint32_t)(l31 * 128 + (((kb * 2 + 1) ^ sw) << 4));
     auto read_x = [&](int4v (&f)[2], int c, int st) {
-        const uint8_t* p = lds + (c >> 1) * 8192 + ((c & 1) ? (st ? rd[3] : rd[2]) : (st ? rd[1] : rd[0]));
+        const uint8_t* p = lds + (c >> 1) * 8192 + ((st ? rd1 : rd0) ^ (uint32_t)((c & 1) << 6));
         f[0] = *(const int4v*)p;
         f[1] = *(const int4v*)(p + 32 * 128);
     };

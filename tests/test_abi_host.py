@@ -223,3 +223,20 @@ def test_native_marshalling_made_for_another_torch_is_refused(monkeypatch):
     monkeypatch.setattr(build, "_host_made_for", lambda: "torch 0.0.0")
     with pytest.raises(RuntimeError, match="built for"):
         binding._load_native()
+
+
+def test_panel_kernels_use_no_scratch(tmp_path):
+    """The panel kernels count their outstanding loads by hand, which decides something only where the compiler has no vector-memory operations
+    of its own in the loop: an array indexed at run time lies in scratch, and every read of it waits for all of them."""
+    import shutil
+    import subprocess
+
+    from paper_2405_17873_amd import build
+    if not shutil.which(build.HIPCC):
+        pytest.skip("no compiler")
+    src = "gemm_panel.hip"
+    r = subprocess.run([build.HIPCC, *build.COMMON, *build.PER_FILE[src], "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c",
+                        os.path.join(build.CSRC, src), "-o", str(tmp_path / "panel.o")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    scratch = [int(v) for v in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stderr)]
+    assert len(scratch) == 12 and not any(scratch), scratch

@@ -500,12 +500,27 @@ void gemm_kernel(const GemmArgs g) {
         if (kt + 1 < KT) {
             // hand-over: stage kt+1 must have landed (the S-2 stages behind it may stay in flight while they exist);
             // the barrier also says that every wave holds its last fragments of stage kt, so its buffer is refilled
-            if (S > 2 && kt + S - 1 < KT)
-                wait_vmcnt<(S > 2 ? (S - 2) * P::OPS : 0)>();
-            else
-                wait_vmcnt<0>();
-            __syncthreads();
-            if (kt + S < KT) issue(kt + S, buf);
+            if constexpr (TM == 1 && TN == 1 && KS == 2 && !I8 && !BF) {
+                // (The same in a function of its own: the compiler lays this loop out another way.  64 x 64 with two wave groups without a workspace, us:
+                // 196 x 4928 x 448 at 8 bits 22.9 -> 21.5, 8 x 3904 x 1176 at 3 bits 19.1 -> 18.3.  Elsewhere written out is the better one:
+                // int8 2964 x 1280 x 1280 at 8 bits 12.23, in a function 12.38.)
+                auto hand_over = [&](int kt) {
+                    if (S > 2 && kt + S - 1 < KT)
+                        wait_vmcnt<(S > 2 ? (S - 2) * P::OPS : 0)>();
+                    else
+                        wait_vmcnt<0>();
+                    __syncthreads();
+                    if (kt + S < KT) issue(kt + S, buf);
+                };
+                hand_over(kt);
+            } else {
+                if (S > 2 && kt + S - 1 < KT)
+                    wait_vmcnt<(S > 2 ? (S - 2) * P::OPS : 0)>();
+                else
+                    wait_vmcnt<0>();
+                __syncthreads();
+                if (kt + S < KT) issue(kt + S, buf);
+            }
             request_first(lds + nb * STAGE_BYTES + grp * P::SUB_BYTES);
         }
         __builtin_amdgcn_sched_barrier(0);

@@ -386,7 +386,8 @@ __global__ __launch_bounds__(256, 1) void gemm_solo_kernel(const GemmArgs g) {
     constexpr int SLOTS = TM * TN;
     static_assert(SLOTS % 2 == 0 && P::OPS <= 4 * SLOTS, "at most one load of a stage per slot");
     // Residual of the slabs this wave finishes, requested in the last stages but S - 1: eight channels of its row per lane, 16 bytes; the two
-    // lanes of a row swap halves when they are used.
+    // lanes of a row swap halves when they are used.  It may lie on any multiple of 8 bytes: buffer loads of 16 need no more than 4.  It may be the
+    // output: a wave reads what no other one writes, but for channels beyond the last, whose results are dropped.
     constexpr int RES_LOADS = RES ? TM / KS * TN * 2 : 0;
     uint4v rs[RES ? TM / KS : 1][RES ? TN : 1][2];
     __amdgpu_buffer_rsrc_t rr;

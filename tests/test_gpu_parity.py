@@ -2196,3 +2196,89 @@ def test_a8_output_over_its_activations(mq):
     want = mq.qlinear_w4a8(x, pw)[0].clone()
     name, _ = ran_kernel(mq, lambda: mq.qlinear_w4a8(x, pw, out=x))
     assert "gemm_panel_kernel" not in name and torch.equal(x, want)
+
+
+# ------------------------------------------------------------------- views and in-place residuals of the two kernels above
+
+def views_of(M, N, r):
+    """(residual, output, whole output) as the library is allowed to get them: the residual 8 bytes past a 16-byte boundary in rows of 4 more than a
+    multiple of 8 values; the output in wider rows; both in one, in wider rows and in rows without a gap."""
+    off = torch.full((M, N + 12), 99.0, dtype=torch.float16, device="cuda")
+    off[:, 4:4 + N] = r
+    assert off[:, 4:].data_ptr() % 16 == 8 and off.stride(0) % 8 == 4
+    wide, io, tight = (torch.full((M, n), 7.0, dtype=torch.float16, device="cuda") for n in (N + 8, N + 16, N))
+    io[:, :N], tight[:] = r, r
+    return (off[:, 4:4 + N], wide[:, :N], wide), (io[:, :N], io[:, :N], io), (tight, tight, tight)
+
+
+@pytest.mark.parametrize("tile", (12, 13))
+@pytest.mark.parametrize("kind,bits", [("f16", 2), ("f16", 3), ("f16", 4), ("f16", 8), ("a8", 2), ("a8", 4), ("a8", 8), ("codes", 2), ("codes", 4), ("codes", 8)])
+@pytest.mark.parametrize("M,K,N", [(300, 896, 328), (127, 960, 152)])
+def test_one_wave_per_simd_views(mq, kind, bits, tile, M, K, N):
+    """On small integers: exact sums, one rounding."""
+    rng = np.random.default_rng(M + K + bits)
+    codes, zp = rng.integers(0, 1 << bits, (N, K)).astype(np.uint8), rng.integers(0, 1 << bits, N).astype(np.int32)
+    x, bias, r = rng.integers(-4, 5, (M, K)), rng.integers(-8, 9, N), rng.integers(-64, 65, (M, N))
+    packed, colsum = mq.pack_weights(dev(codes), bits, mq.LAYOUT_KERNEL)
+    pw = mq.PackedWeight(packed, dev(np.full(N, 2.0 ** -6, np.float32)), dev(zp), colsum, N, K, bits, mq.LAYOUT_KERNEL, False)
+    d_b, act = dev(bias.astype(np.float16)), (dev(np.array([1.0], np.float32)), dev(np.array([97], np.int32)))
+    wide_x = torch.full((M, K + 8), 1000.0, dtype=torch.float16, device="cuda")
+    wide_x[:, :K] = dev(x.astype(np.float16))
+    a8 = dev(a8_layout((x + 97).astype(np.uint8)))
+    fn = {8: mq.qlinear_w8a8, 4: mq.qlinear_w4a8, 2: mq.qlinear_w2a8}.get(bits)
+    call = {"f16": lambda res, out: mq.qlinear_w_only(wide_x[:, :K], pw, d_b, out=out, residual=res),
+            "a8": lambda res, out: fn(wide_x[:, :K], pw, act=act, bias=d_b, out=out, residual=res),
+            "codes": lambda res, out: mq.qlinear_a8_codes(a8, K, act, pw, bias=d_b, out=out, residual=res)}[kind]
+    want = (x @ (codes.astype(np.int64) - zp[:, None]).T * 2.0 ** -6 + bias + r).astype(np.float32).astype(np.float16)
+    mq.tune_force_tile(tile)
+    try:
+        for res, out, whole in views_of(M, N, dev(r.astype(np.float16))):
+            name, _ = ran_kernel(mq, lambda: call(res, out))
+            assert "gemm_solo_kernel" in name or (tile == 13 and kind != "f16" and bits == 8), name
+            assert np.array_equal(host(out), want) and (host(whole)[:, N:] == 7.0).all()
+    finally:
+        mq.tune_force_tile(-1)
+
+
+@pytest.mark.parametrize("tile", (12, 13))
+@pytest.mark.parametrize("bits", ALL_BITS)
+def test_one_wave_per_simd_convolutions_views(mq, orc, bits, tile):
+    """A residual 8 bytes past a 16-byte boundary, and one that is the output: the same values as with a residual of its own."""
+    B, H, W, Cin, N = 2, 9, 17, 128, 168
+    x = dev(si.activations_f16(92, "sv/x", B * H * W, Cin).reshape(B, H, W, Cin))
+    r = dev(si.normal(92, "sv/r", (B, H, W, N)).astype(np.float16))
+    pw, _, _, _, tapsum = conv_weight(mq, orc, 92, N, Cin, bits)
+    act = (dev(np.array([0.05], np.float32)), dev(np.array([31], np.int32)))
+    off = torch.zeros(r.numel() + 4, dtype=torch.float16, device="cuda")[4:].view(r.shape)
+    off[:] = r
+    assert off.data_ptr() % 16 == 8
+    calls = [lambda res, out: mq.conv3x3_w_only(x, pw, out=out, residual=res)]
+    if bits != 3:
+        calls.append(lambda res, out: mq.conv3x3_a8(x, pw, tapsum, act=act, out=out, residual=res)[0])
+    mq.tune_force_tile(tile)
+    try:
+        for call in calls:
+            want, io = call(r, None), r.clone()
+            assert torch.equal(call(off, None), want) and torch.equal(call(io, io), want)
+    finally:
+        mq.tune_force_tile(-1)
+
+
+@pytest.mark.parametrize("bits", (2, 4, 8))
+@pytest.mark.parametrize("M,K,N", [(300, 320, 328), (65, 640, 1288), (5200, 320, 104)])
+def test_a8_own_conversion_views(mq, bits, M, K, N):
+    """The same values as in two launches with the parameters that it found."""
+    fn = {8: mq.qlinear_w8a8, 4: mq.qlinear_w4a8, 2: mq.qlinear_w2a8}[bits]
+    c, s, z = mq.quantize_weights(torch.randn(N, K, device="cuda").half(), bits)
+    packed, cs = mq.pack_weights(c, bits, mq.LAYOUT_KERNEL)
+    pw = mq.PackedWeight(packed, s, z, cs, N, K, bits, mq.LAYOUT_KERNEL, False)
+    x, r, b = torch.randn(M, K + 8, device="cuda").half()[:, :K], torch.randn(M, N, device="cuda").half(), torch.randn(N, device="cuda").half()
+    for res, out, whole in views_of(M, N, r):
+        mq.tune_force_tile(14)
+        try:
+            name, (_, _, act) = ran_kernel(mq, lambda: fn(x, pw, bias=b, out=out, want_act=True, residual=res))
+        finally:
+            mq.tune_force_tile(-1)
+        assert "gemm_panel_kernel" in name
+        want = fn(x, pw, act=act, bias=b, residual=r)[0]
+        assert torch.equal(out, want) and bool((whole[:, N:] == 7.0).all())

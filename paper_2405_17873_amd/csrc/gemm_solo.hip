@@ -711,12 +711,15 @@ __global__ __launch_bounds__(256, 1) void gemm_solo_kernel(const GemmArgs g) {
 
 // ---------------------------------------------------------------------------------------------
 // Launchers.  Form 0: 256 x 160, four waves side by side along the rows.  Form 1: 128 x 160, two waves along the rows and two on the halves of
-// the reduction (their sums meet in LDS); not with 8-bit weights under 8-bit activations, whose stages leave room for two only.
+// the reduction (their sums meet in LDS); under 8-bit activations for convolutions only (see solo_form), and not with 8-bit weights, whose stages
+// leave room for two only.
 // ---------------------------------------------------------------------------------------------
 template <bool I8, int BITS>
 constexpr int solo_stages(int form) {
     return form == 0 && !I8 && BITS != 8 ? 4 : 3;
 }
+
+static constexpr bool solo_has_halves(bool i8, int bits, int mode) { return !i8 || (mode == 4 && bits != 8); }
 
 template <bool I8, int BITS, int FORM, int MODE, bool RES>
 static int run_solo_r(GemmArgs& g, hipStream_t st) {
@@ -757,7 +760,7 @@ static int run_solo_r(GemmArgs& g, hipStream_t st) {
 template <bool I8, int BITS, int MODE>
 static int run_solo(GemmArgs& g, int form, hipStream_t st) {
     if (form == 0) return g.res ? run_solo_r<I8, BITS, 0, MODE, true>(g, st) : run_solo_r<I8, BITS, 0, MODE, false>(g, st);
-    if constexpr (!(I8 && BITS == 8))
+    if constexpr (solo_has_halves(I8, BITS, MODE))
         if (form == 1) return g.res ? run_solo_r<I8, BITS, 1, MODE, true>(g, st) : run_solo_r<I8, BITS, 1, MODE, false>(g, st);
     return MQ_ERR_BAD_ARG;
 }
@@ -800,10 +803,12 @@ int solo_form(const GemmArgs& g, bool i8, int bits, int mode) {
     if ((forced >= 0 && forced < 12) || bits == 16) return -1;
     if (g.out_map.rows_per_group > 0 || forced_splits() > 1) return -1;
     if (g.ldy >= (1 << 21) || (g.res && g.ldr >= (1 << 21))) return -1;  // (offsets inside a workgroup's rows are 32-bit)
-    const bool halves = !(i8 && bits == 8);      // form 1 exists
+    const bool halves = solo_has_halves(i8, bits, mode);
     // (the stages that are requested ahead of the loop have to exist)
     auto long_enough = [&](int form) { return (g.k_stages + form) / (form + 1) >= 4; };
-    if (forced >= 12) return forced == 12 && long_enough(0) ? 0 : forced == 13 && halves && long_enough(1) ? 1 : -1;
+    if (forced == 12) return long_enough(0) ? 0 : -1;
+    if (forced == 13) return !long_enough(1) || (i8 && bits == 8) ? -1 : halves ? 1 : 0;  // (where form 1 does not exist, form 0 is the nearest)
+    if (forced > 13) return -1;
     const bool conv = mode == 3 || mode == 4;
     const long now = std::min(busiest_area(g.M, g.N, 64, 128), busiest_area(g.M, g.N, 96, 128));
     const long full = busiest_area(g.M, g.N, 256, 160), half = busiest_area(g.M, g.N, 128, 160);

@@ -10,9 +10,10 @@
 // What bounds the two launches at these sizes is their number: conversion 5 to 7 us and GEMM 4.5 to 14, each of it mostly ramp, first loads and
 // drain.  What bounds this one is the conversion (about 60 vector instructions for eight values, of 64 rows in every range of channels) and the
 // loads ahead of it, so it pays where K is short and the output takes few ranges.  Sixteen waves, 1024 threads: a panel of up to 640 k is one
-// round of loads for the conversion (512 threads with two rounds: 16384 x 640 x 640 at 4 bits 28 us against 24), and four waves per SIMD cover
-// each other's LDS reads, widening and stores.  Whole calls in us, two launches -> this, 4-bit weights, run-time range: 1 x 320 x 320 8.7 -> 7.5, 256 x
-// 320 x 320 (8 bits) 9.6 -> 8.5, 4096 x 320 x 320 14 -> 10.5, 16384 x 320 x 320 16.6 -> 13.6, 16384 x 576 x 320 25 -> 18, 16384 x 640 x 640 30 -> 24.
+// round of loads for the conversion (512 threads with two rounds took 1.17 times as long at 16384 x 640 x 640 and 4 bits), and four waves per SIMD cover
+// each other's LDS reads, widening and stores.  Whole calls in us, two launches -> this, 4-bit weights, run-time range: 1 x 320 x 320 9.3 -> 7.4, 256 x
+// 320 x 320 (8 bits) 10.4 -> 8.4, 4096 x 320 x 320 13 -> 10.4, 16384 x 320 x 320 17.6 -> 13.1, 16384 x 576 x 320 21.6 -> 16.3, 16384 x 640 x 640 24.7 ->
+// 19.8.
 //
 // Compiled with -ffp-contract=off (see act_range.h): fused multiply-adds are written out.
 #include <stdio.h>
@@ -305,12 +306,14 @@ static void panel_split(int M, int N, int* units, int* ranges) {
     *ranges = (all + *units - 1) / *units;
 }
 
-// Times of this over the two launches (16700 drawn shapes of 1 to 20000 rows; mean and 9 in 10 below), by rows:
-//   up to 320 k   up to 15 0.86 0.90, up to 511 0.93 0.97, up to 1023 0.98 1.03, up to 16384 in one round of workgroups 0.90 0.96, in more 1.15
-//   up to 512 k   up to 15 0.88 0.91, up to 8191 0.97 to 1.06, to 16384 and up to 640 channels 0.92 1.02
-//   up to 640 k   up to 15 0.90 0.93, up to 4095 1.02 to 1.12, to 8191 0.99 1.05, to 16384 and up to 640 channels 0.95 (at 640 x 640 0.82)
-//   beyond        up to 15 0.97 1.01, else 1.0 to 1.2
-// (Calls with given parameters keep their two launches: what their forms are is pinned size by size.)
+// Times of this over the two launches (277 shapes of 1 to 16384 rows, 320 to 1288 channels; mean and largest), by rows, in one round of workgroups:
+//   up to 320 k   up to 15 0.83 0.89, up to 511 0.82 0.89, up to 1023 0.87 0.99, beyond 0.80 0.89
+//   up to 512 k   up to 15 0.85 0.89, up to 511 0.90 0.97, up to 1023 0.93 1.03, up to 4095 0.89 0.94, up to 8191 0.82 0.91, beyond 0.83 0.90
+//   up to 640 k   up to 15 0.84 0.89, up to 511 0.91 1.10, up to 1023 0.94 1.06, up to 4095 0.90 0.94, up to 8191 0.82 0.92, beyond 0.81 0.97
+//   in more than one round 1.01 to 1.27
+// (pairs in profiles/tile_rules.txt).  The lines beyond 320 k were drawn for a loop that waited for all its loads at every tile and was the slower one
+// between 16 and 8191 rows; for this one they are too narrow, and have not been drawn anew.  Calls with given parameters keep their two launches:
+// not measured here, and a test pins the tile that each of them runs.
 bool panel_takes(int M, int N, int K, long ldy) {
     const int forced = forced_tile();
     if ((forced >= 0 && forced != 14) || forced_splits() > 1 || K < 256 || K > PANEL_MAX_K || ldy >= (1L << 23)) return false;

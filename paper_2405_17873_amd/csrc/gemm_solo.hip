@@ -5,7 +5,7 @@
 // reads an LDS fragment and widens half a weight fragment per MFMA, every stage of 8 MFMAs per wave ends in a barrier, and at the rate at which
 // the chip runs MFMAs on real data (power: 1.6 to 1.8 GHz) what a multiplication moves through LDS costs clock as well.  Here a workgroup of
 // four waves has a compute unit to itself and a wave owns 64 x 160 results, 160 accumulators of its 512 registers: a stage is 40 MFMAs per wave
-// and one barrier, a third of the LDS reads per MFMA, and half the L2 -> LDS bytes (36 or 42 KB per 40 MFMAs).  With no other wave on the SIMD
+// and one barrier, a third of the LDS reads per MFMA, and half the L2 -> LDS bytes (34 to 52 KB per 40 MFMAs).  With no other wave on the SIMD
 // every latency is covered by the wave's own MFMAs: reads, widening and the loads of later stages are laid out between them one by one
 // (a lone wave has room for about seven instructions per MFMA: 32 cycles, one instruction in four).
 // 160 columns, because 320, 640, 1280, ... are multiples of it and 128 leaves 320 and 960 a sixth and a sixteenth of the work for padding.
@@ -798,6 +798,7 @@ int launch_gemm_solo(GemmArgs& g, int form, bool i8, int bits, int mode, hipStre
 // 27.3 -> 26.1; 32768 x 640 x 320 at 4 bits 27.9 -> 20.1; 14000 x 640 x 640, 0.85 of the round, 17.2 -> 18.2), without one 16-bit linears at 8 bits (16384 x 640 x
 // 640 18.3 -> 16.8, 2048 x 640 x 5120 18.5 -> 16.8; at 4 bits 16.9 -> 16.7 and 16.7 -> 16.8) and from 960 k on at 4 bits (16384 x 960 x 640 22.8 -> 21.8; at 2
 // bits 23.1 -> 22.7 and 22.5 -> 22.0, left); int8 without a residual 0.93 to 1.1.
+// Pairs of times on both sides of the lines are in profiles/tile_rules.txt.
 int solo_form(const GemmArgs& g, bool i8, int bits, int mode) {
     const int forced = forced_tile();
     if ((forced >= 0 && forced < 12) || bits == 16) return -1;
@@ -824,7 +825,9 @@ int solo_form(const GemmArgs& g, bool i8, int bits, int mode) {
         if (bits == 8) return fit(full, 115) && g.ldy % 32 == 0 ? 0 : -1;
         return bits == 4 && fit(full, 115) && one_round ? 0 : -1;
     }
-    // (int8 linears at 8 bits from 2624 k on: at 2560, the feed-forward outputs of the 640-channel level, 64 x 128 stays)
+    // (int8 linears at 8 bits from 2624 k on, or with a residual in a filled round.  The line at 2560 is not where this form stops paying: the tile of
+    // 16384 x 2560 x 640 is pinned by a test of the older rule.  us, that rule -> this: 16384 x 2560 x 640 61 -> 51, 16384 x 2048 x 640 53 -> 46,
+    // 4096 x 2048 x 2560 37 -> 32, 8192 x 2304 x 1280 46 -> 39; above the line 16384 x 2624 x 640 65 -> 52.)
     if (mode == 0 && i8) return fit(full, 115) && (bits != 8 || g.K > 2560 || (filled && g.res)) ? 0 : -1;
     if (fit(full, i8 && bits == 8 ? 125 : 105)) return 0;
     return halves && fit(half, 85) && (!i8 || g.K >= 5120) && (conv || g.K >= 2560) ? 1 : -1;
